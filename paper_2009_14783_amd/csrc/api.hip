@@ -133,7 +133,7 @@ GemmArgs gemm_args(int dtype, int ak, int bk, int M, int N, int K, const void* A
   g.dtype = dtype; g.a_kmajor = ak; g.b_kmajor = bk; g.M = M; g.N = N; g.K = K;
   g.A = A; g.lda = lda; g.B = B; g.ldb = ldb; g.C = C; g.ldc = ldc;
   g.c_f32 = 0; g.beta = 0.f; g.bias = nullptr; g.epi = 0; g.aux = nullptr; g.ldaux = 0; g.C2 = nullptr;
-  g.ws = nullptr; g.ws_bytes = 0;
+  g.ws = nullptr; g.ws_bytes = 0; g.a_kpad = 0;
   g.drop = nullptr; g.drop_site = 0;
   return g;
 }
@@ -302,6 +302,7 @@ hs_status hs_mlm_loss(hs_ctx* ctx, const void* w, const void* hidden, const int3
   if (overlap) HS_HIP_CHECK(ctx, hipEventRecord(ctx->events[1], sd));
   // dt = dlogits E
   ga = gemm_args(dt, 1, 0, M, H, V, h.dlogits, Vp, W(ctx, w, o.emb_word), H, h.dt, H);
+  ga.a_kpad = 1;      // the loss kernel writes zeros into the padding columns of d logits
   HS_TRY(run_gemm(ga));
   HS_TRY(launch_layernorm_bwd(ctx, dt, h.dt, h.tact, h.stats, W(ctx, w, o.head_ln_g), h.dtact, g + o.head_ln_g, g + o.head_ln_b, nullptr,
                               beta, M, H, h.ln_part, s));

@@ -202,6 +202,7 @@ struct GemmArgs {
   const void* bias;
   int epi; const void* aux; int64_t ldaux; void* C2;
   void* ws; size_t ws_bytes;   // optional scratch for split-K partial sums
+  int a_kpad;                  // A k-major: its rows are zero from K up to the next multiple of 64
   const DropCfg* drop; uint32_t drop_site;   // optional (epi == 1): dropout of product + bias before the residual
 };
 hs_status launch_gemm(hs_ctx* ctx, const GemmArgs& g, hipStream_t s);

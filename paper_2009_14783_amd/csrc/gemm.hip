@@ -5,6 +5,8 @@
 //   fp32: plain tiled SIMT kernel (small reference-precision configurations only).
 #include "gemm_dev.h"
 
+#include <algorithm>
+
 hipError_t gemm_wide_launch_kk(int cfg, const GemmDev& p, int splits, hipStream_t s);
 hipError_t gemm_wide_launch_kn(int cfg, const GemmDev& p, int splits, hipStream_t s);
 hipError_t gemm_wide_launch_nn(int cfg, const GemmDev& p, int splits, hipStream_t s);
@@ -380,14 +382,30 @@ static hipError_t gelu_table(int which, hipStream_t s, const float2** out) {
   return hipSuccess;
 }
 
-// Tile configurations.  0 is gemm_bf16_mfma (128 x 128 x 32, three blocks per CU); 1..6 are gemm_bf16_wide (global ->
-// registers -> LDS), 7..11 gemm_bf16_dma (global -> LDS directly).  In use: 0, 5 and 9 (see launch_gemm) and, for the
-// grouped weight-gradient launch, the tile of 6.  The others are kept as measured alternatives, selectable for
-// timing runs through gemm_set_variant: on the shapes of the training step they were equal or slower.
-struct TileCfg { int bm, bn, bk; };
-constexpr TileCfg kTileCfg[] = {{128, 128, 32}, {256, 256, 64}, {256, 192, 64}, {128, 192, 64}, {256, 128, 32}, {128, 128, 64}, {256, 128, 64},
-                                {128, 128, 32}, {128, 128, 32}, {128, 128, 64}, {256, 128, 64}, {256, 128, 64}};
+// Tile configurations.  0: gemm_bf16_mfma (any shape, every epilogue).  1, 5, 6: gemm_bf16_wide (global -> registers -> LDS; 6
+// is the tile of the grouped weight-gradient launch).  4, 7 .. 11: gemm_bf16_dma (global -> LDS).  2, 3: gemm_bf16_ksplit (the
+// waves of a block share out the contraction).  What a launch takes is modelled as
+//   t0 + k-tiles x (rounds of full CUs x occ w + the last round of r blocks per CU x max(l, r w)) + e x tiles per CU x outputs
+// with l the time of a k-tile of 64 when a block has its CU to itself (a chain of load, LDS read and matrix instruction
+// latencies), w what it adds to a CU whose blocks cover each other (throughput of the feed from the L2), and e the writing
+// of a tile; `use` says whether the automatic choice considers the configuration (the others are slower everywhere or
+// within the error of the fit, and selectable for timing).  The constants (us) are fitted to 4700 launches on this
+// chip: rows 32 .. 16384, the forward and activation-gradient products of widths 512, 768 and 1024 with their epilogues, weights not
+// in the cache of the launch before; the choice made with them is 2 % above the fastest configuration on average over those shapes.
+struct TileCfg { int bm, bn, bk, occ, use; float t0, l, w, e; };
+constexpr TileCfg kTileCfg[] = {
+    {128, 128, 32, 3, 0, 3.2f, 0.560f, 0.470f, 2.00f}, {256, 256, 64, 1, 0, 6.4f, 1.106f, 0.836f, 7.34f}, {32, 32, 64, 1, 1, 1.5f, 0.011f, 0.104f, 0.90f},
+    {32, 32, 64, 2, 0, 2.4f, 0.112f, 0.092f, 0.38f},   {32, 64, 64, 3, 1, 3.0f, 0.146f, 0.120f, 0.33f},   {128, 128, 64, 2, 1, 3.2f, 0.318f, 0.423f, 1.95f},
+    {256, 128, 64, 1, 0, 3.2f, 0.720f, 0.800f, 3.60f}, {64, 128, 64, 2, 0, 2.7f, 0.319f, 0.288f, 0.90f},  {128, 64, 64, 2, 0, 2.6f, 0.316f, 0.289f, 0.84f},
+    {128, 128, 64, 2, 1, 2.9f, 0.548f, 0.447f, 1.57f}, {256, 128, 64, 1, 0, 1.1f, 0.717f, 0.745f, 3.55f}, {64, 64, 64, 3, 1, 2.5f, 0.229f, 0.175f, 0.41f}};
 constexpr int kNumTileCfg = sizeof(kTileCfg) / sizeof(kTileCfg[0]);
+constexpr int kCUs = 256;
+float cfg_time(const TileCfg& c, int M, int N, int K, int splits, float outputs) {
+  const int64_t tiles = (int64_t)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn) * splits;
+  const int per_cu = (int)((tiles + kCUs - 1) / kCUs), full = per_cu / c.occ, rem = per_cu % c.occ;
+  const float steps = (float)((K + 63) / 64) / splits;
+  return c.t0 + steps * (full * std::max(c.l, c.occ * c.w) + (rem ? std::max(c.l, rem * c.w) : 0.0f)) + c.e * per_cu * outputs;
+}
 int gemm_cfg_override = -1;    // >= 0: use this configuration for every bf16 product of some size that it can serve (timing runs)
 
 constexpr int kMaxBK = 64;
@@ -470,6 +488,35 @@ static bool wide_supports(const GemmArgs& g) {
   return g.c_f32 != 0;
 }
 
+// Configuration and number of k-splits of a product: the fastest by the model above among those that can serve it.
+// Configuration 0 where an epilogue is needed that the others are not built with; where rows of a k-major operand end
+// inside a k-tile, 0 or (from 256 rows, columns and contraction steps on, where it is faster) 5.
+static void choose_cfg(const GemmArgs& g, int* cfg, int* splits) {
+  const bool supported = wide_supports(g), whole_k = !g.a_kmajor || g.K % 64 == 0 || g.a_kpad;
+  const bool some_size = g.M >= 256 && g.N >= 256 && g.K >= 256;
+  int only = -1;
+  if (!supported) only = 0;
+  else if (gemm_cfg_override >= 0) only = some_size ? gemm_cfg_override : 0;
+  if (supported && !whole_k && only != 0 && only != 1 && only != 6) only = some_size ? 5 : 0;
+  const float outputs = (g.c_f32 || g.epi) ? 2.0f : 1.0f;
+  float best = 3.0e38f;
+  *cfg = 0; *splits = 1;
+  for (int c = 0; c < kNumTileCfg; ++c) {
+    if (only >= 0 ? c != only : !kTileCfg[c].use) continue;
+    // 5 and 9 are the same tile: the register-staged one is faster for the forward products when the two halves of a batch run
+    // beside each other, the direct one for the others
+    if (only < 0 && c == ((g.a_kmajor && g.b_kmajor) ? 9 : 5)) continue;
+    // With a scratch buffer the contraction can be split over blocks: partial sums go out as fp32 and are added by a second
+    // launch (3 us and their way through memory and back at 3.5 TB/s).
+    const int64_t most = g.ws ? std::min<int64_t>({32, g.K / (4 * kTileCfg[c].bk), (int64_t)(g.ws_bytes / ((size_t)g.M * g.N * sizeof(float)))}) : 1;
+    for (int sp = 1; sp <= std::max<int64_t>(1, most); sp *= 2) {
+      float t = cfg_time(kTileCfg[c], g.M, g.N, g.K, sp, sp > 1 ? 2.0f : outputs);
+      if (sp > 1) t += 3.0f + 8.0f * sp * (float)g.M * (float)g.N / 3.5e6f;
+      if (t < best) { best = t; *cfg = c; *splits = sp; }
+    }
+  }
+}
+
 hs_status launch_gemm(hs_ctx* ctx, const GemmArgs& g, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0) return HS_OK;  // nothing to write
   {
@@ -485,28 +532,10 @@ hs_status launch_gemm(hs_ctx* ctx, const GemmArgs& g, hipStream_t s) {
     dim3 grid((g.N + 63) / 64, (g.M + 63) / 64);
     hipLaunchKernelGGL(gemm_simt<float>, grid, dim3(256), 0, s, p, g.a_kmajor, g.b_kmajor);
   } else {
-    // Configuration for products of some size whose epilogue the wide kernels are built with: 128 x 128 x 64 tiles, two
-    // blocks per CU - the direct-to-LDS kernel for the activation-gradient products (A k-major, B n-major; it gained 6-12 %
-    // on their shapes, whole output matrices of 8192 rows, and lost on the forward pass's half batches), the
-    // register-staged kernel otherwise.  Small or ragged products and the remaining epilogues: the three-blocks-per-CU kernel.
-    int cfg = !(g.M >= 256 && g.N >= 256 && g.K >= 256) ? 0
-              : (gemm_cfg_override >= 0 && gemm_cfg_override < kNumTileCfg) ? gemm_cfg_override
-              : ((g.a_kmajor && !g.b_kmajor) ? 9 : 5);
-    if (cfg != 0 && !wide_supports(g)) cfg = 0;
-    if (cfg >= 7 && g.K % kTileCfg[cfg].bk) cfg = 5;      // the direct-to-LDS kernel takes whole k-tiles only
-    const int kBM = kTileCfg[cfg].bm, kBN = kTileCfg[cfg].bn, kBK = kTileCfg[cfg].bk;
-    // split-K when the output has too few tiles to fill the chip and a scratch buffer was given
-    const int64_t tiles = (int64_t)((g.M + kBM - 1) / kBM) * ((g.N + kBN - 1) / kBN);
-    int splits = 1;
-    if (g.ws && tiles < 256) {
-      int64_t want = (512 + tiles - 1) / tiles;
-      const int64_t by_k = g.K / (4 * kBK), by_ws = (int64_t)(g.ws_bytes / ((size_t)g.M * g.N * sizeof(float)));
-      if (want > by_k) want = by_k;
-      if (want > by_ws) want = by_ws;
-      if (want > 32) want = 32;
-      if (want > 1) splits = (int)want;
-    }
+    int cfg, splits;
+    choose_cfg(g, &cfg, &splits);
     if (splits > 1) {
+      const int kBK = kTileCfg[cfg].bk;
       p.partial = (float*)g.ws;
       p.k_per_split = (int)(((g.K + splits - 1) / splits + kBK - 1) / kBK * kBK);
       splits = (g.K + p.k_per_split - 1) / p.k_per_split;

@@ -8,35 +8,43 @@ namespace {
 // ------------------------------------------------------------------------------------------
 // bf16 MFMA kernel with direct global -> LDS operand loads
 // ------------------------------------------------------------------------------------------
-// Block tile (64 WGM) x 128 x BK, WGM x 2 waves of 64 x 64 (WGM = 2 or 4).  A k-tile is fetched by buffer loads that write LDS
-// themselves (16 bytes per lane, one instruction fills 1 KiB of LDS in lane order), so that an operand byte never
-// passes through a register and no LDS store instruction is issued.  S stages of LDS form a ring: the tile for
-// k-step t + S - 1 is requested when step t starts, one barrier per k-tile.  What orders the loads against their
-// readers is the wave's own load counter (the hardware retires these loads in order) followed by the barrier;
-// both are written out by hand here, because a fence would make every wave wait for all of its loads.
+// Block tile (32 TI WGM) x (32 TJ WGN) x BK; WGM x WGN waves of TI x TJ MFMA tiles, times KW groups of waves that share a
+// k-tile's 16-deep slices (group g takes slices g, g + KW, ...; the groups' sums are added in group order through LDS).
+// A k-tile is fetched by buffer loads that write LDS themselves (16 bytes per lane, one instruction fills 1 KiB of LDS in
+// lane order), so that an operand byte never passes through a register and no LDS store instruction is issued.  S stages
+// of LDS form a ring: the tile for k-step t + S - 1 is requested when step t starts, one barrier per k-tile.  What orders
+// the loads against their readers is the wave's own load counter (the hardware retires these loads in order) followed by
+// the barrier; both are written out by hand here, because a fence would make every wave wait for all of its loads.
 //
 // One instruction's 64 lanes land in consecutive 16-byte slots, so the bank-conflict-free LDS layouts are made on
 // the global side: the lane that fills slot p of a row fetches the chunk whose number is p XOR a function of the row.
 //   k-major operand ([rows, K], a row of the tile is BK contiguous elements): the layout of WideTile, rows
 //     unpadded, chunk ^ ((row >> 1) & 7) for BK = 64 and chunk ^ ((row >> 2) & 3) for BK = 32.
-//   m-major operand ([K, rows], a row of the tile is 128 or 256 contiguous elements of one contraction index k):
-//     chunk ^ ((k & 3) << 2), which spreads the four k-rows that 16 lanes of a transposing read touch over four
-//     64-byte bank groups.
-// The contraction range of a block must be a multiple of BK (the launcher checks); rows beyond the matrix edge are
-// clamped to the last row (their products are never stored).
+//   m-major operand ([K, rows], a row of the tile is R contiguous elements of one contraction index k): a transposing read
+//     takes 64 bytes of each of four k-rows at once.  R >= 128: chunk ^ ((k & 3) << 2) puts the four into four different
+//     64-byte bank groups; R = 64: two k-rows already lie side by side, chunk ^ (((k >> 1) & 1) << 2) parts the others;
+//     R = 32: the four k-rows are one 256-byte line as they are.
+// Small tiles are for products with few of them, where the rate at which a CU is fed does not matter yet: 2048 x 768 x 768 with
+// 64 x 64 tiles 7.5 us (128 x 128: 11.6), 1024 x 768 x 3072 14.4 us (34), 512 x 768 x 3072 with 32 x 64 tiles 10.6 us (33).
+// From about two 128 x 128 tiles per CU on the feed from the L2 binds (8192 x 3072 x 3072: 106 us, its loads alone 103 us,
+// everything but the loads 82 us; 39 bytes per clock and CU), and only the larger tile helps.
+// Rows beyond the matrix edge are clamped to the last row (their products are never stored).  A k-tile that reaches beyond
+// the contraction range reads zeros there: rows of an m-major operand beyond K lie behind the end of the operand, where a
+// buffer load returns zero; a k-major operand has to end on a whole k-tile or be zero up to there (the launcher checks).
 typedef __attribute__((address_space(3))) void* lds_void_ptr;
 
-// R: rows of the tile (128 or 256); NW: waves of the block, which share the tile's load instructions evenly
+// R: rows of the tile; NW: waves of the block, which share the tile's load instructions evenly
 template <bool KMAJ, int BK, int R, int NW>
 struct DmaTile {
   static_assert(BK == 32 || BK == 64, "k-tile of 32 or 64");
-  static_assert(R == 128 || R == 256, "128 or 256 rows");
+  static_assert(R == 32 || R == 64 || R == 128 || R == 256, "32 to 256 rows");
   static constexpr int BYTES = R * BK * 2;
   static constexpr int NI = BYTES / 1024 / NW;         // load instructions per wave and k-tile
   static_assert(NI >= 1 && NI * NW * 1024 == BYTES, "the tile must split evenly over the waves");
   static constexpr int CPR = BK / 8;                   // k-major: chunks per row
   static constexpr int RPI = 64 / CPR;                 // k-major: rows per instruction
   static constexpr int KPI = 64 / (R / 8);             // m-major: k-rows per instruction
+  static __device__ __forceinline__ int mswz(int k) { return R >= 128 ? ((k & 3) << 2) : (R == 64 ? (((k >> 1) & 1) << 2) : 0); }
   struct Cursor {
     __amdgpu_buffer_rsrc_t rsrc;
     unsigned off[NI];
@@ -59,7 +67,7 @@ struct DmaTile {
         cu.off[i] = (unsigned)(((int64_t)r * ld + chunk * 8) * 2);
       } else {
         const int k = j * KPI + lane / (R / 8), slot = lane % (R / 8);
-        const int chunk = slot ^ ((k & 3) << 2);
+        const int chunk = slot ^ mswz(k);
         const int n = min(row0 + chunk * 8, ((rext - 1) >> 3) << 3);
         cu.off[i] = (unsigned)(((int64_t)k * ld + n) * 2);
       }
@@ -75,11 +83,12 @@ struct DmaTile {
   // LDS -> MFMA operand: lane gets elements (row = rbase + lane%32, k = ks*16 + 8*(lane/32) + 0..7)
   static __device__ __forceinline__ bf16x8 frag(const bf16* __restrict__ s, int rbase, int ks, int lane) {
     if (KMAJ) {
-      return WideTile<true, R, BK, 64 * NW>::frag(s, rbase, ks, lane);
+      const int row = rbase + (lane & 31), chunk = ks * 2 + (lane >> 5);
+      return *(const bf16x8*)(s + row * BK + (chunk ^ (BK == 64 ? ((row >> 1) & 7) : ((row >> 2) & 3))) * 8);
     } else {
       const int kb = ks * 16 + 8 * (lane >> 5) + ((lane & 15) >> 2);
       const int nb = rbase + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
-      const int pos = kb * R + ((((nb >> 3) ^ ((kb & 3) << 2))) << 3) + (nb & 7);     // kb + 4 has the same k & 3
+      const int pos = kb * R + (((nb >> 3) ^ mswz(kb)) << 3) + (nb & 7);     // kb + 4 has the same swizzle
       typedef s16x4 __attribute__((address_space(3))) * lds_v4;
       union { struct { s16x4 lo, hi; } p; bf16x8 v; } u;
       u.p.lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4)(s + pos));
@@ -89,12 +98,22 @@ struct DmaTile {
   }
 };
 
-template <int BK, int S, int WGM>
-constexpr size_t dma_lds_bytes() {
-  const size_t pipe = (size_t)S * (64 * WGM + 128) * BK * 2;
-  const size_t stage = (size_t)2 * WGM * 32 * (32 * 2 + 4) * sizeof(float) + kGeluTabN * sizeof(float2);
-  return stage > pipe ? stage : pipe;
-}
+// The tile shape and pipeline of one configuration.
+template <int TI_, int TJ_, int WGM_, int WGN_, int KW_, int BK_, int S_, int OCC_>
+struct DmaCfg {
+  static constexpr int TI = TI_, TJ = TJ_, WGM = WGM_, WGN = WGN_, KW = KW_, BK = BK_, S = S_, OCC = OCC_;   // OCC: blocks per CU
+  static constexpr int NS = WGM * WGN, NW = NS * KW, NT = 64 * NW, BM = 32 * TI * WGM, BN = 32 * TJ * WGN;
+  static constexpr int STAGE = (BM + BN) * BK * 2;                      // bytes of a k-tile of both operands
+  static constexpr int EPI_FLOATS = 32 * (32 * TJ + 4);                 // a wave's epilogue staging area
+  static constexpr size_t RED = (size_t)(KW - 1) * NS * TI * TJ * 16 * 64 * sizeof(float);
+  static constexpr size_t EPI_BYTES = (size_t)NS * EPI_FLOATS * sizeof(float) + kGeluTabN * sizeof(float2);
+  static constexpr size_t PIPE = (size_t)S * STAGE;
+  static constexpr size_t LDS = PIPE > EPI_BYTES ? (PIPE > RED ? PIPE : RED) : (EPI_BYTES > RED ? EPI_BYTES : RED);
+  static constexpr int WPE = OCC * NW / 4;                              // waves per SIMD
+  static_assert(S >= 2 && S <= 16, "two to sixteen stages");
+  static_assert(BK / 16 % KW == 0, "the k-slices must split evenly over the wave groups");
+  static_assert(LDS * OCC <= 160 * 1024, "stages do not fit the LDS of a CU");
+};
 
 // s_waitcnt: the wave's vector-memory loads except the newest VM have completed, and so have all its LDS reads
 template <int VM>
@@ -102,15 +121,22 @@ __device__ __forceinline__ void wait_loads() {
   static_assert(VM >= 0 && VM < 64, "6-bit counter");
   __builtin_amdgcn_s_waitcnt((VM & 15) | ((VM >> 4) << 14) | 0x70);
 }
+// ... with the number of k-tiles that may still be in flight known at run time only (0 .. MAX)
+template <int PER, int MAX>
+__device__ __forceinline__ void wait_tiles(int ahead) {
+  if constexpr (MAX == 0) wait_loads<0>();
+  else { if (ahead >= MAX) wait_loads<MAX * PER>(); else wait_tiles<PER, MAX - 1>(ahead); }
+}
 
 // One k-step: tile `cur` is read (after the wave's share of it has landed and every wave has arrived), the tile
 // S - 1 steps ahead is requested into `nxt`, whose last readers passed the same barrier.
-template <class TA, class TB, int KS, int AHEAD>
+template <class C, class TA, class TB>
 __device__ __forceinline__ void dma_step(typename TA::Cursor& ca, typename TB::Cursor& cb, unsigned char* __restrict__ nxt,
-                                         const unsigned char* __restrict__ cur, f32x16 (&acc)[2][2], bool full_ring, bool request, int wm,
-                                         int wn, int lane, int wave) {
+                                         const unsigned char* __restrict__ cur, f32x16 (&acc)[C::TI][C::TJ], int ahead, bool request, int wm,
+                                         int wn, int kg, int lane, int wave) {
+  constexpr int KS = C::BK / 16 / C::KW;
   asm volatile("" ::: "memory");      // no LDS access of the step before moves below the barrier, none of this step above it
-  if (full_ring) wait_loads<AHEAD*(TA::NI + TB::NI)>(); else wait_loads<0>();
+  wait_tiles<TA::NI + TB::NI, C::S - 2>(ahead);
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
   if (request) {
@@ -119,34 +145,32 @@ __device__ __forceinline__ void dma_step(typename TA::Cursor& ca, typename TB::C
   }
   const bf16* sA = (const bf16*)cur;
   const bf16* sB = (const bf16*)(cur + TA::BYTES);
-  bf16x8 fa[KS][2], fb[KS][2];
+  bf16x8 fa[KS][C::TI], fb[KS][C::TJ];
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) fa[ks][i] = TA::frag(sA, (wm * 2 + i) * 32, ks, lane);
+    for (int i = 0; i < C::TI; ++i) fa[ks][i] = TA::frag(sA, (wm * C::TI + i) * 32, ks * C::KW + kg, lane);
 #pragma unroll
-    for (int j = 0; j < 2; ++j) fb[ks][j] = TB::frag(sB, (wn * 2 + j) * 32, ks, lane);
+    for (int j = 0; j < C::TJ; ++j) fb[ks][j] = TB::frag(sB, (wn * C::TJ + j) * 32, ks * C::KW + kg, lane);
   }
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < C::TI; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[ks][i], fb[ks][j], acc[i][j], 0, 0, 0);
+      for (int j = 0; j < C::TJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[ks][i], fb[ks][j], acc[i][j], 0, 0, 0);
 }
 
-template <bool AK, bool BKM, int BK, int S, int WGM, int EPIS>
+template <class C, bool AK, bool BKM, int EPIS>
 __device__ __forceinline__ void dma_tile(const GemmDev& p, int m0, int n0, int split, unsigned char* lds_raw) {
-  constexpr int TI = 2, TJ = 2, KS = BK / 16, NW = 2 * WGM;
-  static_assert(S >= 2 && S <= 4, "two to four stages");
-  typedef DmaTile<AK, BK, 64 * WGM, NW> TA;
-  typedef DmaTile<BKM, BK, 128, NW> TB;
-  constexpr int STAGE = TA::BYTES + TB::BYTES;
+  constexpr int TI = C::TI, TJ = C::TJ, S = C::S;
+  typedef DmaTile<AK, C::BK, C::BM, C::NW> TA;
+  typedef DmaTile<BKM, C::BK, C::BN, C::NW> TB;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave >> 1, wn = wave & 1;
+  const int kg = wave / C::NS, ws = wave % C::NS, wm = ws / C::WGN, wn = ws % C::WGN;
   const int kbeg = split * p.k_per_split;
   const int kend = min(p.K, kbeg + p.k_per_split);
-  const int nk = (kend - kbeg) / BK;
+  const int nk = (kend - kbeg + C::BK - 1) / C::BK;
 
   f32x16 acc[TI][TJ];
 #pragma unroll
@@ -165,19 +189,18 @@ __device__ __forceinline__ void dma_tile(const GemmDev& p, int m0, int n0, int s
 #pragma unroll
   for (int s = 0; s < S - 1; ++s)
     if (s < nk) {
-      TA::issue(ca, lds_raw + s * STAGE, wave);
-      TB::issue(cb, lds_raw + s * STAGE + TA::BYTES, wave);
+      TA::issue(ca, lds_raw + s * C::STAGE, wave);
+      TB::issue(cb, lds_raw + s * C::STAGE + TA::BYTES, wave);
     }
-  // Step t reads stage t % S and requests tile t + S - 1 into stage (t - 1) % S.  At its start the wave has
-  // requested tiles up to min(t + S - 2, nk - 1): with all S - 2 tiles behind tile t in flight the counter is
-  // waited down to their number of loads, otherwise (the last steps) to zero.
+  // Step t reads stage t % S and requests tile t + S - 1 into stage (t - 1) % S.  At its start the wave has requested
+  // tiles up to min(t + S - 2, nk - 1): the counter is waited down to the loads of the tiles behind tile t.
   for (int t0 = 0; t0 < nk; t0 += S) {
 #pragma unroll
     for (int u = 0; u < S; ++u) {
       const int t = t0 + u;
       if (t < nk)
-        dma_step<TA, TB, KS, S - 2>(ca, cb, lds_raw + ((u + S - 1) % S) * STAGE, lds_raw + u * STAGE, acc, t + S - 2 < nk, t + S - 1 < nk, wm, wn,
-                                    lane, wave);
+        dma_step<C, TA, TB>(ca, cb, lds_raw + ((u + S - 1) % S) * C::STAGE, lds_raw + u * C::STAGE, acc, min(S - 2, nk - 1 - t), t + S - 1 < nk, wm,
+                            wn, kg, lane, wave);
     }
   }
   asm volatile("" ::: "memory");
@@ -185,14 +208,43 @@ __device__ __forceinline__ void dma_tile(const GemmDev& p, int m0, int n0, int s
   __builtin_amdgcn_s_barrier();   // every wave is done with the operand stages: they become the staging area of the epilogue
   asm volatile("" ::: "memory");
 
-  const int rbase = m0 + wm * TI * 32, cbase = n0 + wn * TJ * 32;
-  constexpr int STAGE_FLOATS = 32 * (32 * TJ + 4);
-  float* stage = (float*)lds_raw + wave * STAGE_FLOATS;
-  float2* const tab = (float2*)((float*)lds_raw + NW * STAGE_FLOATS);
-  if (p.gelu_tab && (((EPIS >> EPI_ACT_GELU) | (EPIS >> EPI_ACT_DGELU)) & 1)) {
-    for (int i = tid; i < kGeluTabN / 2; i += 64 * NW) ((float4*)tab)[i] = ((const float4*)p.gelu_tab)[i];
+  if constexpr (C::KW > 1) {      // the other groups' sums, in group order; a lane reads the 16 bytes that its counterpart wrote
+    float4* const red = (float4*)lds_raw;
+    if (kg > 0) {
+#pragma unroll
+      for (int i = 0; i < TI; ++i)
+#pragma unroll
+        for (int j = 0; j < TJ; ++j)
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            red[((((kg - 1) * C::NS + ws) * TI + i) * TJ + j) * 256 + q * 64 + lane] =
+                make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
+    }
+    __syncthreads();
+    if (kg == 0) {
+#pragma unroll
+      for (int g = 0; g < C::KW - 1; ++g)
+#pragma unroll
+        for (int i = 0; i < TI; ++i)
+#pragma unroll
+          for (int j = 0; j < TJ; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              const float4 v = red[(((g * C::NS + ws) * TI + i) * TJ + j) * 256 + q * 64 + lane];
+              acc[i][j][4 * q] += v.x; acc[i][j][4 * q + 1] += v.y; acc[i][j][4 * q + 2] += v.z; acc[i][j][4 * q + 3] += v.w;
+            }
+    }
     __syncthreads();
   }
+
+  const int rbase = m0 + wm * TI * 32, cbase = n0 + wn * TJ * 32;
+  float* stage = (float*)lds_raw + ws * C::EPI_FLOATS;
+  float2* const tab = (float2*)((float*)lds_raw + C::NS * C::EPI_FLOATS);
+  if (p.gelu_tab && (((EPIS >> EPI_ACT_GELU) | (EPIS >> EPI_ACT_DGELU)) & 1)) {
+    for (int i = tid; i < kGeluTabN / 2; i += C::NT) ((float4*)tab)[i] = ((const float4*)p.gelu_tab)[i];
+    __syncthreads();
+  }
+  if (C::KW > 1 && kg > 0) return;
   constexpr auto has = [](int mode) { return (EPIS >> mode) & 1; };
   if (p.partial) { if constexpr (has(EPI_PARTIAL)) tile_epilogue_pipe<EPI_PARTIAL, TI, TJ>(p, acc, rbase, cbase, lane, split, stage, tab); }
   else if (p.c_f32) { if constexpr (has(EPI_F32)) tile_epilogue_pipe<EPI_F32, TI, TJ>(p, acc, rbase, cbase, lane, 0, stage, tab); }
@@ -202,9 +254,8 @@ __device__ __forceinline__ void dma_tile(const GemmDev& p, int m0, int n0, int s
   else { if constexpr (has(EPI_ACT_DGELU)) tile_epilogue_pipe<EPI_ACT_DGELU, TI, TJ>(p, acc, rbase, cbase, lane, 0, stage, tab); }
 }
 
-// OCC: blocks per CU the register allocator leaves room for.
-template <bool AK, bool BKM, int BK, int S, int WGM, int OCC>
-__global__ __launch_bounds__(128 * WGM) __attribute__((amdgpu_waves_per_eu(OCC * WGM / 2, OCC * WGM / 2)))
+template <class C, bool AK, bool BKM>
+__global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(C::WPE, C::WPE)))
 void gemm_bf16_dma(GemmDev p) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char lds_raw[];
   // tile order as in gemm_bf16_wide
@@ -214,37 +265,29 @@ void gemm_bf16_dma(GemmDev p) {
   if (v < 8 * per_xcd) v = (v & 7) * per_xcd + (v >> 3);
   const int split = v / nb;
   int tm, tn;
-  tile_of_block<(WGM >= 4) ? 4 : 8>(v - split * nb, nbx, nby, tm, tn);
-  dma_tile<AK, BKM, BK, S, WGM, wide_epilogues<AK, BKM>()>(p, tm * 64 * WGM, tn * 128, split, lds_raw);
+  tile_of_block<(C::BM >= 256) ? 4 : 8>(v - split * nb, nbx, nby, tm, tn);
+  dma_tile<C, AK, BKM, wide_epilogues<AK, BKM>()>(p, tm * C::BM, tn * C::BN, split, lds_raw);
 }
 
-template <bool AK, bool BKM, int BK, int S, int WGM, int OCC>
+template <class C, bool AK, bool BKM>
 hipError_t launch_dma_one(const GemmDev& p, int splits, hipStream_t s) {
-  constexpr size_t lds = dma_lds_bytes<BK, S, WGM>();
-  static_assert(lds * OCC <= 160 * 1024, "stages do not fit the LDS of a CU");
-  auto kern = gemm_bf16_dma<AK, BKM, BK, S, WGM, OCC>;
+  auto kern = gemm_bf16_dma<C, AK, BKM>;
   static bool configured = false;
-  if (!configured && lds > 48 * 1024) {
-    hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (!configured && C::LDS > 48 * 1024) {
+    hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::LDS);
     if (e != hipSuccess) return e;
   }
   configured = true;
-  hipLaunchKernelGGL(kern, dim3((p.N + 127) / 128, (p.M + 64 * WGM - 1) / (64 * WGM), splits), dim3(128 * WGM), lds, s, p);
+  hipLaunchKernelGGL(kern, dim3((p.N + C::BN - 1) / C::BN, (p.M + C::BM - 1) / C::BM, splits), dim3(C::NT), C::LDS, s, p);
   return hipSuccess;
 }
 
-// the configurations of gemm_bf16_dma that are built: numbers continue those of launch_wide_layout
-constexpr int kFirstDmaCfg = 7;
-template <bool AK, bool BKM>
-hipError_t launch_dma_layout(int cfg, const GemmDev& p, int splits, hipStream_t s) {
-  switch (cfg) {
-    case 7: return launch_dma_one<AK, BKM, 32, 4, 2, 2>(p, splits, s);
-    case 8: return launch_dma_one<AK, BKM, 32, 3, 2, 3>(p, splits, s);
-    case 9: return launch_dma_one<AK, BKM, 64, 2, 2, 2>(p, splits, s);
-    case 10: return launch_dma_one<AK, BKM, 64, 3, 4, 1>(p, splits, s);
-    case 11: return launch_dma_one<AK, BKM, 64, 2, 4, 1>(p, splits, s);
-    default: return hipErrorInvalidValue;
-  }
-}
+// the configurations of gemm_bf16_dma that are built (numbers: kTileCfg in gemm.hip)
+typedef DmaCfg<1, 1, 1, 2, 2, 64, 4, 3> Dma32x64;       // TI TJ WGM WGN KW BK S OCC
+typedef DmaCfg<1, 1, 2, 2, 1, 64, 3, 3> Dma64x64;
+typedef DmaCfg<1, 2, 2, 2, 1, 64, 3, 2> Dma64x128;
+typedef DmaCfg<2, 1, 2, 2, 1, 64, 3, 2> Dma128x64;
+typedef DmaCfg<2, 2, 2, 2, 1, 64, 2, 2> Dma128x128;
+typedef DmaCfg<2, 2, 4, 2, 1, 64, 3, 1> Dma256x128;
 
 }  // namespace

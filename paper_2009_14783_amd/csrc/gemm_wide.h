@@ -457,7 +457,7 @@ hipError_t launch_wide_group_one(const GemmGroupDev& g, hipStream_t s) {
   return hipSuccess;
 }
 
-// the configurations of gemm_bf16_wide that are built (index = configuration number - 1), one layout per translation unit
+// the configurations of gemm_bf16_wide that are built (numbers: kTileCfg in gemm.hip)
 template <bool AK, bool BKM>
 hipError_t launch_wide_layout(int cfg, const GemmDev& p, int splits, hipStream_t s) {
 #define HS_WIDE(TI, TJ, WGM, WGN, BK, NSETS, OCC)                                                        \
@@ -465,9 +465,6 @@ hipError_t launch_wide_layout(int cfg, const GemmDev& p, int splits, hipStream_t
       p, dim3((p.N + 32 * TJ * WGN - 1) / (32 * TJ * WGN), (p.M + 32 * TI * WGM - 1) / (32 * TI * WGM), splits), s)
   switch (cfg) {
     case 1: HS_WIDE(4, 4, 2, 2, 64, 1, 1);
-    case 2: HS_WIDE(4, 3, 2, 2, 64, 2, 1);
-    case 3: HS_WIDE(2, 3, 2, 2, 64, 2, 2);
-    case 4: HS_WIDE(4, 2, 2, 2, 32, 2, 2);
     case 5: HS_WIDE(2, 2, 2, 2, 64, 2, 2);
     case 6: HS_WIDE(4, 2, 2, 2, 64, 2, 1);
     default: return hipErrorInvalidValue;

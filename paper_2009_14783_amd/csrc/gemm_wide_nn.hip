@@ -1,8 +1,8 @@
 // gemm_bf16_wide for A m-major, B n-major
-#include "gemm_dma.h"
+#include "gemm_ksplit.h"
 
 hipError_t gemm_wide_launch_nn(int cfg, const GemmDev& p, int splits, hipStream_t s) {
-  return cfg >= kFirstDmaCfg ? launch_dma_layout<false, false>(cfg, p, splits, s) : launch_wide_layout<false, false>(cfg, p, splits, s);
+  return launch_layout<false, false>(cfg, p, splits, s);
 }
 
 // the weight-gradient products of a layer in one launch: 256 x 128 x 64 tiles, one block per CU

@@ -446,6 +446,7 @@ hs_status hs_s2s_loss(hs_ctx* ctx, const void* w, const void* dec_out, const int
   ga.c_f32 = 1; ga.beta = accumulate ? 1.f : 0.f; ga.ws = h.gemm_ws; ga.ws_bytes = h.gemm_ws_bytes;
   HS_TRY(launch_gemm(ctx, ga, s));
   ga = gemm_args(dt, 1, 0, M, H, V, h.dlogits, Vp, W(dt, w, o.emb), H, dX, H);
+  ga.a_kpad = 1;      // the loss kernel writes zeros into the padding columns of d logits
   ga.ws = h.gemm_ws; ga.ws_bytes = h.gemm_ws_bytes;
   HS_TRY(launch_gemm(ctx, ga, s));
   if (compact) {

@@ -173,6 +173,39 @@ def test_gemm_every_tiling_ragged_edges_and_epilogues(hs, variant):
         hs.hs_tune_gemm_variant(-1)
 
 
+@pytest.mark.parametrize("M,N,K", [(1, 64, 64), (31, 96, 192), (33, 768, 768), (65, 136, 3072), (264, 512, 512), (513, 2048, 128), (1030, 768, 448)])
+@pytest.mark.parametrize("layout", LAYOUTS)
+def test_gemm_bf16_few_tiles(hs, M, N, K, layout):
+    """Products whose rows, columns and contraction end at, before and after the edges of the 32- and 64-wide tiles, from one tile
+    to a few hundred (the automatic choice runs over all of them), with an epilogue and with the contraction split over
+    blocks.  m-major operands: a contraction that ends inside a k-tile."""
+    ak, bk = layout
+    rng = np.random.default_rng(M + N + K)
+    if not ak:
+        K += 24
+    pad = lambda n: (n + 7) // 8 * 8
+    A = np.zeros((M, K) if ak else (K, pad(M)), np.float32)
+    A[:, :K if ak else M] = rng.standard_normal((M, K) if ak else (K, M)) * 0.1
+    B = (rng.standard_normal((N, K) if bk else (K, N)) * 0.1).astype(np.float32)
+    R = rng.standard_normal((M, N)).astype(np.float32)
+    dA, dB, dR = (dev(a, torch.bfloat16) for a in (A, B, R))
+    Ar, Br = rounded(A, 1), rounded(B, 1)
+    prod = (Ar if ak else Ar[:, :M].T) @ (Br if bk else Br.T).T
+    ws = torch.zeros(32 << 20, dtype=torch.uint8, device="cuda")
+    for scratch in (None, ws):
+        sb = 0 if scratch is None else ws.numel()
+        if ak:     # the result is rounded to bf16 once: 2^-9 relative
+            out = torch.zeros(M, N, dtype=torch.bfloat16, device="cuda")
+            hs.hs_op_gemm(1, ak, bk, M, N, K, dA, A.shape[1], dB, B.shape[1], out, N, epi=1, aux=dR, ldaux=N, scratch=scratch, scratch_bytes=sb)
+            torch.cuda.synchronize()
+            assert rel(host(out), prod + rounded(R, 1)) < 4e-3, scratch is None
+        else:      # fp32 result: the order of the sum only
+            dC = dev(R)
+            hs.hs_op_gemm(1, ak, bk, M, N, K, dA, A.shape[1], dB, B.shape[1], dC, N, c_f32=1, beta=1.0, scratch=scratch, scratch_bytes=sb)
+            torch.cuda.synchronize()
+            assert rel(host(dC), R.astype(np.float64) + prod) < 2e-6, scratch is None
+
+
 def test_gemm_variant_out_of_range_is_an_error(hs):
     for v in (-2, 12, 1000):
         with pytest.raises(hs.HsError):
