@@ -6,6 +6,8 @@
 
 namespace {
 
+constexpr int kFewRows = 2048;      // see BwdPlan
+
 struct Carver {
   char* base; size_t off;
   explicit Carver(void* p) : base((char*)p), off(0) {}
@@ -70,10 +72,22 @@ HeadWs carve_head(const hs_model_cfg& c, int M, void* base) {
   return w;
 }
 
+// How the backward pass hands work to the second stream.  The weight-gradient products and the column sums only consume what
+// the chain of activation gradients produces; they run on the second stream behind an event.  An event and the wait for it cost
+// the host 10 us and the GPU about as much, four times a launch, so a pass over few rows, whose kernels take 5 us, hands over several layers at
+// once; the operand buffers then exist once per layer (there is no waiting for them to be free again).  With many rows each layer is
+// handed over by itself, the sooner the better, and the buffers exist twice, by layer parity.
+// 264 rows (BERT-base): 4.63 ms per step with an event per layer, 4.18 with one per four.
+struct BwdPlan { int sets, layers_per_hand_over; };
+BwdPlan bwd_plan(const hs_model_cfg& c, int B, int L) {
+  const bool few = (int64_t)B * L <= kFewRows;
+  return BwdPlan{few ? c.n_layers : std::min(2, c.n_layers), few ? 4 : 1};
+}
+
+struct BwdSet { void *dy2, *dy1, *dy2m, *dy1m, *dh, *dqkv, *ln_part2, *ln_part1; };
 struct BwdWs {
-  // dy2, dy1, dh and dqkv exist twice (by layer parity): the weight-gradient GEMMs that read them run
-  // on a second stream and may still be in flight while the next layer produces its own
-  void *dxa, *dxb, *dy2[2], *dy1[2], *dy2m[2], *dy1m[2], *dh[2], *dqkv[2], *dctx, *ln_part, *ln_part2[2], *ln_part1[2], *cs_part, *emb, *gemm_ws, *gemm_ws_side, *ones;
+  std::vector<BwdSet> set;
+  void *dxa, *dxb, *dctx, *ln_part, *emb, *gemm_ws;
   float* dvec;
   size_t total, gemm_ws_bytes;
 };
@@ -82,23 +96,18 @@ BwdWs carve_bwd(const hs_model_cfg& c, int B, int L, void* base) {
   Carver cv(base);
   BwdWs w;
   w.dxa = cv.take(T * H * es); w.dxb = cv.take(T * H * es); w.dctx = cv.take(T * H * es);
-  for (int k = 0; k < 2; ++k) {
-    w.dy2[k] = cv.take(T * H * es); w.dy1[k] = cv.take(T * H * es);
-    w.dy2m[k] = cv.take(T * H * es); w.dy1m[k] = cv.take(T * H * es);     // masked copies (dropout only)
-    w.dh[k] = cv.take(T * F * es); w.dqkv[k] = cv.take(T * 3 * H * es);
+  w.set.resize(bwd_plan(c, B, L).sets);
+  for (BwdSet& q : w.set) {
+    q.dy2 = cv.take(T * H * es); q.dy1 = cv.take(T * H * es);
+    q.dy2m = cv.take(T * H * es); q.dy1m = cv.take(T * H * es);     // masked copies (dropout only)
+    q.dh = cv.take(T * F * es); q.dqkv = cv.take(T * 3 * H * es);
+    q.ln_part2 = cv.take(layernorm_bwd_scratch((int)T, (int)H)); q.ln_part1 = cv.take(layernorm_bwd_scratch((int)T, (int)H));
   }
   w.dvec = (float*)cv.take((size_t)B * c.n_heads * L * sizeof(float));
   w.ln_part = cv.take(layernorm_bwd_scratch((int)T, (int)H));
-  for (int k = 0; k < 2; ++k) {
-    w.ln_part2[k] = cv.take(layernorm_bwd_scratch((int)T, (int)H));
-    w.ln_part1[k] = cv.take(layernorm_bwd_scratch((int)T, (int)H));
-  }
-  w.cs_part = cv.take(colsum_scratch((int)T, (int)std::max(F, 3 * H)));
   w.emb = cv.take(embed_bwd_scratch((int)T, (int)H));
   w.gemm_ws_bytes = gemm_scratch_bytes(c);
   w.gemm_ws = cv.take(w.gemm_ws_bytes);
-  w.gemm_ws_side = cv.take(w.gemm_ws_bytes);
-  w.ones = cv.take(T * 8 * es);          // [T, 8] of 1.0: bias gradients as products with a column of ones
   w.total = cv.off;
   return w;
 }
@@ -378,157 +387,127 @@ static hs_status encoder_bwd_impl(hs_ctx* ctx, const hs_ctx::Armed& upd, const v
   hipStream_t s = (hipStream_t)stream;
   Acts a = carve_acts(c, B, L, const_cast<void*>(acts));
   BwdWs ws = carve_bwd(c, B, L, workspace);
+  const BwdPlan plan = bwd_plan(c, B, L);
   const float beta = accumulate ? 1.f : 0.f;
   const DropCfg* drop = ctx->drop.thr ? &ctx->drop : nullptr;
   auto run_gemm = [&](GemmArgs& a) { a.ws = ws.gemm_ws; a.ws_bytes = ws.gemm_ws_bytes; return launch_gemm(ctx, a, s); };
 
-  // The weight-gradient GEMMs only consume; they run on a second stream so that their ramp-up and tail
-  // overlap the activation-gradient chain.  Per layer: four "operand ready" events (main -> side),
-  // one "layer done" event (side -> main, waited on before the operand buffers of that parity are
-  // reused two layers later and at the end of the call).  With per-launch timing enabled everything
-  // stays on the caller's stream so that the timings do not overlap.
+  // s: the chain of activation gradients.  sd: what only consumes (see BwdPlan).  su: an armed optimizer update; with few rows it
+  // follows the gradients on sd.  With per-launch timing everything stays on the caller's stream so that the timings do
+  // not overlap.
   const bool overlap = ctx->prof == nullptr;
   const int NL = c.n_layers;
-  if (overlap) HS_TRY(ensure_side_stream(ctx, (size_t)6 * NL + 5));
-  hipStream_t sd = overlap ? ctx->side : s;
-  // third stream for an armed optimizer update (events 6 NL .. 6 NL + 2: head ready, embeddings ready, done)
-  if (overlap && upd.on && !ctx->upd) HS_HIP_CHECK(ctx, hipStreamCreateWithFlags(&ctx->upd, hipStreamNonBlocking));
-  hipStream_t su = (overlap && upd.on) ? ctx->upd : s;
-  // the update stream continues after the caller's stream has got here (the caller's stream may be the
-  // null stream, so it cannot double as a flag) ...
-  auto after_main = [&](hipEvent_t e) -> hs_status {
-    if (!overlap) return HS_OK;
-    HS_HIP_CHECK(ctx, hipEventRecord(e, s));
-    HS_HIP_CHECK(ctx, hipStreamWaitEvent(su, e, 0));
+  const bool own_upd = overlap && upd.on && plan.layers_per_hand_over == 1;
+  if (overlap) HS_TRY(ensure_side_stream(ctx, (size_t)4 * NL + 8));
+  if (own_upd && !ctx->upd) HS_HIP_CHECK(ctx, hipStreamCreateWithFlags(&ctx->upd, hipStreamNonBlocking));
+  hipStream_t sd = overlap ? ctx->side : s, su = own_upd ? ctx->upd : sd;
+  size_t next_event = 0;
+  // work enqueued on `to` from here on comes after what is on `from` now
+  auto order = [&](hipStream_t from, hipStream_t to) -> hs_status {
+    if (from == to) return HS_OK;
+    hipEvent_t e = ctx->events[next_event++];
+    HS_HIP_CHECK(ctx, hipEventRecord(e, from));
+    HS_HIP_CHECK(ctx, hipStreamWaitEvent(to, e, 0));
     return HS_OK;
   };
-  // ... or after an event that has already been recorded on the second stream
-  auto after_event = [&](hipEvent_t e) -> hs_status {
-    if (!overlap) return HS_OK;
-    HS_HIP_CHECK(ctx, hipStreamWaitEvent(su, e, 0));
+  std::vector<GemmArgs> dw;                  // weight and bias gradients not yet enqueued
+  std::vector<LnColsJob> cols;               // ... and LayerNorm column sums
+  std::vector<hipEvent_t> done(NL, nullptr); // recorded on sd behind the gradients of a layer (buffer sets that are used again)
+  auto enqueue_grads = [&]() -> hs_status {
+    HS_TRY(launch_layernorm_bwd_cols_batch(ctx, cols.data(), (int)cols.size(), beta, T, H, sd));
+    HS_TRY(launch_gemm_group(ctx, dw.data(), (int)dw.size(), sd));
+    cols.clear(); dw.clear();
     return HS_OK;
   };
-  if (upd.on) {      // the head's gradients were completed by hs_mlm_loss, earlier on the caller's stream
-    HS_TRY(after_main(ctx->events[(size_t)6 * NL]));
+
+  // the second stream begins here: the sort of the token ids that the embedding gradient needs depends on nothing computed by
+  // this call; the head's gradients were completed by hs_mlm_loss, earlier on the caller's stream
+  HS_TRY(order(s, sd));
+  hipEvent_t sorted = nullptr;
+  if (overlap) {
+    HS_TRY(launch_embed_sort(ctx, ids, T, c.vocab, ws.emb, sd));
+    sorted = ctx->events[next_event++];
+    HS_HIP_CHECK(ctx, hipEventRecord(sorted, sd));
+  }
+  if (upd.on) {
+    HS_TRY(order(sd, su));
     HS_TRY(update_slice(ctx, upd, o.head_t_w, o.total, su));
   }
-  auto ev = [&](int layer, int k) { return ctx->events[(size_t)layer * 6 + k]; };
-  auto hand_over = [&](int layer, int k) -> hs_status {      // main has produced operand k of this layer
-    if (!overlap) return HS_OK;
-    HS_HIP_CHECK(ctx, hipEventRecord(ev(layer, k), s));
-    HS_HIP_CHECK(ctx, hipStreamWaitEvent(sd, ev(layer, k), 0));
-    return HS_OK;
-  };
-  auto side_gemm = [&](GemmArgs& a) { a.ws = ws.gemm_ws_side; a.ws_bytes = ws.gemm_ws_bytes; a.c_f32 = 1; a.beta = beta; return launch_gemm(ctx, a, sd); };
-
-  // bf16: the weight gradients of a layer go out as one grouped launch once the layer's last operand (d qkv) exists
-  const bool grouped = dt == HS_BF16;
-  if (grouped) HS_TRY(launch_fill_value(ctx, dt, ws.ones, (size_t)T * 8, 1.0f, s));
-  // The sort of the token ids that the embedding gradient needs depends on nothing computed here: on the second
-  // stream, ahead of everything else (events 6 NL + 3: the caller's stream has got here, 6 NL + 4: sorted).
-  if (overlap) {
-    HS_HIP_CHECK(ctx, hipEventRecord(ctx->events[(size_t)6 * NL + 3], s));
-    HS_HIP_CHECK(ctx, hipStreamWaitEvent(sd, ctx->events[(size_t)6 * NL + 3], 0));
-    HS_TRY(launch_embed_sort(ctx, ids, T, c.vocab, ws.emb, sd));
-    HS_HIP_CHECK(ctx, hipEventRecord(ctx->events[(size_t)6 * NL + 4], sd));
-  }
   const void* dcur = d_hidden;
+  int chunk_top = NL - 1;                    // the highest layer whose gradients are not yet enqueued
   for (int i = NL - 1; i >= 0; --i) {
     const LayerOff& lo = o.layer[i];
     LayerActs& la = a.layer[i];
     const void* x_in = (i == 0) ? a.x0 : a.layer[i - 1].x2;
-    const int par = i & 1;
-    void *dy2 = ws.dy2[par], *dy1 = ws.dy1[par], *dh = ws.dh[par], *dqkv = ws.dqkv[par];
+    const int nsets = (int)ws.set.size();
+    const BwdSet& q = ws.set[i % nsets];
     // With dropout the gradient that enters the two dropped branches is the masked one; the residual paths
     // keep the unmasked gradient.
-    void* dy2b = drop ? ws.dy2m[par] : dy2;
-    void* dy1b = drop ? ws.dy1m[par] : dy1;
-    if (overlap && i + 2 < NL) HS_HIP_CHECK(ctx, hipStreamWaitEvent(s, ev(i + 2, 4), 0));   // buffers of this parity are free again
-    // LN2 backward: dy2 on the main chain; d gain/bias and colsum(dy2) = d b2 from its partials beside it
-    HS_TRY(launch_layernorm_bwd_rows(ctx, dt, dcur, la.y2, la.st2, W(ctx, w, lo.ln2_g), dy2, T, H, ws.ln_part2[par], s, drop,
-                                     site_ffn_out(i), drop ? 2 : 0, dy2b));
-    if (!grouped) {
-      HS_TRY(hand_over(i, 0));
-      HS_TRY(launch_layernorm_bwd_cols(ctx, ws.ln_part2[par], g + lo.ln2_g, g + lo.ln2_b, g + lo.ffn2_b, beta, T, H, sd));
-    }
-    // dW2 [H,F] = dy2^T h
-    GemmArgs gw2 = gemm_args(dt, 0, 0, H, F, T, dy2b, H, la.h, F, g + lo.ffn2_w, F);
-    if (!grouped) HS_TRY(side_gemm(gw2));
+    void* dy2b = drop ? q.dy2m : q.dy2;
+    void* dy1b = drop ? q.dy1m : q.dy1;
+    if (overlap && i + nsets < NL) HS_HIP_CHECK(ctx, hipStreamWaitEvent(s, done[i + nsets], 0));   // this set's buffers are free again
+    // LN2 backward: dy2 here; d gain/bias and colsum(dy2) = d b2 from its partials
+    HS_TRY(launch_layernorm_bwd_rows(ctx, dt, dcur, la.y2, la.st2, W(ctx, w, lo.ln2_g), q.dy2, T, H, q.ln_part2, s, drop, site_ffn_out(i),
+                                     drop ? 2 : 0, dy2b));
     // dhpre [T,F] = (dy2 W2) * GELU'(hpre)
-    GemmArgs ga = gemm_args(dt, 1, 0, T, F, H, dy2b, H, W(ctx, w, lo.ffn2_w), F, dh, F);
+    GemmArgs ga = gemm_args(dt, 1, 0, T, F, H, dy2b, H, W(ctx, w, lo.ffn2_w), F, q.dh, F);
     ga.epi = 3; ga.aux = la.hpre; ga.ldaux = F;
     HS_TRY(run_gemm(ga));
-    if (!grouped) {
-      HS_TRY(hand_over(i, 1));
-      HS_TRY(launch_colsum(ctx, dt, dh, F, T, F, g + lo.ffn1_b, beta, ws.cs_part, sd));
-    }
-    // dW1 [F,H] = dhpre^T x1
-    GemmArgs gw1 = gemm_args(dt, 0, 0, F, H, T, dh, F, la.x1, H, g + lo.ffn1_w, H);
-    if (!grouped) HS_TRY(side_gemm(gw1));
     // dx1 [T,H] = dhpre W1 + dy2
-    ga = gemm_args(dt, 1, 0, T, H, F, dh, F, W(ctx, w, lo.ffn1_w), H, ws.dxa, H);
-    ga.epi = 1; ga.aux = dy2; ga.ldaux = H;
+    ga = gemm_args(dt, 1, 0, T, H, F, q.dh, F, W(ctx, w, lo.ffn1_w), H, ws.dxa, H);
+    ga.epi = 1; ga.aux = q.dy2; ga.ldaux = H;
     HS_TRY(run_gemm(ga));
     // LN1 backward: dy1, d gain/bias, colsum(dy1) = d bo
-    HS_TRY(launch_layernorm_bwd_rows(ctx, dt, ws.dxa, la.y1, la.st1, W(ctx, w, lo.ln1_g), dy1, T, H, ws.ln_part1[par], s, drop,
+    HS_TRY(launch_layernorm_bwd_rows(ctx, dt, ws.dxa, la.y1, la.st1, W(ctx, w, lo.ln1_g), q.dy1, T, H, q.ln_part1, s, drop,
                                      site_attention_out(i), drop ? 2 : 0, dy1b));
-    if (!grouped) {
-      HS_TRY(hand_over(i, 2));
-      HS_TRY(launch_layernorm_bwd_cols(ctx, ws.ln_part1[par], g + lo.ln1_g, g + lo.ln1_b, g + lo.o_b, beta, T, H, sd));
-    }
-    // dWo [H,H] = dy1^T ctx ; dctx = dy1 Wo
-    GemmArgs gwo = gemm_args(dt, 0, 0, H, H, T, dy1b, H, la.ctx, H, g + lo.o_w, H);
-    if (!grouped) HS_TRY(side_gemm(gwo));
+    // dctx = dy1 Wo
     ga = gemm_args(dt, 1, 0, T, H, H, dy1b, H, W(ctx, w, lo.o_w), H, ws.dctx, H);
     HS_TRY(run_gemm(ga));
-    HS_TRY(launch_attention_bwd(ctx, dt, la.qkv, la.ctx, la.lse, ws.dctx, lens, B, L, c.n_heads, dqkv, ws.dvec, s, drop,
+    HS_TRY(launch_attention_bwd(ctx, dt, la.qkv, la.ctx, la.lse, ws.dctx, lens, B, L, c.n_heads, q.dqkv, ws.dvec, s, drop,
                                 site_attention_prob(i)));
-    HS_TRY(hand_over(i, 3));
-    // dWqkv [3H,H] = dqkv^T x_in ; dx_in = dqkv Wqkv + dy1
-    GemmArgs gwq = gemm_args(dt, 0, 0, 3 * H, H, T, dqkv, 3 * H, x_in, H, g + lo.qkv_w, H);
-    if (!grouped) {
-      HS_TRY(launch_colsum(ctx, dt, dqkv, 3 * H, T, 3 * H, g + lo.qkv_b, beta, ws.cs_part, sd));
-      HS_TRY(side_gemm(gwq));
-    } else {
-      // Every weight gradient of the layer, and the two bias gradients that are not by-products of a LayerNorm
-      // backward (as products with a column of ones), in ONE launch on the second stream: 237 tiles of 256 x 128 for
-      // 256 CUs at BERT-base size, each over the whole contraction, so no partial sums travel through memory.
-      HS_TRY(launch_layernorm_bwd_cols(ctx, ws.ln_part2[par], g + lo.ln2_g, g + lo.ln2_b, g + lo.ffn2_b, beta, T, H, sd));
-      HS_TRY(launch_layernorm_bwd_cols(ctx, ws.ln_part1[par], g + lo.ln1_g, g + lo.ln1_b, g + lo.o_b, beta, T, H, sd));
-      GemmArgs gb1 = gemm_args(dt, 0, 0, F, 1, T, dh, F, ws.ones, 8, g + lo.ffn1_b, 1);
-      GemmArgs gbq = gemm_args(dt, 0, 0, 3 * H, 1, T, dqkv, 3 * H, ws.ones, 8, g + lo.qkv_b, 1);
-      GemmArgs group[6] = {gw2, gw1, gwq, gwo, gb1, gbq};
-      for (GemmArgs& a : group) { a.c_f32 = 1; a.beta = beta; }
-      HS_TRY(launch_gemm_group(ctx, group, 6, sd));
+    // dW2 [H,F] = dy2^T h, dW1 [F,H] = dhpre^T x1, dWqkv [3H,H] = dqkv^T x_in, dWo [H,H] = dy1^T ctx, and the two bias gradients that
+    // are not by-products of a LayerNorm backward (products with a column of ones)
+    cols.push_back({q.ln_part2, g + lo.ln2_g, g + lo.ln2_b, g + lo.ffn2_b});
+    cols.push_back({q.ln_part1, g + lo.ln1_g, g + lo.ln1_b, g + lo.o_b});
+    GemmArgs grad[6] = {gemm_args(dt, 0, 0, H, F, T, dy2b, H, la.h, F, g + lo.ffn2_w, F), gemm_args(dt, 0, 0, F, H, T, q.dh, F, la.x1, H, g + lo.ffn1_w, H),
+                        gemm_args(dt, 0, 0, 3 * H, H, T, q.dqkv, 3 * H, x_in, H, g + lo.qkv_w, H), gemm_args(dt, 0, 0, H, H, T, dy1b, H, la.ctx, H, g + lo.o_w, H),
+                        gemm_args(dt, 0, 0, F, 1, T, q.dh, F, nullptr, 0, g + lo.ffn1_b, 1), gemm_args(dt, 0, 0, 3 * H, 1, T, q.dqkv, 3 * H, nullptr, 0, g + lo.qkv_b, 1)};
+    for (GemmArgs& ga : grad) { ga.c_f32 = 1; ga.beta = beta; dw.push_back(ga); }
+    const bool chunk_done = i == 0 || chunk_top - i + 1 == plan.layers_per_hand_over;
+    if (plan.layers_per_hand_over == 1) {
+      HS_TRY(order(s, sd));
+      HS_TRY(enqueue_grads());
+      if (overlap) { done[i] = ctx->events[next_event++]; HS_HIP_CHECK(ctx, hipEventRecord(done[i], sd)); }
     }
-    if (overlap) HS_HIP_CHECK(ctx, hipEventRecord(ev(i, 4), sd));
-    ga = gemm_args(dt, 1, 0, T, H, 3 * H, dqkv, 3 * H, W(ctx, w, lo.qkv_w), H, ws.dxb, H);
-    ga.epi = 1; ga.aux = dy1; ga.ldaux = H;
+    // dx_in = dqkv Wqkv + dy1
+    ga = gemm_args(dt, 1, 0, T, H, 3 * H, q.dqkv, 3 * H, W(ctx, w, lo.qkv_w), H, ws.dxb, H);
+    ga.epi = 1; ga.aux = q.dy1; ga.ldaux = H;
     HS_TRY(run_gemm(ga));
     dcur = ws.dxb;
-    if (upd.on) {
-      // Every gradient of this layer is final once the second stream has got to its "layer done" event, and
-      // its weights are no longer read once the main chain has finished the GEMM above.
-      HS_TRY(after_event(ev(i, 4)));
-      HS_TRY(after_main(ev(i, 5)));
-      HS_TRY(update_slice(ctx, upd, lo.qkv_w, i + 1 < NL ? o.layer[i + 1].qkv_w : o.head_t_w, su));
+    if (plan.layers_per_hand_over > 1 && chunk_done) {
+      HS_TRY(order(s, sd));
+      HS_TRY(enqueue_grads());
     }
+    if (upd.on && chunk_done) {
+      // The gradients of these layers are final once sd has got here, and their weights are no longer read once s has
+      // finished the product above.
+      if (own_upd) {
+        HS_HIP_CHECK(ctx, hipStreamWaitEvent(su, done[i], 0));
+        HS_TRY(order(s, su));
+      }
+      HS_TRY(update_slice(ctx, upd, lo.qkv_w, chunk_top + 1 < NL ? o.layer[chunk_top + 1].qkv_w : o.head_t_w, su));
+    }
+    if (chunk_done) chunk_top = i - 1;
   }
   // embedding LayerNorm, then the two embedding tables
   HS_TRY(launch_layernorm_bwd(ctx, dt, dcur, a.e_pre, a.emb_stats, W(ctx, w, o.emb_ln_g), ws.dxa, g + o.emb_ln_g,
                               g + o.emb_ln_b, nullptr, beta, T, H, ws.ln_part, s, drop, site_embedding(), drop ? 1 : 0, nullptr));
-  if (overlap) HS_HIP_CHECK(ctx, hipStreamWaitEvent(s, ctx->events[(size_t)6 * NL + 4], 0));
+  if (overlap) HS_HIP_CHECK(ctx, hipStreamWaitEvent(s, sorted, 0));
   HS_TRY(launch_embed_bwd(ctx, dt, ws.dxa, ids, B, L, H, c.vocab, c.max_pos, g + o.emb_word, g + o.emb_pos, beta, ws.emb, s, overlap));
-  if (upd.on) {      // the embedding tables and their LayerNorm last
-    HS_TRY(after_main(ctx->events[(size_t)6 * NL + 1]));
-    HS_TRY(update_slice(ctx, upd, 0, o.layer[0].qkv_w, su));
-    if (overlap) {
-      HS_HIP_CHECK(ctx, hipEventRecord(ctx->events[(size_t)6 * NL + 2], su));
-      HS_HIP_CHECK(ctx, hipStreamWaitEvent(s, ctx->events[(size_t)6 * NL + 2], 0));
-    }
-  }
-  // everything the second stream did is ordered before whatever the caller enqueues next
-  if (overlap) HS_HIP_CHECK(ctx, hipStreamWaitEvent(s, ev(0, 4), 0));
+  if (upd.on) HS_TRY(update_slice(ctx, upd, 0, o.layer[0].qkv_w, s));      // the embedding tables and their LayerNorm last, on the chain
+  // everything the other streams did is ordered before whatever the caller enqueues next
+  HS_TRY(order(sd, s));
+  if (own_upd) HS_TRY(order(su, s));
   return HS_OK;
 }
 
@@ -545,6 +524,8 @@ hs_status hs_op_gemm(int32_t dtype, int32_t a_kmajor, int32_t b_kmajor, int32_t 
                      const void* aux, int64_t ldaux, void* C2, void* scratch, size_t scratch_bytes, void* stream) {
   if (dtype != HS_FP32 && dtype != HS_BF16) return hs_fail(nullptr, HS_ERR_INVALID_ARG, "hs_op_gemm: bad dtype");
   if (M < 0 || N < 0 || K < 0) return hs_fail(nullptr, HS_ERR_INVALID_ARG, "hs_op_gemm: negative size");
+  if (M > 0 && N > 0 && (epi < 0 || epi > 3)) return hs_fail(nullptr, HS_ERR_INVALID_ARG, "hs_op_gemm: bad epilogue");
+  if (M > 0 && N > 0 && !B) return hs_fail(nullptr, HS_ERR_INVALID_ARG, "hs_op_gemm: NULL operand");
   GemmArgs g = gemm_args(dtype, a_kmajor ? 1 : 0, b_kmajor ? 1 : 0, M, N, K, A, lda, B, ldb, C, ldc);
   g.c_f32 = c_f32 ? 1 : 0; g.beta = beta; g.bias = bias; g.epi = epi; g.aux = aux; g.ldaux = ldaux; g.C2 = C2;
   g.ws = scratch; g.ws_bytes = scratch ? scratch_bytes : 0;

@@ -206,12 +206,12 @@ struct GemmArgs {
   const DropCfg* drop; uint32_t drop_site;   // optional (epi == 1): dropout of product + bias before the residual
 };
 hs_status launch_gemm(hs_ctx* ctx, const GemmArgs& g, hipStream_t s);
-// up to 8 weight-gradient products (A m-major, B n-major, fp32 C = beta C + product) in one launch; other argument
-// sets run one by one
+// weight-gradient products (A m-major, B n-major or null for a column of ones, fp32 C = beta C + product, the same beta) in one launch
+// per 48 of them (bf16; fp32: one each)
+hs_status launch_gemm_group(hs_ctx* ctx, const GemmArgs* gs, int n, hipStream_t s);
 // timing runs: every bf16 product with M, N, K >= 256 that configuration `variant` can serve uses it (-1: automatic choice); process-wide
 int gemm_variant_count();
 void gemm_set_variant(int variant);
-hs_status launch_gemm_group(hs_ctx* ctx, const GemmArgs* gs, int n, hipStream_t s);
 
 // stats: R means, then (stat_ld floats after the first mean; default R) R reciprocal standard deviations
 hs_status launch_layernorm_fwd(hs_ctx* ctx, int dtype, const void* x, const void* gain, const void* bias, void* y,
@@ -228,6 +228,9 @@ hs_status launch_layernorm_bwd_rows(hs_ctx* ctx, int dtype, const void* dy, cons
                                     int drop_mode = 0, void* dxm = nullptr);
 hs_status launch_layernorm_bwd_cols(hs_ctx* ctx, const void* partials, float* d_gain, float* d_bias, float* d_colsum, float beta, int R, int H,
                                     hipStream_t s);
+struct LnColsJob { const void* partials; float *d_gain, *d_bias, *d_colsum; };      // what launch_layernorm_bwd_cols is given
+constexpr int kLnColsMax = 48;
+hs_status launch_layernorm_bwd_cols_batch(hs_ctx* ctx, const LnColsJob* jobs, int n, float beta, int R, int H, hipStream_t s);
 hs_status launch_embed_ln_fwd(hs_ctx* ctx, int dtype, const void* word, const void* pos, const void* gain, const void* bias,
                               const int32_t* ids, void* e_pre, void* x0, float* stats, int B, int L, int H, int V, float eps,
                               hipStream_t s, const DropCfg* drop = nullptr, int stat_ld = 0);
@@ -271,8 +274,6 @@ hs_status launch_embed_scale_pos(hs_ctx* ctx, int dtype, const void* emb, const 
                                  float scale, const DropCfg* drop, uint32_t site, hipStream_t s);
 hs_status launch_mask_scale(hs_ctx* ctx, int dtype, const void* x, void* y, size_t n, float alpha, const DropCfg* drop, uint32_t site,
                             hipStream_t s);
-hs_status launch_relu(hs_ctx* ctx, int dtype, void* x, size_t n, hipStream_t s);
-hs_status launch_relu_bwd(hs_ctx* ctx, int dtype, void* dx, const void* h, size_t n, hipStream_t s);
 hs_status launch_real_rows(hs_ctx* ctx, const int32_t* lens, int B, int L, int32_t* rows, int capacity, hipStream_t s);
 hs_status launch_smoothed_ce(hs_ctx* ctx, int dtype, const float* logits, int64_t ldl, const int32_t* labels, const int32_t* lens, int M, int L,
                              int V, float eps, void* dlogits, float* row_loss, float* row_nll, float* loss_sum, float* nll_sum,

@@ -10,7 +10,10 @@
 hipError_t gemm_wide_launch_kk(int cfg, const GemmDev& p, int splits, hipStream_t s);
 hipError_t gemm_wide_launch_kn(int cfg, const GemmDev& p, int splits, hipStream_t s);
 hipError_t gemm_wide_launch_nn(int cfg, const GemmDev& p, int splits, hipStream_t s);
-hipError_t gemm_wide_group_launch_nn(const GemmGroupDev& g, hipStream_t s);
+hipError_t gemm_group_launch_nn(int cfg, const GemmGroupDev& g, hipStream_t s);
+int gemm_f32_tile(int64_t tiles128);
+void gemm_f32_launch(bool a_kmajor, bool b_kmajor, const GemmDev& p, hipStream_t s);
+void gemm_f32_group_launch(int tile, const GemmGroupDev& g, hipStream_t s);
 
 namespace {
 
@@ -232,14 +235,18 @@ void gemm_bf16_mfma(GemmDev p) {
     else if (p.epi == 0) tile_epilogue_lds<EPI_ACT, TI, TJ>(p, acc, rbase, cbase, lane, 0, stage);
     else if (p.epi == 1) tile_epilogue_lds<EPI_ACT_RES, TI, TJ>(p, acc, rbase, cbase, lane, 0, stage);
     else if (p.epi == 2) tile_epilogue_lds<EPI_ACT_GELU, TI, TJ>(p, acc, rbase, cbase, lane, 0, stage);
-    else tile_epilogue_lds<EPI_ACT_DGELU, TI, TJ>(p, acc, rbase, cbase, lane, 0, stage);
+    else if (p.epi == 3) tile_epilogue_lds<EPI_ACT_DGELU, TI, TJ>(p, acc, rbase, cbase, lane, 0, stage);
+    else if (p.epi == 4) tile_epilogue_lds<EPI_ACT_RELU, TI, TJ>(p, acc, rbase, cbase, lane, 0, stage);
+    else tile_epilogue_lds<EPI_ACT_DRELU, TI, TJ>(p, acc, rbase, cbase, lane, 0, stage);
   } else {
     if (p.partial) tile_epilogue<EPI_PARTIAL, TI, TJ>(p, acc, rbase, cbase, lane, split);
     else if (p.c_f32) tile_epilogue<EPI_F32, TI, TJ>(p, acc, rbase, cbase, lane, 0);
     else if (p.epi == 0) tile_epilogue<EPI_ACT, TI, TJ>(p, acc, rbase, cbase, lane, 0);
     else if (p.epi == 1) tile_epilogue<EPI_ACT_RES, TI, TJ>(p, acc, rbase, cbase, lane, 0);
     else if (p.epi == 2) tile_epilogue<EPI_ACT_GELU, TI, TJ>(p, acc, rbase, cbase, lane, 0);
-    else tile_epilogue<EPI_ACT_DGELU, TI, TJ>(p, acc, rbase, cbase, lane, 0);
+    else if (p.epi == 3) tile_epilogue<EPI_ACT_DGELU, TI, TJ>(p, acc, rbase, cbase, lane, 0);
+    else if (p.epi == 4) tile_epilogue<EPI_ACT_RELU, TI, TJ>(p, acc, rbase, cbase, lane, 0);
+    else tile_epilogue<EPI_ACT_DRELU, TI, TJ>(p, acc, rbase, cbase, lane, 0);
   }
 }
 
@@ -261,7 +268,9 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(GemmDev p, int split
     else if (p.epi == 0) store_quad<EPI_ACT>(q, row, col, s, quad_aligned<EPI_ACT>(q), 0);
     else if (p.epi == 1) store_quad<EPI_ACT_RES>(q, row, col, s, quad_aligned<EPI_ACT_RES>(q), 0);
     else if (p.epi == 2) store_quad<EPI_ACT_GELU>(q, row, col, s, quad_aligned<EPI_ACT_GELU>(q), 0);
-    else store_quad<EPI_ACT_DGELU>(q, row, col, s, quad_aligned<EPI_ACT_DGELU>(q), 0);
+    else if (p.epi == 3) store_quad<EPI_ACT_DGELU>(q, row, col, s, quad_aligned<EPI_ACT_DGELU>(q), 0);
+    else if (p.epi == 4) store_quad<EPI_ACT_RELU>(q, row, col, s, quad_aligned<EPI_ACT_RELU>(q), 0);
+    else store_quad<EPI_ACT_DRELU>(q, row, col, s, quad_aligned<EPI_ACT_DRELU>(q), 0);
   } else {
     for (int t = 0; t < 4; ++t) {
       const int64_t idx = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4 + t;
@@ -271,58 +280,6 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(GemmDev p, int split
       epilogue_store<bf16>(p, (int)(idx / p.N), (int)(idx % p.N), s);
     }
   }
-}
-
-// ------------------------------------------------------------------------------------------
-// plain SIMT kernel (any element type, exact bounds checks, fp32 accumulation)
-// ------------------------------------------------------------------------------------------
-template <class T>
-__global__ __launch_bounds__(256) void gemm_simt(GemmDev p, int a_kmajor, int b_kmajor) {
-  constexpr int TS = 64, KS = 16;
-  __shared__ float sA[KS][TS + 1];
-  __shared__ float sB[KS][TS + 1];
-  const int tid = threadIdx.x, ty = tid >> 4, tx = tid & 15;
-  const int m0 = blockIdx.y * TS, n0 = blockIdx.x * TS;
-  const T* A = (const T*)p.A;
-  const T* B = (const T*)p.B;
-  float acc[4][4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = 0.0f;
-  for (int k0 = 0; k0 < p.K; k0 += KS) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int e = tid + i * 256;
-      int r, k;
-      if (a_kmajor) { r = e / KS; k = e % KS; } else { k = e / TS; r = e % TS; }
-      float v = 0.0f;
-      if (m0 + r < p.M && k0 + k < p.K)
-        v = to_f(a_kmajor ? A[(int64_t)(m0 + r) * p.lda + k0 + k] : A[(int64_t)(k0 + k) * p.lda + m0 + r]);
-      sA[k][r] = v;
-      if (b_kmajor) { r = e / KS; k = e % KS; } else { k = e / TS; r = e % TS; }
-      v = 0.0f;
-      if (n0 + r < p.N && k0 + k < p.K)
-        v = to_f(b_kmajor ? B[(int64_t)(n0 + r) * p.ldb + k0 + k] : B[(int64_t)(k0 + k) * p.ldb + n0 + r]);
-      sB[k][r] = v;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < KS; ++k) {
-      float a[4], b[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) { a[i] = sA[k][ty * 4 + i]; b[i] = sB[k][tx * 4 + i]; }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) epilogue_store<T>(p, m0 + ty * 4 + i, n0 + tx * 4 + j, acc[i][j]);
 }
 
 }  // namespace
@@ -382,8 +339,7 @@ static hipError_t gelu_table(int which, hipStream_t s, const float2** out) {
   return hipSuccess;
 }
 
-// Tile configurations.  0: gemm_bf16_mfma (any shape, every epilogue).  1, 5, 6: gemm_bf16_wide (global -> registers -> LDS; 6
-// is the tile of the grouped weight-gradient launch).  4, 7 .. 11: gemm_bf16_dma (global -> LDS).  2, 3: gemm_bf16_ksplit (the
+// Tile configurations.  0: gemm_bf16_mfma (any shape, every epilogue).  1, 5, 6: gemm_bf16_wide (global -> registers -> LDS).  4, 7 .. 11: gemm_bf16_dma (global -> LDS).  2, 3: gemm_bf16_ksplit (the
 // waves of a block share out the contraction).  What a launch takes is modelled as
 //   t0 + k-tiles x (rounds of full CUs x occ w + the last round of r blocks per CU x max(l, r w)) + e x tiles per CU x outputs
 // with l the time of a k-tile of 64 when a block has its CU to itself (a chain of load, LDS read and matrix instruction
@@ -400,11 +356,12 @@ constexpr TileCfg kTileCfg[] = {
     {128, 128, 64, 2, 1, 2.9f, 0.548f, 0.447f, 1.57f}, {256, 128, 64, 1, 0, 1.1f, 0.717f, 0.745f, 3.55f}, {64, 64, 64, 3, 1, 2.5f, 0.229f, 0.175f, 0.41f}};
 constexpr int kNumTileCfg = sizeof(kTileCfg) / sizeof(kTileCfg[0]);
 constexpr int kCUs = 256;
-float cfg_time(const TileCfg& c, int M, int N, int K, int splits, float outputs) {
-  const int64_t tiles = (int64_t)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn) * splits;
+float tiles_time(const TileCfg& c, int64_t tiles, float steps, float outputs) {
   const int per_cu = (int)((tiles + kCUs - 1) / kCUs), full = per_cu / c.occ, rem = per_cu % c.occ;
-  const float steps = (float)((K + 63) / 64) / splits;
   return c.t0 + steps * (full * std::max(c.l, c.occ * c.w) + (rem ? std::max(c.l, rem * c.w) : 0.0f)) + c.e * per_cu * outputs;
+}
+float cfg_time(const TileCfg& c, int M, int N, int K, int splits, float outputs) {
+  return tiles_time(c, (int64_t)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn) * splits, (float)((K + 63) / 64) / splits, outputs);
 }
 int gemm_cfg_override = -1;    // >= 0: use this configuration for every bf16 product of some size that it can serve (timing runs)
 
@@ -415,9 +372,9 @@ constexpr int kMaxBK = 64;
 static hs_status check_gemm_args(hs_ctx* ctx, const GemmArgs& g) {
   if (g.K < 0) return hs_fail(ctx, HS_ERR_INVALID_ARG, "gemm: K < 0");
   if (!g.A || !g.B || !g.C) return hs_fail(ctx, HS_ERR_INVALID_ARG, "gemm: NULL operand");
-  if ((g.epi == 1 || g.epi == 3) && !g.aux) return hs_fail(ctx, HS_ERR_INVALID_ARG, "gemm: epilogue needs aux");
+  if ((g.epi == 1 || g.epi == 3 || g.epi == 5) && !g.aux) return hs_fail(ctx, HS_ERR_INVALID_ARG, "gemm: epilogue needs aux");
   if (g.epi == 2 && (!g.C2 || g.c_f32)) return hs_fail(ctx, HS_ERR_INVALID_ARG, "gemm: GELU epilogue needs C2 and an activation-type C");
-  if (g.epi < 0 || g.epi > 3) return hs_fail(ctx, HS_ERR_INVALID_ARG, "gemm: bad epilogue");
+  if (g.epi < 0 || g.epi > 5) return hs_fail(ctx, HS_ERR_INVALID_ARG, "gemm: bad epilogue");
   if (g.dtype == HS_BF16) {
     if ((g.lda % 8) || (g.ldb % 8) || ((uintptr_t)g.A % 16) || ((uintptr_t)g.B % 16))
       return hs_fail(ctx, HS_ERR_SHAPE, "gemm(bf16): operand rows must be 16-byte aligned");
@@ -447,44 +404,10 @@ static GemmDev gemm_dev_args(const GemmArgs& g) {
 int gemm_variant_count() { return kNumTileCfg; }
 void gemm_set_variant(int variant) { gemm_cfg_override = variant; }
 
-// Several weight-gradient products (A m-major, B n-major, fp32 C = beta C + A^T-style product, no epilogue) in ONE
-// launch of the grouped kernel: no split-K, no partial sums in memory.  Anything else, or more than 8 products,
-// runs as separate launches.
-hs_status launch_gemm_group(hs_ctx* ctx, const GemmArgs* gs, int n, hipStream_t s) {
-  bool groupable = n >= 1 && n <= 8;
-  for (int i = 0; i < n && groupable; ++i) {
-    const GemmArgs& g = gs[i];
-    groupable = g.dtype == HS_BF16 && !g.a_kmajor && !g.b_kmajor && g.c_f32 && g.epi == 0 && !g.bias && g.M > 0 && g.N > 0 && g.K > 0;
-  }
-  if (!groupable) {
-    for (int i = 0; i < n; ++i) { hs_status st = launch_gemm(ctx, gs[i], s); if (st != HS_OK) return st; }
-    return HS_OK;
-  }
-  GemmGroupDev gd;
-  gd.n = n;
-  int tiles = 0;
-  double flops = 0, bytes = 0;
-  for (int i = 0; i < n; ++i) {
-    hs_status st = check_gemm_args(ctx, gs[i]);
-    if (st != HS_OK) return st;
-    gd.prob[i] = gemm_dev_args(gs[i]);
-    gd.first_tile[i] = tiles;
-    tiles += ((gs[i].M + kGroupBM - 1) / kGroupBM) * ((gs[i].N + kGroupBN - 1) / kGroupBN);
-    flops += 2.0 * gs[i].M * gs[i].N * (double)gs[i].K;
-    bytes += ((double)gs[i].M * gs[i].K + (double)gs[i].N * gs[i].K) * 2 + (double)gs[i].M * gs[i].N * 4;
-  }
-  for (int i = n; i <= 8; ++i) gd.first_tile[i] = tiles;
-  KScope scope(ctx ? ctx->prof : nullptr, KC_GEMM_DW, flops, bytes, s);
-  hipError_t e = gemm_wide_group_launch_nn(gd, s);
-  if (e == hipSuccess) e = hipGetLastError();
-  if (e != hipSuccess) return hs_fail(ctx, HS_ERR_HIP, std::string("grouped gemm launch: ") + hipGetErrorString(e));
-  return HS_OK;
-}
-
 // whether gemm_bf16_wide is built with the epilogue this product needs (see wide_epilogues in gemm_wide.h)
 static bool wide_supports(const GemmArgs& g) {
-  if (g.a_kmajor && g.b_kmajor) return g.c_f32 ? true : (g.epi == 0 || g.epi == 1 || g.epi == 2);
-  if (g.a_kmajor) return !g.c_f32 && (g.epi == 0 || g.epi == 1 || g.epi == 3);
+  if (g.a_kmajor && g.b_kmajor) return g.c_f32 ? true : (g.epi == 0 || g.epi == 1 || g.epi == 2 || g.epi == 4);
+  if (g.a_kmajor) return !g.c_f32 && (g.epi == 0 || g.epi == 1 || g.epi == 3 || g.epi == 5);
   return g.c_f32 != 0;
 }
 
@@ -517,6 +440,62 @@ static void choose_cfg(const GemmArgs& g, int* cfg, int* splits) {
   }
 }
 
+// Weight-gradient products (A m-major, B n-major or null for a column of ones, fp32 C = beta C + product, one beta for all) in as
+// few launches of the grouped kernel as their number allows: no split-K, no partial sums in memory, one ramp-up and one tail.
+hs_status launch_gemm_group(hs_ctx* ctx, const GemmArgs* gs, int n, hipStream_t s) {
+  for (int done = 0; done < n;) {
+    GemmGroupDev gd;
+    gd.n = std::min(n - done, kGroupMax);
+    gd.beta = gs[done].beta;
+    const bool f32 = gs[done].dtype == HS_FP32;
+    double flops = 0, bytes = 0;
+    for (int i = 0; i < gd.n; ++i) {
+      const GemmArgs& g = gs[done + i];
+      GemmArgs chk = g;
+      if (!g.B) { chk.B = g.A; chk.ldb = 8; chk.N = 1; }
+      hs_status st = check_gemm_args(ctx, chk);
+      if (st != HS_OK) return st;
+      gd.prob[i] = GroupProb{g.A, g.B, (float*)g.C, (int)g.lda, (int)g.ldb, (int)g.ldc, g.M, g.N, g.K};
+      flops += 2.0 * g.M * g.N * (double)g.K;
+      bytes += ((double)g.M * g.K + (double)g.N * g.K) * esize(g.dtype) + (double)g.M * g.N * 4;
+    }
+    auto count = [&](int bm, int bn) {      // fills first_tile, returns the number of tiles
+      int tiles = 0;
+      for (int i = 0; i < gd.n; ++i) {
+        gd.first_tile[i] = tiles;
+        tiles += ((gd.prob[i].M + bm - 1) / bm) * ((gd.prob[i].N + bn - 1) / bn);
+      }
+      return gd.first_tile[gd.n] = tiles;
+    };
+    int cfg = 9;
+    if (f32) {
+      cfg = gemm_f32_tile(count(128, 128));
+      count(cfg, cfg);
+    } else {      // the tile by the model of choose_cfg, over the tiles of all problems
+      float best = 3.0e38f;
+      for (int c : {9, 11}) {
+        const TileCfg& t = kTileCfg[c];
+        const int tiles = count(t.bm, t.bn);
+        float steps = 0.0f;
+        for (int i = 0; i < gd.n; ++i) steps += (float)(gd.first_tile[i + 1] - gd.first_tile[i]) * ((gd.prob[i].K + 63) / 64);
+        const float time = tiles_time(t, tiles, tiles ? steps / tiles : 0.0f, 2.0f);
+        if (time < best) { best = time; cfg = c; }
+      }
+      count(kTileCfg[cfg].bm, kTileCfg[cfg].bn);
+    }
+    if (gd.first_tile[gd.n] > 0) {
+      KScope scope(ctx ? ctx->prof : nullptr, KC_GEMM_DW, flops, bytes, s);
+      hipError_t e = hipSuccess;
+      if (f32) gemm_f32_group_launch(cfg, gd, s);
+      else e = gemm_group_launch_nn(cfg, gd, s);
+      if (e == hipSuccess) e = hipGetLastError();
+      if (e != hipSuccess) return hs_fail(ctx, HS_ERR_HIP, std::string("grouped gemm launch: ") + hipGetErrorString(e));
+    }
+    done += gd.n;
+  }
+  return HS_OK;
+}
+
 hs_status launch_gemm(hs_ctx* ctx, const GemmArgs& g, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0) return HS_OK;  // nothing to write
   {
@@ -529,8 +508,7 @@ hs_status launch_gemm(hs_ctx* ctx, const GemmArgs& g, hipStream_t s) {
   const int kc = (g.a_kmajor && g.b_kmajor) ? KC_GEMM_FWD : (g.a_kmajor ? KC_GEMM_DX : KC_GEMM_DW);
   KScope scope(ctx ? ctx->prof : nullptr, kc, flops, bytes, s);
   if (g.dtype == HS_FP32) {
-    dim3 grid((g.N + 63) / 64, (g.M + 63) / 64);
-    hipLaunchKernelGGL(gemm_simt<float>, grid, dim3(256), 0, s, p, g.a_kmajor, g.b_kmajor);
+    gemm_f32_launch(g.a_kmajor, g.b_kmajor, p, s);
   } else {
     int cfg, splits;
     choose_cfg(g, &cfg, &splits);

@@ -16,13 +16,19 @@ struct GemmDev {
   uint32_t drop_site;  // element index of the site = row * N + col
 };
 
-// several products for one launch of the grouped kernel (gemm_wide.h)
-struct GemmGroupDev {
-  int n;                   // problems in use
-  int first_tile[9];       // first_tile[i] .. first_tile[i + 1] - 1: the tiles of problem i
-  GemmDev prob[8];
+// Several weight-gradient products C = beta C + sum_k A(k, m) B(k, n) (A m-major, B n-major, fp32 C) for one launch of a grouped
+// kernel.  B == null: a column of ones (C[m] = beta C[m] + sum_k A(k, m), a bias gradient).
+struct GroupProb {
+  const void *A, *B; float* C;
+  int lda, ldb, ldc, M, N, K;
 };
-constexpr int kGroupBM = 256, kGroupBN = 128;   // tile of the grouped kernel
+constexpr int kGroupMax = 48;      // 2.5 KB of kernel arguments
+struct GemmGroupDev {
+  int n;                           // problems in use
+  float beta;
+  int first_tile[kGroupMax + 1];   // first_tile[i] .. first_tile[i + 1] - 1: the tiles of problem i
+  GroupProb prob[kGroupMax];
+};
 
 // Piecewise-linear tables of the normal cdf Phi (GELU(x) = x Phi(x)) and of GELU'(x) = Phi(x) + x pdf(x) on
 // [-6, 6]: entry i holds the value at -6 + i h and the increment to the next node, h = 12 / 1024.  Error of the
@@ -60,6 +66,8 @@ __device__ __forceinline__ void epilogue_store(const GemmDev& p, int row, int co
   if (p.epi == 1 && p.drop.thr) v *= drop_elem(p, row, col);
   if (p.epi == 1) v += to_f(((const T*)p.aux)[(int64_t)row * p.ldaux + col]);
   else if (p.epi == 3) v *= gelu_grad_f(to_f(((const T*)p.aux)[(int64_t)row * p.ldaux + col]));
+  else if (p.epi == 4) v = fmaxf(v, 0.0f);
+  else if (p.epi == 5) v = to_f(((const T*)p.aux)[(int64_t)row * p.ldaux + col]) > 0.0f ? v : 0.0f;
   const int64_t o = (int64_t)row * p.ldc + col;
   if (p.c_f32) {
     float* C = (float*)p.C;
@@ -73,7 +81,9 @@ __device__ __forceinline__ void epilogue_store(const GemmDev& p, int row, int co
 // ------------------------------------------------------------------------------------------
 // bf16 MFMA kernel
 // ------------------------------------------------------------------------------------------
-enum { EPI_PARTIAL = 0, EPI_F32, EPI_ACT, EPI_ACT_RES, EPI_ACT_GELU, EPI_ACT_DGELU };
+// GemmDev::epi: 0 none, 1 residual, 2 GELU (pre-activation and activation), 3 GELU', 4 ReLU, 5 gate of a ReLU (aux: its output)
+enum { EPI_PARTIAL = 0, EPI_F32, EPI_ACT, EPI_ACT_RES, EPI_ACT_GELU, EPI_ACT_DGELU, EPI_ACT_RELU, EPI_ACT_DRELU };
+constexpr bool epi_has_aux(int mode) { return mode == EPI_ACT_RES || mode == EPI_ACT_DGELU || mode == EPI_ACT_DRELU; }
 
 // One group of four consecutive output columns of one row: bias, epilogue, store.  `vec` says that
 // all four columns exist and every pointer involved is aligned for a 4-element access.
@@ -99,9 +109,11 @@ __device__ __forceinline__ void store_quad(const GemmDev& p, int row, int col, f
         drop_row_factors<4>(p, row, col, f);
         v.x *= f[0]; v.y *= f[1]; v.z *= f[2]; v.w *= f[3];
       }
-      if (MODE == EPI_ACT_RES || MODE == EPI_ACT_DGELU) {
+      if (MODE == EPI_ACT_RELU) { v.x = fmaxf(v.x, 0.f); v.y = fmaxf(v.y, 0.f); v.z = fmaxf(v.z, 0.f); v.w = fmaxf(v.w, 0.f); }
+      if (epi_has_aux(MODE)) {
         const bf16x4 a = *(const bf16x4*)(aux + (int64_t)row * p.ldaux + col);
-        if (MODE == EPI_ACT_RES) { v.x += (float)a[0]; v.y += (float)a[1]; v.z += (float)a[2]; v.w += (float)a[3]; }
+        if (MODE == EPI_ACT_DRELU) { v.x = (float)a[0] > 0.f ? v.x : 0.f; v.y = (float)a[1] > 0.f ? v.y : 0.f; v.z = (float)a[2] > 0.f ? v.z : 0.f; v.w = (float)a[3] > 0.f ? v.w : 0.f; }
+        else if (MODE == EPI_ACT_RES) { v.x += (float)a[0]; v.y += (float)a[1]; v.z += (float)a[2]; v.w += (float)a[3]; }
         else { v.x *= gelu_grad_fast((float)a[0]); v.y *= gelu_grad_fast((float)a[1]); v.z *= gelu_grad_fast((float)a[2]); v.w *= gelu_grad_fast((float)a[3]); }
       }
       bf16x4 c;
@@ -129,6 +141,8 @@ __device__ __forceinline__ void store_quad(const GemmDev& p, int row, int col, f
         if (MODE == EPI_ACT_RES && p.drop.thr) x *= drop_elem(p, row, col + t);
         if (MODE == EPI_ACT_RES) x += (float)aux[(int64_t)row * p.ldaux + col + t];
         if (MODE == EPI_ACT_DGELU) x *= gelu_grad_fast((float)aux[(int64_t)row * p.ldaux + col + t]);
+        if (MODE == EPI_ACT_RELU) x = fmaxf(x, 0.f);
+        if (MODE == EPI_ACT_DRELU) x = (float)aux[(int64_t)row * p.ldaux + col + t] > 0.f ? x : 0.f;
         ((bf16*)p.C)[o] = (bf16)x;
         if (MODE == EPI_ACT_GELU) ((bf16*)p.C2)[o] = (bf16)gelu_fast(x);
       }
@@ -142,7 +156,7 @@ __device__ __forceinline__ bool quad_aligned(const GemmDev& p) {
   if (MODE == EPI_PARTIAL) return (p.N & 3) == 0;
   bool ok = (p.ldc & 3) == 0 && ((uintptr_t)p.C & 15) == 0;
   if (p.bias) ok = ok && ((uintptr_t)p.bias & 7) == 0;
-  if (MODE == EPI_ACT_RES || MODE == EPI_ACT_DGELU) ok = ok && (p.ldaux & 3) == 0 && ((uintptr_t)p.aux & 7) == 0;
+  if (epi_has_aux(MODE)) ok = ok && (p.ldaux & 3) == 0 && ((uintptr_t)p.aux & 7) == 0;
   if (MODE == EPI_ACT_GELU) ok = ok && ((uintptr_t)p.C2 & 7) == 0;
   return ok;
 }
@@ -184,6 +198,8 @@ __device__ __forceinline__ void tile_epilogue(const GemmDev& p, const f32x16 (&a
             if (MODE == EPI_ACT_RES && p.drop.thr) v *= drop_elem(p, row, col0 + j * 32);
             if (MODE == EPI_ACT_RES) v += (float)((const bf16*)p.aux)[oa + j * 32];
             if (MODE == EPI_ACT_DGELU) v *= gelu_grad_fast((float)((const bf16*)p.aux)[oa + j * 32]);
+            if (MODE == EPI_ACT_RELU) v = fmaxf(v, 0.f);
+            if (MODE == EPI_ACT_DRELU) v = (float)((const bf16*)p.aux)[oa + j * 32] > 0.f ? v : 0.f;
             ((bf16*)p.C)[oc + j * 32] = (bf16)v;
             if (MODE == EPI_ACT_GELU) ((bf16*)p.C2)[oc + j * 32] = (bf16)gelu_fast(v);
           }
@@ -231,10 +247,15 @@ __device__ __forceinline__ void store_octet(const GemmDev& p, int row, int col, 
 #pragma unroll
         for (int t = 0; t < 8; ++t) v[t] *= f[t];
       }
-      if (MODE == EPI_ACT_RES || MODE == EPI_ACT_DGELU) {
+      if (epi_has_aux(MODE)) {
         const bf16x8 a = *(const bf16x8*)(aux + (int64_t)row * p.ldaux + col);
 #pragma unroll
-        for (int t = 0; t < 8; ++t) v[t] = (MODE == EPI_ACT_RES) ? v[t] + (float)a[t] : v[t] * gelu_grad_fast((float)a[t]);
+        for (int t = 0; t < 8; ++t)
+          v[t] = (MODE == EPI_ACT_RES) ? v[t] + (float)a[t] : (MODE == EPI_ACT_DRELU ? ((float)a[t] > 0.f ? v[t] : 0.f) : v[t] * gelu_grad_fast((float)a[t]));
+      }
+      if (MODE == EPI_ACT_RELU) {
+#pragma unroll
+        for (int t = 0; t < 8; ++t) v[t] = fmaxf(v[t], 0.f);
       }
       bf16x8 c;
 #pragma unroll
@@ -262,6 +283,8 @@ __device__ __forceinline__ void store_octet(const GemmDev& p, int row, int col, 
         if (MODE == EPI_ACT_RES && p.drop.thr) x *= drop_elem(p, row, col + t);
         if (MODE == EPI_ACT_RES) x += (float)aux[(int64_t)row * p.ldaux + col + t];
         if (MODE == EPI_ACT_DGELU) x *= gelu_grad_fast((float)aux[(int64_t)row * p.ldaux + col + t]);
+        if (MODE == EPI_ACT_RELU) x = fmaxf(x, 0.f);
+        if (MODE == EPI_ACT_DRELU) x = (float)aux[(int64_t)row * p.ldaux + col + t] > 0.f ? x : 0.f;
         ((bf16*)p.C)[o] = (bf16)x;
         if (MODE == EPI_ACT_GELU) ((bf16*)p.C2)[o] = (bf16)gelu_fast(x);
       }
@@ -274,7 +297,7 @@ __device__ __forceinline__ bool octet_aligned(const GemmDev& p) {
   if (MODE == EPI_PARTIAL) return (p.N & 3) == 0;
   if (MODE == EPI_F32) return (p.ldc & 3) == 0 && ((uintptr_t)p.C & 15) == 0 && (!p.bias || ((uintptr_t)p.bias & 15) == 0);
   bool ok = (p.ldc & 7) == 0 && ((uintptr_t)p.C & 15) == 0 && (!p.bias || ((uintptr_t)p.bias & 15) == 0);
-  if (MODE == EPI_ACT_RES || MODE == EPI_ACT_DGELU) ok = ok && (p.ldaux & 7) == 0 && ((uintptr_t)p.aux & 15) == 0;
+  if (epi_has_aux(MODE)) ok = ok && (p.ldaux & 7) == 0 && ((uintptr_t)p.aux & 15) == 0;
   if (MODE == EPI_ACT_GELU) ok = ok && ((uintptr_t)p.C2 & 15) == 0;
   return ok;
 }

@@ -251,7 +251,9 @@ __device__ __forceinline__ void dma_tile(const GemmDev& p, int m0, int n0, int s
   else if (p.epi == 0) { if constexpr (has(EPI_ACT)) tile_epilogue_pipe<EPI_ACT, TI, TJ>(p, acc, rbase, cbase, lane, 0, stage, tab); }
   else if (p.epi == 1) { if constexpr (has(EPI_ACT_RES)) tile_epilogue_pipe<EPI_ACT_RES, TI, TJ>(p, acc, rbase, cbase, lane, 0, stage, tab); }
   else if (p.epi == 2) { if constexpr (has(EPI_ACT_GELU)) tile_epilogue_pipe<EPI_ACT_GELU, TI, TJ>(p, acc, rbase, cbase, lane, 0, stage, tab); }
-  else { if constexpr (has(EPI_ACT_DGELU)) tile_epilogue_pipe<EPI_ACT_DGELU, TI, TJ>(p, acc, rbase, cbase, lane, 0, stage, tab); }
+  else if (p.epi == 3) { if constexpr (has(EPI_ACT_DGELU)) tile_epilogue_pipe<EPI_ACT_DGELU, TI, TJ>(p, acc, rbase, cbase, lane, 0, stage, tab); }
+  else if (p.epi == 4) { if constexpr (has(EPI_ACT_RELU)) tile_epilogue_pipe<EPI_ACT_RELU, TI, TJ>(p, acc, rbase, cbase, lane, 0, stage, tab); }
+  else { if constexpr (has(EPI_ACT_DRELU)) tile_epilogue_pipe<EPI_ACT_DRELU, TI, TJ>(p, acc, rbase, cbase, lane, 0, stage, tab); }
 }
 
 template <class C, bool AK, bool BKM>
@@ -279,6 +281,28 @@ hipError_t launch_dma_one(const GemmDev& p, int splits, hipStream_t s) {
   }
   configured = true;
   hipLaunchKernelGGL(kern, dim3((p.N + C::BN - 1) / C::BN, (p.M + C::BM - 1) / C::BM, splits), dim3(C::NT), C::LDS, s, p);
+  return hipSuccess;
+}
+
+// several weight-gradient products in one launch (see group_problem)
+template <class C>
+__global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(C::WPE, C::WPE)))
+void gemm_bf16_dma_group(GemmGroupDev g) {
+  extern __shared__ __attribute__((aligned(1024))) unsigned char lds_raw[];
+  int tm, tn;
+  const GemmDev p = group_problem<C::BM, C::BN>(g, tm, tn);
+  dma_tile<C, false, false, 1 << EPI_F32>(p, tm * C::BM, tn * C::BN, 0, lds_raw);
+}
+template <class C>
+hipError_t launch_dma_group(const GemmGroupDev& g, hipStream_t s) {
+  auto kern = gemm_bf16_dma_group<C>;
+  static bool configured = false;
+  if (!configured && C::LDS > 48 * 1024) {
+    hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::LDS);
+    if (e != hipSuccess) return e;
+  }
+  configured = true;
+  hipLaunchKernelGGL(kern, dim3(g.first_tile[g.n]), dim3(C::NT), C::LDS, s, g);
   return hipSuccess;
 }
 

@@ -122,7 +122,9 @@ __device__ __forceinline__ void ks_tile(const GemmDev& p, int m0, int n0, int sp
   else if (p.epi == 0) { if constexpr (has(EPI_ACT)) finish(std::integral_constant<int, EPI_ACT>{}); }
   else if (p.epi == 1) { if constexpr (has(EPI_ACT_RES)) finish(std::integral_constant<int, EPI_ACT_RES>{}); }
   else if (p.epi == 2) { if constexpr (has(EPI_ACT_GELU)) finish(std::integral_constant<int, EPI_ACT_GELU>{}); }
-  else { if constexpr (has(EPI_ACT_DGELU)) finish(std::integral_constant<int, EPI_ACT_DGELU>{}); }
+  else if (p.epi == 3) { if constexpr (has(EPI_ACT_DGELU)) finish(std::integral_constant<int, EPI_ACT_DGELU>{}); }
+  else if (p.epi == 4) { if constexpr (has(EPI_ACT_RELU)) finish(std::integral_constant<int, EPI_ACT_RELU>{}); }
+  else { if constexpr (has(EPI_ACT_DRELU)) finish(std::integral_constant<int, EPI_ACT_DRELU>{}); }
 }
 
 template <class C, bool AK, bool BKM>

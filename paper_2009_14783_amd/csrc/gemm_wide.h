@@ -124,7 +124,7 @@ __device__ __forceinline__ void tile_epilogue_pipe(const GemmDev& p, const f32x1
                                                    float* stage, const float2* tab) {
   constexpr int WN = 32 * TJ, LDW = WN + 4;
   constexpr int LPR = WN / 8, NIT = 32 * LPR / 64;
-  constexpr bool HAS_AUX = MODE == EPI_ACT_RES || MODE == EPI_ACT_DGELU;
+  constexpr bool HAS_AUX = epi_has_aux(MODE);
   const bool inside = octet_aligned<MODE>(p) && rbase + 32 * TI <= p.M && cbase + WN <= p.N && !(MODE == EPI_ACT_RES && p.drop.thr);
   if (!inside) { tile_epilogue_lds<MODE, TI, TJ>(p, acc, rbase, cbase, lane, split, stage); return; }
   const bf16* bias = (const bf16*)p.bias;
@@ -181,7 +181,13 @@ __device__ __forceinline__ void tile_epilogue_pipe(const GemmDev& p, const f32x1
         const int64_t o = (int64_t)row * p.ldc + col;
         if (HAS_AUX) {
 #pragma unroll
-          for (int t = 0; t < 8; ++t) v[t] = (MODE == EPI_ACT_RES) ? v[t] + (float)acur[it][t] : v[t] * gelu_tab_eval(tab, (float)acur[it][t]);
+          for (int t = 0; t < 8; ++t)
+            v[t] = (MODE == EPI_ACT_RES) ? v[t] + (float)acur[it][t]
+                   : (MODE == EPI_ACT_DRELU ? ((float)acur[it][t] > 0.f ? v[t] : 0.f) : v[t] * gelu_tab_eval(tab, (float)acur[it][t]));
+        }
+        if (MODE == EPI_ACT_RELU) {
+#pragma unroll
+          for (int t = 0; t < 8; ++t) v[t] = fmaxf(v[t], 0.f);
         }
         bf16x8 c;
 #pragma unroll
@@ -366,15 +372,17 @@ __device__ __forceinline__ void wide_tile(const GemmDev& p, int m0, int n0, int 
   else if (p.epi == 0) { if constexpr (has(EPI_ACT)) tile_epilogue_pipe<EPI_ACT, TI, TJ>(p, acc, rbase, cbase, lane, 0, stage, tab); }
   else if (p.epi == 1) { if constexpr (has(EPI_ACT_RES)) tile_epilogue_pipe<EPI_ACT_RES, TI, TJ>(p, acc, rbase, cbase, lane, 0, stage, tab); }
   else if (p.epi == 2) { if constexpr (has(EPI_ACT_GELU)) tile_epilogue_pipe<EPI_ACT_GELU, TI, TJ>(p, acc, rbase, cbase, lane, 0, stage, tab); }
-  else { if constexpr (has(EPI_ACT_DGELU)) tile_epilogue_pipe<EPI_ACT_DGELU, TI, TJ>(p, acc, rbase, cbase, lane, 0, stage, tab); }
+  else if (p.epi == 3) { if constexpr (has(EPI_ACT_DGELU)) tile_epilogue_pipe<EPI_ACT_DGELU, TI, TJ>(p, acc, rbase, cbase, lane, 0, stage, tab); }
+  else if (p.epi == 4) { if constexpr (has(EPI_ACT_RELU)) tile_epilogue_pipe<EPI_ACT_RELU, TI, TJ>(p, acc, rbase, cbase, lane, 0, stage, tab); }
+  else { if constexpr (has(EPI_ACT_DRELU)) tile_epilogue_pipe<EPI_ACT_DRELU, TI, TJ>(p, acc, rbase, cbase, lane, 0, stage, tab); }
 }
 
 // the epilogues each operand layout is built with (the training step needs no others; launch_gemm falls back
 // to gemm_bf16_mfma for the rest)
 template <bool AK, bool BKM>
 constexpr int wide_epilogues() {
-  return (AK && BKM) ? (1 << EPI_PARTIAL | 1 << EPI_F32 | 1 << EPI_ACT | 1 << EPI_ACT_RES | 1 << EPI_ACT_GELU)
-         : AK        ? (1 << EPI_PARTIAL | 1 << EPI_ACT | 1 << EPI_ACT_RES | 1 << EPI_ACT_DGELU)
+  return (AK && BKM) ? (1 << EPI_PARTIAL | 1 << EPI_F32 | 1 << EPI_ACT | 1 << EPI_ACT_RES | 1 << EPI_ACT_GELU | 1 << EPI_ACT_RELU)
+         : AK        ? (1 << EPI_PARTIAL | 1 << EPI_ACT | 1 << EPI_ACT_RES | 1 << EPI_ACT_DGELU | 1 << EPI_ACT_DRELU)
                      : (1 << EPI_PARTIAL | 1 << EPI_F32);
 }
 
@@ -405,26 +413,26 @@ void gemm_bf16_wide(GemmDev p) {
   wide_tile<AK, BKM, TI, TJ, WGM, WGN, BK, NSETS, wide_epilogues<AK, BKM>()>(p, tm * 32 * TI * WGM, tn * 32 * TJ * WGN, split, lds_raw);
 }
 
-// Several products in one launch: block v works on tile v - first_tile[i] of problem i (the problems' tiles are
-// numbered one problem after the other; an XCD gets a contiguous range of them).  No split-K: every tile runs
-// over the whole contraction.
-template <bool AK, bool BKM, int TI, int TJ, int WGM, int WGN, int BK, int NSETS, int OCC>
-__global__ __launch_bounds__(64 * WGM * WGN) __attribute__((amdgpu_waves_per_eu(OCC * WGM * WGN / 4, OCC * WGM * WGN / 4)))
-void gemm_bf16_wide_group(GemmGroupDev g) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
-  constexpr int BM = 32 * TI * WGM, BN = 32 * TJ * WGN;
+// Several products in one launch: block v works on tile v - first_tile[i] of problem i (the problems' tiles are numbered one
+// problem after the other; an XCD gets a contiguous range of them).  No split-K: every tile runs over the whole
+// contraction.  Returns the problem as arguments of the tile function and the tile's position.
+static __device__ const bf16 kOnes[8] = {(bf16)1.0f, (bf16)1.0f, (bf16)1.0f, (bf16)1.0f, (bf16)1.0f, (bf16)1.0f, (bf16)1.0f, (bf16)1.0f};
+template <int BM, int BN>
+__device__ __forceinline__ GemmDev group_problem(const GemmGroupDev& g, int& tm, int& tn) {
   int v = blockIdx.x;
   const int per_xcd = (int)gridDim.x >> 3;
   if (v < 8 * per_xcd) v = (v & 7) * per_xcd + (v >> 3);
-  int i = 0;
-  while (i + 1 < g.n && v >= g.first_tile[i + 1]) ++i;
-  const GemmDev& p = g.prob[i];
+  int lo = 0, hi = g.n - 1;                    // the last problem whose first tile is not beyond v
+  while (lo < hi) { const int mid = (lo + hi + 1) >> 1; if (v >= g.first_tile[mid]) lo = mid; else hi = mid - 1; }
+  const GroupProb& q = g.prob[lo];
+  GemmDev p{};
+  p.A = q.A; p.C = q.C; p.lda = q.lda; p.ldc = q.ldc; p.M = q.M; p.N = q.N; p.K = q.K; p.k_per_split = q.K;
+  p.B = q.B ? q.B : (const void*)kOnes; p.ldb = q.B ? q.ldb : 0;      // row stride 0: every row of the column of ones is the same
+  p.c_f32 = 1; p.beta = g.beta;
   const int nbx = (p.N + BN - 1) / BN, nby = (p.M + BM - 1) / BM;
-  int tm, tn;
-  tile_of_block<(TI * WGM >= 8) ? 4 : 8>(v - g.first_tile[i], nbx, nby, tm, tn);
-  wide_tile<AK, BKM, TI, TJ, WGM, WGN, BK, NSETS, wide_epilogues<AK, BKM>()>(p, tm * BM, tn * BN, 0, lds_raw);
+  tile_of_block<(BM >= 256) ? 4 : 8>(v - g.first_tile[lo], nbx, nby, tm, tn);
+  return p;
 }
-
 template <bool AK, bool BKM, int TI, int TJ, int WGM, int WGN, int BK, int NSETS, int OCC>
 hipError_t launch_wide_one(const GemmDev& p, dim3 grid, hipStream_t s) {
   constexpr int NT = 64 * WGM * WGN;
@@ -438,22 +446,6 @@ hipError_t launch_wide_one(const GemmDev& p, dim3 grid, hipStream_t s) {
   }
   configured = true;
   hipLaunchKernelGGL(kern, grid, dim3(NT), lds, s, p);
-  return hipSuccess;
-}
-
-template <bool AK, bool BKM, int TI, int TJ, int WGM, int WGN, int BK, int NSETS, int OCC>
-hipError_t launch_wide_group_one(const GemmGroupDev& g, hipStream_t s) {
-  constexpr int NT = 64 * WGM * WGN;
-  constexpr size_t lds = wide_lds_bytes<AK, BKM, TI, TJ, WGM, WGN, BK>();
-  static_assert(lds <= 160 * 1024, "tile does not fit the LDS of a CU");
-  auto kern = gemm_bf16_wide_group<AK, BKM, TI, TJ, WGM, WGN, BK, NSETS, OCC>;
-  static bool configured = false;
-  if (!configured && lds > 48 * 1024) {
-    hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-  }
-  configured = true;
-  hipLaunchKernelGGL(kern, dim3(g.first_tile[g.n]), dim3(NT), lds, s, g);
   return hipSuccess;
 }
 

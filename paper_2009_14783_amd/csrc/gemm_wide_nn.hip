@@ -5,5 +5,11 @@ hipError_t gemm_wide_launch_nn(int cfg, const GemmDev& p, int splits, hipStream_
   return launch_layout<false, false>(cfg, p, splits, s);
 }
 
-// the weight-gradient products of a layer in one launch: 256 x 128 x 64 tiles, one block per CU
-hipError_t gemm_wide_group_launch_nn(const GemmGroupDev& g, hipStream_t s) { return launch_wide_group_one<false, false, 4, 2, 2, 2, 64, 2, 1>(g, s); }
+// weight-gradient products in one launch
+hipError_t gemm_group_launch_nn(int cfg, const GemmGroupDev& g, hipStream_t s) {
+  switch (cfg) {
+    case 9: return launch_dma_group<Dma128x128>(g, s);
+    case 11: return launch_dma_group<Dma64x64>(g, s);
+    default: return hipErrorInvalidValue;
+  }
+}

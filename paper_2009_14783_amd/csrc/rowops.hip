@@ -3,6 +3,8 @@
 // kernels; statistics and reductions are fp32 and every reduction has a fixed order.
 #include "common.h"
 
+#include <algorithm>
+
 namespace {
 
 constexpr int MAXC = 16;   // columns per lane (scalar access): hidden <= 1024
@@ -249,6 +251,41 @@ __global__ __launch_bounds__(64 * SP_WAVES) void sum_partials_kernel(const float
 #pragma unroll
     for (int w = 1; w < SP_WAVES; ++w) t += red[w][lane];
     out[col] = (beta != 0.f) ? beta * out[col] + t : t;
+  }
+}
+
+// The same for the LayerNorm backward partials of several layers in one launch (blockIdx.z: the layer): alone, each of them is
+// a launch that costs more than its work (4 us against 1).
+struct LnColsTable { LnColsJob job[kLnColsMax]; };
+__global__ __launch_bounds__(64 * SP_WAVES) void ln_cols_kernel(LnColsTable t, int np, int H, float beta) {
+  __shared__ float red[SP_WAVES][64];
+  const LnColsJob& j = t.job[blockIdx.z];
+  const int q = blockIdx.y;
+  float* out = q == 0 ? j.d_gain : (q == 1 ? j.d_bias : j.d_colsum);
+  if (!out) return;                                   // uniform over the block
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int col = blockIdx.x * 64 + lane;
+  float s = 0.f;
+  if (col < H) {
+    const float* src = (const float*)j.partials + q * H + col;
+    const int64_t pstride = 3 * (int64_t)H;
+    int p = wave;
+    for (; p + 7 * SP_WAVES < np; p += 8 * SP_WAVES) {
+      float a[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) a[u] = src[(int64_t)(p + SP_WAVES * u) * pstride];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) s += a[u];
+    }
+    for (; p < np; p += SP_WAVES) s += src[(int64_t)p * pstride];
+  }
+  red[wave][lane] = s;
+  __syncthreads();
+  if (wave == 0 && col < H) {
+    float r = red[0][lane];
+#pragma unroll
+    for (int w = 1; w < SP_WAVES; ++w) r += red[w][lane];
+    out[col] = (beta != 0.f) ? beta * out[col] + r : r;
   }
 }
 
@@ -654,6 +691,18 @@ hs_status launch_layernorm_bwd_cols(hs_ctx* ctx, const void* partials, float* d_
   hipLaunchKernelGGL(sum_partials_kernel, dim3((H + 63) / 64, 3), dim3(64 * SP_WAVES), 0, s, (const float*)partials, ln_bwd_blocks(R, H), (int64_t)3 * H,
                      (int64_t)H, H, d_gain, d_bias, d_colsum, beta);
   LAUNCH_CHECK(ctx, "layernorm_bwd finalize");
+  return HS_OK;
+}
+// the same for several layers of the same shape
+hs_status launch_layernorm_bwd_cols_batch(hs_ctx* ctx, const LnColsJob* jobs, int n, float beta, int R, int H, hipStream_t s) {
+  for (int done = 0; R > 0 && done < n; done += kLnColsMax) {
+    LnColsTable t;
+    const int m = std::min(n - done, kLnColsMax);
+    for (int i = 0; i < m; ++i) t.job[i] = jobs[done + i];
+    KScope scope(prof_of(ctx), KC_LN_BWD, 0.0, 0.0, s);
+    hipLaunchKernelGGL(ln_cols_kernel, dim3((H + 63) / 64, 3, m), dim3(64 * SP_WAVES), 0, s, t, ln_bwd_blocks(R, H), H, beta);
+    LAUNCH_CHECK(ctx, "layernorm_bwd finalize");
+  }
   return HS_OK;
 }
 hs_status launch_layernorm_bwd(hs_ctx* ctx, int dtype, const void* dy, const void* x, const float* stats, const void* gain, void* dx,

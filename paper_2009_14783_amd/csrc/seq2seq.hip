@@ -143,10 +143,10 @@ LossWs carve_loss(const hs_s2s_cfg& c, int B, int Lt, void* base) {
 // before it overwrites anything; buffers that only the chain touches are shared by all layers.
 struct LayerGrads { void *s2, *m2, *sc, *mc, *s1, *m1, *dh, *dcq, *dckv, *dqkv, *p2, *pc, *p1; };   // p*: LayerNorm column partials
 struct BwdWs {
-  void *da, *db, *dctx, *denc[2], *de_tgt, *de_src, *cs_part, *emb, *gemm_ws_side;
+  void *da, *db, *dctx, *denc[2], *de_tgt, *de_src, *emb;
   std::vector<LayerGrads> enc, dec;
   float* dvec;
-  size_t gemm_ws_bytes, total;
+  size_t total;
 };
 BwdWs carve_bwd(const hs_s2s_cfg& c, int B, int Ls, int Lt, void* base) {
   const size_t Tm = (size_t)B * std::max(Ls, Lt), Ts = (size_t)B * Ls, Tt = (size_t)B * Lt, H = c.hidden, F = c.ffn, es = esize(c.compute);
@@ -170,10 +170,7 @@ BwdWs carve_bwd(const hs_s2s_cfg& c, int B, int Ls, int Lt, void* base) {
     l.p1 = cv.take(layernorm_bwd_scratch((int)Tt, (int)H));
   }
   w.dvec = (float*)cv.take((size_t)B * c.n_heads * std::max(Ls, Lt) * sizeof(float));
-  w.cs_part = cv.take(colsum_scratch((int)Tm, (int)std::max(F, 3 * H)));
   w.emb = cv.take(embed_bwd_scratch((int)Tm, (int)H));
-  w.gemm_ws_bytes = gemm_scratch_bytes(c);
-  w.gemm_ws_side = cv.take(w.gemm_ws_bytes);      // split-K partial sums of the weight-gradient GEMMs (second stream)
   w.total = cv.off;
   return w;
 }
@@ -216,10 +213,10 @@ uint32_t site_tgt() { return 1; }
 uint32_t site_enc(int layer, int which) { return 2 + 2 * (uint32_t)layer + which; }
 uint32_t site_dec(const hs_s2s_cfg& c, int layer, int which) { return 2 + 2 * (uint32_t)c.n_enc + 3 * (uint32_t)layer + which; }
 
-// y = x W^T + b
-hs_status linear(hs_ctx* ctx, int dt, int T, int N, int K, const void* x, const void* Wm, const void* b, void* y, hipStream_t s) {
+// y = x W^T + b, or its ReLU
+hs_status linear(hs_ctx* ctx, int dt, int T, int N, int K, const void* x, const void* Wm, const void* b, void* y, hipStream_t s, bool relu = false) {
   GemmArgs g = gemm_args(dt, 1, 1, T, N, K, x, K, Wm, K, y, N);
-  g.bias = b;
+  g.bias = b; g.epi = relu ? 4 : 0;
   return launch_gemm(ctx, g, s);
 }
 // sum = res + drop(x W^T + b) ; out = LN(sum)
@@ -339,8 +336,7 @@ hs_status hs_s2s_fwd(hs_ctx* ctx, const void* w, const int32_t* src, const int32
       HS_TRY(launch_attention_fwd(ctx, dt, R(la.qkv, 3 * H), src_lens + pt.b0, pt.nb, Ls, A, mut(R(la.ctx, H)), la.lse + (size_t)pt.b0 * A * Ls, st));
       HS_TRY(linear_res_ln(ctx, dt, T, H, H, R(la.ctx, H), W(dt, w, lo.o_w), W(dt, w, lo.o_b), R(x, H), mut(R(la.y1, H)), W(dt, w, lo.ln1_g),
                            W(dt, w, lo.ln1_b), mut(R(la.x1, H)), la.st1 + (size_t)pt.b0 * Ls, Ts, c.ln_eps, drop ? &drop_src[k] : nullptr, site_enc(i, 0), st));
-      HS_TRY(linear(ctx, dt, T, F, H, R(la.x1, H), W(dt, w, lo.ffn1_w), W(dt, w, lo.ffn1_b), mut(R(la.h, F)), st));
-      HS_TRY(launch_relu(ctx, dt, mut(R(la.h, F)), (size_t)T * F, st));
+      HS_TRY(linear(ctx, dt, T, F, H, R(la.x1, H), W(dt, w, lo.ffn1_w), W(dt, w, lo.ffn1_b), mut(R(la.h, F)), st, true));
       HS_TRY(linear_res_ln(ctx, dt, T, H, F, R(la.h, F), W(dt, w, lo.ffn2_w), W(dt, w, lo.ffn2_b), R(la.x1, H), mut(R(la.y2, H)), W(dt, w, lo.ln2_g),
                            W(dt, w, lo.ln2_b), mut(R(la.x2, H)), la.st2 + (size_t)pt.b0 * Ls, Ts, c.ln_eps, drop ? &drop_src[k] : nullptr, site_enc(i, 1), st));
     }
@@ -380,8 +376,7 @@ hs_status hs_s2s_fwd(hs_ctx* ctx, const void* w, const int32_t* src, const int32
       HS_TRY(linear_res_ln(ctx, dt, T, H, H, R(la.cctx, H), W(dt, w, lo.co_w), W(dt, w, lo.co_b), R(la.y1, H), mut(R(la.ycs, H)),
                            W(dt, w, lo.lnc_g), W(dt, w, lo.lnc_b), mut(R(la.yc, H)), la.stc + (size_t)pt.b0 * Lt, Tt, c.ln_eps, drop ? &drop_tgt[k] : nullptr,
                            site_dec(c, i, 1), st));
-      HS_TRY(linear(ctx, dt, T, F, H, R(la.yc, H), W(dt, w, lo.ffn1_w), W(dt, w, lo.ffn1_b), mut(R(la.h, F)), st));
-      HS_TRY(launch_relu(ctx, dt, mut(R(la.h, F)), (size_t)T * F, st));
+      HS_TRY(linear(ctx, dt, T, F, H, R(la.yc, H), W(dt, w, lo.ffn1_w), W(dt, w, lo.ffn1_b), mut(R(la.h, F)), st, true));
       HS_TRY(linear_res_ln(ctx, dt, T, H, F, R(la.h, F), W(dt, w, lo.ffn2_w), W(dt, w, lo.ffn2_b), R(la.yc, H), mut(R(la.y2s, H)),
                            W(dt, w, lo.ln2_g), W(dt, w, lo.ln2_b), mut(R(y2, H)), la.st2 + (size_t)pt.b0 * Lt, Tt, c.ln_eps, drop ? &drop_tgt[k] : nullptr,
                            site_dec(c, i, 2), st));
@@ -483,71 +478,66 @@ hs_status hs_s2s_bwd(hs_ctx* ctx, const void* w, const void* acts, const int32_t
   const DropCfg* drop = ctx->drop.thr ? &ctx->drop : nullptr;
   const float scale = sqrtf((float)H);
 
-  // The weight gradients and bias column sums only consume what the chain of activation gradients produces: they run on
-  // the context's second stream, each after the event that marks its operand ready, and the caller's stream waits for
-  // them once, at the end.  With per-launch timing enabled everything stays on the caller's stream.
+  // The weight gradients and column sums only consume what the chain of activation gradients produces: they run on the
+  // context's second stream, those of several layers (one, with many rows) in one grouped launch and one launch of column sums behind
+  // one event, and the caller's stream waits for them once, at the end.  An event and the wait for it cost the host 10 us, four launches:
+  // with one per operand and a launch per product (and its k-splits' sum) the host took 2.9 of the 4.1 ms of this call at 4096
+  // positions per side.  With per-launch timing enabled everything stays on the caller's stream.
   const bool overlap = ctx->prof == nullptr;
-  const size_t n_events = (size_t)6 * c.n_dec + 4 * c.n_enc + 2 + 1 + (upd.on ? (size_t)2 * (c.n_dec + c.n_enc) + 2 : 0);
+  const int per_hand_over = std::max(Ts, Tt) <= 2048 ? 3 : 1;
+  const size_t n_events = (size_t)c.n_dec + c.n_enc + 6;
   if (overlap) HS_TRY(ensure_side_stream(ctx, n_events));
   hipStream_t sd = overlap ? ctx->side : s;
   size_t next_event = 0;
-  // An armed optimizer update runs on a third stream: the slice of a layer is normalised and updated as soon as both
-  // streams have finished that layer (its gradient is final and its weights are no longer read), the shared embedding last.
-  if (overlap && upd.on && !ctx->upd) HS_HIP_CHECK(ctx, hipStreamCreateWithFlags(&ctx->upd, hipStreamNonBlocking));
-  hipStream_t su = (overlap && upd.on) ? ctx->upd : s;
-  auto update_after_both = [&](int64_t begin, int64_t end) -> hs_status {
-    if (!upd.on) return HS_OK;
-    if (overlap) {
-      hipEvent_t e1 = ctx->events[next_event++], e2 = ctx->events[next_event++];
-      HS_HIP_CHECK(ctx, hipEventRecord(e1, sd));
-      HS_HIP_CHECK(ctx, hipStreamWaitEvent(su, e1, 0));
-      HS_HIP_CHECK(ctx, hipEventRecord(e2, s));
-      HS_HIP_CHECK(ctx, hipStreamWaitEvent(su, e2, 0));
-    }
-    return update_slice(ctx, upd, begin, end, su);
-  };
-  auto hand_over = [&]() -> hs_status {       // what the caller's stream has produced so far may now be read on the second one
-    if (!overlap) return HS_OK;
+  // work enqueued on `to` from here on comes after what is on `from` now
+  auto order = [&](hipStream_t from, hipStream_t to) -> hs_status {
+    if (from == to) return HS_OK;
     hipEvent_t e = ctx->events[next_event++];
-    HS_HIP_CHECK(ctx, hipEventRecord(e, s));
-    HS_HIP_CHECK(ctx, hipStreamWaitEvent(sd, e, 0));
+    HS_HIP_CHECK(ctx, hipEventRecord(e, from));
+    HS_HIP_CHECK(ctx, hipStreamWaitEvent(to, e, 0));
     return HS_OK;
   };
+  std::vector<GemmArgs> dw;                       // weight and bias gradients not yet enqueued
+  std::vector<LnColsJob> cols_tgt, cols_src;      // ... and LayerNorm column sums, over the target and the source rows
   auto wgrad = [&](int M, int N, int K, const void* dy, int64_t ldd, const void* xin, int64_t ldx, float* dst) {   // dst [M,N] (+)= dy^T x
     GemmArgs ga = gemm_args(dt, 0, 0, M, N, K, dy, ldd, xin, ldx, dst, N);
-    // at most four k-splits: these run beside the chain on the second stream, where the round trip of more partial sums
-    // through memory costs the chain more than a fuller grid gains (measured: 32 splits 6.78 ms per step, 8: 6.56, 4: 6.48)
-    ga.c_f32 = 1; ga.beta = beta; ga.ws = ws.gemm_ws_side;
-    ga.ws_bytes = std::min(ws.gemm_ws_bytes, (size_t)4 * M * N * sizeof(float));
-    return launch_gemm(ctx, ga, sd);
+    ga.c_f32 = 1; ga.beta = beta;
+    dw.push_back(ga);
   };
-  auto bias_grad = [&](const void* dy, int T, int N, float* dst) { return launch_colsum(ctx, dt, dy, N, T, N, dst, beta, ws.cs_part, sd); };
+  auto bias_grad = [&](const void* dy, int T, int N, float* dst) { wgrad(N, 1, T, dy, N, nullptr, 0, dst); };   // dst [N] (+)= column sums of dy
+  // the gradients of the layers down to this one go to the second stream; an armed optimizer update of theirs follows them there (their
+  // weights are no longer read), the shared embedding's comes last
+  auto enqueue_grads = [&](int64_t begin, int64_t end) -> hs_status {
+    HS_TRY(order(s, sd));
+    HS_TRY(launch_layernorm_bwd_cols_batch(ctx, cols_tgt.data(), (int)cols_tgt.size(), beta, Tt, H, sd));
+    HS_TRY(launch_layernorm_bwd_cols_batch(ctx, cols_src.data(), (int)cols_src.size(), beta, Ts, H, sd));
+    HS_TRY(launch_gemm_group(ctx, dw.data(), (int)dw.size(), sd));
+    dw.clear(); cols_tgt.clear(); cols_src.clear();
+    return upd.on ? update_slice(ctx, upd, begin, end, sd) : HS_OK;
+  };
   auto dgrad = [&](int T, int N, int K, const void* dy, const void* Wm, void* dx, const void* res) {   // dx [T,N] = dy [T,K] W [K,N] (+ res)
     GemmArgs ga = gemm_args(dt, 1, 0, T, N, K, dy, K, Wm, N, dx, N);
     if (res) { ga.epi = 1; ga.aux = res; ga.ldaux = N; }
-    return launch_gemm(ctx, ga, s);      // no split-K scratch: at K = 512 .. 2048 the reduction pass costs more than the idle CUs
-                                         // (7.13 -> 6.78 ms per step)
+    return launch_gemm(ctx, ga, s);
   };
   // LayerNorm backward of a sub-layer: dsum = d(residual sum); the branch takes dsum through the sub-layer's dropout
-  // (dmask; dsum itself without dropout).  The rows go on the chain; the column sums of its partials (gain and bias
-  // gradients, and the bias gradient of the sub-layer's last linear map = column sums of the branch gradient) on the
-  // second stream, which from here on may read what the chain has produced.  Returns the branch gradient.
-  auto ln_bwd = [&](int T, const void* dy, const void* sum, const float* stats, int64_t gain, int64_t lnb, int64_t last_bias, uint32_t site,
-                    void* dsum, void* dmask, void* partials, const void** branch) -> hs_status {
+  // (dmask; dsum itself without dropout).  The column sums of its partials are the gain and bias gradients, and the bias
+  // gradient of the sub-layer's last linear map (column sums of the branch gradient).  Returns the branch gradient.
+  auto ln_bwd = [&](int T, std::vector<LnColsJob>& cols, const void* dy, const void* sum, const float* stats, int64_t gain, int64_t lnb,
+                    int64_t last_bias, uint32_t site, void* dsum, void* dmask, void* partials, const void** branch) -> hs_status {
     *branch = drop ? dmask : dsum;
-    HS_TRY(launch_layernorm_bwd_rows(ctx, dt, dy, sum, stats, W(dt, w, gain), dsum, T, H, partials, s, drop, site, drop ? 2 : 0,
-                                     drop ? dmask : nullptr));
-    HS_TRY(hand_over());
-    return launch_layernorm_bwd_cols(ctx, partials, g + gain, g + lnb, g + last_bias, beta, T, H, sd);
+    cols.push_back({partials, g + gain, g + lnb, g + last_bias});
+    return launch_layernorm_bwd_rows(ctx, dt, dy, sum, stats, W(dt, w, gain), dsum, T, H, partials, s, drop, site, drop ? 2 : 0,
+                                     drop ? dmask : nullptr);
   };
   // feed-forward backward: from the branch gradient to d(input of the sub-layer) = dsum + dh W1, written to out
   auto ffn_bwd = [&](int T, const BlockOff& lo, const LayerGrads& lg, const void* branch, const void* xin, const void* h, void* out) -> hs_status {
-    HS_TRY(wgrad(H, F, T, branch, H, h, F, g + lo.ffn2_w));
-    HS_TRY(dgrad(T, F, H, branch, W(dt, w, lo.ffn2_w), lg.dh, nullptr));
-    HS_TRY(launch_relu_bwd(ctx, dt, lg.dh, h, (size_t)T * F, s));
-    HS_TRY(hand_over());
-    HS_TRY(bias_grad(lg.dh, T, F, g + lo.ffn1_b));
-    HS_TRY(wgrad(F, H, T, lg.dh, F, xin, H, g + lo.ffn1_w));
+    wgrad(H, F, T, branch, H, h, F, g + lo.ffn2_w);
+    GemmArgs ga = gemm_args(dt, 1, 0, T, F, H, branch, H, W(dt, w, lo.ffn2_w), F, lg.dh, F);     // through the ReLU's gate
+    ga.epi = 5; ga.aux = h; ga.ldaux = F;
+    HS_TRY(launch_gemm(ctx, ga, s));
+    bias_grad(lg.dh, T, F, g + lo.ffn1_b);
+    wgrad(F, H, T, lg.dh, F, xin, H, g + lo.ffn1_w);
     return dgrad(T, H, F, lg.dh, W(dt, w, lo.ffn1_w), out, lg.s2);
   };
 
@@ -556,6 +546,7 @@ hs_status hs_s2s_bwd(hs_ctx* ctx, const void* w, const void* acts, const int32_t
   const void* dcur = d_dec_out;
   int pe = 0;                      // which of the two encoder-gradient buffers holds the running sum
   bool have_denc = false;
+  int dec_top = c.n_dec - 1, enc_top = c.n_enc - 1;      // the highest layers whose gradients are not yet enqueued
   for (int i = c.n_dec - 1; i >= 0; --i) {
     const BlockOff& lo = o.dec[i];
     DecActs& la = a.dec[i];
@@ -563,42 +554,43 @@ hs_status hs_s2s_bwd(hs_ctx* ctx, const void* w, const void* acts, const int32_t
     const void* y_in = (i == 0) ? a.t0 : a.dec[i - 1].y2;
     const void* br;
     // feed-forward sub-layer
-    HS_TRY(ln_bwd(Tt, dcur, la.y2s, la.st2, lo.ln2_g, lo.ln2_b, lo.ffn2_b, site_dec(c, i, 2), lg.s2, lg.m2, lg.p2, &br));
+    HS_TRY(ln_bwd(Tt, cols_tgt, dcur, la.y2s, la.st2, lo.ln2_g, lo.ln2_b, lo.ffn2_b, site_dec(c, i, 2), lg.s2, lg.m2, lg.p2, &br));
     HS_TRY(ffn_bwd(Tt, lo, lg, br, la.yc, la.h, ws.da));
     // attention over the encoder output
-    HS_TRY(ln_bwd(Tt, ws.da, la.ycs, la.stc, lo.lnc_g, lo.lnc_b, lo.co_b, site_dec(c, i, 1), lg.sc, lg.mc, lg.pc, &br));
-    HS_TRY(wgrad(H, H, Tt, br, H, la.cctx, H, g + lo.co_w));
+    HS_TRY(ln_bwd(Tt, cols_tgt, ws.da, la.ycs, la.stc, lo.lnc_g, lo.lnc_b, lo.co_b, site_dec(c, i, 1), lg.sc, lg.mc, lg.pc, &br));
+    wgrad(H, H, Tt, br, H, la.cctx, H, g + lo.co_w);
     HS_TRY(dgrad(Tt, H, H, br, W(dt, w, lo.co_w), ws.dctx, nullptr));
     AttnOperands cross{la.cq, la.ckv, at(dt, (const void*)la.ckv, H), (int64_t)H, 2 * (int64_t)H, tgt_lens, src_lens, Lt, Ls, A, 0};
     HS_TRY(launch_attention_general_bwd(ctx, dt, cross, B, la.cctx, la.clse, ws.dctx, lg.dcq, H, lg.dckv, at(dt, lg.dckv, H), 2 * (int64_t)H,
                                         ws.dvec, s));
-    HS_TRY(hand_over());
-    HS_TRY(bias_grad(lg.dckv, Ts, 2 * H, g + lo.ckv_b));
-    HS_TRY(wgrad(2 * H, H, Ts, lg.dckv, 2 * H, enc_out, H, g + lo.ckv_w));
-    HS_TRY(bias_grad(lg.dcq, Tt, H, g + lo.cq_b));
-    HS_TRY(wgrad(H, H, Tt, lg.dcq, H, la.y1, H, g + lo.cq_w));
+    bias_grad(lg.dckv, Ts, 2 * H, g + lo.ckv_b);
+    wgrad(2 * H, H, Ts, lg.dckv, 2 * H, enc_out, H, g + lo.ckv_w);
+    bias_grad(lg.dcq, Tt, H, g + lo.cq_b);
+    wgrad(H, H, Tt, lg.dcq, H, la.y1, H, g + lo.cq_w);
     HS_TRY(dgrad(Ts, H, 2 * H, lg.dckv, W(dt, w, lo.ckv_w), ws.denc[pe ^ 1], have_denc ? ws.denc[pe] : nullptr));
     pe ^= 1; have_denc = true;
     HS_TRY(dgrad(Tt, H, H, lg.dcq, W(dt, w, lo.cq_w), ws.db, lg.sc));
     // causal self-attention
-    HS_TRY(ln_bwd(Tt, ws.db, la.y1s, la.st1, lo.ln1_g, lo.ln1_b, lo.o_b, site_dec(c, i, 0), lg.s1, lg.m1, lg.p1, &br));
-    HS_TRY(wgrad(H, H, Tt, br, H, la.ctx, H, g + lo.o_w));
+    HS_TRY(ln_bwd(Tt, cols_tgt, ws.db, la.y1s, la.st1, lo.ln1_g, lo.ln1_b, lo.o_b, site_dec(c, i, 0), lg.s1, lg.m1, lg.p1, &br));
+    wgrad(H, H, Tt, br, H, la.ctx, H, g + lo.o_w);
     HS_TRY(dgrad(Tt, H, H, br, W(dt, w, lo.o_w), ws.dctx, nullptr));
     AttnOperands self{la.qkv, at(dt, (const void*)la.qkv, H), at(dt, (const void*)la.qkv, 2 * H), 3 * (int64_t)H, 3 * (int64_t)H, tgt_lens, tgt_lens,
                       Lt, Lt, A, 1};
     HS_TRY(launch_attention_general_bwd(ctx, dt, self, B, la.ctx, la.lse, ws.dctx, lg.dqkv, 3 * (int64_t)H, at(dt, lg.dqkv, H),
                                         at(dt, lg.dqkv, 2 * H), 3 * (int64_t)H, ws.dvec, s));
-    HS_TRY(hand_over());
-    HS_TRY(bias_grad(lg.dqkv, Tt, 3 * H, g + lo.qkv_b));
-    HS_TRY(wgrad(3 * H, H, Tt, lg.dqkv, 3 * H, y_in, H, g + lo.qkv_w));
+    bias_grad(lg.dqkv, Tt, 3 * H, g + lo.qkv_b);
+    wgrad(3 * H, H, Tt, lg.dqkv, 3 * H, y_in, H, g + lo.qkv_w);
     HS_TRY(dgrad(Tt, H, 3 * H, lg.dqkv, W(dt, w, lo.qkv_w), ws.da, lg.s1));
     dcur = ws.da;
-    HS_TRY(update_after_both(lo.qkv_w, i + 1 < c.n_dec ? o.dec[i + 1].qkv_w : o.total));
+    if (i == 0 || dec_top - i + 1 == per_hand_over) {
+      HS_TRY(enqueue_grads(lo.qkv_w, dec_top + 1 < c.n_dec ? o.dec[dec_top + 1].qkv_w : o.total));
+      dec_top = i - 1;
+    }
   }
   // target embedding: d E[id] += sqrt(H) * (gradient through the embedding dropout).  The scatter (sort of the ids, segment
   // sums) runs on the second stream like the weight gradients; both embedding scatters add into the same slice, in this order.
   HS_TRY(launch_mask_scale(ctx, dt, dcur, ws.de_tgt, (size_t)Tt * H, scale, drop, site_tgt(), s));
-  HS_TRY(hand_over());
+  HS_TRY(order(s, sd));
   HS_TRY(launch_embed_bwd(ctx, dt, ws.de_tgt, tgt_in, B, Lt, H, c.vocab, 0, g + o.emb, nullptr, 0.f, ws.emb, sd));
 
   // ---- encoder ----
@@ -609,41 +601,26 @@ hs_status hs_s2s_bwd(hs_ctx* ctx, const void* w, const void* acts, const int32_t
     const LayerGrads& lg = ws.enc[i];
     const void* x_in = (i == 0) ? a.x0 : a.enc[i - 1].x2;
     const void* br;
-    HS_TRY(ln_bwd(Ts, dcur, la.y2, la.st2, lo.ln2_g, lo.ln2_b, lo.ffn2_b, site_enc(i, 1), lg.s2, lg.m2, lg.p2, &br));
+    HS_TRY(ln_bwd(Ts, cols_src, dcur, la.y2, la.st2, lo.ln2_g, lo.ln2_b, lo.ffn2_b, site_enc(i, 1), lg.s2, lg.m2, lg.p2, &br));
     HS_TRY(ffn_bwd(Ts, lo, lg, br, la.x1, la.h, ws.da));
-    HS_TRY(ln_bwd(Ts, ws.da, la.y1, la.st1, lo.ln1_g, lo.ln1_b, lo.o_b, site_enc(i, 0), lg.s1, lg.m1, lg.p1, &br));
-    HS_TRY(wgrad(H, H, Ts, br, H, la.ctx, H, g + lo.o_w));
+    HS_TRY(ln_bwd(Ts, cols_src, ws.da, la.y1, la.st1, lo.ln1_g, lo.ln1_b, lo.o_b, site_enc(i, 0), lg.s1, lg.m1, lg.p1, &br));
+    wgrad(H, H, Ts, br, H, la.ctx, H, g + lo.o_w);
     HS_TRY(dgrad(Ts, H, H, br, W(dt, w, lo.o_w), ws.dctx, nullptr));
     HS_TRY(launch_attention_bwd(ctx, dt, la.qkv, la.ctx, la.lse, ws.dctx, src_lens, B, Ls, A, lg.dqkv, ws.dvec, s));
-    HS_TRY(hand_over());
-    HS_TRY(bias_grad(lg.dqkv, Ts, 3 * H, g + lo.qkv_b));
-    HS_TRY(wgrad(3 * H, H, Ts, lg.dqkv, 3 * H, x_in, H, g + lo.qkv_w));
+    bias_grad(lg.dqkv, Ts, 3 * H, g + lo.qkv_b);
+    wgrad(3 * H, H, Ts, lg.dqkv, 3 * H, x_in, H, g + lo.qkv_w);
     HS_TRY(dgrad(Ts, H, 3 * H, lg.dqkv, W(dt, w, lo.qkv_w), ws.db, lg.s1));
     dcur = ws.db;
-    HS_TRY(update_after_both(lo.qkv_w, i + 1 < c.n_enc ? o.enc[i + 1].qkv_w : o.dec[0].qkv_w));
+    if (i == 0 || enc_top - i + 1 == per_hand_over) {
+      HS_TRY(enqueue_grads(lo.qkv_w, enc_top + 1 < c.n_enc ? o.enc[enc_top + 1].qkv_w : o.dec[0].qkv_w));
+      enc_top = i - 1;
+    }
   }
   HS_TRY(launch_mask_scale(ctx, dt, dcur, ws.de_src, (size_t)Ts * H, scale, drop, site_src(), s));
-  HS_TRY(hand_over());
+  HS_TRY(order(s, sd));
   HS_TRY(launch_embed_bwd(ctx, dt, ws.de_src, src, B, Ls, H, c.vocab, 0, g + o.emb, nullptr, 0.f, ws.emb, sd));
-  if (upd.on) {      // the shared embedding: its gradient is complete only now
-    if (overlap) {
-      hipEvent_t e = ctx->events[next_event++];
-      HS_HIP_CHECK(ctx, hipEventRecord(e, sd));
-      HS_HIP_CHECK(ctx, hipStreamWaitEvent(su, e, 0));
-    }
-    HS_TRY(update_slice(ctx, upd, o.emb, o.enc[0].qkv_w, su));
-    if (overlap) {
-      hipEvent_t e = ctx->events[next_event++];
-      HS_HIP_CHECK(ctx, hipEventRecord(e, su));
-      HS_HIP_CHECK(ctx, hipStreamWaitEvent(s, e, 0));
-    }
-  }
-  if (overlap) {     // everything the second stream did is ordered before whatever the caller enqueues next
-    hipEvent_t e = ctx->events[n_events - 1];
-    HS_HIP_CHECK(ctx, hipEventRecord(e, sd));
-    HS_HIP_CHECK(ctx, hipStreamWaitEvent(s, e, 0));
-  }
-  return HS_OK;
+  if (upd.on) HS_TRY(update_slice(ctx, upd, o.emb, o.enc[0].qkv_w, sd));      // the shared embedding: its gradient is complete only now
+  return order(sd, s);     // everything the second stream did is ordered before whatever the caller enqueues next
 }
 
 hs_status hs_op_attention_general_fwd(int32_t dtype, const void* q, int64_t ldq, const void* k, const void* v, int64_t ldkv,

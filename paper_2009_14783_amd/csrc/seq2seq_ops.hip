@@ -72,26 +72,6 @@ __global__ __launch_bounds__(256) void mask_scale_kernel(const T* __restrict__ x
   V4<T>::st(y + 4 * i, v);
 }
 
-template <class T>
-__global__ __launch_bounds__(256) void relu_kernel(T* __restrict__ x, size_t n4) {
-  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= n4) return;
-  float4 v = V4<T>::ld(x + 4 * i);
-  v.x = fmaxf(v.x, 0.f); v.y = fmaxf(v.y, 0.f); v.z = fmaxf(v.z, 0.f); v.w = fmaxf(v.w, 0.f);
-  V4<T>::st(x + 4 * i, v);
-}
-
-// dx *= (h > 0), h the ReLU's output
-template <class T>
-__global__ __launch_bounds__(256) void relu_bwd_kernel(T* __restrict__ dx, const T* __restrict__ h, size_t n4) {
-  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= n4) return;
-  float4 d = V4<T>::ld(dx + 4 * i);
-  const float4 a = V4<T>::ld(h + 4 * i);
-  d.x = a.x > 0.f ? d.x : 0.f; d.y = a.y > 0.f ? d.y : 0.f; d.z = a.z > 0.f ? d.z : 0.f; d.w = a.w > 0.f ? d.w : 0.f;
-  V4<T>::st(dx + 4 * i, d);
-}
-
 __device__ __forceinline__ float block_reduce256(float v, bool is_max, float* sh) {
   v = is_max ? wave_max(v) : wave_sum(v);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -294,30 +274,6 @@ hs_status launch_mask_scale(hs_ctx* ctx, int dtype, const void* x, void* y, size
   if (dtype == HS_BF16) hipLaunchKernelGGL(mask_scale_kernel<bf16>, grid, dim3(256), 0, s, (const bf16*)x, (bf16*)y, n4, alpha, drop, site);
   else hipLaunchKernelGGL(mask_scale_kernel<float>, grid, dim3(256), 0, s, (const float*)x, (float*)y, n4, alpha, drop, site);
   S2S_LAUNCH_CHECK(ctx, "mask_scale");
-  return HS_OK;
-}
-
-hs_status launch_relu(hs_ctx* ctx, int dtype, void* x, size_t n, hipStream_t s) {
-  if (n == 0) return HS_OK;
-  if (n & 3) return hs_fail(ctx, HS_ERR_SHAPE, "relu: element count must be a multiple of 4");
-  KScope scope(ctx ? ctx->prof : nullptr, KC_ELEMWISE, (double)n, 2.0 * n * esize(dtype), s);
-  const size_t n4 = n / 4;
-  dim3 grid((unsigned)((n4 + 255) / 256));
-  if (dtype == HS_BF16) hipLaunchKernelGGL(relu_kernel<bf16>, grid, dim3(256), 0, s, (bf16*)x, n4);
-  else hipLaunchKernelGGL(relu_kernel<float>, grid, dim3(256), 0, s, (float*)x, n4);
-  S2S_LAUNCH_CHECK(ctx, "relu");
-  return HS_OK;
-}
-
-hs_status launch_relu_bwd(hs_ctx* ctx, int dtype, void* dx, const void* h, size_t n, hipStream_t s) {
-  if (n == 0) return HS_OK;
-  if (n & 3) return hs_fail(ctx, HS_ERR_SHAPE, "relu_bwd: element count must be a multiple of 4");
-  KScope scope(ctx ? ctx->prof : nullptr, KC_ELEMWISE, (double)n, 3.0 * n * esize(dtype), s);
-  const size_t n4 = n / 4;
-  dim3 grid((unsigned)((n4 + 255) / 256));
-  if (dtype == HS_BF16) hipLaunchKernelGGL(relu_bwd_kernel<bf16>, grid, dim3(256), 0, s, (bf16*)dx, (const bf16*)h, n4);
-  else hipLaunchKernelGGL(relu_bwd_kernel<float>, grid, dim3(256), 0, s, (float*)dx, (const float*)h, n4);
-  S2S_LAUNCH_CHECK(ctx, "relu_bwd");
   return HS_OK;
 }
 

@@ -206,6 +206,24 @@ def test_gemm_bf16_few_tiles(hs, M, N, K, layout):
             assert rel(host(dC), R.astype(np.float64) + prod) < 2e-6, scratch is None
 
 
+@pytest.mark.parametrize("M,N,K", [(1, 1, 1), (31, 33, 7), (33, 64, 8), (64, 130, 36), (257, 512, 260), (100, 40, 1029), (1800, 1730, 43), (1793, 1792, 64)])
+def test_gemm_fp32_tilings(hs, M, N, K):
+    """All four layouts around the edges of the 32x32 tiles (contraction over 4 waves up to 256 values, over 16 beyond) and of the
+    128x128 ones (from 192 tiles on), contractions that end inside a step of 8, unaligned rows.  A sum of K products of fp32
+    numbers, in any order, is within K 2^-24 sum |a b| of the exact one, and one more rounding for the addition to C."""
+    rng = np.random.default_rng(M + N + K)
+    for ak in (0, 1):
+        for bk in (0, 1):
+            A, B = rng.standard_normal((M, K)).astype(np.float32), rng.standard_normal((N, K)).astype(np.float32)
+            C = rng.standard_normal((M, N)).astype(np.float32)
+            dA, dB, dC = dev(A if ak else np.ascontiguousarray(A.T)), dev(B if bk else np.ascontiguousarray(B.T)), dev(C)
+            hs.hs_op_gemm(0, ak, bk, M, N, K, dA, K if ak else M, dB, K if bk else N, dC, N, c_f32=1, beta=1.0)
+            torch.cuda.synchronize()
+            a, b = A.astype(np.float64), B.astype(np.float64)
+            bound = K * 2.0 ** -24 * (np.abs(a) @ np.abs(b).T) + 2.0 ** -23 * (np.abs(C) + np.abs(a @ b.T))
+            assert np.all(np.abs(host(dC) - (C + a @ b.T)) <= bound), (ak, bk)
+
+
 def test_gemm_variant_out_of_range_is_an_error(hs):
     for v in (-2, 12, 1000):
         with pytest.raises(hs.HsError):

@@ -400,3 +400,37 @@ def test_update_inside_backward_gives_the_bits_of_the_separate_calls(W, compute)
         wk.close()
     for k in states[0]:
         assert torch.equal(states[0][k], states[1][k]), k
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("compute", ["fp32", "bf16"])
+@pytest.mark.parametrize("B", [32, 33])
+def test_backward_on_both_sides_of_the_few_rows_limit(W, B, compute):
+    """2048 rows (gradients of four layers handed to the second stream at a time, a buffer set per layer) and 2112 (layer by layer, two
+    sets), five layers so that the last hand-over is a partial one: the gradient is the sum over the two halves of the batch, and
+    the update armed inside the pass gives the bits of the separate calls."""
+    model = dict(n_layers=5, hidden=128, n_heads=2, ffn=256, vocab=500, max_pos=64, ln_eps=1e-12)
+    layout = O.param_layout(O.ModelCfg(**model))
+    theta = synth.init_params(layout, 5)
+    rng = synth.rng_for(6)
+    lens = [int(x) for x in rng.integers(1, 65, B)]
+    mb = synth.make_micro_batch(rng, lens, 64, model["vocab"], "uniform")
+    cut = B // 2
+    n = int(np.searchsorted(mb["mlm_pos"], cut * 64))
+    halves = [dict(mb, ids=mb["ids"][:cut], lens=mb["lens"][:cut], mlm_pos=mb["mlm_pos"][:n], mlm_label=mb["mlm_label"][:n]),
+              dict(mb, ids=mb["ids"][cut:], lens=mb["lens"][cut:], mlm_pos=mb["mlm_pos"][n:] - cut * 64, mlm_label=mb["mlm_label"][n:])]
+    adam = dict(lr=1e-3, beta1=0.9, beta2=0.999, eps=1e-8, weight_decay=0.01)
+    wk = W(model, compute, theta)
+    _, whole = gpu_micro_grad(wk, mb)
+    parts = [gpu_micro_grad(wk, h)[1].astype(np.float64) for h in halves]
+    compare_flat(layout, whole, parts[0] + parts[1], TOL[compute], "whole against halves")
+    wk.close()
+    states = []
+    for in_backward in (False, True):
+        wk = W(model, compute, theta)
+        wk.train_step([wk.upload(mb)], adam, update_in_backward=in_backward)
+        torch.cuda.synchronize()
+        states.append({k: getattr(wk, k).clone() for k in ("w", "m", "v", "G")})
+        wk.close()
+    for k in states[0]:
+        assert torch.equal(states[0][k], states[1][k]), k
