@@ -6,8 +6,7 @@
 // outputs only).
 //
 // bf16: MFMA kernels of the same shape as the self-attention ones (a wave owns 32 rows in registers and
-// streams the other side through LDS in blocks of 64 rows; see attention_mfma.hip).  fp32: one thread per
-// owned row, blocks of 64 streamed rows staged in LDS as fp32.
+// streams the other side through LDS in blocks of 64 rows; see attention_mfma.hip).  fp32: attention_f32.hip.
 #include "attention_tiles.h"
 
 namespace {
@@ -266,174 +265,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   }
 }
 
-// ------------------------------------------------------------------------------------------
-// fp32: one thread per owned row
-// ------------------------------------------------------------------------------------------
-constexpr int D = 64;
-
-__device__ __forceinline__ void stage_f32(float (*dst)[D], const float* __restrict__ src, int64_t row_stride, int row0, int nrows_valid,
-                                          int lane) {
-  for (int e = lane; e < 64 * D; e += 64) {
-    const int r = e >> 6, c = e & 63;
-    dst[r][c] = (r < nrows_valid) ? src[(int64_t)(row0 + r) * row_stride + c] : 0.f;
-  }
-}
-
-template <bool CAUSAL>
-__global__ __launch_bounds__(64) void gen_fwd_simt(View a, float* __restrict__ out, float* __restrict__ lse) {
-  __shared__ float Ks[64][D];
-  __shared__ float Vs[64][D];
-  const int lane = threadIdx.x;
-  const int b = blockIdx.z, h = blockIdx.y, qi = blockIdx.x * 64 + lane;
-  const int H = a.A * D;
-  const int klen = clamp_len(a.klens[b], a.Lk);
-  const float* qb_ = (const float*)a.q + (int64_t)b * a.Lq * a.ldq + h * D;
-  const float* kb_ = (const float*)a.k + (int64_t)b * a.Lk * a.ldkv + h * D;
-  const float* vb_ = (const float*)a.v + (int64_t)b * a.Lk * a.ldkv + h * D;
-  const bool active = qi < a.Lq;
-  const int kend = CAUSAL ? min(klen, (int)blockIdx.x * 64 + 64) : klen;
-  float q[D], acc[D];
-#pragma unroll
-  for (int c = 0; c < D; ++c) { q[c] = active ? 0.125f * qb_[(int64_t)qi * a.ldq + c] : 0.f; acc[c] = 0.f; }
-  float m = -1.0e30f, l = 0.f;
-  for (int k0 = 0; k0 < kend; k0 += 64) {
-    const int nv = min(64, kend - k0);
-    __syncthreads();
-    stage_f32(Ks, kb_, a.ldkv, k0, nv, lane);
-    stage_f32(Vs, vb_, a.ldkv, k0, nv, lane);
-    __syncthreads();
-    for (int j = 0; j < nv; ++j) {
-      if (CAUSAL && k0 + j > qi) break;      // keys are visited in ascending order
-      float s = 0.f;
-#pragma unroll
-      for (int c = 0; c < D; ++c) s = fmaf(q[c], Ks[j][c], s);
-      const float mn = fmaxf(m, s);
-      const float alpha = __expf(m - mn), p = __expf(s - mn);
-      l = l * alpha + p;
-#pragma unroll
-      for (int c = 0; c < D; ++c) acc[c] = fmaf(p, Vs[j][c], acc[c] * alpha);
-      m = mn;
-    }
-  }
-  if (active) {
-    const float inv = 1.0f / l;
-    float* o = out + ((int64_t)b * a.Lq + qi) * H + h * D;
-#pragma unroll
-    for (int c = 0; c < D; ++c) o[c] = acc[c] * inv;
-    lse[((int64_t)b * a.A + h) * a.Lq + qi] = m + logf(l);
-  }
-}
-
-template <bool CAUSAL>
-__global__ __launch_bounds__(64) void gen_bwd_dq_simt(View a, const float* __restrict__ out, const float* __restrict__ lse,
-                                                      const float* __restrict__ d_out, float* __restrict__ dq_out, int64_t lddq,
-                                                      float* __restrict__ dvec) {
-  __shared__ float Ks[64][D];
-  __shared__ float Vs[64][D];
-  const int lane = threadIdx.x;
-  const int b = blockIdx.z, h = blockIdx.y, qi = blockIdx.x * 64 + lane;
-  const int H = a.A * D;
-  const int klen = clamp_len(a.klens[b], a.Lk), qlen = clamp_len(a.qlens[b], a.Lq);
-  const float* qb_ = (const float*)a.q + (int64_t)b * a.Lq * a.ldq + h * D;
-  const float* kb_ = (const float*)a.k + (int64_t)b * a.Lk * a.ldkv + h * D;
-  const float* vb_ = (const float*)a.v + (int64_t)b * a.Lk * a.ldkv + h * D;
-  const bool active = qi < qlen;     // padded query rows get zero gradient
-  const int kend = CAUSAL ? min(klen, (int)blockIdx.x * 64 + 64) : klen;
-  float q[D], go[D], dq[D];
-  float dv_ = 0.f;
-#pragma unroll
-  for (int c = 0; c < D; ++c) {
-    q[c] = active ? 0.125f * qb_[(int64_t)qi * a.ldq + c] : 0.f;
-    go[c] = active ? d_out[((int64_t)b * a.Lq + qi) * H + h * D + c] : 0.f;
-    const float o = active ? out[((int64_t)b * a.Lq + qi) * H + h * D + c] : 0.f;
-    dv_ = fmaf(go[c], o, dv_);
-    dq[c] = 0.f;
-  }
-  const float row_lse = active ? lse[((int64_t)b * a.A + h) * a.Lq + qi] : 0.f;
-  for (int k0 = 0; k0 < kend; k0 += 64) {
-    const int nv = min(64, kend - k0);
-    __syncthreads();
-    stage_f32(Ks, kb_, a.ldkv, k0, nv, lane);
-    stage_f32(Vs, vb_, a.ldkv, k0, nv, lane);
-    __syncthreads();
-    if (active) {
-      for (int j = 0; j < nv; ++j) {
-        if (CAUSAL && k0 + j > qi) break;
-        float s = 0.f, dp = 0.f;
-#pragma unroll
-        for (int c = 0; c < D; ++c) { s = fmaf(q[c], Ks[j][c], s); dp = fmaf(go[c], Vs[j][c], dp); }
-        const float ds = __expf(s - row_lse) * (dp - dv_);
-#pragma unroll
-        for (int c = 0; c < D; ++c) dq[c] = fmaf(ds, Ks[j][c], dq[c]);
-      }
-    }
-  }
-  if (qi < a.Lq) {
-    float* o = dq_out + ((int64_t)b * a.Lq + qi) * lddq + h * D;
-#pragma unroll
-    for (int c = 0; c < D; ++c) o[c] = 0.125f * dq[c];
-    dvec[((int64_t)b * a.A + h) * a.Lq + qi] = dv_;
-  }
-}
-
-template <bool CAUSAL>
-__global__ __launch_bounds__(64) void gen_bwd_dkv_simt(View a, const float* __restrict__ lse, const float* __restrict__ d_out,
-                                                       const float* __restrict__ dvec, float* __restrict__ dk_out, float* __restrict__ dv_out,
-                                                       int64_t lddkv) {
-  __shared__ float Qs[64][D];
-  __shared__ float Gs[64][D];
-  __shared__ float lse_s[64], dvec_s[64];
-  const int lane = threadIdx.x;
-  const int b = blockIdx.z, h = blockIdx.y, kj = blockIdx.x * 64 + lane;
-  const int H = a.A * D;
-  const int klen = clamp_len(a.klens[b], a.Lk), qlen = clamp_len(a.qlens[b], a.Lq);
-  const float* qb_ = (const float*)a.q + (int64_t)b * a.Lq * a.ldq + h * D;
-  const float* kb_ = (const float*)a.k + (int64_t)b * a.Lk * a.ldkv + h * D;
-  const float* vb_ = (const float*)a.v + (int64_t)b * a.Lk * a.ldkv + h * D;
-  const bool active = kj < klen;     // padded keys take no part
-  float k[D], v[D], dk[D], dv[D];
-#pragma unroll
-  for (int c = 0; c < D; ++c) {
-    k[c] = active ? kb_[(int64_t)kj * a.ldkv + c] : 0.f;
-    v[c] = active ? vb_[(int64_t)kj * a.ldkv + c] : 0.f;
-    dk[c] = 0.f; dv[c] = 0.f;
-  }
-  for (int q0 = CAUSAL ? (int)blockIdx.x * 64 : 0; q0 < qlen; q0 += 64) {     // padded queries carry zero gradient: skipped
-    const int nv = min(64, qlen - q0);
-    __syncthreads();
-    stage_f32(Qs, qb_, a.ldq, q0, nv, lane);
-    stage_f32(Gs, d_out + (int64_t)b * a.Lq * H + h * D, (int64_t)H, q0, nv, lane);
-    if (lane < nv) {
-      lse_s[lane] = lse[((int64_t)b * a.A + h) * a.Lq + q0 + lane];
-      dvec_s[lane] = dvec[((int64_t)b * a.A + h) * a.Lq + q0 + lane];
-    }
-    __syncthreads();
-    if (active) {
-      for (int i = 0; i < nv; ++i) {
-        if (CAUSAL && q0 + i < kj) continue;
-        float s = 0.f, dp = 0.f;
-#pragma unroll
-        for (int c = 0; c < D; ++c) { s = fmaf(Qs[i][c], k[c], s); dp = fmaf(Gs[i][c], v[c], dp); }
-        const float p = __expf(0.125f * s - lse_s[i]);
-        const float ds = p * (dp - dvec_s[i]);
-#pragma unroll
-        for (int c = 0; c < D; ++c) { dv[c] = fmaf(p, Gs[i][c], dv[c]); dk[c] = fmaf(ds, Qs[i][c], dk[c]); }
-      }
-    }
-  }
-  if (kj < a.Lk) {
-    float* ok_ = dk_out + ((int64_t)b * a.Lk + kj) * lddkv + h * D;
-    float* ov_ = dv_out + ((int64_t)b * a.Lk + kj) * lddkv + h * D;
-#pragma unroll
-    for (int c = 0; c < D; ++c) { ok_[c] = 0.125f * dk[c]; ov_[c] = dv[c]; }
-  }
-}
-
 View make_view(const AttnOperands& x) {
   View v;
   v.q = x.q; v.k = x.k; v.v = x.v; v.ldq = x.ldq; v.ldkv = x.ldkv; v.qlens = x.qlens; v.klens = x.klens;
   v.Lq = x.Lq; v.Lk = x.Lk; v.A = x.A;
   return v;
+}
+
+AttnF32 f32_problem(const AttnOperands& x) {
+  return AttnF32{(const float*)x.q, (const float*)x.k, (const float*)x.v, x.ldq, x.ldkv, x.qlens, x.klens, x.Lq, x.Lk, x.A, x.causal,
+                 DropCfg{0u, 1.0f, 0u, 0u, 0u}, 0};
 }
 
 hs_status check_operands(hs_ctx* ctx, int dtype, const AttnOperands& x, const char* who) {
@@ -463,9 +304,7 @@ hs_status launch_attention_general_fwd(hs_ctx* ctx, int dtype, const AttnOperand
     if (x.causal) hipLaunchKernelGGL(gen_fwd_mfma<true>, grid, dim3(256), 0, s, v, (bf16*)out, lse);
     else hipLaunchKernelGGL(gen_fwd_mfma<false>, grid, dim3(256), 0, s, v, (bf16*)out, lse);
   } else {
-    dim3 grid((x.Lq + 63) / 64, x.A, B);
-    if (x.causal) hipLaunchKernelGGL(gen_fwd_simt<true>, grid, dim3(64), 0, s, v, (float*)out, lse);
-    else hipLaunchKernelGGL(gen_fwd_simt<false>, grid, dim3(64), 0, s, v, (float*)out, lse);
+    launch_attention_f32_fwd(f32_problem(x), B, (float*)out, lse, s);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hs_fail(ctx, HS_ERR_HIP, std::string("attention_general_fwd: ") + hipGetErrorString(e));
@@ -494,14 +333,7 @@ hs_status launch_attention_general_bwd(hs_ctx* ctx, int dtype, const AttnOperand
       hipLaunchKernelGGL(gen_bwd_dkv_mfma<false>, gk, dim3(256), 0, s, v, lse, (const bf16*)d_out, (const float*)dvec, (bf16*)dk, (bf16*)dv, lddkv);
     }
   } else {
-    dim3 gq((x.Lq + 63) / 64, x.A, B), gk((x.Lk + 63) / 64, x.A, B);
-    if (x.causal) {
-      hipLaunchKernelGGL(gen_bwd_dq_simt<true>, gq, dim3(64), 0, s, v, (const float*)out, lse, (const float*)d_out, (float*)dq, lddq, dvec);
-      hipLaunchKernelGGL(gen_bwd_dkv_simt<true>, gk, dim3(64), 0, s, v, lse, (const float*)d_out, (const float*)dvec, (float*)dk, (float*)dv, lddkv);
-    } else {
-      hipLaunchKernelGGL(gen_bwd_dq_simt<false>, gq, dim3(64), 0, s, v, (const float*)out, lse, (const float*)d_out, (float*)dq, lddq, dvec);
-      hipLaunchKernelGGL(gen_bwd_dkv_simt<false>, gk, dim3(64), 0, s, v, lse, (const float*)d_out, (const float*)dvec, (float*)dk, (float*)dv, lddkv);
-    }
+    launch_attention_f32_bwd(f32_problem(x), B, (const float*)out, lse, (const float*)d_out, (float*)dq, lddq, (float*)dk, (float*)dv, lddkv, s);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hs_fail(ctx, HS_ERR_HIP, std::string("attention_general_bwd: ") + hipGetErrorString(e));

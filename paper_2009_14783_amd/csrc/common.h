@@ -264,6 +264,18 @@ struct AttnOperands {
   const int32_t *qlens, *klens;
   int Lq, Lk, A, causal;
 };
+// fp32 attention: sequences of Lq queries and Lk keys, q/k/v the first rows of sequence 0, lengths per sequence (clamped to 1 .. L)
+struct AttnF32 {
+  const float *q, *k, *v;
+  int64_t ldq, ldkv;
+  const int32_t *qlens, *klens;
+  int Lq, Lk, A, causal;
+  DropCfg drop;       // of the probabilities; element (query, key) of the site = ((b*A + h)*Lq + query)*Lk + key
+  uint32_t site;
+};
+void launch_attention_f32_fwd(const AttnF32& x, int B, float* out, float* lse, hipStream_t s);
+void launch_attention_f32_bwd(const AttnF32& x, int B, const float* out, const float* lse, const float* d_out, float* dq, int64_t lddq, float* dk,
+                              float* dv, int64_t lddkv, hipStream_t s);
 hs_status launch_attention_general_fwd(hs_ctx* ctx, int dtype, const AttnOperands& x, int B, void* out, float* lse, hipStream_t s);
 hs_status launch_attention_general_bwd(hs_ctx* ctx, int dtype, const AttnOperands& x, int B, const void* out, const float* lse,
                                        const void* d_out, void* dq, int64_t lddq, void* dk, void* dv, int64_t lddkv, float* dvec,
