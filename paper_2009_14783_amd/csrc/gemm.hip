@@ -2,7 +2,7 @@
 //   bf16: MFMA 32x32x16 tiles, fp32 accumulation, LDS double buffering.  Operands whose
 //         contraction index is NOT the contiguous one are staged in their natural layout and read
 //         with the LDS transpose read of gfx950, so every global and LDS access is 16/8 bytes wide.
-//   fp32: plain tiled SIMT kernel (small reference-precision configurations only).
+//   fp32: gemm_f32.hip.
 #include "gemm_dev.h"
 
 #include <algorithm>

@@ -1,4 +1,4 @@
-// gemm_bf16_wide for A k-major, B n-major
+// the wide, direct-to-LDS and split-contraction kernels for A k-major, B n-major
 #include "gemm_ksplit.h"
 
 hipError_t gemm_wide_launch_kn(int cfg, const GemmDev& p, int splits, hipStream_t s) {

@@ -1,6 +1,6 @@
 // Training-step entry points of the translation workload (encoder-decoder Transformer): forward, label-smoothed
 // loss with the output projection, backward.  Host orchestration only: every arithmetic step is a kernel in
-// gemm.hip / attention*.hip / rowops.hip / seq2seq_ops.hip.  One stream; the optimizer entry points are shared with
+// gemm*.hip / attention*.hip / rowops.hip / seq2seq_ops.hip.  The optimizer entry points are shared with
 // the encoder-only path.
 #include <algorithm>
 #include <cmath>

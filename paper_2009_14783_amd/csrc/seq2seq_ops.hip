@@ -1,6 +1,5 @@
 // Row and element kernels of the translation workload that the encoder-only path does not have:
-// scaled token embedding plus the fixed sinusoidal position table, ReLU and its gradient, a dropout
-// mask with a scale applied to a gradient, and the label-smoothed cross-entropy over fp32 logits.
+// scaled token embedding plus the fixed sinusoidal position table, a dropout mask with a scale applied to a gradient, and the label-smoothed cross-entropy over fp32 logits.
 #include "common.h"
 
 namespace {
