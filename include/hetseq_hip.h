@@ -288,6 +288,12 @@ hs_status hs_adam_step(float* w, float* m, float* v, const float* G, void* w_low
                        double lr, double beta1, double beta2, double eps, double weight_decay, int64_t t,
                        void* stream);
 
+/* hs_grad_accum_normalize(G, NULL, n, 0, denom) and hs_adam_step on the result in one pass over the buffers: the same
+ * arithmetic, the same bits in w, m, v, G and w_lowp_out. */
+hs_status hs_normalize_adam_step(float* w, float* m, float* v, float* G, void* w_lowp_out, size_t n, double denom,
+                                 double lr, double beta1, double beta2, double eps, double weight_decay, int64_t t,
+                                 void* stream);
+
 /* The loss that a step reports (section "Optimizer and Learning Rate Scheduler": every worker's loss comes with a
  * weight, and the weighted sum over all workers divided by the global weight equals the non-distributed loss):
  * *loss_out = (loss_sums[0] + ... + loss_sums[n - 1]) / denom, the sums added in index order.  loss_sums [n] dev:

@@ -65,6 +65,7 @@ _SIGNATURES = {
     "hs_encoder_bwd": (_I32, [_P, _P, _P, _P, _P, _I32, _I32, _P, _P, _I32, _P, _SZ, _P]),
     "hs_grad_accum_normalize": (_I32, [_P, _P, _SZ, _I32, _D, _P]),
     "hs_adam_step": (_I32, [_P, _P, _P, _P, _P, _SZ, _D, _D, _D, _D, _D, _I64, _P]),
+    "hs_normalize_adam_step": (_I32, [_P, _P, _P, _P, _P, _SZ, _D, _D, _D, _D, _D, _D, _I64, _P]),
     "hs_cast_params": (_I32, [_P, _P, _SZ, _I32, _P]),
     "hs_arm_update": (_I32, [_P, _P, _P, _P, _P, _P, _D, _D, _D, _D, _D, _D, _I64]),
     "hs_set_dropout": (_I32, [_P, _D, C.c_uint64, C.c_uint32]),
@@ -335,6 +336,11 @@ def hs_grad_accum_normalize(G, g, n, ignore, denom, stream=None):
 def hs_adam_step(w, m, v, G, w_lowp_out, n, lr, beta1, beta2, eps, weight_decay, t, stream=None):
     _check(lib().hs_adam_step(_ptr(w), _ptr(m), _ptr(v), _ptr(G), _ptr(w_lowp_out), n, lr, beta1, beta2, eps, weight_decay,
                               t, _stream(stream)))
+
+
+def hs_normalize_adam_step(w, m, v, G, w_lowp_out, n, denom, lr, beta1, beta2, eps, weight_decay, t, stream=None):
+    _check(lib().hs_normalize_adam_step(_ptr(w), _ptr(m), _ptr(v), _ptr(G), _ptr(w_lowp_out), n, denom, lr, beta1, beta2, eps,
+                                        weight_decay, t, _stream(stream)))
 
 
 def hs_cast_params(src, dst, n, dst_dtype, stream=None):

@@ -343,14 +343,16 @@ hs_status hs_arm_update(hs_ctx* ctx, float* w, float* m, float* v, float* G, voi
 
 }  // extern "C"
 
-// normalise + Adam on the parameters [begin, end) of an armed update
-hs_status update_slice(hs_ctx* ctx, const hs_ctx::Armed& u, int64_t begin, int64_t end, hipStream_t s) {
+// normalise + Adam on the parameters [begin, end) of an armed update; one_pass: both in one kernel, for slices that no large products
+// run beside (beside them the one kernel, with four streams read and five written, measured slower than the two)
+hs_status update_slice(hs_ctx* ctx, const hs_ctx::Armed& u, int64_t begin, int64_t end, hipStream_t s, bool one_pass) {
   const size_t n = (size_t)(end - begin);
   if (n == 0) return HS_OK;
-  hs_status st = hs_grad_accum_normalize(u.G + begin, nullptr, n, 0, u.denom, s);
+  hs_status st = HS_OK;
+  if (!one_pass) st = hs_grad_accum_normalize(u.G + begin, nullptr, n, 0, u.denom, s);
   if (st != HS_OK) return hs_fail(ctx, st, hs_last_error(nullptr));
   void* wl = u.wl ? (void*)((bf16*)u.wl + begin) : nullptr;
-  st = hs_adam_step(u.w + begin, u.m + begin, u.v + begin, u.G + begin, wl, n, u.lr, u.beta1, u.beta2, u.eps, u.wd, u.t, s);
+  st = hs_normalize_adam_step(u.w + begin, u.m + begin, u.v + begin, u.G + begin, wl, n, one_pass ? u.denom : 0.0, u.lr, u.beta1, u.beta2, u.eps, u.wd, u.t, s);
   if (st != HS_OK) return hs_fail(ctx, st, hs_last_error(nullptr));
   return HS_OK;
 }
@@ -376,7 +378,7 @@ static hs_status encoder_bwd_impl(hs_ctx* ctx, const hs_ctx::Armed& upd, const v
   std::string why;
   if (!shape_ok(ctx, B, L, &why)) return hs_fail(ctx, HS_ERR_SHAPE, "hs_encoder_bwd: " + why);
   if (B == 0) {      // nothing to back-propagate: an armed update still takes place, on the caller's stream
-    if (upd.on) return update_slice(ctx, upd, 0, ctx->off.total, (hipStream_t)stream);
+    if (upd.on) return update_slice(ctx, upd, 0, ctx->off.total, (hipStream_t)stream, true);
     return HS_OK;
   }
   if (!w || !acts || !ids || !lens || !d_hidden || !g || !workspace) return hs_fail(ctx, HS_ERR_INVALID_ARG, "hs_encoder_bwd: NULL buffer");
@@ -431,7 +433,7 @@ static hs_status encoder_bwd_impl(hs_ctx* ctx, const hs_ctx::Armed& upd, const v
   }
   if (upd.on) {
     HS_TRY(order(sd, su));
-    HS_TRY(update_slice(ctx, upd, o.head_t_w, o.total, su));
+    HS_TRY(update_slice(ctx, upd, o.head_t_w, o.total, su, !own_upd));
   }
   const void* dcur = d_hidden;
   int chunk_top = NL - 1;                    // the highest layer whose gradients are not yet enqueued
@@ -495,7 +497,7 @@ static hs_status encoder_bwd_impl(hs_ctx* ctx, const hs_ctx::Armed& upd, const v
         HS_HIP_CHECK(ctx, hipStreamWaitEvent(su, done[i], 0));
         HS_TRY(order(s, su));
       }
-      HS_TRY(update_slice(ctx, upd, lo.qkv_w, chunk_top + 1 < NL ? o.layer[chunk_top + 1].qkv_w : o.head_t_w, su));
+      HS_TRY(update_slice(ctx, upd, lo.qkv_w, chunk_top + 1 < NL ? o.layer[chunk_top + 1].qkv_w : o.head_t_w, su, !own_upd));
     }
     if (chunk_done) chunk_top = i - 1;
   }
@@ -504,7 +506,7 @@ static hs_status encoder_bwd_impl(hs_ctx* ctx, const hs_ctx::Armed& upd, const v
                               g + o.emb_ln_b, nullptr, beta, T, H, ws.ln_part, s, drop, site_embedding(), drop ? 1 : 0, nullptr));
   if (overlap) HS_HIP_CHECK(ctx, hipStreamWaitEvent(s, sorted, 0));
   HS_TRY(launch_embed_bwd(ctx, dt, ws.dxa, ids, B, L, H, c.vocab, c.max_pos, g + o.emb_word, g + o.emb_pos, beta, ws.emb, s, overlap));
-  if (upd.on) HS_TRY(update_slice(ctx, upd, 0, o.layer[0].qkv_w, s));      // the embedding tables and their LayerNorm last, on the chain
+  if (upd.on) HS_TRY(update_slice(ctx, upd, 0, o.layer[0].qkv_w, s, true));      // the embedding tables and their LayerNorm last, on the chain
   // everything the other streams did is ordered before whatever the caller enqueues next
   HS_TRY(order(sd, s));
   if (own_upd) HS_TRY(order(su, s));

@@ -463,7 +463,7 @@ hs_status hs_s2s_bwd(hs_ctx* ctx, const void* w, const void* acts, const int32_t
   std::string why;
   if (!shape_ok(c, B, Ls, Lt, &why)) return hs_fail(ctx, HS_ERR_SHAPE, "hs_s2s_bwd: " + why);
   if (B == 0) {      // nothing to back-propagate: an armed update still takes place, on the caller's stream
-    if (upd.on) return update_slice(ctx, upd, 0, s2s_offsets(c).total, (hipStream_t)stream);
+    if (upd.on) return update_slice(ctx, upd, 0, s2s_offsets(c).total, (hipStream_t)stream, true);
     return HS_OK;
   }
   if (!w || !acts || !src || !src_lens || !tgt_in || !tgt_lens || !d_dec_out || !g || !workspace)
@@ -513,7 +513,7 @@ hs_status hs_s2s_bwd(hs_ctx* ctx, const void* w, const void* acts, const int32_t
     HS_TRY(launch_layernorm_bwd_cols_batch(ctx, cols_src.data(), (int)cols_src.size(), beta, Ts, H, sd));
     HS_TRY(launch_gemm_group(ctx, dw.data(), (int)dw.size(), sd));
     dw.clear(); cols_tgt.clear(); cols_src.clear();
-    return upd.on ? update_slice(ctx, upd, begin, end, sd) : HS_OK;
+    return upd.on ? update_slice(ctx, upd, begin, end, sd, per_hand_over > 1) : HS_OK;
   };
   auto dgrad = [&](int T, int N, int K, const void* dy, const void* Wm, void* dx, const void* res) {   // dx [T,N] = dy [T,K] W [K,N] (+ res)
     GemmArgs ga = gemm_args(dt, 1, 0, T, N, K, dy, K, Wm, N, dx, N);
@@ -619,7 +619,7 @@ hs_status hs_s2s_bwd(hs_ctx* ctx, const void* w, const void* acts, const int32_t
   HS_TRY(launch_mask_scale(ctx, dt, dcur, ws.de_src, (size_t)Ts * H, scale, drop, site_src(), s));
   HS_TRY(order(s, sd));
   HS_TRY(launch_embed_bwd(ctx, dt, ws.de_src, src, B, Ls, H, c.vocab, 0, g + o.emb, nullptr, 0.f, ws.emb, sd));
-  if (upd.on) HS_TRY(update_slice(ctx, upd, o.emb, o.enc[0].qkv_w, sd));      // the shared embedding: its gradient is complete only now
+  if (upd.on) HS_TRY(update_slice(ctx, upd, o.emb, o.enc[0].qkv_w, sd, true));      // the shared embedding: its gradient is complete only now
   return order(sd, s);     // everything the second stream did is ordered before whatever the caller enqueues next
 }
 

@@ -150,10 +150,9 @@ class Worker:
             return D
         n_total = self.accumulate_micro_batches(batches, fused)
         D = n_total if denom is None else denom
-        hs.hs_grad_accum_normalize(self.G, None, self.P, 0, float(D))
+        hs.hs_normalize_adam_step(self.w, self.m, self.v, self.G, self.w_lowp, self.P, float(D), adam["lr"], adam["beta1"], adam["beta2"],
+                                  adam["eps"], wd, self.t + 1)
         self.t += 1
-        hs.hs_adam_step(self.w, self.m, self.v, self.G, self.w_lowp, self.P, adam["lr"], adam["beta1"], adam["beta2"],
-                        adam["eps"], wd, self.t)
         return D
 
     def reported_loss(self, D) -> float:
@@ -305,9 +304,8 @@ class PairWorker:
         if first:
             hs.hs_fill_zero(self.G, 4 * self.P)
         if first or not update_in_backward:
-            hs.hs_grad_accum_normalize(self.G, None, self.P, 0, D)
-            hs.hs_adam_step(self.w, self.m, self.v, self.G, self.w_lowp, self.P, adam["lr"], adam["beta1"], adam["beta2"], adam["eps"],
-                            adam.get("weight_decay", 0.0), self.t)
+            hs.hs_normalize_adam_step(self.w, self.m, self.v, self.G, self.w_lowp, self.P, D, adam["lr"], adam["beta1"], adam["beta2"],
+                                      adam["eps"], adam.get("weight_decay", 0.0), self.t)
         return D
 
     def reported_loss(self, D):

@@ -381,6 +381,25 @@ def test_adam_matches_oracle_over_steps(hs, n):
         hs.hs_adam_step(w, m, v, w, None, n, 1e-4, 0.9, 0.999, 1e-8, 0.0, 0)
 
 
+@pytest.mark.parametrize("n,denom,lowp", [(3, 7.0, True), (4, 88.0, False), (1_000_003, 88.0, True), (1027, 0.0, True)])
+def test_normalize_adam_in_one_pass_gives_the_bits_of_the_two_calls(hs, n, denom, lowp):
+    rng = np.random.default_rng(n)
+    bufs = [rng.standard_normal(n).astype(np.float32) * s for s in (1e-2, 1e-3, 1.0, 1.0)]
+    bufs[2] = bufs[2] ** 2 * 1e-6
+    two, one = [dev(b.copy()) for b in bufs], [dev(b.copy()) for b in bufs]
+    wl = [torch.zeros(n, dtype=torch.bfloat16, device="cuda") if lowp else None for _ in range(2)]
+    w, m, v, G = two
+    hs.hs_grad_accum_normalize(G, None, n, 0, denom)
+    hs.hs_adam_step(w, m, v, G, wl[0], n, 1e-4, 0.9, 0.999, 1e-8, 0.01, 3)
+    w, m, v, G = one
+    hs.hs_normalize_adam_step(w, m, v, G, wl[1], n, denom, 1e-4, 0.9, 0.999, 1e-8, 0.01, 3)
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(two, one))
+    assert not lowp or torch.equal(wl[0], wl[1])
+    with pytest.raises(hs.HsError):
+        hs.hs_normalize_adam_step(w, m, v, G, wl[1], n, -1.0, 1e-4, 0.9, 0.999, 1e-8, 0.0, 3)
+
+
 def test_error_paths_launch_nothing(hs):
     a = torch.zeros(64, 64, dtype=torch.bfloat16, device="cuda")
     c = torch.zeros(64, 64, dtype=torch.float32, device="cuda")
