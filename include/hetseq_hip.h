@@ -95,7 +95,8 @@ hs_status hs_param_layout(const hs_model_cfg* cfg, hs_param_entry* out, int32_t*
  * a batch of B sequences padded to L (M, the number of masked-LM targets, does not enter). */
 size_t hs_acts_bytes(const hs_model_cfg* cfg, int32_t B, int32_t L, int32_t M);
 /* Bytes of scratch that hs_encoder_fwd / hs_mlm_loss / hs_encoder_bwd need for (B, L, M): the
- * maximum over the three calls, so one buffer serves all. */
+ * maximum over the three calls, so one buffer serves all.  Never falls as B, L or M grow: a buffer
+ * of this size for the largest batch serves every smaller one, with the same results. */
 size_t hs_workspace_bytes(const hs_model_cfg* cfg, int32_t B, int32_t L, int32_t M);
 
 /* ---- optimizer update inside the last backward pass ----------------------------------------

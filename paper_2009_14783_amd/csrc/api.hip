@@ -75,14 +75,11 @@ HeadWs carve_head(const hs_model_cfg& c, int M, void* base) {
 // How the backward pass hands work to the second stream.  The weight-gradient products and the column sums only consume what
 // the chain of activation gradients produces; they run on the second stream behind an event.  An event and the wait for it cost
 // the host 10 us and the GPU about as much, four times a launch, so a pass over few rows, whose kernels take 5 us, hands over several layers at
-// once; the operand buffers then exist once per layer (there is no waiting for them to be free again).  With many rows each layer is
-// handed over by itself, the sooner the better, and the buffers exist twice, by layer parity.
+// once; the operand buffers then exist twice per layer of a hand-over, so that one hand-over's are filled while the one before is read.
+// With many rows each layer is handed over by itself, the sooner the better, and there are two sets.
 // 264 rows (BERT-base): 4.63 ms per step with an event per layer, 4.18 with one per four.
+// The plan follows the workspace that a call is given: two sets always do, more layers are handed over at once where their sets fit.
 struct BwdPlan { int sets, layers_per_hand_over; };
-BwdPlan bwd_plan(const hs_model_cfg& c, int B, int L) {
-  const bool few = (int64_t)B * L <= kFewRows;
-  return BwdPlan{few ? c.n_layers : std::min(2, c.n_layers), few ? 4 : 1};
-}
 
 struct BwdSet { void *dy2, *dy1, *dy2m, *dy1m, *dh, *dqkv, *ln_part2, *ln_part1; };
 struct BwdWs {
@@ -91,12 +88,12 @@ struct BwdWs {
   float* dvec;
   size_t total, gemm_ws_bytes;
 };
-BwdWs carve_bwd(const hs_model_cfg& c, int B, int L, void* base) {
+BwdWs carve_bwd(const hs_model_cfg& c, int B, int L, int sets, void* base) {
   const size_t T = (size_t)B * L, H = c.hidden, F = c.ffn, es = esize(c.compute);
   Carver cv(base);
   BwdWs w;
   w.dxa = cv.take(T * H * es); w.dxb = cv.take(T * H * es); w.dctx = cv.take(T * H * es);
-  w.set.resize(bwd_plan(c, B, L).sets);
+  w.set.resize(sets);
   for (BwdSet& q : w.set) {
     q.dy2 = cv.take(T * H * es); q.dy1 = cv.take(T * H * es);
     q.dy2m = cv.take(T * H * es); q.dy1m = cv.take(T * H * es);     // masked copies (dropout only)
@@ -110,6 +107,17 @@ BwdWs carve_bwd(const hs_model_cfg& c, int B, int L, void* base) {
   w.gemm_ws = cv.take(w.gemm_ws_bytes);
   w.total = cv.off;
   return w;
+}
+
+constexpr int kMaxHandOver = 4;
+int bwd_sets(const hs_model_cfg& c, int layers_per_hand_over) { return std::min(2 * layers_per_hand_over, c.n_layers); }
+size_t bwd_bytes(const hs_model_cfg& c, int B, int L, int layers_per_hand_over) {
+  return carve_bwd(c, B, L, bwd_sets(c, layers_per_hand_over), nullptr).total;
+}
+BwdPlan bwd_plan(const hs_model_cfg& c, int B, int L, size_t workspace_bytes) {
+  int n = (int64_t)B * L <= kFewRows ? kMaxHandOver : 1;
+  while (n > 1 && bwd_bytes(c, B, L, n) > workspace_bytes) --n;
+  return BwdPlan{bwd_sets(c, n), n};
 }
 
 // second stream + ordering events of a context, created on first use
@@ -161,8 +169,10 @@ size_t hs_acts_bytes(const hs_model_cfg* cfg, int32_t B, int32_t L, int32_t M) {
 
 size_t hs_workspace_bytes(const hs_model_cfg* cfg, int32_t B, int32_t L, int32_t M) {
   if (!hs_cfg_valid(cfg, nullptr) || B < 0 || L < 0 || M < 0) return 0;
-  const size_t a = carve_head(*cfg, M, nullptr).total, b = carve_bwd(*cfg, B, L, nullptr).total;
-  return std::max<size_t>(std::max(a, b), 256);
+  // two buffer sets, and room for the others of a pass over few rows up to the size of one more split-K scratch: the sum never falls as
+  // B, L or M grow, so a workspace that is sized for the largest batch serves all of them
+  const size_t two = bwd_bytes(*cfg, B, L, 1), all = bwd_bytes(*cfg, B, L, kMaxHandOver);
+  return std::max<size_t>({carve_head(*cfg, M, nullptr).total, two + std::min(all - two, gemm_scratch_bytes(*cfg)), 256});
 }
 
 hs_status hs_encoder_fwd(hs_ctx* ctx, const void* w, const int32_t* ids, const int32_t* lens, const int32_t* lens_host, int32_t B,
@@ -384,12 +394,12 @@ static hs_status encoder_bwd_impl(hs_ctx* ctx, const hs_ctx::Armed& upd, const v
   if (!w || !acts || !ids || !lens || !d_hidden || !g || !workspace) return hs_fail(ctx, HS_ERR_INVALID_ARG, "hs_encoder_bwd: NULL buffer");
   const hs_model_cfg& c = ctx->cfg;
   const ModelOff& o = ctx->off;
-  if (workspace_bytes < carve_bwd(c, B, L, nullptr).total) return hs_fail(ctx, HS_ERR_WORKSPACE, "hs_encoder_bwd: workspace too small");
+  if (workspace_bytes < bwd_bytes(c, B, L, 1)) return hs_fail(ctx, HS_ERR_WORKSPACE, "hs_encoder_bwd: workspace too small");
   const int dt = c.compute, H = c.hidden, F = c.ffn, T = B * L;
   hipStream_t s = (hipStream_t)stream;
   Acts a = carve_acts(c, B, L, const_cast<void*>(acts));
-  BwdWs ws = carve_bwd(c, B, L, workspace);
-  const BwdPlan plan = bwd_plan(c, B, L);
+  const BwdPlan plan = bwd_plan(c, B, L, workspace_bytes);
+  BwdWs ws = carve_bwd(c, B, L, plan.sets, workspace);
   const float beta = accumulate ? 1.f : 0.f;
   const DropCfg* drop = ctx->drop.thr ? &ctx->drop : nullptr;
   auto run_gemm = [&](GemmArgs& a) { a.ws = ws.gemm_ws; a.ws_bytes = ws.gemm_ws_bytes; return launch_gemm(ctx, a, s); };
@@ -414,7 +424,7 @@ static hs_status encoder_bwd_impl(hs_ctx* ctx, const hs_ctx::Armed& upd, const v
   };
   std::vector<GemmArgs> dw;                  // weight and bias gradients not yet enqueued
   std::vector<LnColsJob> cols;               // ... and LayerNorm column sums
-  std::vector<hipEvent_t> done(NL, nullptr); // recorded on sd behind the gradients of a layer (buffer sets that are used again)
+  std::vector<hipEvent_t> done(NL, nullptr); // of the lowest layer of a hand-over: recorded on sd behind its gradients
   auto enqueue_grads = [&]() -> hs_status {
     HS_TRY(launch_layernorm_bwd_cols_batch(ctx, cols.data(), (int)cols.size(), beta, T, H, sd));
     HS_TRY(launch_gemm_group(ctx, dw.data(), (int)dw.size(), sd));
@@ -441,13 +451,14 @@ static hs_status encoder_bwd_impl(hs_ctx* ctx, const hs_ctx::Armed& upd, const v
     const LayerOff& lo = o.layer[i];
     LayerActs& la = a.layer[i];
     const void* x_in = (i == 0) ? a.x0 : a.layer[i - 1].x2;
-    const int nsets = (int)ws.set.size();
-    const BwdSet& q = ws.set[i % nsets];
+    const BwdSet& q = ws.set[i % plan.sets];
     // With dropout the gradient that enters the two dropped branches is the masked one; the residual paths
     // keep the unmasked gradient.
     void* dy2b = drop ? q.dy2m : q.dy2;
     void* dy1b = drop ? q.dy1m : q.dy1;
-    if (overlap && i + nsets < NL) HS_HIP_CHECK(ctx, hipStreamWaitEvent(s, done[i + nsets], 0));   // this set's buffers are free again
+    // The sets of this hand-over are free again once the last but one is done (its lowest layer is two hand-overs further up).
+    const int free_after = chunk_top + plan.layers_per_hand_over + 1;
+    if (overlap && i == chunk_top && free_after < NL) HS_HIP_CHECK(ctx, hipStreamWaitEvent(s, done[free_after], 0));
     // LN2 backward: dy2 here; d gain/bias and colsum(dy2) = d b2 from its partials
     HS_TRY(launch_layernorm_bwd_rows(ctx, dt, dcur, la.y2, la.st2, W(ctx, w, lo.ln2_g), q.dy2, T, H, q.ln_part2, s, drop, site_ffn_out(i),
                                      drop ? 2 : 0, dy2b));
@@ -489,6 +500,10 @@ static hs_status encoder_bwd_impl(hs_ctx* ctx, const hs_ctx::Armed& upd, const v
     if (plan.layers_per_hand_over > 1 && chunk_done) {
       HS_TRY(order(s, sd));
       HS_TRY(enqueue_grads());
+      if (overlap && i > plan.layers_per_hand_over) {      // a later hand-over will wait for it
+        done[i] = ctx->events[next_event++];
+        HS_HIP_CHECK(ctx, hipEventRecord(done[i], sd));
+      }
     }
     if (upd.on && chunk_done) {
       // The gradients of these layers are final once sd has got here, and their weights are no longer read once s has

@@ -11,7 +11,6 @@ hipError_t gemm_wide_launch_kk(int cfg, const GemmDev& p, int splits, hipStream_
 hipError_t gemm_wide_launch_kn(int cfg, const GemmDev& p, int splits, hipStream_t s);
 hipError_t gemm_wide_launch_nn(int cfg, const GemmDev& p, int splits, hipStream_t s);
 hipError_t gemm_group_launch_nn(int cfg, const GemmGroupDev& g, hipStream_t s);
-int gemm_f32_tile(int64_t tiles128);
 void gemm_f32_launch(bool a_kmajor, bool b_kmajor, const GemmDev& p, hipStream_t s);
 void gemm_f32_group_launch(int tile, const GemmGroupDev& g, hipStream_t s);
 
@@ -469,7 +468,10 @@ hs_status launch_gemm_group(hs_ctx* ctx, const GemmArgs* gs, int n, hipStream_t 
     };
     int cfg = 9;
     if (f32) {
-      cfg = gemm_f32_tile(count(128, 128));
+      // Decided by the mean over the products, not by their sum: the two tilings add in different orders, and the same layers have
+      // to give the same bits however many of them go out together.  24 each are 144 for the six products of an encoder layer,
+      // where the tilings are within an eighth of each other (see gemm_f32_tile).
+      cfg = count(128, 128) >= 24 * gd.n ? 128 : 32;
       count(cfg, cfg);
     } else {      // the tile by the model of choose_cfg, over the tiles of all problems
       float best = 3.0e38f;

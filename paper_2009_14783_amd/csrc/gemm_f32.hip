@@ -163,7 +163,7 @@ void launch(const GemmDev& p, int tile, hipStream_t s) {
 
 // Side of the square tiles for products with this many 128x128 tiles in all: 128 once they are enough to give most CUs one.  At
 // 192 (1024 x 3072 x 768) the two sides take 87 and 96 us, at 144 (768 x 3072 x 1024) 106 and 94 us.
-int gemm_f32_tile(int64_t tiles128) { return tiles128 >= 192 ? 128 : 32; }
+static int gemm_f32_tile(int64_t tiles128) { return tiles128 >= 192 ? 128 : 32; }
 
 void gemm_f32_launch(bool a_kmajor, bool b_kmajor, const GemmDev& p, hipStream_t s) {
   const int tile = gemm_f32_tile((int64_t)((p.M + 127) / 128) * ((p.N + 127) / 128));

@@ -406,8 +406,8 @@ def test_update_inside_backward_gives_the_bits_of_the_separate_calls(W, compute)
 @pytest.mark.parametrize("compute", ["fp32", "bf16"])
 @pytest.mark.parametrize("B", [32, 33])
 def test_backward_on_both_sides_of_the_few_rows_limit(W, B, compute):
-    """2048 rows (gradients of four layers handed to the second stream at a time, a buffer set per layer) and 2112 (layer by layer, two
-    sets), five layers so that the last hand-over is a partial one: the gradient is the sum over the two halves of the batch, and
+    """2048 rows (gradients of up to four layers handed to the second stream at a time) and 2112 (layer by layer, two
+    buffer sets), five layers so that the last hand-over is a partial one: the gradient is the sum over the two halves of the batch, and
     the update armed inside the pass gives the bits of the separate calls."""
     model = dict(n_layers=5, hidden=128, n_heads=2, ffn=256, vocab=500, max_pos=64, ln_eps=1e-12)
     layout = O.param_layout(O.ModelCfg(**model))
@@ -434,3 +434,53 @@ def test_backward_on_both_sides_of_the_few_rows_limit(W, B, compute):
         wk.close()
     for k in states[0]:
         assert torch.equal(states[0][k], states[1][k]), k
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("compute", ["fp32", "bf16"])
+@pytest.mark.parametrize("layers", [1, 2, 9])
+def test_backward_gives_the_same_bits_in_every_workspace_it_accepts(W, layers, compute):
+    """A batch of few rows in the workspace of its own size, of larger batches and in the smallest that is accepted: how many layers the
+    backward pass hands over at once (and so how its buffer sets are used again) follows the workspace, the results do not.
+    One byte less is refused before anything is launched."""
+    from paper_2009_14783_amd import binding as hs
+    model = dict(n_layers=layers, hidden=256, n_heads=4, ffn=1024, vocab=500, max_pos=64, ln_eps=1e-12)
+    theta = synth.init_params(O.param_layout(O.ModelCfg(**model)), 5)
+    rng = synth.rng_for(6)
+    mb = synth.make_micro_batch(rng, [int(x) for x in rng.integers(1, 65, 16)], 64, model["vocab"], "uniform")
+    adam = dict(lr=1e-3, beta1=0.9, beta2=0.999, eps=1e-8, weight_decay=0.01)
+    wk = W(model, compute, theta)
+    d = wk.upload(mb)
+    own = hs.hs_workspace_bytes(wk.cfg, 16, 64, d["M"])
+    assert own <= hs.hs_workspace_bytes(wk.cfg, 33, 64, d["M"]) <= hs.hs_workspace_bytes(wk.cfg, 64, 64, d["M"])
+    wk.forward_backward(d, wk.G, 0, 0)
+    lo, hi = 0, own                        # the smallest accepted size: refused calls launch nothing
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        try:
+            hs.hs_encoder_bwd(wk.ctx, wk.w_compute, wk._acts, d["ids"], d["lens"], 16, 64, wk._dhidden, wk.G, 0, wk._ws, mid)
+            hi = mid
+        except hs.HsError as e:
+            assert e.status == 3
+            lo = mid
+    torch.cuda.synchronize()
+    wk.close()
+    states = []
+    for size in [hi + (own - hi) * k // 6 for k in range(7)] + [4 * own]:
+        wk = W(model, compute, theta)
+        d = wk.upload(mb)
+        wk._ws = torch.full((max(size, own),), 255, dtype=torch.uint8, device="cuda")
+        for armed in (False, True):        # the head's calls need more than the smallest size: only the backward pass is given it
+            w = wk.w_compute
+            hs.hs_encoder_fwd(wk.ctx, w, d["ids"], d["lens"], d["lens_host"], 16, 64, wk._acts, wk._hidden, wk._ws, wk._ws.numel())
+            hs.hs_mlm_loss(wk.ctx, w, wk._hidden, d["mlm_pos"], d["mlm_label"], d["M"], 16, 64, wk.loss_buf, wk._dhidden, wk.G, 0, wk._ws,
+                           wk._ws.numel())
+            if armed:
+                hs.hs_arm_update(wk.ctx, wk.w, wk.m, wk.v, wk.G, wk.w_lowp, 16.0, adam["lr"], adam["beta1"], adam["beta2"], adam["eps"], 0.01, 1)
+            hs.hs_encoder_bwd(wk.ctx, w, wk._acts, d["ids"], d["lens"], 16, 64, wk._dhidden, wk.G, 0, wk._ws, size)
+            torch.cuda.synchronize()
+            states.append((armed, {k: getattr(wk, k).clone() for k in ("w", "m", "v", "G")}))
+        wk.close()
+    for armed, s in states[2:]:
+        for k in s:
+            assert torch.equal(s[k], states[int(armed)][1][k]), (armed, k)

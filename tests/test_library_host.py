@@ -52,6 +52,27 @@ def test_sizes_and_invalid_configs():
     hs.hs_ctx_destroy(ctx)
 
 
+@pytest.mark.parametrize("model", ["tiny", "bert_base", "bert_large"])
+def test_workspace_of_the_largest_batch_covers_every_smaller_one(model):
+    """The size never falls as sequences, length or targets grow, across the row count where the backward pass changes its plan."""
+    cfg = hs.make_cfg(**synth.MODELS[model])
+    for L in (8, 64):
+        rows = [8, 64, 264, 1024, 1536, 2040, 2048, 2056, 2112, 3072, 4096, 8192, 16384]
+        sizes = [hs.hs_workspace_bytes(cfg, r // L, L, 0) for r in rows if r % L == 0]
+        assert sizes == sorted(sizes)
+        assert hs.hs_workspace_bytes(cfg, 2048 // L, L, 100) <= hs.hs_workspace_bytes(cfg, 2048 // L + 1, L, 101)
+    assert hs.hs_workspace_bytes(cfg, 16, 56, 0) <= hs.hs_workspace_bytes(cfg, 16, 64, 0)
+
+
+@pytest.mark.parametrize("model", ["s2s_tiny", "transformer_base"])
+def test_pair_workspace_never_falls_as_the_batch_grows(model):
+    cfg = hs.make_s2s_cfg(**synth.S2S_MODELS[model])
+    sizes = [hs.hs_s2s_workspace_bytes(cfg, B, 32, 32) for B in (1, 8, 63, 64, 65, 66, 128, 256)]
+    assert sizes == sorted(sizes)
+    assert hs.hs_s2s_workspace_bytes(cfg, 64, 24, 32) <= hs.hs_s2s_workspace_bytes(cfg, 64, 32, 32)
+    assert hs.hs_s2s_workspace_bytes(cfg, 64, 32, 24) <= hs.hs_s2s_workspace_bytes(cfg, 64, 32, 32)
+
+
 @pytest.mark.parametrize("model", ["s2s_tiny", "transformer_base"])
 def test_pair_model_layout_matches_oracle_layout(model):
     from oracle import seq2seq_oracle as S
