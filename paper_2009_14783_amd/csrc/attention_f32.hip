@@ -45,12 +45,17 @@ __device__ __forceinline__ f32x16 dot_rows(const f32x4u (&a)[8], const f32x4u (&
   return s;
 }
 __device__ __forceinline__ int row_of(int r, int half) { return 8 * (r >> 2) + 4 * half + (r & 3); }
-// columns 32 db + l%32 of the 32 rows from row0 (at most n - 1), in the order of row_of: loaded ahead of the scores that weigh them
+// columns 32 db + l%32 of the 32 rows from row0 (zeros from row n on), in the order of row_of: loaded ahead of the scores that weigh them
 __device__ __forceinline__ void load_cols(float (&f)[2][16], const Rows& x, int row0, int n, int l31, int half) {
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
     const float* q = x.p + (int64_t)min(row0 + row_of(r, half), n - 1) * x.ld + l31;
     f[0][r] = q[0]; f[1][r] = q[32];
+  }
+  if (row0 + 32 > n) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+      if (row0 + row_of(r, half) >= n) { f[0][r] = 0.f; f[1][r] = 0.f; }
   }
 }
 // acc[db] (head columns 32 db .. +31 by rows, owned row by lane) += sum over the 32 rows of f[row] w[row]
@@ -59,6 +64,30 @@ __device__ __forceinline__ void add_rows(f32x16 (&acc)[2], const float (&f)[2][1
   for (int r = 0; r < 16; ++r)
 #pragma unroll
     for (int db = 0; db < 2; ++db) acc[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(f[db][r], w[r], acc[db], 0, 0, 0);
+}
+// The same where causality leaves pairs of the block out: their weights are zeros, and a zero times an infinity or a NaN would reach
+// the owned rows that must not see it.  Where the block holds such a value, its rows are added one at a time, each to the owned rows
+// that take part (`takes`: whether the lane's owned row takes the streamed row).
+template <class Takes>
+__device__ __forceinline__ void add_rows_causal(f32x16 (&acc)[2], const float (&f)[2][16], const f32x16& w, const Rows& x, int row0, int l31,
+                                                int half, Takes takes) {
+  bool finite = true;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) finite = finite && fabsf(f[0][r]) <= 3.4028235e38f && fabsf(f[1][r]) <= 3.4028235e38f;
+  if (__all(finite)) { add_rows(acc, f, w); return; }
+  for (int i = 0; i < 32; ++i) {
+    float wi = 0.f;      // the weight of row i lies at register 4 (i/8) + i%4 of the half wave (i/4) % 2
+#pragma unroll
+    for (int r = 0; r < 16; ++r) wi = r == 4 * (i >> 3) + (i & 3) ? w[r] : wi;
+    wi = __shfl(wi, l31 + 32 * ((i >> 2) & 1));
+    if (takes(row0 + i)) {
+      const float* q = x.p + (int64_t)(row0 + i) * x.ld;
+#pragma unroll
+      for (int db = 0; db < 2; ++db)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[db][r] = fmaf(wi, q[32 * db + row_of(r, half)], acc[db][r]);
+    }
+  }
 }
 __device__ __forceinline__ void store_row(float* o, const f32x16 (&acc)[2], float scale, int half) {
 #pragma unroll
@@ -109,7 +138,7 @@ __global__ __launch_bounds__(64) void attn_f32_fwd(AttnF32 x, float* __restrict_
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int key = k0 + row_of(r, half);
-      s[r] = (key < p.klen && (!x.causal || key <= qi)) ? 0.125f * s[r] : -1.0e30f;
+      s[r] = (key < p.klen && (!x.causal || key <= qi)) ? 0.125f * s[r] : -INFINITY;
       mloc = fmaxf(mloc, s[r]);
     }
     const float mn = fmaxf(mloc, __shfl_xor(mloc, 32));
@@ -117,7 +146,7 @@ __global__ __launch_bounds__(64) void attn_f32_fwd(AttnF32 x, float* __restrict_
     float ps = 0.f;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      const float e = s[r] > -1.0e30f ? __expf(s[r] - mn) : 0.f;
+      const float e = __expf(s[r] - mn);      // 0 for the pairs left out (mn is never below the finite start of m); a NaN score stays one
       ps += e;
       // dropout acts on the normalised probabilities: the row sum keeps every key, the value sum the survivors
       s[r] = x.drop.thr ? e * p.factor(qi, k0 + row_of(r, half)) : e;
@@ -128,7 +157,8 @@ __global__ __launch_bounds__(64) void attn_f32_fwd(AttnF32 x, float* __restrict_
     for (int db = 0; db < 2; ++db)
 #pragma unroll
       for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
-    add_rows(o, vc, s);
+    if (x.causal && k0 == (int)blockIdx.x * 32) add_rows_causal(o, vc, s, p.v, k0, l31, half, [&](int key) { return key < p.klen && key <= qi; });
+    else add_rows(o, vc, s);
   }
   l += __shfl_xor(l, 32);
   if (qi < x.Lq) {
@@ -176,8 +206,11 @@ __global__ __launch_bounds__(64) void attn_f32_bwd(AttnF32 x, int q_blocks, cons
         const float f = x.drop.thr ? p.factor(qi, key) : 1.0f;
         s[r] = ok ? __expf(0.125f * s[r] - row_lse) * (f * dp[r] - row_dot) : 0.f;
       }
-      add_rows(acc, kc, s);
+      if (x.causal && k0 == q0)
+        add_rows_causal(acc, kc, s, p.k, k0, l31, half, [&](int key) { return key < p.klen && qi < p.qlen && key <= qi; });
+      else add_rows(acc, kc, s);
     }
+    if (qi >= p.qlen) { acc[0] = zero16(); acc[1] = zero16(); }      // whatever the keys held
     if (qi < x.Lq) store_row(dq + ((int64_t)p.b * x.Lq + qi) * lddq + p.h * D, acc, 0.125f, half);
   } else {
     const int k0 = ((int)blockIdx.x - q_blocks) * 32, kj = k0 + l31;
@@ -206,9 +239,16 @@ __global__ __launch_bounds__(64) void attn_f32_bwd(AttnF32 x, int q_blocks, cons
         dp[r] = ok ? e * (f * dp[r] - dot_i) : 0.f;
         s[r] = e * f;
       }
-      add_rows(av, gc, s);
-      add_rows(ak, qc, dp);
+      if (x.causal && q0 == k0) {
+        auto takes = [&](int qi) { return qi < p.qlen && kj < p.klen && kj <= qi; };
+        add_rows_causal(av, gc, s, go, q0, l31, half, takes);
+        add_rows_causal(ak, qc, dp, p.q, q0, l31, half, takes);
+      } else {
+        add_rows(av, gc, s);
+        add_rows(ak, qc, dp);
+      }
     }
+    if (kj >= p.klen) { ak[0] = ak[1] = zero16(); av[0] = av[1] = zero16(); }
     if (kj < x.Lk) {
       store_row(dk + ((int64_t)p.b * x.Lk + kj) * lddkv + p.h * D, ak, 0.125f, half);
       store_row(dv + ((int64_t)p.b * x.Lk + kj) * lddkv + p.h * D, av, 1.0f, half);

@@ -327,6 +327,60 @@ def test_attention_fwd_bwd(hs, mode, B, L, A, lens):
     assert rel(got, want) < (5e-5 if mode == 0 else 1e-2)
 
 
+@pytest.mark.parametrize("causal", [0, 1])
+@pytest.mark.parametrize("L,length", [(40, 37), (72, 72), (104, 65)])
+@pytest.mark.parametrize("what,row", [("k", 20), ("v", 33), ("v_inf", 36), ("q", 7), ("dO", 31)])
+def test_fp32_attention_keeps_nan_and_infinity_where_they_belong(hs, causal, L, length, what, row):
+    """One NaN (or infinite value) in a query, key, value or output gradient: it reaches every result that it is part of, as in plain
+    arithmetic over the allowed pairs, and none that it is not part of (earlier queries, later keys, padding)."""
+    rng = np.random.default_rng(L + row + causal)
+    H = 64
+    x = {n: rng.standard_normal((L, H)).astype(np.float32) for n in ("q", "k", "v", "dO")}
+    x["dO"][length:] = 0.0
+    x[what[:1] if what != "dO" else "dO"][row, 5] = np.inf if what == "v_inf" else np.nan
+    key, query = np.arange(L)[None, :], np.arange(L)[:, None]
+    ok = (key < length) & ((key <= query) | (causal == 0))
+    q, k, v, dO = (x[n].astype(np.float64) for n in ("q", "k", "v", "dO"))
+    real = np.arange(L) < length
+    with np.errstate(all="ignore"):
+        ctx, dq, dk, dv = (np.zeros((L, H)) for _ in range(4))
+        for i in range(L):
+            j = np.flatnonzero(ok[i])
+            s = (k[j] * q[i]).sum(1) / 8.0
+            p = np.exp(s - np.nanmax(s)) if not np.isnan(s).all() else s
+            p /= p.sum()
+            ctx[i] = (p[:, None] * v[j]).sum(0)
+            if real[i]:
+                ds = p * ((v[j] * dO[i]).sum(1) - (dO[i] * ctx[i]).sum())
+                dq[i] = (ds[:, None] * k[j]).sum(0) / 8.0
+                dk[j] += ds[:, None] * q[i] / 8.0
+                dv[j] += p[:, None] * dO[i]
+    t = {n: dev(a) for n, a in x.items()}
+    kv = torch.cat([t["k"], t["v"]], 1).contiguous()
+    lens = dev(np.asarray([length], np.int32))
+    o, lse, dvec = torch.zeros(L, H, device="cuda"), torch.zeros(L, device="cuda"), torch.zeros(L, device="cuda")
+    gq, gkv = torch.full((L, H), 7.0, device="cuda"), torch.full((L, 2 * H), 7.0, device="cuda")
+    hs.hs_op_attention_general_fwd(0, t["q"], H, kv.data_ptr(), kv.data_ptr() + 4 * H, 2 * H, lens, lens, 1, L, L, 1, causal, o, lse)
+    hs.hs_op_attention_general_bwd(0, t["q"], H, kv.data_ptr(), kv.data_ptr() + 4 * H, 2 * H, lens, lens, 1, L, L, 1, causal, o, lse, t["dO"],
+                                   gq, H, gkv.data_ptr(), gkv.data_ptr() + 4 * H, 2 * H, dvec)
+    torch.cuda.synchronize()
+    pairs = [("ctx", o, ctx), ("dq", gq, dq), ("dk", gkv[:, :H], dk), ("dv", gkv[:, H:], dv)]
+    if not causal:      # the same through the packed form
+        qkv = torch.cat([t["q"], kv], 1).contiguous()
+        o2, gqkv = torch.zeros(L, H, device="cuda"), torch.full((L, 3 * H), 7.0, device="cuda")
+        hs.hs_op_attention_fwd(0, qkv, lens, 1, L, 1, o2, lse)
+        hs.hs_op_attention_bwd(0, qkv, o2, lse, t["dO"], lens, 1, L, 1, gqkv, dvec)
+        torch.cuda.synchronize()
+        pairs += [("packed " + n, g, w) for n, g, w in (("ctx", o2, ctx), ("dq", gqkv[:, :H], dq), ("dk", gqkv[:, H:2 * H], dk), ("dv", gqkv[:, 2 * H:], dv))]
+    for name, got, want in pairs:
+        got = host(got)
+        fin = np.isfinite(want)
+        assert np.array_equal(np.isfinite(got), fin), name
+        if name.endswith("ctx"):      # infinities keep their sign
+            assert np.array_equal(got[~fin], want[~fin], equal_nan=True), name
+        assert rel(got[fin], want[fin]) < 5e-5, name
+
+
 def test_key_mask_bit_exact(hs):
     rng = np.random.default_rng(3)
     B, L = 37, 136
