@@ -6,6 +6,7 @@
 #include "gemm_dev.h"
 
 #include <algorithm>
+#include <atomic>
 
 hipError_t gemm_wide_launch_kk(int cfg, const GemmDev& p, int splits, hipStream_t s);
 hipError_t gemm_wide_launch_kn(int cfg, const GemmDev& p, int splits, hipStream_t s);
@@ -308,33 +309,55 @@ hipError_t launch_cfg(const GemmArgs& g, const GemmDev& p, int splits, hipStream
   return launch_one<false, false, BM, BN, BK, WGM, WGN>(p, grid, s);
 }
 
-// the two tables of gelu_tab_eval, filled once per process by a kernel on the stream of the first product that needs them
-static __device__ float2 gelu_tables[2][kGeluTabN];
-__global__ __launch_bounds__(256) void gelu_table_kernel(float2* tab) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= 2 * kGeluTabN) return;
-  const int which = i / kGeluTabN, k = i % kGeluTabN;
-  const double h = 2.0 * (double)kGeluTabR / kGeluTabN;
-  auto f = [&](double x) {
-    const double cdf = 0.5 * (1.0 + erf(x * 0.70710678118654752440));
-    return which == 0 ? cdf : cdf + x * 0.39894228040143267794 * exp(-0.5 * x * x);
-  };
-  const double a = f(-(double)kGeluTabR + k * h), b = f(-(double)kGeluTabR + (k + 1) * h);
-  tab[i] = make_float2((float)a, (float)(b - a));
+// The two tables of gelu_tab_eval (the normal cdf, then GELU'), computed by the compiler: nothing has to be launched or waited for before
+// the first product that reads them, which may be one that a graph captures.
+// exp(-y) and the normal cdf for non-negative arguments, by series whose terms are all positive: exp(y) = sum y^n / n!,
+// Phi(x) = 1/2 + exp(-x^2/2) / sqrt(2 pi) x sum x^(2n) / (1 3 ... (2n + 1)).
+constexpr double series_exp_neg(double y) {
+  double term = 1.0, sum = 1.0;
+  for (int n = 1; term > 1e-18 * sum; ++n) { term *= y / n; sum += term; }
+  return 1.0 / sum;
 }
-static hipError_t gelu_table(int which, hipStream_t s, const float2** out) {
-  static float2* dev_tab = nullptr;
-  if (!dev_tab) {
-    void* p = nullptr;
-    hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(gelu_tables));
-    if (e != hipSuccess) return e;
-    // every later use is ordered behind this launch only on `s`; other streams wait for it once, here
-    hipLaunchKernelGGL(gelu_table_kernel, dim3(2 * kGeluTabN / 256), dim3(256), 0, s, (float2*)p);
-    e = hipStreamSynchronize(s);
-    if (e != hipSuccess) return e;
-    dev_tab = (float2*)p;
+constexpr double series_cdf(double x, double pdf) {
+  double term = x, sum = x;
+  for (int n = 1; term > 1e-18 * sum; ++n) { term *= x * x / (2 * n + 1); sum += term; }
+  return 0.5 + pdf * sum;
+}
+struct alignas(16) GeluTables { float2 entry[2][kGeluTabN]; };      // read 16 bytes at a time
+constexpr GeluTables make_gelu_tables() {
+  GeluTables t{};
+  double node[2][kGeluTabN + 1] = {};
+  for (int k = 0; k <= kGeluTabN / 2; ++k) {
+    const double x = 2.0 * (double)kGeluTabR / kGeluTabN * k;
+    const double pdf = 0.39894228040143267794 * series_exp_neg(0.5 * x * x), cdf = series_cdf(x, pdf);
+    const int hi = kGeluTabN / 2 + k, lo = kGeluTabN / 2 - k;
+    node[0][hi] = cdf; node[1][hi] = cdf + x * pdf;
+    node[0][lo] = 1.0 - cdf; node[1][lo] = 1.0 - cdf - x * pdf;
   }
-  *out = dev_tab + which * kGeluTabN;
+  for (int w = 0; w < 2; ++w)
+    for (int k = 0; k < kGeluTabN; ++k) {
+      t.entry[w][k].x = (float)node[w][k];
+      t.entry[w][k].y = (float)(node[w][k + 1] - node[w][k]);
+    }
+  return t;
+}
+static __device__ GeluTables gelu_tables = make_gelu_tables();
+// the address of a table on the current device
+static hipError_t gelu_table(int which, const float2** out) {
+  constexpr int kMaxDevices = 64;
+  static std::atomic<const float2*> known[kMaxDevices] = {};
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  const float2* p = dev < kMaxDevices ? known[dev].load(std::memory_order_relaxed) : nullptr;
+  if (!p) {
+    void* q = nullptr;
+    e = hipGetSymbolAddress(&q, HIP_SYMBOL(gelu_tables));
+    if (e != hipSuccess) return e;
+    p = (const float2*)q;
+    if (dev < kMaxDevices) known[dev].store(p, std::memory_order_relaxed);
+  }
+  *out = p + which * kGeluTabN;
   return hipSuccess;
 }
 
@@ -522,7 +545,7 @@ hs_status launch_gemm(hs_ctx* ctx, const GemmArgs& g, hipStream_t s) {
     }
     hipError_t e;
     if (cfg != 0 && (g.epi == 2 || g.epi == 3)) {
-      e = gelu_table(g.epi == 2 ? 0 : 1, s, &p.gelu_tab);
+      e = gelu_table(g.epi == 2 ? 0 : 1, &p.gelu_tab);
       if (e != hipSuccess) return hs_fail(ctx, HS_ERR_HIP, std::string("gemm: GELU table: ") + hipGetErrorString(e));
     }
     if (cfg == 0) e = launch_cfg<128, 128, 32, 2, 2>(g, p, splits, s);

@@ -224,6 +224,54 @@ def test_gemm_fp32_tilings(hs, M, N, K):
             assert np.all(np.abs(host(dC) - (C + a @ b.T)) <= bound), (ak, bk)
 
 
+FIRST_CALLS_IN_A_GRAPH = """
+import sys
+import torch
+from oracle import hetseq_oracle as O
+from paper_2009_14783_amd import binding as hs
+hs.lib()
+gen = torch.Generator(device="cuda").manual_seed(1)
+cases = []
+for M, N, K in ((100, 256, 256), (264, 2048, 128)):
+    r = lambda *s: torch.randn(*s, generator=gen, device="cuda").bfloat16()
+    cases.append((M, N, K, r(M, K), r(N, K), r(K, N), r(M, N), [torch.zeros(M, N, dtype=torch.bfloat16, device="cuda") for _ in range(3)]))
+def calls():
+    for M, N, K, A, Bk, Bn, R, (c, c2, d) in cases:
+        hs.hs_op_gemm(1, 1, 1, M, N, K, A, K, Bk, K, c, N, epi=2, C2=c2)
+        hs.hs_op_gemm(1, 1, 0, M, N, K, A, K, Bn, N, d, N, epi=3, aux=R, ldaux=N)
+graph = torch.cuda.CUDAGraph()
+with torch.cuda.graph(graph):
+    calls()
+replays = []
+for _ in range(3):
+    for case in cases:
+        for t in case[-1]:
+            t.zero_()
+    graph.replay()
+    torch.cuda.synchronize()
+    replays.append([t.clone() for case in cases for t in case[-1]])
+calls()
+torch.cuda.synchronize()
+eager = [t for case in cases for t in case[-1]]
+assert all(torch.equal(a, b) for rep in replays for a, b in zip(rep, eager))
+for M, N, K, A, Bk, Bn, R, (c, c2, d) in cases:
+    pre = A.double() @ Bk.double().t()
+    grad = torch.from_numpy(O.gelu_grad(R.double().cpu().numpy())).cuda() * (A.double() @ Bn.double())
+    for got, want in ((c2, torch.nn.functional.gelu(pre)), (d, grad)):
+        assert float((got.double() - want).norm() / want.norm()) < 4e-3
+print("captured")
+"""
+
+
+def test_first_gelu_products_of_a_process_can_be_captured(hs):
+    """Products of few rows with the GELU epilogues as the very first calls of a process, inside a graph capture (nothing may wait for
+    the stream there), replayed three times against the eager results."""
+    import os, subprocess, sys
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", FIRST_CALLS_IN_A_GRAPH], cwd=root, capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0 and "captured" in r.stdout, r.stderr[-2000:]
+
+
 def test_gemm_variant_out_of_range_is_an_error(hs):
     for v in (-2, 12, 1000):
         with pytest.raises(hs.HsError):
