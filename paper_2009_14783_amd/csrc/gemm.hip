@@ -473,6 +473,9 @@ hs_status launch_gemm_group(hs_ctx* ctx, const GemmArgs* gs, int n, hipStream_t 
     double flops = 0, bytes = 0;
     for (int i = 0; i < gd.n; ++i) {
       const GemmArgs& g = gs[done + i];
+      if (g.a_kmajor || g.b_kmajor || !g.c_f32 || g.bias || g.epi || g.drop || g.dtype != gs[done].dtype || g.beta != gd.beta ||
+          std::max({g.lda, g.ldb, g.ldc}) > INT32_MAX)
+        return hs_fail(ctx, HS_ERR_INVALID_ARG, "grouped gemm: only m-major x n-major products with fp32 results and one type and beta");
       GemmArgs chk = g;
       if (!g.B) { chk.B = g.A; chk.ldb = 8; chk.N = 1; }
       hs_status st = check_gemm_args(ctx, chk);

@@ -416,7 +416,8 @@ void gemm_bf16_wide(GemmDev p) {
 // Several products in one launch: block v works on tile v - first_tile[i] of problem i (the problems' tiles are numbered one
 // problem after the other; an XCD gets a contiguous range of them).  No split-K: every tile runs over the whole
 // contraction.  Returns the problem as arguments of the tile function and the tile's position.
-static __device__ const bf16 kOnes[8] = {(bf16)1.0f, (bf16)1.0f, (bf16)1.0f, (bf16)1.0f, (bf16)1.0f, (bf16)1.0f, (bf16)1.0f, (bf16)1.0f};
+alignas(16) static __device__ const bf16 kOnes[8] =      // read 16 bytes at a time
+    {(bf16)1.0f, (bf16)1.0f, (bf16)1.0f, (bf16)1.0f, (bf16)1.0f, (bf16)1.0f, (bf16)1.0f, (bf16)1.0f};
 template <int BM, int BN>
 __device__ __forceinline__ GemmDev group_problem(const GemmGroupDev& g, int& tm, int& tn) {
   int v = blockIdx.x;
