@@ -337,6 +337,12 @@ __device__ __forceinline__ float gelu_tab_eval(const float2* tab, float x) {
   const float2 e = tab[(int)t];
   return fmaf(e.y, __builtin_amdgcn_fractf(t), e.x);
 }
+// GELU' of a stored pre-activation: a NaN stays one (the clamp above turns it into the interval's end; the cdf needs no such care, being
+// multiplied by its argument)
+__device__ __forceinline__ float gelu_grad_tab(const float2* tab, float x) {
+  const float d = gelu_tab_eval(tab, x);
+  return x == x ? d : x;
+}
 
 constexpr int MPAD = 32;   // m-major LDS rows: R + 32 elements  (row stride = 64 B mod 256 B)
 

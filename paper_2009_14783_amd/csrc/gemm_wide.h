@@ -183,7 +183,7 @@ __device__ __forceinline__ void tile_epilogue_pipe(const GemmDev& p, const f32x1
 #pragma unroll
           for (int t = 0; t < 8; ++t)
             v[t] = (MODE == EPI_ACT_RES) ? v[t] + (float)acur[it][t]
-                   : (MODE == EPI_ACT_DRELU ? ((float)acur[it][t] > 0.f ? v[t] : 0.f) : v[t] * gelu_tab_eval(tab, (float)acur[it][t]));
+                   : (MODE == EPI_ACT_DRELU ? ((float)acur[it][t] > 0.f ? v[t] : 0.f) : v[t] * gelu_grad_tab(tab, (float)acur[it][t]));
         }
         if (MODE == EPI_ACT_RELU) {
 #pragma unroll

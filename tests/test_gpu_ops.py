@@ -272,6 +272,20 @@ def test_first_gelu_products_of_a_process_can_be_captured(hs):
     assert r.returncode == 0 and "captured" in r.stdout, r.stderr[-2000:]
 
 
+@pytest.mark.parametrize("M,N,K", [(100, 136, 64), (264, 2048, 128), (1000, 1024, 192), (520, 3072, 768)])
+def test_gelu_gradient_epilogue_keeps_nan(hs, M, N, K):
+    """A NaN in the saved pre-activation reaches its own entry of the result and no other, in every tiling the sizes are sent to."""
+    gen = torch.Generator(device="cuda").manual_seed(M)
+    A, B, R = (torch.randn(*s, generator=gen, device="cuda").bfloat16() for s in ((M, K), (K, N), (M, N)))
+    bad = torch.zeros(M, N, dtype=torch.bool, device="cuda")
+    bad[0, 0] = bad[M // 2, N // 2 + 1] = bad[M - 1, N - 1] = True
+    R[bad] = float("nan")
+    out = torch.zeros(M, N, dtype=torch.bfloat16, device="cuda")
+    hs.hs_op_gemm(1, 1, 0, M, N, K, A, K, B, N, out, N, epi=3, aux=R, ldaux=N)
+    torch.cuda.synchronize()
+    assert torch.equal(torch.isnan(out), bad) and bool(torch.isfinite(out[~bad]).all())
+
+
 def test_gemm_variant_out_of_range_is_an_error(hs):
     for v in (-2, 12, 1000):
         with pytest.raises(hs.HsError):
