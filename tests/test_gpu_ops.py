@@ -173,12 +173,14 @@ def test_gemm_every_tiling_ragged_edges_and_epilogues(hs, variant):
         hs.hs_tune_gemm_variant(-1)
 
 
-@pytest.mark.parametrize("M,N,K", [(1, 64, 64), (31, 96, 192), (33, 768, 768), (65, 136, 3072), (264, 512, 512), (513, 2048, 128), (1030, 768, 448)])
+@pytest.mark.parametrize("M,N,K", [(1, 64, 64), (31, 96, 192), (33, 768, 768), (65, 136, 3072), (264, 512, 512), (513, 2048, 128), (1030, 768, 448),
+                                   (1, 8200, 512), (31, 8200, 512), (33, 6152, 512), (65, 3080, 512), (129, 3080, 512), (72, 3072, 768), (96, 1024, 4096)])
 @pytest.mark.parametrize("layout", LAYOUTS)
 def test_gemm_bf16_few_tiles(hs, M, N, K, layout):
     """Products whose rows, columns and contraction end at, before and after the edges of the 32- and 64-wide tiles, from one tile
-    to a few hundred (the automatic choice runs over all of them), with an epilogue and with the contraction split over
-    blocks.  m-major operands: a contraction that ends inside a k-tile."""
+    to a few hundred, with an epilogue and with the contraction split over blocks.  The automatic choice sends the first five to the
+    32 x 32 tiles whose waves share out the contraction, the next two to 64 x 64 and the others to 32 x 64 (the last one only with scratch,
+    in four splits).  m-major operands: a contraction that ends inside a k-tile."""
     ak, bk = layout
     rng = np.random.default_rng(M + N + K)
     if not ak:

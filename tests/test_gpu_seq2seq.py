@@ -315,7 +315,7 @@ def test_large_pair_batch_runs_as_two_halves_with_the_masks_of_the_whole_batch(h
 @pytest.mark.parametrize("compute", ["fp32", "bf16"])
 def test_update_inside_backward_gives_the_bits_of_the_separate_calls(hs, compute):
     """Two workers from the same state take three updates over unequal micro-batches: one with normalisation and Adam armed
-    for the last backward pass (layer slices on the third stream), one with the two separate calls afterwards."""
+    for the last backward pass (layer slices on the stream of the gradients), one with the two separate calls afterwards."""
     model, ocfg, theta, a = _setup("s2s_tiny", compute, 33, dict(hidden=256, n_heads=4, ffn=512, vocab=3000))
     from paper_2009_14783_amd.step import PairWorker
     b = PairWorker(model, compute, theta)
@@ -333,6 +333,53 @@ def test_update_inside_backward_gives_the_bits_of_the_separate_calls(hs, compute
         if compute == "bf16":
             assert torch.equal(a.w_lowp, b.w_lowp)
     a.close(); b.close()
+
+
+@pytest.mark.parametrize("compute", ["fp32", "bf16"])
+@pytest.mark.parametrize("B,Ls,Lt", [(64, 32, 32), (65, 32, 32), (64, 40, 24), (64, 24, 40)])
+def test_backward_on_both_sides_of_the_few_rows_limit(hs, compute, B, Ls, Lt):
+    """2048 rows on both sides (gradients of three layers handed over at a time), above that on both and on one side only (layer by layer),
+    five layers per stack so that the last hand-over is a partial one: the update armed inside the backward pass gives the bits of the
+    separate calls for every parameter, and the fp32 gradient is the oracle's."""
+    model, ocfg, theta, a = _setup("s2s_tiny", compute, 41, dict(n_enc=5, n_dec=5, hidden=128, n_heads=2, ffn=256, vocab=500, max_pos=64))
+    from paper_2009_14783_amd.step import PairWorker
+    rng = synth.rng_for(B + Ls)
+    mb = synth.make_pair_batch(rng, [int(x) for x in rng.integers(1, Ls + 1, B)], [int(x) for x in rng.integers(1, Lt + 1, B)], Ls, Lt, model["vocab"],
+                               "uniform")
+    b = PairWorker(model, compute, theta)
+    for _ in range(2):
+        a.train_step([a.upload(mb)], ADAM, update_in_backward=True)
+        b.train_step([b.upload(mb)], ADAM, update_in_backward=False)
+        torch.cuda.synchronize()
+        for k in ("w", "m", "v", "G", "loss_buf") + (("w_lowp",) if compute == "bf16" else ()):
+            assert torch.equal(getattr(a, k), getattr(b, k)), k
+    a.close(); b.close()
+    if compute == "fp32":
+        wk = PairWorker(model, compute, theta)
+        loss, nll, g = _gpu_grad(wk, mb)
+        wk.close()
+        ol, on, og, _, _ = S.micro_batch_grad(ocfg, theta.astype(np.float64), mb, 0.1)
+        assert abs(loss - ol) / abs(ol) < 1e-4
+        compare_flat_decided(ocfg, g, og, 1e-4, "grad", undecided_units(ocfg, theta, mb))
+
+
+@pytest.mark.parametrize("compute", ["fp32", "bf16"])
+@pytest.mark.parametrize("B,Ls,Lt", [(3, 24, 40), (11, 48, 56)])
+def test_relu_epilogues_and_grouped_gradients_on_ragged_tiles(hs, compute, B, Ls, Lt):
+    """Widths of 192 and 320 and rows that end inside every tile (72 and 120, 528 and 616 rows): the feed-forward products with ReLU
+    and its gate as epilogues, and the grouped weight and bias gradients over contractions that end inside a k-tile."""
+    model, ocfg, theta, wk = _setup("s2s_tiny", compute, 43, dict(n_enc=1, n_dec=1, hidden=192, n_heads=3, ffn=320, vocab=520, max_pos=64))
+    rng = synth.rng_for(44)
+    mb = synth.make_pair_batch(rng, [Ls] + [int(x) for x in rng.integers(1, Ls + 1, B - 1)], [int(x) for x in rng.integers(1, Lt + 1, B - 1)] + [Lt], Ls, Lt,
+                               model["vocab"], "uniform")
+    loss, nll, g = _gpu_grad(wk, mb)
+    ol, on, og, _, _ = S.micro_batch_grad(ocfg, theta.astype(np.float64), mb, 0.1)
+    assert abs(loss - ol) / abs(ol) < TOL[compute]
+    if compute == "fp32":
+        compare_flat_decided(ocfg, g, og, TOL[compute], "grad", undecided_units(ocfg, theta, mb))
+    else:
+        compare_flat(S.param_layout(ocfg), g, og, TOL[compute], "grad", rounded_weights_grad(ocfg, theta, mb))
+    wk.close()
 
 
 def test_edge_cases_empty_batch_and_longest_buffers(hs):

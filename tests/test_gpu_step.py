@@ -438,6 +438,25 @@ def test_backward_on_both_sides_of_the_few_rows_limit(W, B, compute):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("compute", ["fp32", "bf16"])
+@pytest.mark.parametrize("B,L", [(3, 24), (11, 48), (9, 232)])
+def test_grouped_gradients_on_ragged_tiles(W, B, L, compute):
+    """Widths of 192 and 320 and 72, 528 and 2088 rows: the grouped weight and bias gradients end inside a tile in both directions and
+    their contraction inside a k-tile."""
+    model = dict(n_layers=2, hidden=192, n_heads=3, ffn=320, vocab=520, max_pos=256, ln_eps=1e-12)
+    ocfg = O.ModelCfg(**model)
+    theta = synth.init_params(O.param_layout(ocfg), 8)
+    rng = synth.rng_for(9)
+    mb = synth.make_micro_batch(rng, [L] + [int(x) for x in rng.integers(1, L + 1, B - 1)], L, model["vocab"], "uniform")
+    worker = W(model, compute, theta)
+    loss, g = gpu_micro_grad(worker, mb)
+    ol, og = oracle_micro_grad(ocfg, theta, mb, np.float64)
+    assert abs(loss - ol) / abs(ol) < TOL[compute]
+    compare_flat(O.param_layout(ocfg), g, og, TOL[compute], "grad")
+    worker.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("compute", ["fp32", "bf16"])
 @pytest.mark.parametrize("layers", [1, 2, 9])
 def test_backward_gives_the_same_bits_in_every_workspace_it_accepts(W, layers, compute):
     """A batch of few rows in the workspace of its own size, of larger batches and in the smallest that is accepted: how many layers the
