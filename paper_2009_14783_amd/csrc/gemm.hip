@@ -382,8 +382,11 @@ float tiles_time(const TileCfg& c, int64_t tiles, float steps, float outputs) {
   const int per_cu = (int)((tiles + kCUs - 1) / kCUs), full = per_cu / c.occ, rem = per_cu % c.occ;
   return c.t0 + steps * (full * std::max(c.l, c.occ * c.w) + (rem ? std::max(c.l, rem * c.w) : 0.0f)) + c.e * per_cu * outputs;
 }
+// A long contraction costs more per k-tile: blocks that share operand panels drift apart and fetch them again (3072 x 768 with one
+// tile per CU: 0.46 us per k-tile at K = 8192, 0.58 at 16384).
 float cfg_time(const TileCfg& c, int M, int N, int K, int splits, float outputs) {
-  return tiles_time(c, (int64_t)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn) * splits, (float)((K + 63) / 64) / splits, outputs);
+  const float steps = (float)((K + 63) / 64) / splits;
+  return tiles_time(c, (int64_t)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn) * splits, steps * (1.0f + std::max(0.0f, steps - 128.0f) / 512.0f), outputs);
 }
 int gemm_cfg_override = -1;    // >= 0: use this configuration for every bf16 product of some size that it can serve (timing runs)
 
@@ -444,19 +447,29 @@ static void choose_cfg(const GemmArgs& g, int* cfg, int* splits) {
   else if (gemm_cfg_override >= 0) only = some_size ? gemm_cfg_override : 0;
   if (supported && !whole_k && only != 0 && only != 1 && only != 6) only = some_size ? 5 : 0;
   const float outputs = (g.c_f32 || g.epi) ? 2.0f : 1.0f;
+  const bool forward = g.a_kmajor && g.b_kmajor;
   float best = 3.0e38f;
   *cfg = 0; *splits = 1;
   for (int c = 0; c < kNumTileCfg; ++c) {
     if (only >= 0 ? c != only : !kTileCfg[c].use) continue;
-    // 5 and 9 are the same tile: the register-staged one is faster for the forward products when the two halves of a batch run
-    // beside each other, the direct one for the others
-    if (only < 0 && c == ((g.a_kmajor && g.b_kmajor) ? 9 : 5)) continue;
     // With a scratch buffer the contraction can be split over blocks: partial sums go out as fp32 and are added by a second
-    // launch (3 us and their way through memory and back at 3.5 TB/s).
+    // launch (3 us and their way through memory and back at 3.5 TB/s; for contractions beyond 8192, where a block's share of the
+    // operands costs more the longer it is, 5 us at the 10 TB/s that these sums get on their way through the caches: 768 x 768 x 32768,
+    // A k-major, 82 -> 68 us).
     const int64_t most = g.ws ? std::min<int64_t>({32, g.K / (4 * kTileCfg[c].bk), (int64_t)(g.ws_bytes / ((size_t)g.M * g.N * sizeof(float)))}) : 1;
+    const int64_t tiles = (int64_t)((g.M + kTileCfg[c].bm - 1) / kTileCfg[c].bm) * ((g.N + kTileCfg[c].bn - 1) / kTileCfg[c].bn);
     for (int sp = 1; sp <= std::max<int64_t>(1, most); sp *= 2) {
+      // 5 and 9 are the same tile.  The register-staged pipeline (5) has four k-tiles in flight, the direct one (9) two: a block that has
+      // its CU to itself is faster with the first from about 16 k-tiles on (A m-major, 3072 x 768 x 8192: 62 against 78 us, at K = 1216 17.0
+      // against 18.3, at 520 16.2 against 12.7; 4096 x 1024 x 4096, A k-major: 38 against 46), two blocks that cover each other with the second
+      // (the embedding gradient of the translation step, 37000 x 512: 4.97 against 4.83 ms for the step).  Of split contractions
+      // beyond 8192 the second with twice the splits is (1216 x 768 x 32768: 10 %).  Forward products are faster with the first either way, the two
+      // halves of a batch running beside each other.
+      const bool lone = tiles * sp <= kCUs && g.K > 1024 && (sp == 1 || g.K <= 8192);
+      if (only < 0 && (c == 5 || c == 9) && c != (forward || lone ? 5 : 9)) continue;
       float t = cfg_time(kTileCfg[c], g.M, g.N, g.K, sp, sp > 1 ? 2.0f : outputs);
-      if (sp > 1) t += 3.0f + 8.0f * sp * (float)g.M * (float)g.N / 3.5e6f;
+      const float mbytes = 8e-6f * sp * (float)g.M * (float)g.N;
+      if (sp > 1) t += g.K > 8192 ? 5.0f + mbytes / 10.0f : 3.0f + mbytes / 3.5f;
       if (t < best) { best = t; *cfg = c; *splits = sp; }
     }
   }

@@ -208,6 +208,26 @@ def test_gemm_bf16_few_tiles(hs, M, N, K, layout):
             assert rel(host(dC), R.astype(np.float64) + prod) < 2e-6, scratch is None
 
 
+@pytest.mark.parametrize("M,N,K", [(3080, 776, 1088), (1032, 4104, 1024), (2056, 1032, 8192), (520, 3080, 8256), (264, 776, 16448)])
+@pytest.mark.parametrize("layout", LAYOUTS)
+def test_gemm_bf16_long_contractions(hs, M, N, K, layout):
+    """Contractions on both sides of the lengths (1024, 8192) where the choice between the two 128 x 128 tilings and the cost of splitting
+    change, with at most a tile per CU, unsplit and with scratch; fp32 result where the layout has one (a sum of K products in any
+    order is within K 2^-24 of the sum of their sizes, bf16 products being exact), else one rounding to bf16."""
+    ak, bk = layout
+    gen = torch.Generator(device="cuda").manual_seed(K)
+    A, B = (torch.randn(*s, generator=gen, device="cuda").bfloat16() for s in ((M, K) if ak else (K, M), (N, K) if bk else (K, N)))
+    a, b = (A if ak else A.t()).double(), (B.t() if bk else B).double()
+    want, size = a @ b, a.abs() @ b.abs()
+    ws = torch.zeros(76 << 20, dtype=torch.uint8, device="cuda")
+    for scratch in (None, ws):
+        C = torch.full((M, N), 7.0, dtype=torch.bfloat16 if ak else torch.float32, device="cuda")
+        hs.hs_op_gemm(1, ak, bk, M, N, K, A, A.shape[1], B, B.shape[1], C, N, c_f32=0 if ak else 1, scratch=scratch, scratch_bytes=0 if scratch is None else ws.numel())
+        torch.cuda.synchronize()
+        bound = K * 2.0 ** -24 * size + (2.0 ** -8 * want.abs() if ak else 0.0)
+        assert bool(((C.double() - want).abs() <= bound).all()), scratch is None
+
+
 @pytest.mark.parametrize("M,N,K", [(1, 1, 1), (31, 33, 7), (33, 64, 8), (64, 130, 36), (257, 512, 260), (100, 40, 1029), (1800, 1730, 43), (1793, 1792, 64)])
 def test_gemm_fp32_tilings(hs, M, N, K):
     """All four layouts around the edges of the 32x32 tiles (contraction over 4 waves up to 256 values, over 16 beyond) and of the
