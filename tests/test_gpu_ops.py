@@ -208,11 +208,11 @@ def test_gemm_bf16_few_tiles(hs, M, N, K, layout):
             assert rel(host(dC), R.astype(np.float64) + prod) < 2e-6, scratch is None
 
 
-@pytest.mark.parametrize("M,N,K", [(3080, 776, 1088), (1032, 4104, 1024), (2056, 1032, 8192), (520, 3080, 8256), (264, 776, 16448)])
+@pytest.mark.parametrize("M,N,K", [(2056, 2120, 64), (2056, 2120, 192), (3080, 776, 1088), (1032, 4104, 1024), (2056, 1032, 8192), (520, 3080, 8256), (264, 776, 16448)])
 @pytest.mark.parametrize("layout", LAYOUTS)
-def test_gemm_bf16_long_contractions(hs, M, N, K, layout):
-    """Contractions on both sides of the lengths (1024, 8192) where the choice between the two 128 x 128 tilings and the cost of splitting
-    change, with at most a tile per CU, unsplit and with scratch; fp32 result where the layout has one (a sum of K products in any
+def test_gemm_bf16_short_and_long_contractions(hs, M, N, K, layout):
+    """Contractions of a few k-tiles with more than a tile per CU, and on both sides of the lengths (1024, 8192) where the choice between the
+    two 128 x 128 tilings and the cost of splitting change, unsplit and with scratch; fp32 result where the layout has one (a sum of K products in any
     order is within K 2^-24 of the sum of their sizes, bf16 products being exact), else one rounding to bf16."""
     ak, bk = layout
     gen = torch.Generator(device="cuda").manual_seed(K)
