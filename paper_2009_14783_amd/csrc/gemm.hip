@@ -429,7 +429,7 @@ static GemmDev gemm_dev_args(const GemmArgs& g) {
 int gemm_variant_count() { return kNumTileCfg; }
 void gemm_set_variant(int variant) { gemm_cfg_override = variant; }
 
-// whether gemm_bf16_wide is built with the epilogue this product needs (see wide_epilogues in gemm_wide.h)
+// whether the kernels other than gemm_bf16_mfma are built with the epilogue this product needs (see wide_epilogues in gemm_wide.h)
 static bool wide_supports(const GemmArgs& g) {
   if (g.a_kmajor && g.b_kmajor) return g.c_f32 ? true : (g.epi == 0 || g.epi == 1 || g.epi == 2 || g.epi == 4);
   if (g.a_kmajor) return !g.c_f32 && (g.epi == 0 || g.epi == 1 || g.epi == 3 || g.epi == 5);
@@ -450,6 +450,8 @@ static void choose_cfg(const GemmArgs& g, int* cfg, int* splits) {
   // fp32 result the two win)
   if (only < 0 && g.a_kmajor && g.b_kmajor && g.epi == 0 && !g.c_f32 && g.K < 256 && (int64_t)((g.M + 127) / 128) * ((g.N + 127) / 128) > kCUs) only = 0;
   if (supported && !whole_k && only != 0 && only != 1 && only != 6) only = some_size ? 5 : 0;
+  const bool gate = g.epi == 5;      // not in the register-staged kernels
+  if (gate && (only == 1 || only == 5 || only == 6)) only = 0;
   const float outputs = (g.c_f32 || g.epi) ? 2.0f : 1.0f;
   const bool forward = g.a_kmajor && g.b_kmajor;
   float best = 3.0e38f;
@@ -469,7 +471,7 @@ static void choose_cfg(const GemmArgs& g, int* cfg, int* splits) {
       // (the embedding gradient of the translation step, 37000 x 512: 4.97 against 4.83 ms for the step).  Of split contractions
       // beyond 8192 the second with twice the splits is (1216 x 768 x 32768: 10 %).  Forward products are faster with the first either way, the two
       // halves of a batch running beside each other.
-      const bool lone = tiles * sp <= kCUs && g.K > 1024 && (sp == 1 || g.K <= 8192);
+      const bool lone = !gate && tiles * sp <= kCUs && g.K > 1024 && (sp == 1 || g.K <= 8192);
       if (only < 0 && (c == 5 || c == 9) && c != (forward || lone ? 5 : 9)) continue;
       float t = cfg_time(kTileCfg[c], g.M, g.N, g.K, sp, sp > 1 ? 2.0f : outputs);
       const float mbytes = 8e-6f * sp * (float)g.M * (float)g.N;

@@ -386,6 +386,11 @@ constexpr int wide_epilogues() {
                      : (1 << EPI_PARTIAL | 1 << EPI_F32);
 }
 
+// The register-staged kernel goes without the ReLU gate: one more epilogue beside GELU' costs it 8 more spilled registers (30522 x 768 x 520,
+// B n-major: 50 against 54 us), and the products that have the gate, contractions of at most 1024, never prefer it.
+template <bool AK, bool BKM>
+constexpr int reg_staged_epilogues() { return wide_epilogues<AK, BKM>() & ~(1 << EPI_ACT_DRELU); }
+
 // position of linear block v in a grid of nbx x nby tiles: tile rows in groups of GM, rows fastest inside a group,
 // so that the tiles in flight on one XCD share operand panels
 template <int GM>
@@ -410,7 +415,7 @@ void gemm_bf16_wide(GemmDev p) {
   const int split = v / nb;
   int tm, tn;
   tile_of_block<(TI * WGM >= 8) ? 4 : 8>(v - split * nb, nbx, nby, tm, tn);
-  wide_tile<AK, BKM, TI, TJ, WGM, WGN, BK, NSETS, wide_epilogues<AK, BKM>()>(p, tm * 32 * TI * WGM, tn * 32 * TJ * WGN, split, lds_raw);
+  wide_tile<AK, BKM, TI, TJ, WGM, WGN, BK, NSETS, reg_staged_epilogues<AK, BKM>()>(p, tm * 32 * TI * WGM, tn * 32 * TJ * WGN, split, lds_raw);
 }
 
 // Several products in one launch: block v works on tile v - first_tile[i] of problem i (the problems' tiles are numbered one
