@@ -466,14 +466,16 @@ static void choose_cfg(const GemmArgs& g, int* cfg, int* splits) {
     const int64_t tiles = (int64_t)((g.M + kTileCfg[c].bm - 1) / kTileCfg[c].bm) * ((g.N + kTileCfg[c].bn - 1) / kTileCfg[c].bn);
     for (int sp = 1; sp <= std::max<int64_t>(1, most); sp *= 2) {
       // 5 and 9 are the same tile.  The register-staged pipeline (5) has four k-tiles in flight, the direct one (9) two: a block that has
-      // its CU to itself is faster with the first from about 16 k-tiles on (A m-major, 3072 x 768 x 8192: 62 against 78 us, at K = 1216 17.0
-      // against 18.3, at 520 16.2 against 12.7; 4096 x 1024 x 4096, A k-major: 38 against 46), two blocks that cover each other with the second
-      // (the embedding gradient of the translation step, 37000 x 512: 4.97 against 4.83 ms for the step).  Of split contractions
-      // beyond 8192 the second with twice the splits is (1216 x 768 x 32768: 10 %).  Forward products are faster with the first either way, the two
-      // halves of a batch running beside each other.
-      const bool lone = !gate && tiles * sp <= kCUs && g.K > 1024 && (sp == 1 || g.K <= 8192);
+      // its CU to itself is faster with the first from about 16 whole k-tiles on (A m-major, 3072 x 768 x 8192: 62 against 78 us, at K = 1216
+      // 17.0 against 18.3; 4096 x 1024 x 4096, A k-major: 38 against 46), two blocks that cover each other with the second (the
+      // embedding gradient of the translation step, 37000 x 512: 4.97 against 4.83 ms for the step), and so is any block whose contraction
+      // ends inside a k-tile (3072 x 768 x 520: 16.2 against 12.7).  Of split contractions beyond 8192 the second with twice the splits
+      // is (1216 x 768 x 32768: 10 %).  Forward products are faster with the first either way, the two halves of a batch running
+      // beside each other.
+      const bool lone = !gate && tiles * sp <= kCUs && g.K > 1024 && g.K % 64 == 0 && (sp == 1 || g.K <= 8192);
       if (only < 0 && (c == 5 || c == 9) && c != (forward || lone ? 5 : 9)) continue;
-      float t = cfg_time(kTileCfg[c], g.M, g.N, g.K, sp, sp > 1 ? 2.0f : outputs);
+      // rows that end inside a k-tile do not start on cache lines either: half as much again per k-tile (768 x 768 x 2008: 0.7 us)
+      float t = cfg_time(kTileCfg[c], g.M, g.N, whole_k ? g.K : g.K + g.K / 2, sp, sp > 1 ? 2.0f : outputs);
       const float mbytes = 8e-6f * sp * (float)g.M * (float)g.N;
       if (sp > 1) t += g.K > 8192 ? 5.0f + mbytes / 10.0f : 3.0f + mbytes / 3.5f;
       if (t < best) { best = t; *cfg = c; *splits = sp; }
