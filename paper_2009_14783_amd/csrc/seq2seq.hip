@@ -479,12 +479,13 @@ hs_status hs_s2s_bwd(hs_ctx* ctx, const void* w, const void* acts, const int32_t
   const float scale = sqrtf((float)H);
 
   // The weight gradients and column sums only consume what the chain of activation gradients produces: they run on the
-  // context's second stream, those of several layers (one, with many rows) in one grouped launch and one launch of column sums behind
-  // one event, and the caller's stream waits for them once, at the end.  An event and the wait for it cost the host 10 us, four launches:
-  // with one per operand and a launch per product (and its k-splits' sum) the host took 2.9 of the 4.1 ms of this call at 4096
-  // positions per side.  With per-launch timing enabled everything stays on the caller's stream.
+  // context's second stream, those of three layers in one grouped launch and one launch of column sums behind one event, and the
+  // caller's stream waits for them once, at the end.  An event and the wait for it cost the host 10 us, four launches, and a layer's
+  // gradients alone do not fill the chip (474 tiles of BERT-base against 296 here).  Ms per step, one, two, three and six layers at a time:
+  // 512 rows per side 2.38 / 2.35 / 2.32 / 2.31, 2048 3.22 / 3.18 / 3.17 / 3.18, 4096 4.77 / 4.58 / 4.60 / 4.60, 8192 8.17 / 7.52 / 7.56 / 7.54.
+  // With per-launch timing enabled everything stays on the caller's stream.
   const bool overlap = ctx->prof == nullptr;
-  const int per_hand_over = std::max(Ts, Tt) <= 2048 ? 3 : 1;
+  constexpr int per_hand_over = 3;
   const size_t n_events = (size_t)c.n_dec + c.n_enc + 6;
   if (overlap) HS_TRY(ensure_side_stream(ctx, n_events));
   hipStream_t sd = overlap ? ctx->side : s;
@@ -513,7 +514,7 @@ hs_status hs_s2s_bwd(hs_ctx* ctx, const void* w, const void* acts, const int32_t
     HS_TRY(launch_layernorm_bwd_cols_batch(ctx, cols_src.data(), (int)cols_src.size(), beta, Ts, H, sd));
     HS_TRY(launch_gemm_group(ctx, dw.data(), (int)dw.size(), sd));
     dw.clear(); cols_tgt.clear(); cols_src.clear();
-    return upd.on ? update_slice(ctx, upd, begin, end, sd, per_hand_over > 1) : HS_OK;
+    return upd.on ? update_slice(ctx, upd, begin, end, sd, true) : HS_OK;
   };
   auto dgrad = [&](int T, int N, int K, const void* dy, const void* Wm, void* dx, const void* res) {   // dx [T,N] = dy [T,K] W [K,N] (+ res)
     GemmArgs ga = gemm_args(dt, 1, 0, T, N, K, dy, K, Wm, N, dx, N);

@@ -337,9 +337,9 @@ def test_update_inside_backward_gives_the_bits_of_the_separate_calls(hs, compute
 
 @pytest.mark.parametrize("compute", ["fp32", "bf16"])
 @pytest.mark.parametrize("B,Ls,Lt", [(64, 32, 32), (65, 32, 32), (64, 40, 24), (64, 24, 40)])
-def test_backward_on_both_sides_of_the_few_rows_limit(hs, compute, B, Ls, Lt):
-    """2048 rows on both sides (gradients of three layers handed over at a time), above that on both and on one side only (layer by layer),
-    five layers per stack so that the last hand-over is a partial one: the update armed inside the backward pass gives the bits of the
+def test_armed_update_over_several_hand_overs(hs, compute, B, Ls, Lt):
+    """Five layers per stack, whose gradients go to the second stream three layers at a time, the last hand-over being a partial one, with
+    equal and unequal rows of the two sides: the update armed inside the backward pass gives the bits of the
     separate calls for every parameter, and the fp32 gradient is the oracle's."""
     model, ocfg, theta, a = _setup("s2s_tiny", compute, 41, dict(n_enc=5, n_dec=5, hidden=128, n_heads=2, ffn=256, vocab=500, max_pos=64))
     from paper_2009_14783_amd.step import PairWorker
