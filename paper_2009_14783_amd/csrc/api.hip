@@ -77,7 +77,10 @@ HeadWs carve_head(const hs_model_cfg& c, int M, void* base) {
 // the host 10 us and the GPU about as much, four times a launch, so a pass over few rows, whose kernels take 5 us, hands over several layers at
 // once; the operand buffers then exist twice per layer of a hand-over, so that one hand-over's are filled while the one before is read.
 // With many rows each layer is handed over by itself, the sooner the better, and there are two sets.
-// 264 rows (BERT-base): 4.63 ms per step with an event per layer, 4.18 with one per four.
+// Ms per step (BERT-base, 128 tokens per sequence; one, two, three, four layers at a time): 256 rows 2.61 / 2.44 / 2.46 / 2.47, 1024
+// 3.21 / 3.12 / 3.14 / 3.18, 2048 4.02 / 4.00 / 4.02 / 4.03, 3072 4.84 / 4.84 / 4.85 / 4.85, 6144 7.02 / 7.10 / 7.19 / 7.24; a pass without the
+// update at 256 rows 1.85 / 1.82 / 1.79 / 1.77; BERT-large 1024 rows 8.05 / 7.99 / 7.93 / 8.00, 2048 10.44 / 10.28 / 10.25 / 10.32, 3072 12.90 / 12.99 /
+// 13.09 / 13.07.
 // The plan follows the workspace that a call is given: two sets always do, more layers are handed over at once where their sets fit.
 struct BwdPlan { int sets, layers_per_hand_over; };
 
@@ -109,7 +112,7 @@ BwdWs carve_bwd(const hs_model_cfg& c, int B, int L, int sets, void* base) {
   return w;
 }
 
-constexpr int kMaxHandOver = 4;
+constexpr int kMaxHandOver = 3;
 int bwd_sets(const hs_model_cfg& c, int layers_per_hand_over) { return std::min(2 * layers_per_hand_over, c.n_layers); }
 size_t bwd_bytes(const hs_model_cfg& c, int B, int L, int layers_per_hand_over) {
   return carve_bwd(c, B, L, bwd_sets(c, layers_per_hand_over), nullptr).total;

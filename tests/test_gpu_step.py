@@ -406,7 +406,7 @@ def test_update_inside_backward_gives_the_bits_of_the_separate_calls(W, compute)
 @pytest.mark.parametrize("compute", ["fp32", "bf16"])
 @pytest.mark.parametrize("B", [32, 33])
 def test_backward_on_both_sides_of_the_few_rows_limit(W, B, compute):
-    """2048 rows (gradients of up to four layers handed to the second stream at a time) and 2112 (layer by layer, two
+    """2048 rows (gradients of up to three layers handed to the second stream at a time) and 2112 (layer by layer, two
     buffer sets), five layers so that the last hand-over is a partial one: the gradient is the sum over the two halves of the batch, and
     the update armed inside the pass gives the bits of the separate calls."""
     model = dict(n_layers=5, hidden=128, n_heads=2, ffn=256, vocab=500, max_pos=64, ln_eps=1e-12)
