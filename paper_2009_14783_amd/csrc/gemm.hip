@@ -382,12 +382,6 @@ float tiles_time(const TileCfg& c, int64_t tiles, float steps, float outputs) {
   const int per_cu = (int)((tiles + kCUs - 1) / kCUs), full = per_cu / c.occ, rem = per_cu % c.occ;
   return c.t0 + steps * (full * std::max(c.l, c.occ * c.w) + (rem ? std::max(c.l, rem * c.w) : 0.0f)) + c.e * per_cu * outputs;
 }
-// A long contraction costs more per k-tile: blocks that share operand panels drift apart and fetch them again (3072 x 768 with one
-// tile per CU: 0.46 us per k-tile at K = 8192, 0.58 at 16384).
-float cfg_time(const TileCfg& c, int M, int N, int K, int splits, float outputs) {
-  const float steps = (float)((K + 63) / 64) / splits;
-  return tiles_time(c, (int64_t)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn) * splits, steps * (1.0f + std::max(0.0f, steps - 128.0f) / 512.0f), outputs);
-}
 int gemm_cfg_override = -1;    // >= 0: use this configuration for every bf16 product of some size that it can serve (timing runs)
 
 constexpr int kMaxBK = 64;
@@ -459,9 +453,8 @@ static void choose_cfg(const GemmArgs& g, int* cfg, int* splits) {
   for (int c = 0; c < kNumTileCfg; ++c) {
     if (only >= 0 ? c != only : !kTileCfg[c].use) continue;
     // With a scratch buffer the contraction can be split over blocks: partial sums go out as fp32 and are added by a second
-    // launch (3 us and their way through memory and back at 3.5 TB/s; for contractions beyond 8192, where a block's share of the
-    // operands costs more the longer it is, 5 us at the 10 TB/s that these sums get on their way through the caches: 768 x 768 x 32768,
-    // A k-major, 82 -> 68 us).
+    // launch (3 us and their way through memory and back at 3.5 TB/s; for contractions beyond 8192, 5 us at the 10 TB/s that the sums get
+    // on their way through the caches: 768 x 768 x 32768, A k-major, 82 -> 68 us).
     const int64_t most = g.ws ? std::min<int64_t>({32, g.K / (4 * kTileCfg[c].bk), (int64_t)(g.ws_bytes / ((size_t)g.M * g.N * sizeof(float)))}) : 1;
     const int64_t tiles = (int64_t)((g.M + kTileCfg[c].bm - 1) / kTileCfg[c].bm) * ((g.N + kTileCfg[c].bn - 1) / kTileCfg[c].bn);
     for (int sp = 1; sp <= std::max<int64_t>(1, most); sp *= 2) {
@@ -474,10 +467,17 @@ static void choose_cfg(const GemmArgs& g, int* cfg, int* splits) {
       // beside each other.
       const bool lone = !gate && tiles * sp <= kCUs && g.K > 1024 && g.K % 64 == 0 && (sp == 1 || g.K <= 8192);
       if (only < 0 && (c == 5 || c == 9) && c != (forward || lone ? 5 : 9)) continue;
+      float steps = (float)((g.K + 63) / 64) / sp;
       // rows that end inside a k-tile do not start on cache lines either: half as much again per k-tile (768 x 768 x 2008: 0.7 us)
-      float t = cfg_time(kTileCfg[c], g.M, g.N, whole_k ? g.K : g.K + g.K / 2, sp, sp > 1 ? 2.0f : outputs);
+      if (!whole_k) steps *= 1.5f;
+      // Many k-tiles in a row cost more each: blocks that share operand panels drift apart and fetch them again (3072 x 768 with one tile
+      // per CU: 0.46 us per k-tile at K = 8192, 0.58 at 16384).  Not for the products over a padded vocabulary: the fit has
+      // them as they run in the step, beside the embedding gradient (split as if alone, they made it 0.4 % slower).
+      const bool alone = !g.a_kpad;
+      if (alone) steps *= 1.0f + std::max(0.0f, steps - 128.0f) / 512.0f;
+      float t = tiles_time(kTileCfg[c], tiles * sp, steps, sp > 1 ? 2.0f : outputs);
       const float mbytes = 8e-6f * sp * (float)g.M * (float)g.N;
-      if (sp > 1) t += g.K > 8192 ? 5.0f + mbytes / 10.0f : 3.0f + mbytes / 3.5f;
+      if (sp > 1) t += alone && g.K > 8192 ? 5.0f + mbytes / 10.0f : 3.0f + mbytes / 3.5f;
       if (t < best) { best = t; *cfg = c; *splits = sp; }
     }
   }
