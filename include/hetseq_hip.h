@@ -105,9 +105,9 @@ size_t hs_workspace_bytes(const hs_model_cfg* cfg, int32_t B, int32_t L, int32_t
  * parameters.  hs_arm_update arms exactly that (hs_grad_accum_normalize with `denom`, then
  * hs_adam_step with the given arguments, same arithmetic, same results bit for bit) for the NEXT
  * hs_encoder_bwd call on ctx whose gradient buffer g is G: that call then normalises and updates
- * every parameter group (head, each layer, embeddings) on a stream of its own as soon as the
- * group's gradient is final, beside the rest of the backward pass, and joins that work before it
- * returns work to the caller's stream.  Arm it for the LAST micro-batch of an update only (denom is
+ * every parameter group (head, each layer, embeddings) as soon as the group's gradient is final, on
+ * streams of the context beside the rest of the backward pass (what is final last on the caller's), and
+ * joins that work before it returns work to the caller's stream.  Arm it for the LAST micro-batch of an update only (denom is
  * the global sample count of the whole update); hs_mlm_loss of that micro-batch must already have been
  * enqueued on the same stream with the same G.  All pointers dev, sizes = hs_param_count; the
  * armed state is cleared by the backward call that consumes it (also when that call fails).
@@ -290,7 +290,7 @@ hs_status hs_adam_step(float* w, float* m, float* v, const float* G, void* w_low
                        void* stream);
 
 /* hs_grad_accum_normalize(G, NULL, n, 0, denom) and hs_adam_step on the result in one pass over the buffers: the same
- * arithmetic, the same bits in w, m, v, G and w_lowp_out. */
+ * arithmetic, the same bits in w, m, v, G and w_lowp_out.  denom == 0 means no scaling; then G is only read. */
 hs_status hs_normalize_adam_step(float* w, float* m, float* v, float* G, void* w_lowp_out, size_t n, double denom,
                                  double lr, double beta1, double beta2, double eps, double weight_decay, int64_t t,
                                  void* stream);

@@ -169,8 +169,8 @@ struct hs_ctx {
   hipStream_t side;
   std::vector<hipEvent_t> events;
   DropCfg drop;    // dropout of the forward/backward calls on this context (thr == 0: off)
-  // an optimizer update armed for the next backward call: each parameter group is normalised and updated
-  // on a third stream as soon as its gradient is final
+  // an optimizer update armed for the next backward call: each parameter group is normalised and updated as soon as its gradient is
+  // final, on the stream of the gradients, or (encoder with many rows) on the third stream `upd`; what is final last on the caller's
   struct Armed { bool on; float *w, *m, *v, *G; void* wl; double denom, lr, beta1, beta2, eps, wd; int64_t t; } armed;
   hipStream_t upd;
   // translation workload (contexts made by hs_s2s_ctx_create): cfg above holds the shared sizes (n_layers = encoder layers)
@@ -206,8 +206,8 @@ struct GemmArgs {
   const DropCfg* drop; uint32_t drop_site;   // optional (epi == 1): dropout of product + bias before the residual
 };
 hs_status launch_gemm(hs_ctx* ctx, const GemmArgs& g, hipStream_t s);
-// weight-gradient products (A m-major, B n-major or null for a column of ones, fp32 C = beta C + product, the same beta) in one launch
-// per 48 of them (bf16; fp32: one each)
+// weight-gradient products (A m-major, B n-major or null for a column of ones, fp32 C = beta C + product, one type and beta; anything
+// else is refused) in one launch per 48 of them
 hs_status launch_gemm_group(hs_ctx* ctx, const GemmArgs* gs, int n, hipStream_t s);
 // timing runs: every bf16 product with M, N, K >= 256 that configuration `variant` can serve uses it (-1: automatic choice); process-wide
 int gemm_variant_count();
@@ -251,7 +251,6 @@ hs_status launch_colsum(hs_ctx* ctx, int dtype, const void* x, int64_t ldx, int 
 hs_status launch_gather_rows(hs_ctx* ctx, int dtype, const void* src, const int32_t* idx, int M, int H, void* dst, hipStream_t s);
 hs_status launch_scatter_rows(hs_ctx* ctx, int dtype, const void* src, const int32_t* idx, int M, int H, void* dst, hipStream_t s);
 hs_status launch_fill_zero(hs_ctx* ctx, void* p, size_t bytes, hipStream_t s);
-hs_status launch_fill_value(hs_ctx* ctx, int dtype, void* p, size_t n, float value, hipStream_t s);   // n elements of the activation type
 hs_status launch_gelu_fwd(hs_ctx* ctx, int dtype, const void* x, void* y, size_t n, hipStream_t s);
 hs_status launch_gelu_bwd(hs_ctx* ctx, int dtype, const void* dy, const void* pre, void* dx, size_t n, hipStream_t s);
 // Attention with separate query and key/value sequences (attention_general.hip).  Row b*Lq + i of q (stride ldq) is

@@ -218,22 +218,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NC <= 3 ? 4
   }
 }
 
-// out_q[col] = beta*out_q[col] + sum_p partials[p*pstride + q*qstride + col] for up to three quantities q
-// (blockIdx.y).  Fixed summation tree: wave w of the block's 16 waves adds p = w, w+16, w+32, ... in
-// ascending order, then the wave sums are added in wave order.
+// out[col] = beta*out[col] + sum_p src[p*pstride + col] over the block's 64 columns.  Fixed summation tree: wave w of the block's
+// 16 waves adds p = w, w+16, w+32, ... in ascending order, then the wave sums are added in wave order.
 constexpr int SP_WAVES = 16;
-__global__ __launch_bounds__(64 * SP_WAVES) void sum_partials_kernel(const float* __restrict__ partials, int np, int64_t pstride,
-                                                                    int64_t qstride, int C, float* __restrict__ out0,
-                                                                    float* __restrict__ out1, float* __restrict__ out2, float beta) {
+__device__ __forceinline__ void sum_partials(const float* __restrict__ src, int np, int64_t pstride, int C, float* __restrict__ out, float beta) {
   __shared__ float red[SP_WAVES][64];
-  const int q = blockIdx.y;
-  float* out = q == 0 ? out0 : (q == 1 ? out1 : out2);
   if (!out) return;                                   // uniform over the block
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int col = blockIdx.x * 64 + lane;
   float s = 0.f;
   if (col < C) {
-    const float* src = partials + q * qstride + col;
+    src += col;
     int p = wave;
     for (; p + 7 * SP_WAVES < np; p += 8 * SP_WAVES) {
       float a[8];
@@ -254,39 +249,21 @@ __global__ __launch_bounds__(64 * SP_WAVES) void sum_partials_kernel(const float
   }
 }
 
-// The same for the LayerNorm backward partials of several layers in one launch (blockIdx.z: the layer): alone, each of them is
-// a launch that costs more than its work (4 us against 1).
+// for up to three quantities (blockIdx.y), `qstride` apart in every partial
+__global__ __launch_bounds__(64 * SP_WAVES) void sum_partials_kernel(const float* __restrict__ partials, int np, int64_t pstride,
+                                                                    int64_t qstride, int C, float* __restrict__ out0,
+                                                                    float* __restrict__ out1, float* __restrict__ out2, float beta) {
+  const int q = blockIdx.y;
+  sum_partials(partials + q * qstride, np, pstride, C, q == 0 ? out0 : (q == 1 ? out1 : out2), beta);
+}
+
+// for the LayerNorm backward partials of several layers in one launch (blockIdx.z: the layer): alone, each of them is
+// a launch that costs more than its work (4 us against 1)
 struct LnColsTable { LnColsJob job[kLnColsMax]; };
 __global__ __launch_bounds__(64 * SP_WAVES) void ln_cols_kernel(LnColsTable t, int np, int H, float beta) {
-  __shared__ float red[SP_WAVES][64];
   const LnColsJob& j = t.job[blockIdx.z];
   const int q = blockIdx.y;
-  float* out = q == 0 ? j.d_gain : (q == 1 ? j.d_bias : j.d_colsum);
-  if (!out) return;                                   // uniform over the block
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int col = blockIdx.x * 64 + lane;
-  float s = 0.f;
-  if (col < H) {
-    const float* src = (const float*)j.partials + q * H + col;
-    const int64_t pstride = 3 * (int64_t)H;
-    int p = wave;
-    for (; p + 7 * SP_WAVES < np; p += 8 * SP_WAVES) {
-      float a[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) a[u] = src[(int64_t)(p + SP_WAVES * u) * pstride];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) s += a[u];
-    }
-    for (; p < np; p += SP_WAVES) s += src[(int64_t)p * pstride];
-  }
-  red[wave][lane] = s;
-  __syncthreads();
-  if (wave == 0 && col < H) {
-    float r = red[0][lane];
-#pragma unroll
-    for (int w = 1; w < SP_WAVES; ++w) r += red[w][lane];
-    out[col] = (beta != 0.f) ? beta * out[col] + r : r;
-  }
+  sum_partials((const float*)j.partials + q * H, np, 3 * (int64_t)H, H, q == 0 ? j.d_gain : (q == 1 ? j.d_bias : j.d_colsum), beta);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -325,11 +302,6 @@ __global__ void gather_rows_kernel(const T* __restrict__ src, const int32_t* __r
   }
 }
 
-template <class T>
-__global__ __launch_bounds__(256) void fill_value_kernel(T* p, size_t n, float value) {
-  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < n) p[i] = from_f<T>(value);
-}
 __global__ void fill_bytes_kernel(unsigned char* p, size_t n) {
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = 0;
@@ -824,16 +796,6 @@ hs_status launch_fill_zero(hs_ctx* ctx, void* p, size_t bytes, hipStream_t s) {
   if (blocks > 4096) blocks = 4096;
   hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)blocks), dim3(256), 0, s, (uint4*)p, n16, (unsigned char*)p + n16 * 16, ntail);
   LAUNCH_CHECK(ctx, "fill_zero");
-  return HS_OK;
-}
-
-hs_status launch_fill_value(hs_ctx* ctx, int dtype, void* p, size_t n, float value, hipStream_t s) {
-  if (n == 0) return HS_OK;
-  KScope scope(prof_of(ctx), KC_ELEMWISE, 0.0, (double)n * esize(dtype), s);
-  dim3 grid((unsigned)((n + 255) / 256));
-  if (dtype == HS_BF16) hipLaunchKernelGGL(fill_value_kernel<bf16>, grid, dim3(256), 0, s, (bf16*)p, n, value);
-  else hipLaunchKernelGGL(fill_value_kernel<float>, grid, dim3(256), 0, s, (float*)p, n, value);
-  LAUNCH_CHECK(ctx, "fill_value");
   return HS_OK;
 }
 

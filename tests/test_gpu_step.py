@@ -377,8 +377,8 @@ def test_workload4_bert_large_shape(W):
 @pytest.mark.gpu
 @pytest.mark.parametrize("compute", ["fp32", "bf16"])
 def test_update_inside_backward_gives_the_bits_of_the_separate_calls(W, compute):
-    """Normalise + Adam armed for the last micro-batch's backward pass (per parameter group, on a third
-    stream) against hs_grad_accum_normalize + hs_adam_step after it: identical state, two updates in a row,
+    """Normalise + Adam armed for the last micro-batch's backward pass (per parameter group, beside the
+    rest of the pass) against hs_grad_accum_normalize + hs_adam_step after it: identical state, two updates in a row,
     unequal micro-batches and workers without data in between."""
     from paper_2009_14783_amd import binding as hs
     Worker = W
