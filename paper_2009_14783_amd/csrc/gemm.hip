@@ -366,10 +366,13 @@ static hipError_t gelu_table(int which, const float2** out) {
 //   t0 + k-tiles x (rounds of full CUs x occ w + the last round of r blocks per CU x max(l, r w)) + e x tiles per CU x outputs
 // with l the time of a k-tile of 64 when a block has its CU to itself (a chain of load, LDS read and matrix instruction
 // latencies), w what it adds to a CU whose blocks cover each other (throughput of the feed from the L2), and e the writing
-// of a tile; `use` says whether the automatic choice considers the configuration (the others are slower everywhere or
-// within the error of the fit, and selectable for timing).  The constants (us) are fitted to 4700 launches on this
-// chip: rows 32 .. 16384, the forward and activation-gradient products of widths 512, 768 and 1024 with their epilogues, weights not
-// in the cache of the launch before; the choice made with them is 2 % above the fastest configuration on average over those shapes.
+// of a tile.  The constants (us) are fitted to launches on this chip: rows 32 .. 16384, the forward and activation-gradient products of
+// widths 512, 768 and 1024 with their epilogues, weights not in the cache of the launch before.  `use`: the automatic choice considers
+// the configuration; the others can be selected for timing.  0 and 3 are slower nearly everywhere; of 1, 7, 8 and 10 one or the other
+// is faster than the choice on many products by themselves (over 168 products the choice is 5 % above the fastest of all twelve on
+// average and 34 % at most, 7 at 2056 and 4104 rows, 10 at 8192, 1 at 16384 rows of width 1024), but forced on the whole
+// BERT-base step the best of them, 10, takes 7.86 ms against 7.92 with the choice.  (python -m paper_2009_14783_amd.gemm_variants
+// --choice, --step)
 struct TileCfg { int bm, bn, bk, occ, use; float t0, l, w, e; };
 constexpr TileCfg kTileCfg[] = {
     {128, 128, 32, 3, 0, 3.2f, 0.560f, 0.470f, 2.00f}, {256, 256, 64, 1, 0, 6.4f, 1.106f, 0.836f, 7.34f}, {32, 32, 64, 1, 1, 1.5f, 0.011f, 0.104f, 0.90f},

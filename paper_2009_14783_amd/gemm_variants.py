@@ -1,6 +1,7 @@
 """Times every tiling of the library's bf16 GEMM kernel on the products of one BERT-base layer (64 x 128 tokens).
 
-    python -m paper_2009_14783_amd.gemm_variants [--iters 50] [--step] [--variants -1,5,9] [--products "fwd ffn1,dx qkv"] [--cube]
+    python -m paper_2009_14783_amd.gemm_variants [--iters 50] [--step] [--variants -1,5,9] [--products "fwd ffn1,dx qkv"] [--cube] [--large]
+                                                 [--choice]
 
 Stand-alone: each product runs `iters` times back to back on fixed buffers with the epilogue it has in the training
 step (bias, bias + residual, bias + GELU with both outputs, GELU' of a saved pre-activation, fp32 accumulate); the
@@ -8,6 +9,9 @@ table gives TFLOP/s per variant.  A variant that is not built with a product's e
 contraction length, is served by the library's fallback kernel; the automatic choice is the row `auto`.
 --step adds the whole training step (ms per step, 10 warm-up + 30 timed) with the variant forced for every product of the
 forward pass and of the activation-gradient chain (the grouped weight-gradient launch keeps its own tiling).
+--large takes the products of a BERT-large layer instead (16384 tokens = 32 x 512, and `half`: the 8192 of a forward half-batch).
+--choice times the forward and activation-gradient products of widths 512, 768 and 1024 over 264 to 16384 rows with every tiling, operands
+rotating over eight copies, and prints what the automatic choice takes beside the fastest tiling.
 --cube times 8192 x 8192 x 8192 products in the three operand layouts instead (no epilogue; fp32 output for the m-major layout).
 --products keeps the named products only (for counter runs under a profiler).
 Prints Markdown.  Needs the GPU and the built library; no oracle, no CPU path.
@@ -30,6 +34,15 @@ PRODUCTS = [
     ("dx ffn2", 1, 0, T, F, H, 3, 0), ("dx ffn1", 1, 0, T, H, F, 0, 0), ("dx out", 1, 0, T, H, H, 0, 0), ("dx qkv", 1, 0, T, H, 3 * H, 0, 0),
     ("dW ffn1", 0, 0, F, H, T, 0, 1), ("dW ffn2", 0, 0, H, F, T, 0, 1), ("dW out", 0, 0, H, H, T, 0, 1), ("dW qkv", 0, 0, 3 * H, H, T, 0, 1),
 ]
+
+
+def layer_products(rows, H, F, tag=""):
+    return [(f"fwd qkv{tag}", 1, 1, rows, 3 * H, H, 0, 0), (f"fwd out{tag}", 1, 1, rows, H, H, 1, 0), (f"fwd ffn1{tag}", 1, 1, rows, F, H, 2, 0),
+            (f"fwd ffn2{tag}", 1, 1, rows, H, F, 1, 0)], [(f"dx ffn2{tag}", 1, 0, rows, F, H, 3, 0), (f"dx ffn1{tag}", 1, 0, rows, H, F, 1, 0),
+            (f"dx out{tag}", 1, 0, rows, H, H, 0, 0), (f"dx qkv{tag}", 1, 0, rows, H, 3 * H, 1, 0)]
+
+
+LARGE = layer_products(16384, 1024, 4096)[0] + layer_products(8192, 1024, 4096, " half")[0] + layer_products(16384, 1024, 4096)[1]
 # A and B k-major; A k-major, B n-major; A and B m-major
 CUBES = [("cube kk", 1, 1, 8192, 8192, 8192, 0, 0), ("cube kn", 1, 0, 8192, 8192, 8192, 0, 0), ("cube nn", 0, 0, 8192, 8192, 8192, 0, 1)]
 NAMES = {-1: "auto", 0: "0: 128x128x32, 3/CU", 1: "1: 256x256x64", 2: "2: 32x32, waves split K", 3: "3: 32x32, waves split K, 2/CU",
@@ -59,6 +72,52 @@ def time_product(prod, iters, bufs):
     return us, 2.0 * M * N * K / us / 1e6
 
 
+def choice(iters):
+    """Markdown: per product and row count the time of the automatic choice, and of the fastest tiling where that is another."""
+    rows_of, copies = (264, 520, 1032, 2056, 4104, 8192, 16384), 8
+    n = 16384 * 4096
+    mk = lambda scale: [(torch.randn(n, device="cuda") * scale).to(torch.bfloat16) for _ in range(copies)]
+    As, Bs, Xs = mk(0.5), mk(0.05), mk(1.0)
+    Cs, C2 = [torch.empty(n, dtype=torch.bfloat16, device="cuda") for _ in range(copies)], torch.empty(n, dtype=torch.bfloat16, device="cuda")
+    bias = torch.zeros(4096, dtype=torch.bfloat16, device="cuda")
+
+    def us(prod, v):
+        _, ak, bk, M, N, K, epi, _ = prod
+        hs.hs_tune_gemm_variant(v)
+        def run(i):
+            i %= copies
+            hs.hs_op_gemm(1, ak, bk, M, N, K, As[i], K, Bs[i], K if bk else N, Cs[i], N, epi=epi, bias=None if epi == 3 else bias,
+                          aux=Xs[i] if epi in (1, 3) else None, ldaux=N if epi in (1, 3) else 0, C2=C2 if epi == 2 else None)
+        times = []
+        for rep in range(3):
+            run(0)
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            for i in range(iters):
+                run(i)
+            e1.record()
+            torch.cuda.synchronize()
+            times.append(e0.elapsed_time(e1) * 1e3 / iters)
+        return min(times)
+
+    print("| width, product | " + " | ".join(f"{r} rows" for r in rows_of) + " |")
+    print("|---|" + "---|" * len(rows_of))
+    ratios = []
+    for H in (512, 768, 1024):
+        lists = [sum(layer_products(r, H, 4 * H), []) for r in rows_of]
+        for j in range(len(lists[0])):
+            cells = []
+            for r, products in zip(rows_of, lists):
+                t = {v: us(products[j], v) for v in [-1] + list(range(12))}
+                best = min(range(12), key=lambda v: t[v])
+                ratios.append(t[-1] / min(t.values()))
+                cells.append(f"{t[-1]:.1f}" + (f" ({t[best]:.1f}: {best})" if t[best] < 0.98 * t[-1] else ""))
+            print(f"| {H}, {lists[0][j][0]} | " + " | ".join(cells) + " |", flush=True)
+    hs.hs_tune_gemm_variant(-1)
+    print(f"\nus; in brackets the fastest tiling and its time where it is more than 2 % faster.  Automatic choice over fastest: mean "
+          f"{sum(ratios) / len(ratios):.3f}, largest {max(ratios):.2f} over {len(ratios)} products.")
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--iters", type=int, default=50)
@@ -66,9 +125,13 @@ def main():
     ap.add_argument("--variants", default="", help="comma-separated variant numbers (-1: automatic); default: all")
     ap.add_argument("--products", default="", help="comma-separated product names; default: all")
     ap.add_argument("--cube", action="store_true")
+    ap.add_argument("--large", action="store_true")
+    ap.add_argument("--choice", action="store_true")
     args = ap.parse_args()
     hs.lib()
-    products = CUBES if args.cube else PRODUCTS
+    if args.choice:
+        return choice(args.iters)
+    products = CUBES if args.cube else LARGE if args.large else PRODUCTS
     if args.products:
         products = [p for p in products if p[0] in [q.strip() for q in args.products.split(",")]]
         if not products:
