@@ -284,8 +284,8 @@ class PairWorker:
         """One optimizer step over the uploaded micro-batches (None = a pass without data).  Returns the weight D used
         (the number of real target tokens by default).  update_in_backward: normalisation and Adam are armed for the last
         micro-batch's backward pass, which applies them layer by layer as soon as a layer's gradient is final (same
-        arithmetic, same bits as the two separate calls).  Off by default: at this model's sizes the update's memory
-        traffic beside the small GEMMs of the backward pass costs more than it hides (6.58 against 6.49 ms per step)."""
+        arithmetic, same bits as the two separate calls).  Off by default: at this model's sizes it gains 1 to 4 %
+        (4096 positions per side: 4.60 -> 4.55 ms per step), and a forward pass that fails would leave the update armed."""
         assert len(batches) <= 64
         hs.hs_fill_zero(self.loss_buf, 4 * self.loss_buf.numel())
         real = [i for i, d in enumerate(batches) if d is not None]
