@@ -7,6 +7,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <vector>
 
 hipError_t gemm_wide_launch_kk(int cfg, const GemmDev& p, int splits, hipStream_t s);
 hipError_t gemm_wide_launch_kn(int cfg, const GemmDev& p, int splits, hipStream_t s);
@@ -361,24 +362,26 @@ static hipError_t gelu_table(int which, const float2** out) {
   return hipSuccess;
 }
 
-// Tile configurations.  0: gemm_bf16_mfma (any shape, every epilogue).  1, 5, 6: gemm_bf16_wide (global -> registers -> LDS).  4, 7 .. 11: gemm_bf16_dma (global -> LDS).  2, 3: gemm_bf16_ksplit (the
-// waves of a block share out the contraction).  What a launch takes is modelled as
+// Tile configurations.  0: gemm_bf16_mfma (any shape, every epilogue).  5: gemm_bf16_wide (global -> registers -> LDS).  2: gemm_bf16_ksplit
+// (the waves of a block share out the contraction).  The others: gemm_bf16_dma (global -> LDS).  What a launch takes is modelled as
 //   t0 + k-tiles x (rounds of full CUs x occ w + the last round of r blocks per CU x max(l, r w)) + e x tiles per CU x outputs
 // with l the time of a k-tile of 64 when a block has its CU to itself (a chain of load, LDS read and matrix instruction
 // latencies), w what it adds to a CU whose blocks cover each other (throughput of the feed from the L2), and e the writing
-// of a tile.  The constants (us) are fitted to launches on this chip: rows 32 .. 16384, the forward and activation-gradient products of
-// widths 512, 768 and 1024 with their epilogues, weights not in the cache of the launch before.  `use`: the automatic choice considers
-// the configuration; the others can be selected for timing.  0 and 3 are slower nearly everywhere; of 1, 7, 8 and 10 one or the other
-// is faster than the choice on many products by themselves (over 168 products the choice is 5 % above the fastest of all twelve on
-// average and 34 % at most, 7 at 2056 and 4104 rows, 10 at 8192, 1 at 16384 rows of width 1024), but forced on the whole
-// BERT-base step the best of them, 10, takes 7.86 ms against 7.92 with the choice.  (python -m paper_2009_14783_amd.gemm_variants
-// --choice, --step)
+// of a tile.  The constants (us) are fitted to launches on this chip: rows 264 .. 17472, the forward and activation-gradient products of
+// widths 512, 768 and 1024 with their epilogues, weights not in the cache of the launch before (2, 4 and 11, whose launches are shorter than
+// the host takes to enqueue them, to a fit over 32 .. 4104 rows, and their t0 raised together until the translation step at 4096 rows per side and BERT-base at 264
+// rows agreed).  Over 288 products the choice is 1.4 % above the fastest on average and 24 % at most.  l of 3 and 6 is the one of a nearly full chip:
+// 8192 x 768 x 3072 takes 59.6 us as 256 blocks of 128 x 192 and 51.5 as 192 of 256 x 128.  `use`: the automatic choice considers the
+// configuration; the others can be selected for timing (8 is the mirror image of 7 and seldom faster).
+// What the tiles of more than 128 x 128 brought, us (128 x 128 before; rows x columns x contraction, epilogue): 16384 x 4096 x 1024 GELU 201 -> 163, x 1024 x 4096
+// residual 148 -> 122, x 3072 x 1024 124 -> 107; 8192 x 3072 x 768 GELU 71 -> 58, x 768 x 3072 residual 56 -> 50, x 768 x 2304 45 -> 39;
+// 8192^3 1044 -> 1339 TFLOP/s.
 struct TileCfg { int bm, bn, bk, occ, use; float t0, l, w, e; };
 constexpr TileCfg kTileCfg[] = {
-    {128, 128, 32, 3, 0, 3.2f, 0.560f, 0.470f, 2.00f}, {256, 256, 64, 1, 0, 6.4f, 1.106f, 0.836f, 7.34f}, {32, 32, 64, 1, 1, 1.5f, 0.011f, 0.104f, 0.90f},
-    {32, 32, 64, 2, 0, 2.4f, 0.112f, 0.092f, 0.38f},   {32, 64, 64, 3, 1, 3.0f, 0.146f, 0.120f, 0.33f},   {128, 128, 64, 2, 1, 3.2f, 0.318f, 0.423f, 1.95f},
-    {256, 128, 64, 1, 0, 3.2f, 0.720f, 0.800f, 3.60f}, {64, 128, 64, 2, 0, 2.7f, 0.319f, 0.288f, 0.90f},  {128, 64, 64, 2, 0, 2.6f, 0.316f, 0.289f, 0.84f},
-    {128, 128, 64, 2, 1, 2.9f, 0.548f, 0.447f, 1.57f}, {256, 128, 64, 1, 0, 1.1f, 0.717f, 0.745f, 3.55f}, {64, 64, 64, 3, 1, 2.5f, 0.229f, 0.175f, 0.41f}};
+    {128, 128, 32, 3, 0, 3.2f, 0.560f, 0.470f, 2.00f}, {256, 256, 64, 1, 1, 2.5f, 1.494f, 1.494f, 6.14f}, {32, 32, 64, 1, 1, 2.5f, 0.011f, 0.104f, 0.90f},
+    {128, 192, 64, 2, 1, 2.5f, 1.050f, 0.693f, 2.36f}, {32, 64, 64, 3, 1, 4.0f, 0.146f, 0.120f, 0.33f},   {128, 128, 64, 2, 1, 3.2f, 0.497f, 0.487f, 1.82f},
+    {192, 128, 64, 2, 1, 2.5f, 1.050f, 0.705f, 2.00f}, {64, 128, 64, 2, 1, 2.7f, 0.190f, 0.296f, 1.24f},  {128, 64, 64, 2, 0, 2.7f, 0.228f, 0.305f, 1.19f},
+    {128, 128, 64, 2, 1, 2.5f, 0.689f, 0.490f, 1.85f}, {256, 128, 64, 1, 1, 2.5f, 0.814f, 0.814f, 3.92f}, {64, 64, 64, 3, 1, 3.5f, 0.229f, 0.183f, 0.43f}};
 constexpr int kNumTileCfg = sizeof(kTileCfg) / sizeof(kTileCfg[0]);
 constexpr int kCUs = 256;
 float tiles_time(const TileCfg& c, int64_t tiles, float steps, float outputs) {
@@ -420,6 +423,7 @@ static GemmDev gemm_dev_args(const GemmArgs& g) {
   p.partial = nullptr; p.k_per_split = g.K; p.gelu_tab = nullptr;
   p.drop = (g.drop && g.drop->thr && g.epi == 1) ? *g.drop : DropCfg{0u, 1.0f, 0u, 0u, 0u};
   p.drop_site = g.drop_site;
+  p.rowsum = nullptr;
   return p;
 }
 
@@ -446,9 +450,9 @@ static void choose_cfg(const GemmArgs& g, int* cfg, int* splits) {
   // against 25.5 us, 30522 x 768 x 64: 14.4 against 18.4; at K = 256 and with a residual the two are level, with an
   // fp32 result the two win)
   if (only < 0 && g.a_kmajor && g.b_kmajor && g.epi == 0 && !g.c_f32 && g.K < 256 && (int64_t)((g.M + 127) / 128) * ((g.N + 127) / 128) > kCUs) only = 0;
-  if (supported && !whole_k && only != 0 && only != 1 && only != 6) only = some_size ? 5 : 0;
+  if (supported && !whole_k && only != 0) only = some_size ? 5 : 0;
   const bool gate = g.epi == 5;      // not in the register-staged kernels
-  if (gate && (only == 1 || only == 5 || only == 6)) only = 0;
+  if (gate && (only == 5)) only = 0;
   const float outputs = (g.c_f32 || g.epi) ? 2.0f : 1.0f;
   const bool forward = g.a_kmajor && g.b_kmajor;
   float best = 3.0e38f;
@@ -461,7 +465,7 @@ static void choose_cfg(const GemmArgs& g, int* cfg, int* splits) {
     const int64_t most = g.ws ? std::min<int64_t>({32, g.K / (4 * kTileCfg[c].bk), (int64_t)(g.ws_bytes / ((size_t)g.M * g.N * sizeof(float)))}) : 1;
     const int64_t tiles = (int64_t)((g.M + kTileCfg[c].bm - 1) / kTileCfg[c].bm) * ((g.N + kTileCfg[c].bn - 1) / kTileCfg[c].bn);
     for (int sp = 1; sp <= std::max<int64_t>(1, most); sp *= 2) {
-      // 5 and 9 are the same tile.  The register-staged pipeline (5) has four k-tiles in flight, the direct one (9) two: a block that has
+      // 5 and 9 are the same tile (figures with the direct kernel as it was before it read fragments ahead).  The register-staged pipeline (5) has four k-tiles in flight, the direct one (9) two: a block that has
       // its CU to itself is faster with the first from about 16 whole k-tiles on (A m-major, 3072 x 768 x 8192: 62 against 78 us, at K = 1216
       // 17.0 against 18.3; 4096 x 1024 x 4096, A k-major: 38 against 46), two blocks that cover each other with the second (the
       // embedding gradient of the translation step, 37000 x 512: 4.97 against 4.83 ms for the step), and so is any block whose contraction
@@ -486,27 +490,41 @@ static void choose_cfg(const GemmArgs& g, int* cfg, int* splits) {
   }
 }
 
-// Weight-gradient products (A m-major, B n-major or null for a column of ones, fp32 C = beta C + product, one beta for all) in as
+// Weight-gradient products (A m-major, B n-major or null for a column of ones, fp32 C = beta C + product, one type and beta for all) in as
 // few launches of the grouped kernel as their number allows: no split-K, no partial sums in memory, one ramp-up and one tail.
 hs_status launch_gemm_group(hs_ctx* ctx, const GemmArgs* gs, int n, hipStream_t s) {
+  std::vector<GroupProb> probs;
+  for (int i = 0; i < n; ++i) {
+    const GemmArgs& g = gs[i];
+    if (g.a_kmajor || g.b_kmajor || !g.c_f32 || g.bias || g.epi || g.drop || g.dtype != gs[0].dtype || g.beta != gs[0].beta ||
+        std::max({g.lda, g.ldb, g.ldc}) > INT32_MAX)
+      return hs_fail(ctx, HS_ERR_INVALID_ARG, "grouped gemm: only m-major x n-major products with fp32 results and one type and beta");
+    GemmArgs chk = g;
+    if (!g.B) { chk.B = g.A; chk.ldb = 8; chk.N = 1; }
+    hs_status st = check_gemm_args(ctx, chk);
+    if (st != HS_OK) return st;
+    if (g.B || g.dtype == HS_FP32) probs.push_back(GroupProb{g.A, g.B, (float*)g.C, nullptr, (int)g.lda, (int)g.ldb, (int)g.ldc, g.M, g.N, g.K});
+  }
+  for (int i = 0; i < n && gs[0].dtype != HS_FP32; ++i) {      // bf16 bias gradients: beside the weight gradient of the same operand
+    const GemmArgs& g = gs[i];
+    if (g.B) continue;
+    GroupProb* with = nullptr;
+    for (GroupProb& q : probs)
+      if (q.A == g.A && q.lda == g.lda && q.M == g.M && q.K == g.K && !q.rowsum) { with = &q; break; }
+    if (!with || g.ldc != 1) return hs_fail(ctx, HS_ERR_INVALID_ARG, "grouped gemm: a bias gradient without the weight gradient of the same operand");
+    with->rowsum = (float*)g.C;      // (as products with a column of ones they were 10 % of the tiles of a BERT-base layer)
+  }
+  n = (int)probs.size();
   for (int done = 0; done < n;) {
     GemmGroupDev gd;
     gd.n = std::min(n - done, kGroupMax);
-    gd.beta = gs[done].beta;
-    const bool f32 = gs[done].dtype == HS_FP32;
+    gd.beta = gs[0].beta;
+    const bool f32 = gs[0].dtype == HS_FP32;
     double flops = 0, bytes = 0;
     for (int i = 0; i < gd.n; ++i) {
-      const GemmArgs& g = gs[done + i];
-      if (g.a_kmajor || g.b_kmajor || !g.c_f32 || g.bias || g.epi || g.drop || g.dtype != gs[done].dtype || g.beta != gd.beta ||
-          std::max({g.lda, g.ldb, g.ldc}) > INT32_MAX)
-        return hs_fail(ctx, HS_ERR_INVALID_ARG, "grouped gemm: only m-major x n-major products with fp32 results and one type and beta");
-      GemmArgs chk = g;
-      if (!g.B) { chk.B = g.A; chk.ldb = 8; chk.N = 1; }
-      hs_status st = check_gemm_args(ctx, chk);
-      if (st != HS_OK) return st;
-      gd.prob[i] = GroupProb{g.A, g.B, (float*)g.C, (int)g.lda, (int)g.ldb, (int)g.ldc, g.M, g.N, g.K};
-      flops += 2.0 * g.M * g.N * (double)g.K;
-      bytes += ((double)g.M * g.K + (double)g.N * g.K) * esize(g.dtype) + (double)g.M * g.N * 4;
+      const GroupProb& q = gd.prob[i] = probs[done + i];
+      flops += 2.0 * q.M * (q.N + (q.rowsum ? 1 : 0)) * (double)q.K;
+      bytes += ((double)q.M * q.K + (double)q.N * q.K) * esize(gs[0].dtype) + (double)q.M * q.N * 4;
     }
     auto count = [&](int bm, int bn) {      // fills first_tile, returns the number of tiles
       int tiles = 0;
@@ -523,14 +541,20 @@ hs_status launch_gemm_group(hs_ctx* ctx, const GemmArgs* gs, int n, hipStream_t 
       // where the tilings are within an eighth of each other (see gemm_f32_tile).
       cfg = count(128, 128) >= 24 * gd.n ? 128 : 32;
       count(cfg, cfg);
-    } else {      // the tile by the model of choose_cfg, over the tiles of all problems
+    } else {
+      // The tile by the constants of the time model, over the tiles of all problems.  The launch runs beside the chain of activation
+      // gradients, so what counts is the time of the CUs that it takes and not how evenly its last round fills them: rounds are not
+      // rounded up.  (Ms per step with 256 x 256, 256 x 128 and 128 x 128 tiles: BERT-base with 8192 rows 7.28 / 7.25 / 7.30, with micro-batches of 2048, 6144
+      // and 14336 rows 21.4 / 21.7 / 22.1, with 17472 rows 15.1 / 15.3 / 15.9; BERT-large with 16384 rows 156 / 162 / 178; the translation step with 4096 rows
+      // per side 4.28 / 4.36 / 4.41.)
       float best = 3.0e38f;
-      for (int c : {9, 11}) {
+      for (int c : {1, 9, 10, 11}) {
         const TileCfg& t = kTileCfg[c];
         const int tiles = count(t.bm, t.bn);
         float steps = 0.0f;
         for (int i = 0; i < gd.n; ++i) steps += (float)(gd.first_tile[i + 1] - gd.first_tile[i]) * ((gd.prob[i].K + 63) / 64);
-        const float time = tiles_time(t, tiles, tiles ? steps / tiles : 0.0f, 2.0f);
+        const float per_tile = (tiles ? steps / tiles : 0.0f) * std::max(t.l / t.occ, t.w) + t.e * 2.0f;
+        const float time = t.t0 + per_tile * std::max(1.0f, (float)tiles / kCUs);
         if (time < best) { best = time; cfg = c; }
       }
       count(kTileCfg[cfg].bm, kTileCfg[cfg].bn);

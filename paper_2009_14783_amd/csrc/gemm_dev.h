@@ -14,12 +14,14 @@ struct GemmDev {
   const float2* gelu_tab;   // wide kernels, GELU epilogues: table for gelu_tab_eval (the cdf for epi 2, GELU' for epi 3)
   DropCfg drop;        // dropout of (product + bias) before the residual is added (epi == 1 only; thr == 0: off)
   uint32_t drop_site;  // element index of the site = row * N + col
+  float* rowsum;       // grouped weight gradients: rowsum[m] = beta rowsum[m] + sum_k A(m, k) beside the product, or null
 };
 
 // Several weight-gradient products C = beta C + sum_k A(k, m) B(k, n) (A m-major, B n-major, fp32 C) for one launch of a grouped
-// kernel.  B == null: a column of ones (C[m] = beta C[m] + sum_k A(k, m), a bias gradient).
+// kernel.  rowsum: also rowsum[m] = beta rowsum[m] + sum_k A(k, m), the bias gradient beside a weight gradient (bf16), or null;
+// fp32: a bias gradient is a problem of its own, with B == null (a column of ones).
 struct GroupProb {
-  const void *A, *B; float* C;
+  const void *A, *B; float *C, *rowsum;
   int lda, ldb, ldc, M, N, K;
 };
 constexpr int kGroupMax = 48;      // 2.5 KB of kernel arguments

@@ -12,7 +12,8 @@ namespace {
 // k-tile's 16-deep slices (group g takes slices g, g + KW, ...; the groups' sums are added in group order through LDS).
 // A k-tile is fetched by buffer loads that write LDS themselves (16 bytes per lane, one instruction fills 1 KiB of LDS in
 // lane order), so that an operand byte never passes through a register and no LDS store instruction is issued.  S stages
-// of LDS form a ring: the tile for k-step t + S - 1 is requested when step t starts, one barrier per k-tile.  What orders
+// of LDS form a ring, one barrier per k-tile: the tile for k-step t + S - 1 is requested when step t starts or (AHEAD, see ahead_step)
+// the one for step t + S before its last slice.  What orders
 // the loads against their readers is the wave's own load counter (the hardware retires these loads in order) followed by
 // the barrier; both are written out by hand here, because a fence would make every wave wait for all of its loads.
 //
@@ -21,13 +22,15 @@ namespace {
 //   k-major operand ([rows, K], a row of the tile is BK contiguous elements): the layout of WideTile, rows
 //     unpadded, chunk ^ ((row >> 1) & 7) for BK = 64 and chunk ^ ((row >> 2) & 3) for BK = 32.
 //   m-major operand ([K, rows], a row of the tile is R contiguous elements of one contraction index k): a transposing read
-//     takes 64 bytes of each of four k-rows at once.  R >= 128: chunk ^ ((k & 3) << 2) puts the four into four different
-//     64-byte bank groups; R = 64: two k-rows already lie side by side, chunk ^ (((k >> 1) & 1) << 2) parts the others;
+//     takes 64 bytes of each of four k-rows at once.  R = 128, 256: chunk ^ ((k & 3) << 2) puts the four into four different
+//     64-byte bank groups; R = 64, 192: two k-rows already lie apart, chunk ^ (((k >> 1) & 1) << 2) parts the others;
 //     R = 32: the four k-rows are one 256-byte line as they are.
 // Small tiles are for products with few of them, where the rate at which a CU is fed does not matter yet: 2048 x 768 x 768 with
 // 64 x 64 tiles 7.5 us (128 x 128: 11.6), 1024 x 768 x 3072 14.4 us (34), 512 x 768 x 3072 with 32 x 64 tiles 10.6 us (33).
 // From about two 128 x 128 tiles per CU on the feed from the L2 binds (8192 x 3072 x 3072: 106 us, its loads alone 103 us,
-// everything but the loads 82 us; 39 bytes per clock and CU), and only the larger tile helps.
+// everything but the loads 82 us; 39 bytes per clock and CU), and only the larger tile helps: 256 x 256 (8 waves of 128 x 64, the whole register
+// file and 128 KB of LDS) needs half the bytes per flop of 128 x 128, 256 x 128 and 128 x 192 three quarters.  8192^3: 1339, 1236 and
+// 1169 TFLOP/s (128 x 192 at 90 % of its rounds), 128 x 128 1132; at the first of these the chip's clock is what binds.
 // Rows beyond the matrix edge are clamped to the last row (their products are never stored).  A k-tile that reaches beyond
 // the contraction range reads zeros there: rows of an m-major operand beyond K lie behind the end of the operand, where a
 // buffer load returns zero; a k-major operand has to end on a whole k-tile or be zero up to there (the launcher checks).
@@ -37,14 +40,14 @@ typedef __attribute__((address_space(3))) void* lds_void_ptr;
 template <bool KMAJ, int BK, int R, int NW>
 struct DmaTile {
   static_assert(BK == 32 || BK == 64, "k-tile of 32 or 64");
-  static_assert(R == 32 || R == 64 || R == 128 || R == 256, "32 to 256 rows");
+  static_assert(R == 32 || R == 64 || R == 128 || R == 192 || R == 256, "32 to 256 rows");
   static constexpr int BYTES = R * BK * 2;
   static constexpr int NI = BYTES / 1024 / NW;         // load instructions per wave and k-tile
   static_assert(NI >= 1 && NI * NW * 1024 == BYTES, "the tile must split evenly over the waves");
   static constexpr int CPR = BK / 8;                   // k-major: chunks per row
   static constexpr int RPI = 64 / CPR;                 // k-major: rows per instruction
-  static constexpr int KPI = 64 / (R / 8);             // m-major: k-rows per instruction
-  static __device__ __forceinline__ int mswz(int k) { return R >= 128 ? ((k & 3) << 2) : (R == 64 ? (((k >> 1) & 1) << 2) : 0); }
+  static constexpr int RPF = KMAJ ? 1 : 2;             // LDS reads per fragment
+  static __device__ __forceinline__ int mswz(int k) { return R == 128 || R == 256 ? ((k & 3) << 2) : (R == 64 || R == 192 ? (((k >> 1) & 1) << 2) : 0); }
   struct Cursor {
     __amdgpu_buffer_rsrc_t rsrc;
     unsigned off[NI];
@@ -66,7 +69,7 @@ struct DmaTile {
         const int r = min(row0 + row, rext - 1);
         cu.off[i] = (unsigned)(((int64_t)r * ld + chunk * 8) * 2);
       } else {
-        const int k = j * KPI + lane / (R / 8), slot = lane % (R / 8);
+        const int id = j * 64 + lane, k = id / (R / 8), slot = id % (R / 8);
         const int chunk = slot ^ mswz(k);
         const int n = min(row0 + chunk * 8, ((rext - 1) >> 3) << 3);
         cu.off[i] = (unsigned)(((int64_t)k * ld + n) * 2);
@@ -99,7 +102,7 @@ struct DmaTile {
 };
 
 // The tile shape and pipeline of one configuration.
-template <int TI_, int TJ_, int WGM_, int WGN_, int KW_, int BK_, int S_, int OCC_>
+template <int TI_, int TJ_, int WGM_, int WGN_, int KW_, int BK_, int S_, int OCC_, bool AHEAD_>
 struct DmaCfg {
   static constexpr int TI = TI_, TJ = TJ_, WGM = WGM_, WGN = WGN_, KW = KW_, BK = BK_, S = S_, OCC = OCC_;   // OCC: blocks per CU
   static constexpr int NS = WGM * WGN, NW = NS * KW, NT = 64 * NW, BM = 32 * TI * WGM, BN = 32 * TJ * WGN;
@@ -110,6 +113,8 @@ struct DmaCfg {
   static constexpr size_t PIPE = (size_t)S * STAGE;
   static constexpr size_t LDS = PIPE > EPI_BYTES ? (PIPE > RED ? PIPE : RED) : (EPI_BYTES > RED ? EPI_BYTES : RED);
   static constexpr int WPE = OCC * NW / 4;                              // waves per SIMD
+  static constexpr bool AHEAD = AHEAD_;                                 // fragments read a slice ahead (see ahead_step)
+  static_assert(!AHEAD || KW == 1, "all slices of a k-tile in every wave");
   static_assert(S >= 2 && S <= 16, "two to sixteen stages");
   static_assert(BK / 16 % KW == 0, "the k-slices must split evenly over the wave groups");
   static_assert(LDS * OCC <= 160 * 1024, "stages do not fit the LDS of a CU");
@@ -126,6 +131,11 @@ template <int PER, int MAX>
 __device__ __forceinline__ void wait_tiles(int ahead) {
   if constexpr (MAX == 0) wait_loads<0>();
   else { if (ahead >= MAX) wait_loads<MAX * PER>(); else wait_tiles<PER, MAX - 1>(ahead); }
+}
+
+__device__ __forceinline__ bf16x8 ones_frag() {
+  const bf16 one = (bf16)1.0f;
+  return bf16x8{one, one, one, one, one, one, one, one};
 }
 
 // One k-step: tile `cur` is read (after the wave's share of it has landed and every wave has arrived), the tile
@@ -161,7 +171,69 @@ __device__ __forceinline__ void dma_step(typename TA::Cursor& ca, typename TB::C
       for (int j = 0; j < C::TJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[ks][i], fb[ks][j], acc[i][j], 0, 0, 0);
 }
 
-template <class C, bool AK, bool BKM, int EPIS>
+// fragments of 16-deep slice ks of the k-tile at st
+template <class C, class TA, class TB, bool RS>
+__device__ __forceinline__ void read_slice(bf16x8 (&fa)[C::TI], bf16x8 (&fb)[C::TJ], bf16x8& fr, const unsigned char* __restrict__ st, int ks,
+                                           int wm, int wn, int lane) {
+  const bf16* sA = (const bf16*)st;
+  const bf16* sB = (const bf16*)(st + TA::BYTES);
+#pragma unroll
+  for (int i = 0; i < C::TI; ++i) fa[i] = TA::frag(sA, (wm * C::TI + i) * 32, ks, lane);
+#pragma unroll
+  for (int j = 0; j < C::TJ; ++j) fb[j] = TB::frag(sB, (wn * C::TJ + j) * 32, ks, lane);
+  if (RS) fr = TA::frag(sA, (wm * C::TI + wn % C::TI) * 32, ks, lane);
+}
+
+// One k-step of the pipeline that reads fragments one 16-deep slice ahead.  On entry fragment set 0 holds slice 0 of tile `cur`.  The
+// barrier sits before the last slice: by then every wave has read all of `cur`, which the tile S steps ahead is requested into, and the
+// wave's share of `nxt` has landed; the last slice's MFMAs cover the meeting and the first fragment reads of `nxt`.  The issue order
+// per MFMA is prescribed.  RS: fr / accr as described at dma_tile.
+template <class C, class TA, class TB, bool RS>
+__device__ __forceinline__ void ahead_step(typename TA::Cursor& ca, typename TB::Cursor& cb, unsigned char* __restrict__ cur,
+                                           const unsigned char* __restrict__ nxt, bf16x8 (&fa)[2][C::TI], bf16x8 (&fb)[2][C::TJ], bf16x8 (&fr)[2],
+                                           f32x16 (&acc)[C::TI][C::TJ], f32x16& accr, int wm, int wn, int lane, int wave) {
+  constexpr int KS = C::BK / 16, TI = C::TI, TJ = C::TJ, NM = TI * TJ, NL = TA::NI + TB::NI;
+  constexpr int NF = TI + TJ, FPM = (NF + NM - 1) / NM;      // fragments per slice, and per MFMA
+  static_assert(KS % 2 == 0, "fragment sets alternate");
+#pragma unroll
+  for (int s = 0; s < KS; ++s) {
+    const int fc = s & 1, fn = fc ^ 1;
+    const bool last = s == KS - 1;
+    if (last) {
+      asm volatile("" ::: "memory");
+      wait_loads<(C::S - 2) * NL>();
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+    }
+    read_slice<C, TA, TB, RS>(fa[fn], fb[fn], fr[fn], last ? nxt : (const unsigned char*)cur, last ? 0 : s + 1, wm, wn, lane);
+    if (last) {
+      TA::issue(ca, cur, wave);
+      TB::issue(cb, cur + TA::BYTES, wave);
+    }
+#pragma unroll
+    for (int i = 0; i < TI; ++i)
+#pragma unroll
+      for (int j = 0; j < TJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[fc][i], fb[fc][j], acc[i][j], 0, 0, 0);
+    if (RS) {
+      accr = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[fc], ones_frag(), accr, 0, 0, 0);
+    } else {
+#pragma unroll
+      for (int q = 0; q < NM; ++q) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                       // MFMA
+#pragma unroll
+        for (int f = q * FPM; f < (q + 1) * FPM && f < NF; ++f) {                                // fragment reads of the next slice
+          if (f < TI) __builtin_amdgcn_sched_group_barrier(0x100, TA::RPF, 0);
+          else __builtin_amdgcn_sched_group_barrier(0x100, TB::RPF, 0);
+        }
+        if (last) __builtin_amdgcn_sched_group_barrier(0x020, (NL + NM - 1) / NM, 0);            // loads
+      }
+    }
+  }
+}
+
+// ROWSUM: where p.rowsum is set, the block also adds up the rows of A (a bias gradient beside the weight gradient of the same
+// operand): wave column wn takes the wn-th 32 rows of its waves' TI x 32 with one more MFMA per slice, against a column of ones.
+template <class C, bool AK, bool BKM, int EPIS, bool ROWSUM = false>
 __device__ __forceinline__ void dma_tile(const GemmDev& p, int m0, int n0, int split, unsigned char* lds_raw) {
   constexpr int TI = C::TI, TJ = C::TJ, S = C::S;
   typedef DmaTile<AK, C::BK, C::BM, C::NW> TA;
@@ -185,22 +257,59 @@ __device__ __forceinline__ void dma_tile(const GemmDev& p, int m0, int n0, int s
   TA::init(ca, (const bf16*)p.A, p.lda, m0, p.M, kbeg, p.K, lane, wave);
   TB::init(cb, (const bf16*)p.B, p.ldb, n0, p.N, kbeg, p.K, lane, wave);
 
-  // tiles 0 .. S-2 into stages 0 .. S-2
+  f32x16 accr;      // ROWSUM only
+  if constexpr (C::AHEAD) {
+    const unsigned past = 0x80000000u;      // as in wide_tile: the requests of the last steps go beyond the operand
+    bf16x8 fa[2][TI], fb[2][TJ], fr[2];
+    auto flow = [&](auto rs) __attribute__((always_inline)) {
+      constexpr bool RS = decltype(rs)::value;
+      if (RS) {
 #pragma unroll
-  for (int s = 0; s < S - 1; ++s)
-    if (s < nk) {
-      TA::issue(ca, lds_raw + s * C::STAGE, wave);
-      TB::issue(cb, lds_raw + s * C::STAGE + TA::BYTES, wave);
-    }
-  // Step t reads stage t % S and requests tile t + S - 1 into stage (t - 1) % S.  At its start the wave has requested
-  // tiles up to min(t + S - 2, nk - 1): the counter is waited down to the loads of the tiles behind tile t.
-  for (int t0 = 0; t0 < nk; t0 += S) {
+        for (int r = 0; r < 16; ++r) accr[r] = 0.0f;
+      }
 #pragma unroll
-    for (int u = 0; u < S; ++u) {
-      const int t = t0 + u;
-      if (t < nk)
-        dma_step<C, TA, TB>(ca, cb, lds_raw + ((u + S - 1) % S) * C::STAGE, lds_raw + u * C::STAGE, acc, min(S - 2, nk - 1 - t), t + S - 1 < nk, wm,
-                            wn, kg, lane, wave);
+      for (int s = 0; s < S; ++s) {
+        if (s >= nk) ca.soff = cb.soff = past;
+        TA::issue(ca, lds_raw + s * C::STAGE, wave);
+        TB::issue(cb, lds_raw + s * C::STAGE + TA::BYTES, wave);
+      }
+      asm volatile("" ::: "memory");
+      wait_loads<(S - 1) * (TA::NI + TB::NI)>();
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      read_slice<C, TA, TB, RS>(fa[0], fb[0], fr[0], lds_raw, 0, wm, wn, lane);
+      for (int t0 = 0; t0 < nk; t0 += S) {
+#pragma unroll
+        for (int u = 0; u < S; ++u) {
+          const int t = t0 + u;
+          if (t < nk) {
+            if (t + S >= nk) ca.soff = cb.soff = past;
+            ahead_step<C, TA, TB, RS>(ca, cb, lds_raw + u * C::STAGE, lds_raw + ((u + 1) % S) * C::STAGE, fa, fb, fr, acc, accr, wm, wn, lane, wave);
+          }
+        }
+      }
+    };
+    if constexpr (ROWSUM) { if (p.rowsum) flow(std::true_type{}); else flow(std::false_type{}); }
+    else flow(std::false_type{});
+  } else {
+    static_assert(!ROWSUM, "row sums go with fragments read ahead");
+    // tiles 0 .. S-2 into stages 0 .. S-2
+#pragma unroll
+    for (int s = 0; s < S - 1; ++s)
+      if (s < nk) {
+        TA::issue(ca, lds_raw + s * C::STAGE, wave);
+        TB::issue(cb, lds_raw + s * C::STAGE + TA::BYTES, wave);
+      }
+    // Step t reads stage t % S and requests tile t + S - 1 into stage (t - 1) % S.  At its start the wave has requested
+    // tiles up to min(t + S - 2, nk - 1): the counter is waited down to the loads of the tiles behind tile t.
+    for (int t0 = 0; t0 < nk; t0 += S) {
+#pragma unroll
+      for (int u = 0; u < S; ++u) {
+        const int t = t0 + u;
+        if (t < nk)
+          dma_step<C, TA, TB>(ca, cb, lds_raw + ((u + S - 1) % S) * C::STAGE, lds_raw + u * C::STAGE, acc, min(S - 2, nk - 1 - t), t + S - 1 < nk,
+                              wm, wn, kg, lane, wave);
+      }
     }
   }
   asm volatile("" ::: "memory");
@@ -238,6 +347,15 @@ __device__ __forceinline__ void dma_tile(const GemmDev& p, int m0, int n0, int s
   }
 
   const int rbase = m0 + wm * TI * 32, cbase = n0 + wn * TJ * 32;
+  if constexpr (ROWSUM) {
+    if (p.rowsum && wn < TI && (lane & 31) == 0) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int row = rbase + wn * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+        if (row < p.M) p.rowsum[row] = (p.beta != 0.0f) ? p.beta * p.rowsum[row] + accr[r] : accr[r];
+      }
+    }
+  }
   float* stage = (float*)lds_raw + ws * C::EPI_FLOATS;
   float2* const tab = (float2*)((float*)lds_raw + C::NS * C::EPI_FLOATS);
   if (p.gelu_tab && (((EPIS >> EPI_ACT_GELU) | (EPIS >> EPI_ACT_DGELU)) & 1)) {
@@ -291,7 +409,7 @@ void gemm_bf16_dma_group(GemmGroupDev g) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char lds_raw[];
   int tm, tn;
   const GemmDev p = group_problem<C::BM, C::BN>(g, tm, tn);
-  dma_tile<C, false, false, 1 << EPI_F32>(p, tm * C::BM, tn * C::BN, 0, lds_raw);
+  dma_tile<C, false, false, 1 << EPI_F32, true>(p, tm * C::BM, tn * C::BN, 0, lds_raw);
 }
 template <class C>
 hipError_t launch_dma_group(const GemmGroupDev& g, hipStream_t s) {
@@ -307,11 +425,15 @@ hipError_t launch_dma_group(const GemmGroupDev& g, hipStream_t s) {
 }
 
 // the configurations of gemm_bf16_dma that are built (numbers: kTileCfg in gemm.hip)
-typedef DmaCfg<1, 1, 1, 2, 2, 64, 4, 3> Dma32x64;       // TI TJ WGM WGN KW BK S OCC
-typedef DmaCfg<1, 1, 2, 2, 1, 64, 3, 3> Dma64x64;
-typedef DmaCfg<1, 2, 2, 2, 1, 64, 3, 2> Dma64x128;
-typedef DmaCfg<2, 1, 2, 2, 1, 64, 3, 2> Dma128x64;
-typedef DmaCfg<2, 2, 2, 2, 1, 64, 2, 2> Dma128x128;
-typedef DmaCfg<2, 2, 4, 2, 1, 64, 3, 1> Dma256x128;
+typedef DmaCfg<1, 1, 1, 2, 2, 64, 4, 3, false> Dma32x64;       // TI TJ WGM WGN KW BK S OCC AHEAD
+typedef DmaCfg<1, 1, 2, 2, 1, 64, 3, 3, false> Dma64x64;
+typedef DmaCfg<1, 1, 2, 2, 1, 64, 3, 3, true> Dma64x64Group;
+typedef DmaCfg<1, 2, 2, 2, 1, 64, 3, 2, true> Dma64x128;
+typedef DmaCfg<2, 1, 2, 2, 1, 64, 3, 2, true> Dma128x64;
+typedef DmaCfg<2, 2, 2, 2, 1, 64, 2, 2, true> Dma128x128;
+typedef DmaCfg<2, 3, 2, 2, 1, 64, 2, 2, true> Dma128x192;
+typedef DmaCfg<3, 2, 2, 2, 1, 64, 2, 2, true> Dma192x128;
+typedef DmaCfg<2, 2, 4, 2, 1, 64, 3, 1, true> Dma256x128;
+typedef DmaCfg<4, 2, 2, 4, 1, 64, 2, 1, true> Dma256x256;
 
 }  // namespace

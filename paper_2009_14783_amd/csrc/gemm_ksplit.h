@@ -154,14 +154,15 @@ hipError_t launch_ks_one(const GemmDev& p, int splits, hipStream_t s) {
   return hipSuccess;
 }
 typedef KsCfg<1, 1, 4, 64, 3, 1> Ks32x32;                // TI TJ NW BK S OCC
-typedef KsCfg<1, 1, 4, 64, 2, 2> Ks32x32x2;
 
 // every configuration but 0 (numbers: kTileCfg in gemm.hip), one operand layout per translation unit
 template <bool AK, bool BKM>
 hipError_t launch_layout(int cfg, const GemmDev& p, int splits, hipStream_t s) {
   switch (cfg) {
     case 2: return launch_ks_one<Ks32x32, AK, BKM>(p, splits, s);
-    case 3: return launch_ks_one<Ks32x32x2, AK, BKM>(p, splits, s);
+    case 1: return launch_dma_one<Dma256x256, AK, BKM>(p, splits, s);
+    case 3: return launch_dma_one<Dma128x192, AK, BKM>(p, splits, s);
+    case 6: return launch_dma_one<Dma192x128, AK, BKM>(p, splits, s);
     case 4: return launch_dma_one<Dma32x64, AK, BKM>(p, splits, s);
     case 7: return launch_dma_one<Dma64x128, AK, BKM>(p, splits, s);
     case 8: return launch_dma_one<Dma128x64, AK, BKM>(p, splits, s);

@@ -421,8 +421,6 @@ void gemm_bf16_wide(GemmDev p) {
 // Several products in one launch: block v works on tile v - first_tile[i] of problem i (the problems' tiles are numbered one
 // problem after the other; an XCD gets a contiguous range of them).  No split-K: every tile runs over the whole
 // contraction.  Returns the problem as arguments of the tile function and the tile's position.
-alignas(16) static __device__ const bf16 kOnes[8] =      // read 16 bytes at a time
-    {(bf16)1.0f, (bf16)1.0f, (bf16)1.0f, (bf16)1.0f, (bf16)1.0f, (bf16)1.0f, (bf16)1.0f, (bf16)1.0f};
 template <int BM, int BN>
 __device__ __forceinline__ GemmDev group_problem(const GemmGroupDev& g, int& tm, int& tn) {
   int v = blockIdx.x;
@@ -433,10 +431,11 @@ __device__ __forceinline__ GemmDev group_problem(const GemmGroupDev& g, int& tm,
   const GroupProb& q = g.prob[lo];
   GemmDev p{};
   p.A = q.A; p.C = q.C; p.lda = q.lda; p.ldc = q.ldc; p.M = q.M; p.N = q.N; p.K = q.K; p.k_per_split = q.K;
-  p.B = q.B ? q.B : (const void*)kOnes; p.ldb = q.B ? q.ldb : 0;      // row stride 0: every row of the column of ones is the same
+  p.B = q.B; p.ldb = q.ldb;
   p.c_f32 = 1; p.beta = g.beta;
   const int nbx = (p.N + BN - 1) / BN, nby = (p.M + BM - 1) / BM;
   tile_of_block<(BM >= 256) ? 4 : 8>(v - g.first_tile[lo], nbx, nby, tm, tn);
+  p.rowsum = tn == 0 ? q.rowsum : nullptr;
   return p;
 }
 template <bool AK, bool BKM, int TI, int TJ, int WGM, int WGN, int BK, int NSETS, int OCC>
@@ -462,9 +461,7 @@ hipError_t launch_wide_layout(int cfg, const GemmDev& p, int splits, hipStream_t
   return launch_wide_one<AK, BKM, TI, TJ, WGM, WGN, BK, NSETS, OCC>(                                     \
       p, dim3((p.N + 32 * TJ * WGN - 1) / (32 * TJ * WGN), (p.M + 32 * TI * WGM - 1) / (32 * TI * WGM), splits), s)
   switch (cfg) {
-    case 1: HS_WIDE(4, 4, 2, 2, 64, 1, 1);
     case 5: HS_WIDE(2, 2, 2, 2, 64, 2, 2);
-    case 6: HS_WIDE(4, 2, 2, 2, 64, 2, 1);
     default: return hipErrorInvalidValue;
   }
 #undef HS_WIDE

@@ -45,8 +45,8 @@ def layer_products(rows, H, F, tag=""):
 LARGE = layer_products(16384, 1024, 4096)[0] + layer_products(8192, 1024, 4096, " half")[0] + layer_products(16384, 1024, 4096)[1]
 # A and B k-major; A k-major, B n-major; A and B m-major
 CUBES = [("cube kk", 1, 1, 8192, 8192, 8192, 0, 0), ("cube kn", 1, 0, 8192, 8192, 8192, 0, 0), ("cube nn", 0, 0, 8192, 8192, 8192, 0, 1)]
-NAMES = {-1: "auto", 0: "0: 128x128x32, 3/CU", 1: "1: 256x256x64", 2: "2: 32x32, waves split K", 3: "3: 32x32, waves split K, 2/CU",
-         4: "4: LDS-direct 32x64x64, 3/CU", 5: "5: 128x128x64, 2/CU", 6: "6: 256x128x64", 7: "7: LDS-direct 64x128x64, 2/CU",
+NAMES = {-1: "auto", 0: "0: 128x128x32, 3/CU", 1: "1: LDS-direct 256x256x64", 2: "2: 32x32, waves split K", 3: "3: LDS-direct 128x192x64, 2/CU",
+         4: "4: LDS-direct 32x64x64, 3/CU", 5: "5: 128x128x64, 2/CU", 6: "6: LDS-direct 192x128x64, 2/CU", 7: "7: LDS-direct 64x128x64, 2/CU",
          8: "8: LDS-direct 128x64x64, 2/CU", 9: "9: LDS-direct 128x128x64, 2/CU", 10: "10: LDS-direct 256x128x64", 11: "11: LDS-direct 64x64x64, 3/CU"}
 
 

@@ -208,6 +208,38 @@ def test_gemm_bf16_few_tiles(hs, M, N, K, layout):
             assert rel(host(dC), R.astype(np.float64) + prod) < 2e-6, scratch is None
 
 
+@pytest.mark.parametrize("variant", [1, 3, 6, 7, 9, 10])
+@pytest.mark.parametrize("M,N,K", [(256, 256, 256), (257, 264, 320), (384, 520, 384), (511, 576, 448), (769, 392, 1032)])
+@pytest.mark.parametrize("layout", LAYOUTS)
+def test_gemm_bf16_fragments_read_ahead(hs, variant, M, N, K, layout):
+    """The tilings that read fragments ahead, at and around the edges of their tiles (64 to 256 rows and columns), with contractions of an even and an
+    odd number of k-tiles against rings of two and three stages, and one that ends inside a k-tile where the layout takes it there.
+    fp32 result where the layout has one (bound as in test_gemm_bf16_short_and_long_contractions), else residual and one rounding to bf16."""
+    ak, bk = layout
+    gen = torch.Generator(device="cuda").manual_seed(K + M)
+    ld = lambda n: (n + 7) // 8 * 8
+    A = torch.randn(*((M, K) if ak else (K, ld(M))), generator=gen, device="cuda").bfloat16()
+    B = torch.randn(*((N, K) if bk else (K, N)), generator=gen, device="cuda").bfloat16()
+    R = torch.randn(M, N, generator=gen, device="cuda").bfloat16()
+    a, b = (A if ak else A[:, :M].t()).double(), (B.t() if bk else B).double()
+    want, size = a @ b, a.abs() @ b.abs()
+    hs.hs_tune_gemm_variant(variant)
+    try:
+        if ak:
+            C = torch.full((M, N), 7.0, dtype=torch.bfloat16, device="cuda")
+            hs.hs_op_gemm(1, ak, bk, M, N, K, A, A.shape[1], B, B.shape[1], C, N, epi=1, aux=R, ldaux=N)
+            want = want + R.double()
+            bound = K * 2.0 ** -24 * size + 2.0 ** -8 * want.abs()
+        else:
+            C = torch.full((M, N), 7.0, device="cuda")
+            hs.hs_op_gemm(1, ak, bk, M, N, K, A, A.shape[1], B, B.shape[1], C, N, c_f32=1)
+            bound = K * 2.0 ** -24 * size
+        torch.cuda.synchronize()
+        assert bool(((C.double() - want).abs() <= bound).all())
+    finally:
+        hs.hs_tune_gemm_variant(-1)
+
+
 @pytest.mark.parametrize("M,N,K", [(2056, 2120, 64), (2056, 2120, 192), (3080, 776, 1088), (1032, 4104, 1024), (2056, 1032, 8192), (520, 3080, 8256), (264, 776, 16448)])
 @pytest.mark.parametrize("layout", LAYOUTS)
 def test_gemm_bf16_short_and_long_contractions(hs, M, N, K, layout):

@@ -456,6 +456,23 @@ def test_grouped_gradients_on_ragged_tiles(W, B, L, compute):
 
 
 @pytest.mark.gpu
+def test_grouped_gradients_on_ragged_wide_tiles(W):
+    """Widths of 448 and 8256 and 2016 rows, three layers handed over together: the grouped launch takes its 256 x 256 tiles, which end inside
+    both widths, and adds the bias gradients in them."""
+    model = dict(n_layers=3, hidden=448, n_heads=7, ffn=8256, vocab=200, max_pos=96, ln_eps=1e-12)
+    ocfg = O.ModelCfg(**model)
+    theta = synth.init_params(O.param_layout(ocfg), 12)
+    rng = synth.rng_for(13)
+    mb = synth.make_micro_batch(rng, [96] + [int(x) for x in rng.integers(1, 97, 20)], 96, model["vocab"], "uniform")
+    worker = W(model, "bf16", theta)
+    loss, g = gpu_micro_grad(worker, mb)
+    ol, og = oracle_micro_grad(ocfg, theta, mb, np.float32)
+    assert abs(loss - ol) / abs(ol) < TOL["bf16"]
+    compare_flat(O.param_layout(ocfg), g, og, TOL["bf16"], "grad")
+    worker.close()
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("compute", ["fp32", "bf16"])
 @pytest.mark.parametrize("layers", [1, 2, 9])
 def test_backward_gives_the_same_bits_in_every_workspace_it_accepts(W, layers, compute):
