@@ -1,12 +1,31 @@
-// Softmax attention with separate query and key/value sequences (head dimension 64), forward and backward:
-// the decoder's causal self-attention and its attention over the encoder output.  Queries, keys and values
+// Softmax attention with separate query and key/value sequences (head dimension 64), forward and backward: self-attention over
+// sequences of any length (backward: more than 128 positions), the decoder's causal self-attention and its attention over the
+// encoder output.  Queries, keys and values
 // are row ranges of token-major matrices with their own row strides (head h = columns h*64 .. h*64+63);
 // key j of sequence b takes part iff j < klens[b] and, when causal, j <= query index; queries at or beyond
-// qlens[b] get zero gradients.  No dropout of the probabilities (the translation model drops sub-layer
+// qlens[b] get zero gradients.  Dropout of the probabilities: self-attention only (the translation model drops sub-layer
 // outputs only).
 //
-// bf16: MFMA kernels of the same shape as the self-attention ones (a wave owns 32 rows in registers and
-// streams the other side through LDS in blocks of 64 rows; see attention_mfma.hip).  fp32: attention_f32.hip.
+// bf16: the MFMA kernels below.  fp32: attention_f32.hip.
+//
+// A wave OWNS 32 rows (queries, or keys in the dK/dV kernel) whose vectors stay in registers as MFMA B operands, and the block STREAMS
+// the other side through LDS in blocks of 64 rows.  Score tiles are computed transposed,
+// tile[streamed row][owned row], so that each lane holds ONE owned row (lane % 32) and 16 streamed
+// rows: reductions over the streamed index are then in-lane plus one exchange between the two
+// half-waves.  The second product needs the score tile as a B operand and the streamed block
+// transposed as the A operand; the transposed fragment comes from the LDS transpose read, with
+// the 16 contraction slots ordered exactly as the result registers of the score tile are
+// (register r of lane l is streamed row 8*(r/4) + 4*(l/32) + r%4), so no data moves between lanes.
+//
+// What bounds these kernels at the sizes of the encoder is the vector ALU and the latency of a block's chain of load, product, softmax
+// and product.  So the next 64 rows are loaded straight into the other half of LDS while the current ones are worked on (one barrier per
+// block, no register holds a streamed byte); scores start from -8 lse and their gradients from the row term, which the matrix cores
+// then add for nothing, so that a gradient score costs a multiplication, an exponential and a multiplication; masks are applied only in
+// the tiles that an end or the diagonal cuts; the forward pass takes 64 keys per softmax step and rescales its sums only when a
+// maximum moved.  The query blocks of one head run on one XCD, whose L2 then holds that head's keys and values.
+// 32 sequences of 512 positions, 16 heads, in the BERT-large step, against kernels that staged through registers between two barriers, masked
+// every score and took 32 keys per softmax step: forward 78.7 -> 56.4 us (610 TFLOP/s), dq 132.5 -> 72.9, dk and dv 179.6 -> 90.8 (755).  BERT-base
+// with micro-batches of 8 + 24 + 56 x 256: 25.4 -> 19.8, 38.9 -> 25.9 and 49.0 -> 24.9 us on average.
 #include "attention_tiles.h"
 
 namespace {
@@ -25,244 +44,391 @@ __device__ __forceinline__ int clamp_len(int n, int L) { return n < 1 ? 1 : (n >
 // ------------------------------------------------------------------------------------------
 // bf16 MFMA
 // ------------------------------------------------------------------------------------------
-template <bool CAUSAL>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void gen_fwd_mfma(View a, bf16* __restrict__ out, float* __restrict__ lse) {
-  __shared__ __attribute__((aligned(16))) bf16 Ks[64 * LDT];
-  __shared__ __attribute__((aligned(16))) bf16 Vs[64 * LDT];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int b = blockIdx.z, h = blockIdx.y;
-  const int H = a.A * DH;
-  const int klen = clamp_len(a.klens[b], a.Lk);
-  const bf16* qb_ = (const bf16*)a.q + (int64_t)b * a.Lq * a.ldq + h * DH;
-  const bf16* kb_ = (const bf16*)a.k + (int64_t)b * a.Lk * a.ldkv + h * DH;
-  const bf16* vb_ = (const bf16*)a.v + (int64_t)b * a.Lk * a.ldkv + h * DH;
-  const int q = blockIdx.x * 128 + wave * 32 + (lane & 31);
-  const int wave_qmax = blockIdx.x * 128 + wave * 32 + 31;
-  const int kend = CAUSAL ? min(klen, (int)blockIdx.x * 128 + 128) : klen;      // block-uniform
+constexpr int kTileBytes = 64 * DH * 2;                        // 64 streamed rows of one matrix
+constexpr int kStageBytes = 2 * kTileBytes;                    // of both streamed matrices
+static_assert(2 * kStageBytes >= 4 * 32 * LDT * (int)sizeof(bf16), "the stages hold the four waves' store areas");
 
-  bf16x8 qf[4];
-#pragma unroll
-  for (int ks = 0; ks < 4; ++ks) qf[ks] = frag_rows_global(qb_, a.ldq, q, a.Lq, ks, lane);
-  f32x16 o[2];
-#pragma unroll
-  for (int db = 0; db < 2; ++db)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) o[db][r] = 0.f;
-  float m2 = -1.0e30f, lsum = 0.f;
-
-  for (int k0 = 0; k0 < kend; k0 += 64) {
-    __syncthreads();
-    stage64(Ks, kb_, a.ldkv, k0, klen, tid);
-    stage64(Vs, vb_, a.ldkv, k0, klen, tid);
-    __syncthreads();
-#pragma unroll
-    for (int sub = 0; sub < 2; ++sub) {
-      const int kb = 32 * sub;
-      if (k0 + kb < kend && (!CAUSAL || k0 + kb <= wave_qmax)) {
-        f32x16 st;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) st[r] = 0.f;
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) st = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows(Ks, kb, ks, lane), qf[ks], st, 0, 0, 0);
-        float mloc = -1.0e30f;
-        bool okr[16];
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int key = k0 + kb + tile_row(r, lane);
-          okr[r] = key < klen && (!CAUSAL || key <= q);
-          st[r] = okr[r] ? st[r] * SCALE2 : -1.0e30f;
-          mloc = fmaxf(mloc, st[r]);
-        }
-        mloc = fmaxf(mloc, __shfl_xor(mloc, 32));
-        const float mn = fmaxf(m2, mloc);
-        const float alpha = fast_exp2(m2 - mn);
-        float ps = 0.f;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const float p = okr[r] ? fast_exp2(st[r] - mn) : 0.f;
-          st[r] = p;
-          ps += p;
-        }
-        lsum = lsum * alpha + ps;
-        m2 = mn;
-#pragma unroll
-        for (int db = 0; db < 2; ++db)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
-        const bf16x8 p0 = pack8(st, 0), p1 = pack8(st, 1);
-#pragma unroll
-        for (int db = 0; db < 2; ++db) {
-          o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_cols_t(Vs, kb, 0, 32 * db, lane), p0, o[db], 0, 0, 0);
-          o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_cols_t(Vs, kb, 1, 32 * db, lane), p1, o[db], 0, 0, 0);
-        }
-      }
-    }
-  }
-  lsum += __shfl_xor(lsum, 32);
-  if (q < a.Lq) {
-    store_owned_rows(out + ((int64_t)b * a.Lq + q) * H + h * DH, o, 1.0f / lsum, lane);
-    if (lane < 32) lse[((int64_t)b * a.A + h) * a.Lq + q] = (m2 + __log2f(lsum)) * LN2;
-  }
+// (sequence, head, block of 128 owned rows) of a thread block.  Blocks go round the XCDs one by one; each XCD gets a contiguous range of
+// the order in which the row blocks of a head are neighbours.
+__device__ __forceinline__ void block_place(int& b, int& h, int& row0) {
+  const int nx = gridDim.x, ny = gridDim.y, per_xcd = (nx * ny * (int)gridDim.z) >> 3;
+  int v = ((int)blockIdx.z * ny + blockIdx.y) * nx + blockIdx.x;
+  if (v < 8 * per_xcd) v = (v & 7) * per_xcd + (v >> 3);
+  row0 = (v % nx) * 128;
+  const int bh = v / nx;
+  h = bh % ny;
+  b = bh / ny;
 }
 
-// dq and dvec[q] = sum_d dO[q,d] O[q,d]
-template <bool CAUSAL>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void gen_bwd_dq_mfma(View a, const bf16* __restrict__ out, const float* __restrict__ lse,
-                                                       const bf16* __restrict__ d_out, bf16* __restrict__ dq, int64_t lddq,
-                                                       float* __restrict__ dvec) {
-  __shared__ __attribute__((aligned(16))) bf16 Ks[64 * LDT];
-  __shared__ __attribute__((aligned(16))) bf16 Vs[64 * LDT];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int b = blockIdx.z, h = blockIdx.y;
-  const int H = a.A * DH;
-  const int klen = clamp_len(a.klens[b], a.Lk), qlen = clamp_len(a.qlens[b], a.Lq);
-  const bf16* qb_ = (const bf16*)a.q + (int64_t)b * a.Lq * a.ldq + h * DH;
-  const bf16* kb_ = (const bf16*)a.k + (int64_t)b * a.Lk * a.ldkv + h * DH;
-  const bf16* vb_ = (const bf16*)a.v + (int64_t)b * a.Lk * a.ldkv + h * DH;
-  const bf16* go = d_out + (int64_t)b * a.Lq * H + h * DH;
-  const bf16* oo = out + (int64_t)b * a.Lq * H + h * DH;
-  const int q = blockIdx.x * 128 + wave * 32 + (lane & 31);
-  const int wave_qmax = blockIdx.x * 128 + wave * 32 + 31;
-  const int kend = CAUSAL ? min(klen, (int)blockIdx.x * 128 + 128) : klen;
+// A streamed block in LDS: 64 rows of 128 bytes, unpadded because one load instruction fills 1 KiB in lane order.  Chunk c (16 bytes) of row r
+// sits at c ^ chunk_swizzle(r): 16 consecutive rows put the same chunk into 16 different places of 256 bytes (row fragments), and the two
+// 64-byte halves change sides every other row (a transposing read takes one half of each of four rows at once).
+__device__ __forceinline__ int chunk_swizzle(int row) { return (((row >> 1) & 1) << 2) | (((row >> 2) & 1) << 1) | ((row >> 3) & 1); }
 
-  // padded queries (q >= qlen) own all-zero fragments and therefore produce zero rows
-  bf16x8 qf[4], gf[4];
-  float dpart = 0.f;
+typedef __attribute__((address_space(3))) void* lds_void_ptr;
+
+// Loads of one streamed matrix: wave w fetches rows 16 w .. 16 w + 15 of a block, 8 rows per instruction.
+struct Stream {
+  const bf16* base;       // of row 16 w of the sequence
+  int64_t ld;
+  unsigned off[2];
+  __device__ __forceinline__ void init(const bf16* first, int64_t ld_, int lane, int wave) {
+    ld = ld_;
+    base = first + (int64_t)wave * 16 * ld;
 #pragma unroll
-  for (int ks = 0; ks < 4; ++ks) {
-    qf[ks] = frag_rows_global(qb_, a.ldq, q, qlen, ks, lane);
-    gf[ks] = frag_rows_global(go, H, q, qlen, ks, lane);
-    const bf16x8 of = frag_rows_global(oo, H, q, qlen, ks, lane);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) dpart = fmaf((float)gf[ks][e], (float)of[e], dpart);
+    for (int i = 0; i < 2; ++i) {
+      const int row = i * 8 + (lane >> 3);
+      off[i] = (unsigned)(((int64_t)row * ld + (((lane & 7) ^ chunk_swizzle(row)) << 3)) * 2);
+    }
   }
-  const float dq_row = dpart + __shfl_xor(dpart, 32);
-  const float lse2 = (q < qlen) ? lse[((int64_t)b * a.A + h) * a.Lq + q] * LOG2E : 0.f;
-  f32x16 acc[2];
+  // rows r0 .. r0 + 63 to dst; rows at or beyond limit lie behind the end of the buffer and read as zero
+  __device__ __forceinline__ void issue(int r0, int limit, unsigned char* __restrict__ dst, int wave) const {
+    const int n = min(16, limit - r0 - wave * 16);
+    const int bytes = n > 0 ? (int)(unsigned)(((n - 1) * ld + DH) * 2) : 0;
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)(base + (int64_t)r0 * ld), 0, bytes, 0x00020000);
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void_ptr)(dst + (wave * 2 + i) * 1024), 16, (int)off[i], 0, 0, 0);
+  }
+};
+
+// every load of this wave has landed, every LDS read of it is done, and so it is with the other waves of the block
+__device__ __forceinline__ void stage_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0x70);
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+// frag_rows and frag_cols_t of the swizzled layout (rbase a multiple of 32, c0 of 32)
+__device__ __forceinline__ bf16x8 srows(const unsigned char* __restrict__ tile, int rbase, int ks, int lane) {
+  return *(const bf16x8*)(tile + (rbase + (lane & 31)) * 128 + (((ks * 2 + (lane >> 5)) ^ chunk_swizzle(lane & 15)) << 4));
+}
+__device__ __forceinline__ bf16x8 scols_t(const unsigned char* __restrict__ tile, int rbase, int step, int c0, int lane) {
+  const int r = 4 * (lane >> 5) + ((lane & 15) >> 2), col = c0 + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+  const unsigned char* const row = tile + (rbase + 16 * step + r) * 128 + (col & 7) * 2;
+  typedef s16x4 __attribute__((address_space(3))) * lds_v4;
+  union { struct { s16x4 lo, hi; } p; bf16x8 v; } u;
+  u.p.lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4)(row + (((col >> 3) ^ chunk_swizzle(r)) << 4)));
+  u.p.hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4)(row + 8 * 128 + (((col >> 3) ^ chunk_swizzle(r + 8)) << 4)));
+  return u.v;
+}
+
+// rows row0 + 0..31 of the wave to dst (the matrix row of sequence row 0): whole rows through the wave's LDS area where 16-byte stores may be used
+__device__ __forceinline__ void store_wave_rows(bf16* __restrict__ dst, int64_t ld, int row0, int limit, const f32x16 (&acc)[2], float scale,
+                                                int lane, bf16* area, bool wide) {
+  if (wide) store_owned_rows_lds(dst, ld, row0, limit, acc, scale, lane, area);
+  else if (row0 + (lane & 31) < limit) store_owned_rows(dst + (int64_t)(row0 + (lane & 31)) * ld, acc, scale, lane);
+}
+
+__device__ __forceinline__ void clear(f32x16 (&acc)[2]) {
 #pragma unroll
   for (int db = 0; db < 2; ++db)
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[db][r] = 0.f;
+}
 
-  for (int k0 = 0; k0 < kend; k0 += 64) {
-    __syncthreads();
-    stage64(Ks, kb_, a.ldkv, k0, klen, tid);
-    stage64(Vs, vb_, a.ldkv, k0, klen, tid);
-    __syncthreads();
+template <bool CAUSAL, bool DROP>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DROP ? 3 : 4, DROP ? 3 : 4))) void stream_fwd_mfma(View a, bf16* __restrict__ out, float* __restrict__ lse,
+                                                                                                 bool wide, DropCfg drop, uint32_t site) {
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[2 * kStageBytes];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int b, h, row0;
+  block_place(b, h, row0);
+  const int H = a.A * DH;
+  const int klen = clamp_len(a.klens[b], a.Lk);
+  const int w0 = row0 + wave * 32, q = w0 + (lane & 31);
+  const int kend = CAUSAL ? min(klen, row0 + 128) : klen;      // block-uniform
+  Stream ks_, vs_;
+  ks_.init((const bf16*)a.k + (int64_t)b * a.Lk * a.ldkv + h * DH, a.ldkv, lane, wave);
+  vs_.init((const bf16*)a.v + (int64_t)b * a.Lk * a.ldkv + h * DH, a.ldkv, lane, wave);
+  auto request = [&](int k0, unsigned char* __restrict__ st) __attribute__((always_inline)) {
+    ks_.issue(k0, klen, st, wave);
+    vs_.issue(k0, klen, st + kTileBytes, wave);
+  };
+  request(0, lds);
+
+  bf16x8 qf[4];
 #pragma unroll
-    for (int sub = 0; sub < 2; ++sub) {
-      const int kb = 32 * sub;
-      if (k0 + kb < kend && (!CAUSAL || k0 + kb <= wave_qmax)) {
+  for (int ks = 0; ks < 4; ++ks) qf[ks] = frag_rows_global((const bf16*)a.q + (int64_t)b * a.Lq * a.ldq + h * DH, a.ldq, q, a.Lq, ks, lane);
+  f32x16 o[2];
+  clear(o);
+  float m2 = -1.0e30f, lsum = 0.f;
+
+  auto step = [&](int k0, const unsigned char* __restrict__ cur, unsigned char* __restrict__ nxt) __attribute__((always_inline)) {
+    stage_barrier();
+    if (k0 + 64 < kend) request(k0 + 64, nxt);
+    if (w0 >= a.Lq || (CAUSAL && k0 > w0 + 31)) return;
+    const unsigned char* const Ks = cur;
+    const unsigned char* const Vs = cur + kTileBytes;
+    const bool two = k0 + 32 < kend && (!CAUSAL || k0 + 32 <= w0 + 31);      // wave-uniform, as is the next
+    const bool edge = k0 + 64 > klen || (CAUSAL && k0 + 63 > w0);
+    f32x16 st[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) st[t][r] = 0.f;
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+      if (t == 0 || two) {
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) st[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(srows(Ks, 32 * t, ks, lane), qf[ks], st[t], 0, 0, 0);
+      }
+    auto seen = [&](int t, int r) __attribute__((always_inline)) {
+      const int key = k0 + 32 * t + tile_row(r, lane);
+      return key < klen && (!CAUSAL || key <= q);
+    };
+    if (edge) {
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) st[t][r] = seen(t, r) ? st[t][r] : -3.0e38f;
+    }
+    float mloc = st[0][0];
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) mloc = fmaxf(mloc, st[t][r]);
+    mloc = fmaxf(mloc, __shfl_xor(mloc, 32));
+    const float mn = fmaxf(m2, mloc * SCALE2);
+    if (__any(mn != m2)) {      // otherwise every lane's factor is 1
+      const float alpha = fast_exp2(m2 - mn);
+      lsum *= alpha;
+#pragma unroll
+      for (int db = 0; db < 2; ++db)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
+      m2 = mn;
+    }
+    float ps = 0.f;
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) st[t][r] = fast_exp2(fmaf(st[t][r], SCALE2, -m2));
+    if (edge) {
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) st[t][r] = seen(t, r) ? st[t][r] : 0.f;
+    }
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) ps += st[t][r];
+    lsum += ps;
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+      if (t == 0 || two) {
+        if (DROP) {      // the row sum keeps every key, the value sum only the survivors (scaled)
+          f32x16 f;
+          drop_tile_keys(drop, site, (((uint64_t)b * a.A + h) * a.Lq + q) * (uint64_t)a.Lk, k0 + 32 * t, lane, f);
+#pragma unroll
+          for (int r = 0; r < 16; ++r) st[t][r] *= f[r];
+        }
+        const bf16x8 p0 = pack8(st[t], 0), p1 = pack8(st[t], 1);
+#pragma unroll
+        for (int db = 0; db < 2; ++db) {
+          o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(scols_t(Vs, 32 * t, 0, 32 * db, lane), p0, o[db], 0, 0, 0);
+          o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(scols_t(Vs, 32 * t, 1, 32 * db, lane), p1, o[db], 0, 0, 0);
+        }
+      }
+  };
+  // (one copy of the step: a second one for the other stage made launches over short sequences 1 us longer, and took more registers)
+  for (int k0 = 0, at = 0; k0 < kend; k0 += 64, at = kStageBytes - at) step(k0, lds + at, lds + kStageBytes - at);
+  lsum += __shfl_xor(lsum, 32);
+  if (q < a.Lq && lane < 32) lse[((int64_t)b * a.A + h) * a.Lq + q] = (m2 + __log2f(lsum)) * LN2;
+  __syncthreads();      // every wave is done with the stages
+  store_wave_rows(out + (int64_t)b * a.Lq * H + h * DH, H, w0, a.Lq, o, 1.0f / lsum, lane, (bf16*)lds + wave * 32 * LDT, wide);
+}
+
+// dq and dvec[q] = sum_d dO[q,d] O[q,d]
+template <bool CAUSAL, bool DROP>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void stream_bwd_dq_mfma(View a, const bf16* __restrict__ out, const float* __restrict__ lse,
+                                                       const bf16* __restrict__ d_out, bf16* __restrict__ dq, int64_t lddq,
+                                                       float* __restrict__ dvec, bool wide, DropCfg drop, uint32_t site) {
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[2 * kStageBytes];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int b, h, row0;
+  block_place(b, h, row0);
+  const int H = a.A * DH;
+  const int klen = clamp_len(a.klens[b], a.Lk), qlen = clamp_len(a.qlens[b], a.Lq);
+  const int w0 = row0 + wave * 32, q = w0 + (lane & 31);
+  const int kend = row0 >= qlen ? 0 : (CAUSAL ? min(klen, row0 + 128) : klen);
+  Stream ks_, vs_;
+  ks_.init((const bf16*)a.k + (int64_t)b * a.Lk * a.ldkv + h * DH, a.ldkv, lane, wave);
+  vs_.init((const bf16*)a.v + (int64_t)b * a.Lk * a.ldkv + h * DH, a.ldkv, lane, wave);
+  auto request = [&](int k0, unsigned char* __restrict__ st) __attribute__((always_inline)) {
+    ks_.issue(k0, klen, st, wave);
+    vs_.issue(k0, klen, st + kTileBytes, wave);
+  };
+  if (kend > 0) request(0, lds);
+
+  // padded queries (q >= qlen) own all-zero fragments and therefore produce zero rows
+  bf16x8 qf[4], gf[4];
+  float drow = 0.f;
+  const bf16* const go = d_out + (int64_t)b * a.Lq * H + h * DH;
+  const bf16* const oo = out + (int64_t)b * a.Lq * H + h * DH;
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) {
+    qf[ks] = frag_rows_global((const bf16*)a.q + (int64_t)b * a.Lq * a.ldq + h * DH, a.ldq, q, qlen, ks, lane);
+    gf[ks] = frag_rows_global(go, H, q, qlen, ks, lane);
+    const bf16x8 of = frag_rows_global(oo, H, q, qlen, ks, lane);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) drow = fmaf((float)gf[ks][e], (float)of[e], drow);
+  }
+  drow += __shfl_xor(drow, 32);
+  const float st0 = (q < qlen) ? lse[((int64_t)b * a.A + h) * a.Lq + q] * -8.0f : 0.f;      // 8: the scores are not scaled yet
+  f32x16 acc[2];
+  clear(acc);
+
+  auto step = [&](int k0, const unsigned char* __restrict__ cur, unsigned char* __restrict__ nxt) __attribute__((always_inline)) {
+    stage_barrier();
+    if (k0 + 64 < kend) request(k0 + 64, nxt);
+    const unsigned char* const Ks = cur;
+    const unsigned char* const Vs = cur + kTileBytes;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const int kb = k0 + 32 * t;
+      if (kb < kend && w0 < qlen && (!CAUSAL || kb <= w0 + 31)) {      // wave-uniform
         f32x16 st, dp;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) { st[r] = 0.f; dp[r] = 0.f; }
+        for (int r = 0; r < 16; ++r) { st[r] = st0; dp[r] = DROP ? 0.f : -drow; }
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) {
-          st = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows(Ks, kb, ks, lane), qf[ks], st, 0, 0, 0);
-          dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows(Vs, kb, ks, lane), gf[ks], dp, 0, 0, 0);
+          st = __builtin_amdgcn_mfma_f32_32x32x16_bf16(srows(Ks, 32 * t, ks, lane), qf[ks], st, 0, 0, 0);
+          dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(srows(Vs, 32 * t, ks, lane), gf[ks], dp, 0, 0, 0);
+        }
+        if (DROP) {
+          f32x16 f;
+          drop_tile_keys(drop, site, (((uint64_t)b * a.A + h) * a.Lq + q) * (uint64_t)a.Lk, kb, lane, f);
+#pragma unroll
+          for (int r = 0; r < 16; ++r) dp[r] = fmaf(dp[r], f[r], -drow);
         }
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int key = k0 + kb + tile_row(r, lane);
-          const bool ok = key < klen && q < qlen && (!CAUSAL || key <= q);
-          const float p = ok ? fast_exp2(st[r] * SCALE2 - lse2) : 0.f;
-          st[r] = p * (dp[r] - dq_row);
+        for (int r = 0; r < 16; ++r) st[r] = fast_exp2(st[r] * SCALE2);
+        if (kb + 32 > klen || w0 + 32 > qlen || (CAUSAL && kb + 31 > w0)) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const int key = kb + tile_row(r, lane);
+            st[r] = (key < klen && q < qlen && (!CAUSAL || key <= q)) ? st[r] : 0.f;
+          }
         }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) st[r] *= dp[r];
         const bf16x8 s0 = pack8(st, 0), s1 = pack8(st, 1);
 #pragma unroll
         for (int db = 0; db < 2; ++db) {
-          acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_cols_t(Ks, kb, 0, 32 * db, lane), s0, acc[db], 0, 0, 0);
-          acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_cols_t(Ks, kb, 1, 32 * db, lane), s1, acc[db], 0, 0, 0);
+          acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(scols_t(Ks, 32 * t, 0, 32 * db, lane), s0, acc[db], 0, 0, 0);
+          acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(scols_t(Ks, 32 * t, 1, 32 * db, lane), s1, acc[db], 0, 0, 0);
         }
       }
     }
-  }
-  if (q < a.Lq) {
-    store_owned_rows(dq + ((int64_t)b * a.Lq + q) * lddq + h * DH, acc, 0.125f, lane);
-    if (lane < 32) dvec[((int64_t)b * a.A + h) * a.Lq + q] = dq_row;
-  }
+  };
+  for (int k0 = 0, at = 0; k0 < kend; k0 += 64, at = kStageBytes - at) step(k0, lds + at, lds + kStageBytes - at);
+  if (q < a.Lq && lane < 32) dvec[((int64_t)b * a.A + h) * a.Lq + q] = drow;
+  __syncthreads();      // every wave is done with the stages
+  store_wave_rows(dq + (int64_t)b * a.Lq * lddq + h * DH, lddq, w0, a.Lq, acc, 0.125f, lane, (bf16*)lds + wave * 32 * LDT, wide);
 }
 
-// wave owns 32 keys, streams queries / output gradients -> dk, dv
-template <bool CAUSAL>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void gen_bwd_dkv_mfma(View a, const float* __restrict__ lse, const bf16* __restrict__ d_out,
+// wave owns 32 keys, streams queries / output gradients and the two numbers of each query -> dk, dv
+template <bool CAUSAL, bool DROP>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void stream_bwd_dkv_mfma(View a, const float* __restrict__ lse, const bf16* __restrict__ d_out,
                                                         const float* __restrict__ dvec, bf16* __restrict__ dk_out,
-                                                        bf16* __restrict__ dv_out, int64_t lddkv) {
-  __shared__ __attribute__((aligned(16))) bf16 Qs[64 * LDT];
-  __shared__ __attribute__((aligned(16))) bf16 Gs[64 * LDT];
-  __shared__ float lse2_s[64], dvec_s[64];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int b = blockIdx.z, h = blockIdx.y;
+                                                        bf16* __restrict__ dv_out, int64_t lddkv, bool wide, DropCfg drop, uint32_t site) {
+  constexpr int kStage = kStageBytes + 2 * 64 * (int)sizeof(float);
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[2 * kStage];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int b, h, row0;
+  block_place(b, h, row0);
   const int H = a.A * DH;
   const int klen = clamp_len(a.klens[b], a.Lk), qlen = clamp_len(a.qlens[b], a.Lq);
-  const bf16* qb_ = (const bf16*)a.q + (int64_t)b * a.Lq * a.ldq + h * DH;
-  const bf16* kb_ = (const bf16*)a.k + (int64_t)b * a.Lk * a.ldkv + h * DH;
-  const bf16* vb_ = (const bf16*)a.v + (int64_t)b * a.Lk * a.ldkv + h * DH;
-  const bf16* go = d_out + (int64_t)b * a.Lq * H + h * DH;
-  const int kj = blockIdx.x * 128 + wave * 32 + (lane & 31);    // the key this lane owns
-  const int wave_kmin = blockIdx.x * 128 + wave * 32;
-  const bool wave_active = wave_kmin < klen;                    // wave-uniform
+  const int w0 = row0 + wave * 32, kj = w0 + (lane & 31);       // the key this lane owns
+  const int qend = row0 >= klen ? 0 : qlen;
+  Stream qs_, gs_;
+  qs_.init((const bf16*)a.q + (int64_t)b * a.Lq * a.ldq + h * DH, a.ldq, lane, wave);
+  gs_.init(d_out + (int64_t)b * a.Lq * H + h * DH, H, lane, wave);
+  const float* const row_num = (wave == 0 ? lse : dvec) + ((int64_t)b * a.A + h) * a.Lq;
+  auto request = [&](int q0, unsigned char* __restrict__ st) __attribute__((always_inline)) {
+    qs_.issue(q0, qlen, st, wave);
+    gs_.issue(q0, qlen, st + kTileBytes, wave);
+    if (wave < 2) {      // one of the two numbers of 64 queries, zero beyond the last
+      const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)(row_num + q0), 0, min(64, qlen - q0) * 4, 0x00020000);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void_ptr)(st + kStageBytes + wave * 256), 4, lane * 4, 0, 0, 0);
+    }
+  };
+  // queries before the block's first key never see it when causal (block-uniform start)
+  const int qbeg = CAUSAL ? row0 : 0;
+  if (qbeg < qend) request(qbeg, lds);
 
   bf16x8 kf[4], vf[4];
 #pragma unroll
   for (int ks = 0; ks < 4; ++ks) {
-    kf[ks] = frag_rows_global(kb_, a.ldkv, kj, klen, ks, lane);
-    vf[ks] = frag_rows_global(vb_, a.ldkv, kj, klen, ks, lane);
+    kf[ks] = frag_rows_global((const bf16*)a.k + (int64_t)b * a.Lk * a.ldkv + h * DH, a.ldkv, kj, klen, ks, lane);
+    vf[ks] = frag_rows_global((const bf16*)a.v + (int64_t)b * a.Lk * a.ldkv + h * DH, a.ldkv, kj, klen, ks, lane);
   }
   f32x16 dk[2], dv[2];
-#pragma unroll
-  for (int db = 0; db < 2; ++db)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) { dk[db][r] = 0.f; dv[db][r] = 0.f; }
+  clear(dk);
+  clear(dv);
 
-  // queries before the block's first key never see it when causal (block-uniform start, a multiple of 64)
-  for (int q0 = CAUSAL ? (int)blockIdx.x * 128 : 0; q0 < qlen; q0 += 64) {
-    __syncthreads();
-    stage64(Qs, qb_, a.ldq, q0, qlen, tid);
-    stage64(Gs, go, H, q0, qlen, tid);
-    if (tid < 64) {
-      const bool ok = q0 + tid < qlen;
-      lse2_s[tid] = ok ? lse[((int64_t)b * a.A + h) * a.Lq + q0 + tid] * LOG2E : 0.f;
-      dvec_s[tid] = ok ? dvec[((int64_t)b * a.A + h) * a.Lq + q0 + tid] : 0.f;
-    }
-    __syncthreads();
-    if (wave_active) {
+  auto step = [&](int q0, const unsigned char* __restrict__ cur, unsigned char* __restrict__ nxt) __attribute__((always_inline)) {
+    stage_barrier();
+    if (q0 + 64 < qend) request(q0 + 64, nxt);
+    const unsigned char* const Qs = cur;
+    const unsigned char* const Gs = cur + kTileBytes;
+    const float* const lse_s = (const float*)(cur + kStageBytes);
 #pragma unroll
-      for (int sub = 0; sub < 2; ++sub) {
-        const int qb = 32 * sub;
-        if (q0 + qb < qlen && (!CAUSAL || q0 + qb + 31 >= wave_kmin)) {
-          f32x16 st, dp;
+    for (int t = 0; t < 2; ++t) {
+      const int qb = q0 + 32 * t;
+      if (qb < qend && w0 < klen && (!CAUSAL || qb + 31 >= w0)) {      // wave-uniform
+        f32x16 st, dp, dvr;
 #pragma unroll
-          for (int r = 0; r < 16; ++r) { st[r] = 0.f; dp[r] = 0.f; }
+        for (int g = 0; g < 4; ++g) {
+          const f32x4 lv = *(const f32x4*)(lse_s + 32 * t + 8 * g + 4 * (lane >> 5));
+          const f32x4 dvv = *(const f32x4*)(lse_s + 64 + 32 * t + 8 * g + 4 * (lane >> 5));
 #pragma unroll
-          for (int ks = 0; ks < 4; ++ks) {
-            st = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows(Qs, qb, ks, lane), kf[ks], st, 0, 0, 0);
-            dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows(Gs, qb, ks, lane), vf[ks], dp, 0, 0, 0);
-          }
+          for (int e = 0; e < 4; ++e) { st[4 * g + e] = -8.0f * lv[e]; dvr[4 * g + e] = -dvv[e]; }
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) dp[r] = DROP ? 0.f : dvr[r];
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+          st = __builtin_amdgcn_mfma_f32_32x32x16_bf16(srows(Qs, 32 * t, ks, lane), kf[ks], st, 0, 0, 0);
+          dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(srows(Gs, 32 * t, ks, lane), vf[ks], dp, 0, 0, 0);
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) st[r] = fast_exp2(st[r] * SCALE2);
+        if (qb + 32 > qlen || w0 + 32 > klen || (CAUSAL && qb < w0 + 31)) {
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
             const int qi = qb + tile_row(r, lane);
-            const bool ok = (q0 + qi < qlen) && (kj < klen) && (!CAUSAL || kj <= q0 + qi);
-            const float p = ok ? fast_exp2(st[r] * SCALE2 - lse2_s[qi]) : 0.f;
-            st[r] = p;
-            dp[r] = p * (dp[r] - dvec_s[qi]);
+            st[r] = (qi < qlen && kj < klen && (!CAUSAL || kj <= qi)) ? st[r] : 0.f;
           }
-          const bf16x8 p0 = pack8(st, 0), p1 = pack8(st, 1), s0 = pack8(dp, 0), s1 = pack8(dp, 1);
+        }
+        if (DROP) {
+          f32x16 f;
+          drop_tile_queries(drop, site, ((uint64_t)b * a.A + h) * a.Lq, a.Lk, qb, kj, lane, f);
 #pragma unroll
-          for (int db = 0; db < 2; ++db) {
-            dv[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_cols_t(Gs, qb, 0, 32 * db, lane), p0, dv[db], 0, 0, 0);
-            dv[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_cols_t(Gs, qb, 1, 32 * db, lane), p1, dv[db], 0, 0, 0);
-            dk[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_cols_t(Qs, qb, 0, 32 * db, lane), s0, dk[db], 0, 0, 0);
-            dk[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_cols_t(Qs, qb, 1, 32 * db, lane), s1, dk[db], 0, 0, 0);
-          }
+          for (int r = 0; r < 16; ++r) { dp[r] = st[r] * fmaf(f[r], dp[r], dvr[r]); st[r] *= f[r]; }
+        } else {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) dp[r] *= st[r];
+        }
+        const bf16x8 p0 = pack8(st, 0), p1 = pack8(st, 1), s0 = pack8(dp, 0), s1 = pack8(dp, 1);
+#pragma unroll
+        for (int db = 0; db < 2; ++db) {
+          dv[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(scols_t(Gs, 32 * t, 0, 32 * db, lane), p0, dv[db], 0, 0, 0);
+          dv[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(scols_t(Gs, 32 * t, 1, 32 * db, lane), p1, dv[db], 0, 0, 0);
+          dk[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(scols_t(Qs, 32 * t, 0, 32 * db, lane), s0, dk[db], 0, 0, 0);
+          dk[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(scols_t(Qs, 32 * t, 1, 32 * db, lane), s1, dk[db], 0, 0, 0);
         }
       }
     }
-  }
-  if (kj < a.Lk) {
-    store_owned_rows(dk_out + ((int64_t)b * a.Lk + kj) * lddkv + h * DH, dk, 0.125f, lane);
-    store_owned_rows(dv_out + ((int64_t)b * a.Lk + kj) * lddkv + h * DH, dv, 1.0f, lane);
-  }
+  };
+  for (int q0 = qbeg, at = 0; q0 < qend; q0 += 64, at = kStage - at) step(q0, lds + at, lds + kStage - at);
+  __syncthreads();      // every wave is done with the stages
+  bf16* const area = (bf16*)lds + wave * 32 * LDT;
+  store_wave_rows(dk_out + (int64_t)b * a.Lk * lddkv + h * DH, lddkv, w0, a.Lk, dk, 0.125f, lane, area, wide);
+  store_wave_rows(dv_out + (int64_t)b * a.Lk * lddkv + h * DH, lddkv, w0, a.Lk, dv, 1.0f, lane, area, wide);
 }
 
 View make_view(const AttnOperands& x) {
@@ -270,6 +436,43 @@ View make_view(const AttnOperands& x) {
   v.q = x.q; v.k = x.k; v.v = x.v; v.ldq = x.ldq; v.ldkv = x.ldkv; v.qlens = x.qlens; v.klens = x.klens;
   v.Lq = x.Lq; v.Lk = x.Lk; v.A = x.A;
   return v;
+}
+
+const DropCfg kNoDrop{0u, 1.0f, 0u, 0u, 0u};
+
+bool wide_rows(const void* p, int64_t ld) { return !((uintptr_t)p & 15) && !(ld & 7); }
+
+void stream_fwd(const AttnOperands& x, int B, void* out, float* lse, hipStream_t s, const DropCfg& drop, uint32_t site) {
+  const View v = make_view(x);
+  const bool wide = wide_rows(out, 8);
+  const dim3 grid((x.Lq + 127) / 128, x.A, B);
+  if (x.causal) hipLaunchKernelGGL((stream_fwd_mfma<true, false>), grid, dim3(256), 0, s, v, (bf16*)out, lse, wide, kNoDrop, 0u);
+  else if (drop.thr) hipLaunchKernelGGL((stream_fwd_mfma<false, true>), grid, dim3(256), 0, s, v, (bf16*)out, lse, wide, drop, site);
+  else hipLaunchKernelGGL((stream_fwd_mfma<false, false>), grid, dim3(256), 0, s, v, (bf16*)out, lse, wide, kNoDrop, 0u);
+}
+
+void stream_bwd(const AttnOperands& x, int B, const void* out, const float* lse, const void* d_out, void* dq, int64_t lddq, void* dk, void* dv,
+                int64_t lddkv, float* dvec, hipStream_t s, const DropCfg& drop, uint32_t site) {
+  const View v = make_view(x);
+  const bool wq = wide_rows(dq, lddq), wkv = wide_rows(dk, lddkv) && wide_rows(dv, lddkv);
+  const dim3 gq((x.Lq + 127) / 128, x.A, B), gk((x.Lk + 127) / 128, x.A, B);
+#define HS_STREAM_BWD(CAUSAL, DROP, D, SITE)                                                                                                \
+  do {                                                                                                                                      \
+    hipLaunchKernelGGL((stream_bwd_dq_mfma<CAUSAL, DROP>), gq, dim3(256), 0, s, v, (const bf16*)out, lse, (const bf16*)d_out, (bf16*)dq,    \
+                       lddq, dvec, wq, D, SITE);                                                                                            \
+    hipLaunchKernelGGL((stream_bwd_dkv_mfma<CAUSAL, DROP>), gk, dim3(256), 0, s, v, lse, (const bf16*)d_out, (const float*)dvec, (bf16*)dk, \
+                       (bf16*)dv, lddkv, wkv, D, SITE);                                                                                     \
+  } while (0)
+  if (x.causal) HS_STREAM_BWD(true, false, kNoDrop, 0u);
+  else if (drop.thr) HS_STREAM_BWD(false, true, drop, site);
+  else HS_STREAM_BWD(false, false, kNoDrop, 0u);
+#undef HS_STREAM_BWD
+}
+
+AttnOperands self_operands(const void* qkv, const int32_t* lens, int L, int A) {
+  const bf16* q = (const bf16*)qkv;
+  const int64_t H = (int64_t)A * DH;
+  return AttnOperands{q, q + H, q + 2 * H, 3 * H, 3 * H, lens, lens, L, L, A, 0};
 }
 
 AttnF32 f32_problem(const AttnOperands& x) {
@@ -298,11 +501,8 @@ hs_status launch_attention_general_fwd(hs_ctx* ctx, int dtype, const AttnOperand
   if (st != HS_OK) return st;
   const double pairs = (double)B * x.A * x.Lq * x.Lk * (x.causal ? 0.5 : 1.0);
   KScope scope(ctx ? ctx->prof : nullptr, KC_ATTN_FWD, 4.0 * pairs * 64, (double)B * x.A * 64 * (2.0 * x.Lq + 2.0 * x.Lk) * esize(dtype), s);
-  const View v = make_view(x);
   if (dtype == HS_BF16) {
-    dim3 grid((x.Lq + 127) / 128, x.A, B);
-    if (x.causal) hipLaunchKernelGGL(gen_fwd_mfma<true>, grid, dim3(256), 0, s, v, (bf16*)out, lse);
-    else hipLaunchKernelGGL(gen_fwd_mfma<false>, grid, dim3(256), 0, s, v, (bf16*)out, lse);
+    stream_fwd(x, B, out, lse, s, kNoDrop, 0);
   } else {
     launch_attention_f32_fwd(f32_problem(x), B, (float*)out, lse, s);
   }
@@ -322,20 +522,24 @@ hs_status launch_attention_general_bwd(hs_ctx* ctx, int dtype, const AttnOperand
     return hs_fail(ctx, HS_ERR_SHAPE, "attention_general_bwd: bf16 gradients must be 8-byte aligned with strides that are multiples of 4");
   const double pairs = (double)B * x.A * x.Lq * x.Lk * (x.causal ? 0.5 : 1.0);
   KScope scope(ctx ? ctx->prof : nullptr, KC_ATTN_BWD, 8.0 * pairs * 64, (double)B * x.A * 64 * (4.0 * x.Lq + 4.0 * x.Lk) * esize(dtype), s);
-  const View v = make_view(x);
   if (dtype == HS_BF16) {
-    dim3 gq((x.Lq + 127) / 128, x.A, B), gk((x.Lk + 127) / 128, x.A, B);
-    if (x.causal) {
-      hipLaunchKernelGGL(gen_bwd_dq_mfma<true>, gq, dim3(256), 0, s, v, (const bf16*)out, lse, (const bf16*)d_out, (bf16*)dq, lddq, dvec);
-      hipLaunchKernelGGL(gen_bwd_dkv_mfma<true>, gk, dim3(256), 0, s, v, lse, (const bf16*)d_out, (const float*)dvec, (bf16*)dk, (bf16*)dv, lddkv);
-    } else {
-      hipLaunchKernelGGL(gen_bwd_dq_mfma<false>, gq, dim3(256), 0, s, v, (const bf16*)out, lse, (const bf16*)d_out, (bf16*)dq, lddq, dvec);
-      hipLaunchKernelGGL(gen_bwd_dkv_mfma<false>, gk, dim3(256), 0, s, v, lse, (const bf16*)d_out, (const float*)dvec, (bf16*)dk, (bf16*)dv, lddkv);
-    }
+    stream_bwd(x, B, out, lse, d_out, dq, lddq, dk, dv, lddkv, dvec, s, kNoDrop, 0);
   } else {
     launch_attention_f32_bwd(f32_problem(x), B, (const float*)out, lse, (const float*)d_out, (float*)dq, lddq, (float*)dk, (float*)dv, lddkv, s);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hs_fail(ctx, HS_ERR_HIP, std::string("attention_general_bwd: ") + hipGetErrorString(e));
   return HS_OK;
+}
+
+// bf16 self-attention over packed q | k | v rows (see attention.hip)
+void launch_attention_self_fwd(const void* qkv, const int32_t* lens, int B, int L, int A, void* out, float* lse, hipStream_t s, const DropCfg& drop,
+                               uint32_t site) {
+  stream_fwd(self_operands(qkv, lens, L, A), B, out, lse, s, drop, site);
+}
+void launch_attention_self_bwd(const void* qkv, const void* out, const float* lse, const void* d_out, const int32_t* lens, int B, int L, int A,
+                               void* dqkv, float* dvec, hipStream_t s, const DropCfg& drop, uint32_t site) {
+  const int64_t H = (int64_t)A * DH;
+  bf16* const d = (bf16*)dqkv;
+  stream_bwd(self_operands(qkv, lens, L, A), B, out, lse, d_out, d, 3 * H, d + H, d + 2 * H, 3 * H, dvec, s, drop, site);
 }

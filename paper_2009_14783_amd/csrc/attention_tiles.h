@@ -1,5 +1,4 @@
-// Tile helpers of the bf16 MFMA attention kernels (head dimension 64): staging of 64-row blocks into LDS,
-// row and transposed fragments, the result-register -> streamed-row map, dropout factors per tile,
+// Tile helpers of the bf16 MFMA attention kernels (head dimension 64): row and transposed fragments, the result-register -> streamed-row map, dropout factors per tile,
 // packing and the store of owned rows.  Included by the kernels' translation units only.
 #pragma once
 #include "common.h"
@@ -13,19 +12,6 @@ constexpr float LN2 = 0.6931471805599453f;
 constexpr float SCALE2 = 0.125f * LOG2E;   // 1/sqrt(64) folded with the change to base 2
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
-
-// rows r0..r0+63 of a [*, ld] bf16 matrix (64 columns starting at the given pointer) -> LDS tile;
-// rows at or beyond row_limit are zero.  256 threads, two 16-byte chunks each.
-__device__ __forceinline__ void stage64(bf16* tile, const bf16* __restrict__ src, int64_t ld, int r0, int row_limit, int tid) {
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int c = tid + i * 256;
-    const int r = c >> 3, col = (c & 7) * 8;
-    uint4 v = make_uint4(0, 0, 0, 0);
-    if (r0 + r < row_limit) v = *(const uint4*)(src + (int64_t)(r0 + r) * ld + col);
-    *(uint4*)(tile + r * LDT + col) = v;
-  }
-}
 
 // A/B fragment of tile rows: lane gets row rbase + lane%32, columns 16*ks + 8*(lane/32) .. +7
 __device__ __forceinline__ bf16x8 frag_rows(const bf16* tile, int rbase, int ks, int lane) {
@@ -122,6 +108,7 @@ __device__ __forceinline__ void store_owned_rows_lds(bf16* __restrict__ dst, int
       for (int e = 0; e < 4; ++e) o[e] = (bf16)(acc[db][4 * qd + e] * scale);
       *(bf16x4*)(stage + (lane & 31) * LDT + 32 * db + 8 * qd + 4 * (lane >> 5)) = o;
     }
+  asm volatile("" ::: "memory");      // pieces and rows are accessed as different types
 #pragma unroll
   for (int it = 0; it < 4; ++it) {
     const int c = it * 64 + lane;
@@ -129,6 +116,7 @@ __device__ __forceinline__ void store_owned_rows_lds(bf16* __restrict__ dst, int
     const uint4 v = *(const uint4*)(stage + r * LDT + col);
     if (row0 + r < row_limit) *(uint4*)(dst + (int64_t)(row0 + r) * ld + col) = v;
   }
+  asm volatile("" ::: "memory");
 }
 
 }  // namespace attn_tiles

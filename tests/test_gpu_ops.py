@@ -443,6 +443,54 @@ def test_attention_fwd_bwd(hs, mode, B, L, A, lens):
     assert rel(got, want) < (5e-5 if mode == 0 else 1e-2)
 
 
+# lengths at which the streaming kernels end a 64-row block, one of its 32-row tiles or a block of 128 owned rows, one before and one behind
+@pytest.mark.parametrize("causal", [0, 1])
+@pytest.mark.parametrize("L,lens", [(128, [128, 127, 33]), (136, [129, 96, 65]), (192, [192, 161, 64]), (264, [264, 257, 193]), (40, [32, 31, 1])])
+def test_streaming_attention_at_block_edges(hs, causal, L, lens):
+    """bf16 with separate operands: against float64 at the tolerances of test_attention_fwd_bwd, and results that are only 8-byte aligned
+    bit for bit those that are 16-byte aligned (the two are stored differently)."""
+    rng = np.random.default_rng(L + causal)
+    B, A, H = len(lens), 2, 128
+    q, k, v, dctx = (rounded(rng.standard_normal((B * L, H)).astype(np.float32), 1) for _ in range(4))
+    lens_np = np.asarray(lens, dtype=np.int32)
+    real = O.key_mask(lens_np, L).astype(bool)
+    dctx[~real.reshape(-1)] = 0.0
+    tq, tk, tv, tdo = (dev(x.astype(np.float32), torch.bfloat16) for x in (q, k, v, dctx))
+    tl = dev(lens_np)
+    lse = torch.zeros(B * A * L, dtype=torch.float32, device="cuda")
+    dvec = torch.zeros(B * A * L, dtype=torch.float32, device="cuda")
+
+    def padded(width):      # rows of `width` elements that start 8 bytes behind a 16-byte boundary
+        return torch.full((B * L * width + 4,), 7.0, dtype=torch.bfloat16, device="cuda")[4:].view(B * L, width)
+
+    ctx, ctx8 = torch.zeros(B * L, H, dtype=torch.bfloat16, device="cuda"), padded(H)
+    for o in (ctx8, ctx):
+        hs.hs_op_attention_general_fwd(1, tq, H, tk, tv, H, tl, tl, B, L, L, A, causal, o.data_ptr(), lse)
+    wide = [torch.full((B * L, H), 7.0, dtype=torch.bfloat16, device="cuda") for _ in range(3)]
+    narrow = [padded(H + 4) for _ in range(3)]
+    for g, ld in ((wide, H), (narrow, H + 4)):
+        hs.hs_op_attention_general_bwd(1, tq, H, tk, tv, H, tl, tl, B, L, L, A, causal, ctx, lse, tdo, g[0].data_ptr(), ld, g[1].data_ptr(),
+                                       g[2].data_ptr(), ld, dvec)
+    torch.cuda.synchronize()
+    assert torch.equal(ctx, ctx8)
+    for a, b in zip(wide, narrow):
+        assert torch.equal(a, b[:, :H]) and torch.all(b[:, H:] == 7.0)
+    heads = lambda x: x.astype(np.float64).reshape(B, L, A, 64).transpose(0, 2, 1, 3)
+    flat = lambda x: x.transpose(0, 2, 1, 3).reshape(B * L, H)
+    qh, kh, vh, dO = heads(q), heads(k), heads(v), heads(dctx)
+    s = np.where(real[:, None, None, :] & (np.tril(np.ones((L, L), bool)) if causal else True), qh @ kh.transpose(0, 1, 3, 2) / 8.0, -np.inf)
+    p = np.exp(s - s.max(-1, keepdims=True))
+    p /= p.sum(-1, keepdims=True)
+    rows = real.reshape(-1)
+    assert rel(host(ctx)[rows], flat(p @ vh)[rows]) < 5e-3
+    p = p * real[:, None, :, None]
+    dp = dO @ vh.transpose(0, 1, 3, 2)
+    ds = p * (dp - (dp * p).sum(-1, keepdims=True))
+    for got, want in zip(wide, (ds @ kh / 8.0, ds.transpose(0, 1, 3, 2) @ qh / 8.0, p.transpose(0, 1, 3, 2) @ dO)):
+        assert np.all(host(got)[~rows] == 0.0)
+        assert rel(host(got), flat(want)) < 1e-2
+
+
 @pytest.mark.parametrize("causal", [0, 1])
 @pytest.mark.parametrize("L,length", [(40, 37), (72, 72), (104, 65)])
 @pytest.mark.parametrize("what,row", [("k", 20), ("v", 33), ("v_inf", 36), ("q", 7), ("dO", 31)])
