@@ -544,9 +544,10 @@ hs_status launch_gemm_group(hs_ctx* ctx, const GemmArgs* gs, int n, hipStream_t 
     } else {
       // The tile by the constants of the time model, over the tiles of all problems.  The launch runs beside the chain of activation
       // gradients, so what counts is the time of the CUs that it takes and not how evenly its last round fills them: rounds are not
-      // rounded up.  (Ms per step with 256 x 256, 256 x 128 and 128 x 128 tiles: BERT-base with 8192 rows 7.28 / 7.25 / 7.30, with micro-batches of 2048, 6144
-      // and 14336 rows 21.4 / 21.7 / 22.1, with 17472 rows 15.1 / 15.3 / 15.9; BERT-large with 16384 rows 156 / 162 / 178; the translation step with 4096 rows
-      // per side 4.28 / 4.36 / 4.41.)
+      // rounded up, and tiles for half of the CUs are as good as tiles for all of them (fewer would last too long behind the last layer).  Ms per
+      // step if all CUs have to be filled -> half of them: BERT-large with 16384 rows 153.3 -> 148.8 (256 x 256 tiles on 192 CUs, and the chain on
+      // the others: 480 us against 530, its LayerNorm backward 27 against 54), two updates of 4096 rows 10.7 -> 10.2 (256 x 128), the
+      // translation step with 4096 rows per side 4.56 -> 4.47 and 4.74 -> 4.67 (256 x 256); a quarter of them: BERT-base with 8192 rows 7.52 -> 7.69.
       float best = 3.0e38f;
       for (int c : {1, 9, 10, 11}) {
         const TileCfg& t = kTileCfg[c];
@@ -554,7 +555,7 @@ hs_status launch_gemm_group(hs_ctx* ctx, const GemmArgs* gs, int n, hipStream_t 
         float steps = 0.0f;
         for (int i = 0; i < gd.n; ++i) steps += (float)(gd.first_tile[i + 1] - gd.first_tile[i]) * ((gd.prob[i].K + 63) / 64);
         const float per_tile = (tiles ? steps / tiles : 0.0f) * std::max(t.l / t.occ, t.w) + t.e * 2.0f;
-        const float time = t.t0 + per_tile * std::max(1.0f, (float)tiles / kCUs);
+        const float time = t.t0 + per_tile * std::max(0.5f, (float)tiles / kCUs);
         if (time < best) { best = time; cfg = c; }
       }
       count(kTileCfg[cfg].bm, kTileCfg[cfg].bn);
