@@ -1,14 +1,6 @@
-// bf16 MFMA attention (head dimension 64), forward and backward, fp32 softmax statistics.
-//
-// Every kernel has the same shape.  A wave OWNS 32 rows (queries, or keys in the dK/dV kernel)
-// whose vectors stay in registers as MFMA B operands, and STREAMS the other side through LDS in
-// blocks of 64 rows kept in their natural [row][64] layout.  Score tiles are computed transposed,
-// tile[streamed row][owned row], so that each lane holds ONE owned row (lane % 32) and 16 streamed
-// rows: reductions over the streamed index are then in-lane plus one exchange between the two
-// half-waves.  The second product needs the score tile as a B operand and the streamed block
-// transposed as the A operand; the transposed fragment comes from the LDS transpose read, with
-// the 16 contraction slots ordered exactly as the result registers of the score tile are
-// (register r of lane l is streamed row 8*(r/4) + 4*(l/32) + r%4), so no data moves between lanes.
+// bf16 MFMA self-attention (head dimension 64), fp32 softmax statistics: the backward pass of sequences of at most 128 positions.
+// Everything else goes to the streaming kernels of attention_general.hip, where the tile scheme of both (owned rows in registers,
+// transposed score tiles) is described.
 #include "attention_tiles.h"
 
 namespace {
@@ -36,6 +28,11 @@ __device__ __forceinline__ void stage128(bf16* tile, const bf16* __restrict__ sr
   }
 }
 
+// Up to this many (sequence, head) pairs, the two halves go to a block each: the chip has room for both, and a block's chain is half as long
+// (BERT-base, 5 sequences of 88 positions in two passes: 4.23 -> 4.08 ms per step).  Beyond, the second set of loads costs what the shorter chain
+// gives (768 pairs: 7.50 -> 7.54 ms per step; 384: level).
+constexpr int kFewHeads = 256;
+
 template <bool DROP>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3)))
 void attn_bwd_fused128_mfma(const bf16* __restrict__ qkv, const bf16* __restrict__ out, const float* __restrict__ lse,
@@ -58,8 +55,9 @@ void attn_bwd_fused128_mfma(const bf16* __restrict__ qkv, const bf16* __restrict
   const int own = wave * 32 + (lane & 31);       // the query, then the key, this lane owns
   const bool wave_active = wave * 32 < len;      // wave-uniform
 
-  stage128(T0, base + H, ld, len, tid);
-  stage128(T1, base + 2 * H, ld, len, tid);
+  const bool queries = blockIdx.z == 0, keys = queries == (gridDim.z == 1);      // the halves this block does
+  stage128(T0, queries ? base + H : base, ld, len, tid);
+  stage128(T1, queries ? base + 2 * H : go, queries ? ld : H, len, tid);
   // the owned queries' fragments of Q and dO, and the row dot product sum_d dO*O (lanes l and l + 32 hold the two halves of a row)
   bf16x8 qf[4], gf[4];
   float drow = 0.f;
@@ -83,7 +81,7 @@ void attn_bwd_fused128_mfma(const bf16* __restrict__ qkv, const bf16* __restrict
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[db][r] = 0.f;
   // ---- queries owned: dq ----
-  if (wave_active) {
+  if (queries && wave_active) {
     for (int kb = 0; kb < len; kb += 32) {
       f32x16 st, dp;
 #pragma unroll
@@ -116,18 +114,29 @@ void attn_bwd_fused128_mfma(const bf16* __restrict__ qkv, const bf16* __restrict
     }
   }
   // ---- keys owned: dk, dv ----
-  // The owned key/value fragments are the last thing read from K and V.  After the barrier a wave's own 32 rows of
-  // tile 0 stage the whole-row stores of dq; after the next one the tiles are refilled with Q and dO.
   bf16x8 kf[4], vf[4];
-#pragma unroll
-  for (int ks = 0; ks < 4; ++ks) { kf[ks] = frag_rows(T0, wave * 32, ks, lane); vf[ks] = frag_rows(T1, wave * 32, ks, lane); }
-  __syncthreads();
   bf16* const dst = dqkv + (int64_t)b * L * ld + h * DH;
-  store_owned_rows_lds(dst, ld, wave * 32, L, acc, 0.125f, lane, T0 + wave * 32 * LDT);
-  __syncthreads();
-  stage128(T0, base, ld, len, tid);
-  stage128(T1, go, H, len, tid);
-  __syncthreads();
+  if (queries) {
+    // The owned key/value fragments are the last thing read from K and V.  After the barrier a wave's own 32 rows of
+    // tile 0 stage the whole-row stores of dq; after the next one the tiles are refilled with Q and dO.
+    if (keys) {
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) { kf[ks] = frag_rows(T0, wave * 32, ks, lane); vf[ks] = frag_rows(T1, wave * 32, ks, lane); }
+    }
+    __syncthreads();
+    store_owned_rows_lds(dst, ld, wave * 32, L, acc, 0.125f, lane, T0 + wave * 32 * LDT);
+    if (!keys) return;
+    __syncthreads();
+    stage128(T0, base, ld, len, tid);
+    stage128(T1, go, H, len, tid);
+    __syncthreads();
+  } else {
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      kf[ks] = frag_rows_global(base + H, ld, own, len, ks, lane);
+      vf[ks] = frag_rows_global(base + 2 * H, ld, own, len, ks, lane);
+    }
+  }
 #pragma unroll
   for (int db = 0; db < 2; ++db)
 #pragma unroll
@@ -200,9 +209,10 @@ void launch_attention_bwd_mfma(const void* qkv, const void* out, const float* ls
       (void)hipFuncSetAttribute((const void*)attn_bwd_fused128_mfma<true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
       configured = true;
     }
-    if (drop.thr) hipLaunchKernelGGL(attn_bwd_fused128_mfma<true>, dim3(A, B), dim3(256), lds, s, (const bf16*)qkv, (const bf16*)out, lse,
+    const dim3 grid(A, B, (int64_t)A * B <= kFewHeads ? 2 : 1);
+    if (drop.thr) hipLaunchKernelGGL(attn_bwd_fused128_mfma<true>, grid, dim3(256), lds, s, (const bf16*)qkv, (const bf16*)out, lse,
                                      (const bf16*)d_out, lens, L, A, (bf16*)dqkv, drop, site);
-    else hipLaunchKernelGGL(attn_bwd_fused128_mfma<false>, dim3(A, B), dim3(256), lds, s, (const bf16*)qkv, (const bf16*)out, lse,
+    else hipLaunchKernelGGL(attn_bwd_fused128_mfma<false>, grid, dim3(256), lds, s, (const bf16*)qkv, (const bf16*)out, lse,
                             (const bf16*)d_out, lens, L, A, (bf16*)dqkv, drop, site);
     return;
   }

@@ -443,6 +443,33 @@ def test_attention_fwd_bwd(hs, mode, B, L, A, lens):
     assert rel(got, want) < (5e-5 if mode == 0 else 1e-2)
 
 
+# 264 (sequence, head) pairs take one block each, 132 take two: the same numbers either way
+@pytest.mark.parametrize("L", [8, 40, 104, 128])
+def test_attention_backward_in_one_block_and_in_two(hs, L):
+    rng = np.random.default_rng(L)
+    B, A = 22, 12
+    H = A * 64
+    lens = np.asarray([max(1, L - 5 * (i % 20)) for i in range(B)], dtype=np.int32)
+    real = O.key_mask(lens, L).astype(bool).reshape(-1)
+    qkv = dev(rng.standard_normal((B * L, 3 * H)).astype(np.float32), torch.bfloat16)
+    dctx = rng.standard_normal((B * L, H)).astype(np.float32)
+    dctx[~real] = 0.0
+    dctx, dl = dev(dctx, torch.bfloat16), dev(lens)
+    ctx = torch.zeros(B * L, H, dtype=torch.bfloat16, device="cuda")
+    lse, dvec = (torch.zeros(B * A * L, dtype=torch.float32, device="cuda") for _ in range(2))
+    hs.hs_op_attention_fwd(1, qkv, dl, B, L, A, ctx, lse)
+    whole, parts = (torch.full((B * L, 3 * H), 7.0, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    hs.hs_op_attention_bwd(1, qkv, ctx, lse, dctx, dl, B, L, A, whole, dvec)
+    n = B // 2
+    for k in range(2):
+        r = slice(k * n * L, (k + 1) * n * L)
+        hs.hs_op_attention_bwd(1, qkv[r], ctx[r], lse[k * n * A * L:(k + 1) * n * A * L], dctx[r], dl[k * n:(k + 1) * n], n, L, A, parts[r],
+                               dvec[k * n * A * L:(k + 1) * n * A * L])
+    torch.cuda.synchronize()
+    assert torch.equal(whole, parts)
+    assert torch.all(whole[dev(~real)] == 0.0)
+
+
 # lengths at which the streaming kernels end a 64-row block, one of its 32-row tiles or a block of 128 owned rows, one before and one behind
 @pytest.mark.parametrize("causal", [0, 1])
 @pytest.mark.parametrize("L,lens", [(128, [128, 127, 33]), (136, [129, 96, 65]), (192, [192, 161, 64]), (264, [264, 257, 193]), (40, [32, 31, 1])])
