@@ -432,8 +432,10 @@ static hs_status encoder_bwd_impl(hs_ctx* ctx, const hs_ctx::Armed& upd, const v
   std::vector<LnColsJob> cols;               // ... and LayerNorm column sums
   std::vector<hipEvent_t> done(NL, nullptr); // of the lowest layer of a hand-over: recorded on sd behind its gradients
   auto enqueue_grads = [&]() -> hs_status {
-    HS_TRY(launch_layernorm_bwd_cols_batch(ctx, cols.data(), (int)cols.size(), beta, T, H, sd));
+    // the products first: in front of them the column sums (4 us) wait until the chain leaves them room (28 us with 8192 rows, 92 with 16384 of
+    // 1024 columns), and the products with them; BERT-base with 8192 rows 7.29 -> 7.16 ms per step, BERT-large with 16384 145.2 -> 144.0
     HS_TRY(launch_gemm_group(ctx, dw.data(), (int)dw.size(), sd));
+    HS_TRY(launch_layernorm_bwd_cols_batch(ctx, cols.data(), (int)cols.size(), beta, T, H, sd));
     cols.clear(); dw.clear();
     return HS_OK;
   };
@@ -485,7 +487,7 @@ static hs_status encoder_bwd_impl(hs_ctx* ctx, const hs_ctx::Armed& upd, const v
     HS_TRY(launch_attention_bwd(ctx, dt, la.qkv, la.ctx, la.lse, ws.dctx, lens, B, L, c.n_heads, q.dqkv, ws.dvec, s, drop,
                                 site_attention_prob(i)));
     // dW2 [H,F] = dy2^T h, dW1 [F,H] = dhpre^T x1, dWqkv [3H,H] = dqkv^T x_in, dWo [H,H] = dy1^T ctx, and the two bias gradients that
-    // are not by-products of a LayerNorm backward (products with a column of ones)
+    // are not by-products of a LayerNorm backward
     cols.push_back({q.ln_part2, g + lo.ln2_g, g + lo.ln2_b, g + lo.ffn2_b});
     cols.push_back({q.ln_part1, g + lo.ln1_g, g + lo.ln1_b, g + lo.o_b});
     GemmArgs grad[6] = {gemm_args(dt, 0, 0, H, F, T, dy2b, H, la.h, F, g + lo.ffn2_w, F), gemm_args(dt, 0, 0, F, H, T, q.dh, F, la.x1, H, g + lo.ffn1_w, H),
