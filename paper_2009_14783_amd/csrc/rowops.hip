@@ -427,15 +427,33 @@ __global__ __launch_bounds__(256) void sum_vector_kernel(const float* __restrict
 // ------------------------------------------------------------------------------------------
 // embedding backward
 // ------------------------------------------------------------------------------------------
-// position table: g_pos[l, :] = beta*g_pos[l, :] + sum_b de[b, l, :]; rows l >= L get beta*old
+// position table: g_pos[l, :] = beta*g_pos[l, :] + sum_b de[b, l, :]; rows l >= L get beta*old.  Four columns per thread, the rows of eight
+// sequences requested together (they are added one after the other): bound by those latencies.  64 x 128 x 768: 61 -> 17 us against
+// one column per thread.
 template <class T>
-__global__ void pos_grad_kernel(const T* __restrict__ de, int B, int L, int H, int max_pos, float* __restrict__ g_pos, float beta) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+__global__ __launch_bounds__(64) void pos_grad_kernel(const T* __restrict__ de, int B, int L, int H, int max_pos, float* __restrict__ g_pos, float beta) {
+  const int64_t i = 4 * ((int64_t)blockIdx.x * blockDim.x + threadIdx.x);
   if (i >= (int64_t)max_pos * H) return;
-  const int l = (int)(i / H), c = (int)(i % H);
-  float s = 0.f;
-  if (l < L) for (int b = 0; b < B; ++b) s += to_f(de[((int64_t)b * L + l) * H + c]);
-  g_pos[i] = (beta != 0.f) ? beta * g_pos[i] + s : s;
+  const int64_t l = i / H, step = (int64_t)L * H;
+  float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (l < L) {
+    const T* row = de + i;
+    int b = 0;
+    for (; b + 8 <= B; b += 8, row += 8 * step) {
+      float4 v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = Vec4<T>::ld(row + u * step);
+#pragma unroll
+      for (int u = 0; u < 8; ++u) { s.x += v[u].x; s.y += v[u].y; s.z += v[u].z; s.w += v[u].w; }
+    }
+    for (; b < B; ++b, row += step) {
+      const float4 v = Vec4<T>::ld(row);
+      s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+    }
+  }
+  float4* const d = (float4*)(g_pos + i);
+  if (beta != 0.f) { const float4 o = *d; s.x += beta * o.x; s.y += beta * o.y; s.z += beta * o.z; s.w += beta * o.w; }
+  *d = s;
 }
 
 // Stable LSD radix sort of (id, position) by id, 4 bits per pass, one block of 512 threads.
@@ -492,57 +510,43 @@ __global__ __launch_bounds__(512) void sort_ids_kernel(const int32_t* __restrict
 // to the left, or spanning the whole chunk) or carry[chunk][1] (run open to the right only).
 // All CH gradient rows of a chunk are fetched before any is used, so the loads overlap.
 constexpr int CH = 8;
+// A wave takes 256 columns of a chunk (blockIdx.y: which), so that the rows of the chunk and the rows of g_word that it adds to (different
+// rows, each of this chunk alone) are all requested before the first is needed.  8192 x 768: 51 -> 25 us against one wave
+// per chunk, 16384 x 1024 201 -> 39.
 template <class T>
 __global__ __launch_bounds__(256) void word_grad_chunks_kernel(const T* __restrict__ de, const int32_t* __restrict__ skey,
                                                                const int32_t* __restrict__ sval, int Ttok, int H,
                                                                float* __restrict__ g_word, float* __restrict__ carry) {
-  const int lane = threadIdx.x & 63;
-  const int chunk = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int chunk = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int col = 256 * blockIdx.y + 4 * (threadIdx.x & 63);
   const int i0 = chunk * CH;
-  if (i0 >= Ttok) return;
+  if (i0 >= Ttok || col >= H) return;
   const int n = min(CH, Ttok - i0);
-  const int nch = H / 4;
   int key[CH];
-  float4 rowv[CH][MAXCH];
+  float4 rowv[CH], old[CH];
 #pragma unroll
   for (int e = 0; e < CH; ++e) {
     key[e] = (e < n) ? skey[i0 + e] : -1;
-    const int64_t t = (e < n) ? sval[i0 + e] : 0;
-#pragma unroll
-    for (int c = 0; c < MAXCH; ++c)
-      rowv[e][c] = (e < n && c * 64 + lane < nch) ? Vec4<T>::ld(de + t * H + 4 * (c * 64 + lane)) : make_float4(0.f, 0.f, 0.f, 0.f);
+    rowv[e] = (e < n) ? Vec4<T>::ld(de + (int64_t)sval[i0 + e] * H + col) : make_float4(0.f, 0.f, 0.f, 0.f);
   }
   const int key_left = (i0 > 0) ? skey[i0 - 1] : -1;
   const int key_right = (i0 + n < Ttok) ? skey[i0 + n] : -1;
-  float4 acc[MAXCH];
+  // the last entry of a run (keys ascend: the run that reaches back to the chunk's start is that of key[0])
+  auto ends = [&](int e) __attribute__((always_inline)) { return e < n && (e + 1 == n || key[(e + 1) % CH] != key[e]); };
+  auto open_left = [&](int e) __attribute__((always_inline)) { return key[e] == key[0] && key_left == key[e]; };
+  auto open_right = [&](int e) __attribute__((always_inline)) { return e + 1 == n && key_right == key[e]; };
 #pragma unroll
-  for (int c = 0; c < MAXCH; ++c) acc[c] = make_float4(0.f, 0.f, 0.f, 0.f);
-  bool run_from_start = true;
+  for (int e = 0; e < CH; ++e)
+    if (ends(e) && !open_left(e) && !open_right(e)) old[e] = *(const float4*)(g_word + (int64_t)key[e] * H + col);
+  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
   for (int e = 0; e < CH; ++e) {
-    if (e < n) {
-#pragma unroll
-      for (int c = 0; c < MAXCH; ++c) { acc[c].x += rowv[e][c].x; acc[c].y += rowv[e][c].y; acc[c].z += rowv[e][c].z; acc[c].w += rowv[e][c].w; }
-      const bool last = (e + 1 == n);
-      const bool run_ends = last || key[(e + 1) % CH] != key[e];
-      if (run_ends) {
-        const bool open_left = run_from_start && key_left == key[e];
-        const bool open_right = last && key_right == key[e];
-        float* dst;
-        bool add;
-        if (open_left) { dst = carry + ((int64_t)chunk * 2 + 0) * H; add = false; }
-        else if (open_right) { dst = carry + ((int64_t)chunk * 2 + 1) * H; add = false; }
-        else { dst = g_word + (int64_t)key[e] * H; add = true; }
-#pragma unroll
-        for (int c = 0; c < MAXCH; ++c) if (c * 64 + lane < nch) {
-          float4* d4 = (float4*)(dst + 4 * (c * 64 + lane));
-          float4 o = acc[c];
-          if (add) { const float4 old = *d4; o.x += old.x; o.y += old.y; o.z += old.z; o.w += old.w; }
-          *d4 = o;
-          acc[c] = make_float4(0.f, 0.f, 0.f, 0.f);
-        }
-        run_from_start = false;
-      }
+    acc.x += rowv[e].x; acc.y += rowv[e].y; acc.z += rowv[e].z; acc.w += rowv[e].w;
+    if (ends(e)) {
+      if (open_left(e)) *(float4*)(carry + ((int64_t)chunk * 2 + 0) * H + col) = acc;
+      else if (open_right(e)) *(float4*)(carry + ((int64_t)chunk * 2 + 1) * H + col) = acc;
+      else *(float4*)(g_word + (int64_t)key[e] * H + col) = make_float4(acc.x + old[e].x, acc.y + old[e].y, acc.z + old[e].z, acc.w + old[e].w);
+      acc = make_float4(0.f, 0.f, 0.f, 0.f);
     }
   }
 }
@@ -550,13 +554,14 @@ __global__ __launch_bounds__(256) void word_grad_chunks_kernel(const T* __restri
 // Joins the runs that cross chunk borders: the wave of the chunk in which such a run STARTS adds
 // its right-open piece and every following left-open piece, in chunk order, then updates g_word.
 // The end of the run is found by bisection in the sorted keys, after which the pieces are fetched
-// eight at a time.
+// sixteen at a time; a wave takes 256 columns (blockIdx.y: which).  The longest run (in masked-LM batches the mask, 15 % of the tokens) is
+// what the launch lasts.  8192 x 768: 48 -> 18 us against one wave per run and eight at a time.
 __global__ __launch_bounds__(256) void word_grad_join_kernel(const int32_t* __restrict__ skey, int Ttok, int H,
                                                              float* __restrict__ g_word, const float* __restrict__ carry) {
-  const int lane = threadIdx.x & 63;
-  const int chunk = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int chunk = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int col = 256 * blockIdx.y + 4 * (threadIdx.x & 63);
   const int i0 = chunk * CH;
-  if (i0 >= Ttok) return;
+  if (i0 >= Ttok || col >= H) return;
   const int i1 = min(Ttok, i0 + CH);
   if (i1 >= Ttok) return;                       // nothing to the right
   const int key = skey[i1 - 1];
@@ -570,31 +575,19 @@ __global__ __launch_bounds__(256) void word_grad_join_kernel(const int32_t* __re
     if (skey[mid] == key) lo = mid; else hi = mid - 1;
   }
   const int last_chunk = lo / CH;               // every chunk in (chunk, last_chunk] starts with this key
-  const int nch = H / 4;
-  float4 acc[MAXCH];
+  constexpr int U = 16;
+  float4* const d4 = (float4*)(g_word + (int64_t)key * H + col);
+  const float4 old = *d4;
+  float4 acc = *(const float4*)(carry + ((int64_t)chunk * 2 + 1) * H + col);
+  for (int ch = chunk + 1; ch <= last_chunk; ch += U) {
+    float4 v[U];
 #pragma unroll
-  for (int c = 0; c < MAXCH; ++c)
-    acc[c] = (c * 64 + lane < nch) ? *(const float4*)(carry + ((int64_t)chunk * 2 + 1) * H + 4 * (c * 64 + lane)) : make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int ch = chunk + 1; ch <= last_chunk; ch += 8) {
-    float4 v[8][MAXCH];
+    for (int u = 0; u < U; ++u)
+      v[u] = (ch + u <= last_chunk) ? *(const float4*)(carry + ((int64_t)(ch + u) * 2 + 0) * H + col) : make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-    for (int u = 0; u < 8; ++u)
-#pragma unroll
-      for (int c = 0; c < MAXCH; ++c)
-        v[u][c] = (ch + u <= last_chunk && c * 64 + lane < nch)
-                      ? *(const float4*)(carry + ((int64_t)(ch + u) * 2 + 0) * H + 4 * (c * 64 + lane)) : make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-    for (int u = 0; u < 8; ++u)
-#pragma unroll
-      for (int c = 0; c < MAXCH; ++c) { acc[c].x += v[u][c].x; acc[c].y += v[u][c].y; acc[c].z += v[u][c].z; acc[c].w += v[u][c].w; }
+    for (int u = 0; u < U; ++u) { acc.x += v[u].x; acc.y += v[u].y; acc.z += v[u].z; acc.w += v[u].w; }
   }
-#pragma unroll
-  for (int c = 0; c < MAXCH; ++c) if (c * 64 + lane < nch) {
-    float4* d4 = (float4*)(g_word + (int64_t)key * H + 4 * (c * 64 + lane));
-    float4 o = *d4;
-    o.x += acc[c].x; o.y += acc[c].y; o.z += acc[c].z; o.w += acc[c].w;
-    *d4 = o;
-  }
+  *d4 = make_float4(old.x + acc.x, old.y + acc.y, old.z + acc.z, old.w + acc.w);
 }
 
 }  // namespace
@@ -733,15 +726,15 @@ hs_status launch_embed_bwd(hs_ctx* ctx, int dtype, const void* de, const int32_t
   if (g_pos) {     // a model with a fixed position table has no position gradient
     const int64_t n = (int64_t)max_pos * H;
     dim3 grid((unsigned)((n + 255) / 256));
-    if (dtype == HS_BF16) hipLaunchKernelGGL(pos_grad_kernel<bf16>, grid, dim3(256), 0, s, (const bf16*)de, B, L, H, max_pos, g_pos, beta_pos);
-    else hipLaunchKernelGGL(pos_grad_kernel<float>, grid, dim3(256), 0, s, (const float*)de, B, L, H, max_pos, g_pos, beta_pos);
+    if (dtype == HS_BF16) hipLaunchKernelGGL(pos_grad_kernel<bf16>, grid, dim3(64), 0, s, (const bf16*)de, B, L, H, max_pos, g_pos, beta_pos);
+    else hipLaunchKernelGGL(pos_grad_kernel<float>, grid, dim3(64), 0, s, (const float*)de, B, L, H, max_pos, g_pos, beta_pos);
     LAUNCH_CHECK(ctx, "pos_grad");
   }
   int32_t* k0 = (int32_t*)scratch;
   int32_t* v0 = k0 + T;
   float* carry = (float*)((char*)scratch + align_up(4 * (size_t)T * sizeof(int32_t), 256));
   const int chunks = (T + CH - 1) / CH;
-  dim3 grid((chunks + 3) / 4);
+  dim3 grid((chunks + 3) / 4, (H + 255) / 256);
   if (dtype == HS_BF16) hipLaunchKernelGGL(word_grad_chunks_kernel<bf16>, grid, dim3(256), 0, s, (const bf16*)de, k0, v0, T, H, g_word, carry);
   else hipLaunchKernelGGL(word_grad_chunks_kernel<float>, grid, dim3(256), 0, s, (const float*)de, k0, v0, T, H, g_word, carry);
   LAUNCH_CHECK(ctx, "word_grad_chunks");

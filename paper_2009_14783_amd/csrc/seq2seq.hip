@@ -593,6 +593,7 @@ hs_status hs_s2s_bwd(hs_ctx* ctx, const void* w, const void* acts, const int32_t
   HS_TRY(launch_mask_scale(ctx, dt, dcur, ws.de_tgt, (size_t)Tt * H, scale, drop, site_tgt(), s));
   HS_TRY(order(s, sd));
   HS_TRY(launch_embed_bwd(ctx, dt, ws.de_tgt, tgt_in, B, Lt, H, c.vocab, 0, g + o.emb, nullptr, 0.f, ws.emb, sd));
+  HS_TRY(launch_embed_sort(ctx, src, Ts, c.vocab, ws.emb, sd));      // now, and not behind the last product of the chain
 
   // ---- encoder ----
   dcur = ws.denc[pe];
@@ -619,7 +620,7 @@ hs_status hs_s2s_bwd(hs_ctx* ctx, const void* w, const void* acts, const int32_t
   }
   HS_TRY(launch_mask_scale(ctx, dt, dcur, ws.de_src, (size_t)Ts * H, scale, drop, site_src(), s));
   HS_TRY(order(s, sd));
-  HS_TRY(launch_embed_bwd(ctx, dt, ws.de_src, src, B, Ls, H, c.vocab, 0, g + o.emb, nullptr, 0.f, ws.emb, sd));
+  HS_TRY(launch_embed_bwd(ctx, dt, ws.de_src, src, B, Ls, H, c.vocab, 0, g + o.emb, nullptr, 0.f, ws.emb, sd, true));
   if (upd.on) HS_TRY(update_slice(ctx, upd, o.emb, o.enc[0].qkv_w, sd, true));      // the shared embedding: its gradient is complete only now
   return order(sd, s);     // everything the second stream did is ordered before whatever the caller enqueues next
 }

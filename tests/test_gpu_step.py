@@ -183,6 +183,23 @@ def test_unequal_micro_batches_dummy_and_fused_accumulation(W, compute):
     compare_flat(layout, results[0], results[1], 1e-5 if compute == "fp32" else 1e-3, "fused vs unfused")
 
 
+@pytest.mark.parametrize("hidden,vocab,B,L", [(64, 1000, 1, 8), (64, 8, 33, 64), (320, 24, 9, 40), (768, 400, 8, 24), (1024, 24, 17, 16)])
+def test_embedding_gradients_over_widths_and_run_lengths(W, hidden, vocab, B, L):
+    """Rows that end inside a block of 256 columns, token counts that end inside a chunk, runs of one token over many chunks, sequences
+    beyond a multiple of eight."""
+    model = dict(synth.MODELS["tiny"], hidden=hidden, n_heads=hidden // 64, ffn=128, vocab=vocab)
+    ocfg = O.ModelCfg(**model)
+    layout = O.param_layout(ocfg)
+    theta = synth.init_params(layout, hidden + vocab)
+    mb = synth.make_micro_batch(synth.rng_for(B * L), [max(1, L - 3 * (i % 4)) for i in range(B)], L, vocab, "uniform")
+    worker = W(model, "fp32", theta)
+    loss, g = gpu_micro_grad(worker, mb)
+    worker.close()
+    ol, og = oracle_micro_grad(ocfg, theta, mb, np.float64)
+    assert abs(loss - ol) / abs(ol) < TOL["fp32"]
+    compare_flat(layout, g, og, TOL["fp32"], f"hidden={hidden}")
+
+
 def test_run_to_run_bit_reproducible(W):
     model = dict(synth.MODELS["tiny"])
     ocfg = O.ModelCfg(**model)
