@@ -21,11 +21,12 @@
 // and product.  So the next 64 rows are loaded straight into the other half of LDS while the current ones are worked on (one barrier per
 // block, no register holds a streamed byte); scores start from -8 lse and their gradients from the row term, which the matrix cores
 // then add for nothing, so that a gradient score costs a multiplication, an exponential and a multiplication; masks are applied only in
-// the tiles that an end or the diagonal cuts; the forward pass takes 64 keys per softmax step and rescales its sums only when a
-// maximum moved.  The query blocks of one head run on one XCD, whose L2 then holds that head's keys and values.
+// the tiles that an end or the diagonal cuts; the forward pass works out the scores and exponentials of two 32-key softmax steps side by side
+// and rescales its sums only when a maximum moved.  The query blocks of one head run on one XCD, whose L2 then holds that head's keys and values.
 // 32 sequences of 512 positions, 16 heads, in the BERT-large step, against kernels that staged through registers between two barriers, masked
-// every score and took 32 keys per softmax step: forward 78.7 -> 56.4 us (610 TFLOP/s), dq 132.5 -> 72.9, dk and dv 179.6 -> 90.8 (755).  BERT-base
-// with micro-batches of 8 + 24 + 56 x 256: 25.4 -> 19.8, 38.9 -> 25.9 and 49.0 -> 24.9 us on average.
+// every score and took one softmax step after the other: dq 132.5 -> 72.9 us, dk and dv 179.6 -> 90.8 (755 TFLOP/s); forward by itself 80.1 -> 55.9 (615).
+// A maximum over 64 keys at once would give 52.9 us there (56 x 256 x 12 heads 24.0 instead of 25.3; up to 32 positions all the same), but fewer probabilities are
+// then exactly one when they are rounded to bf16: results 0.4 to 1.4 % further from float64 between 40 and 512 positions.
 #include "attention_tiles.h"
 
 namespace {
@@ -161,8 +162,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DROP ? 3 : 
     if (w0 >= a.Lq || (CAUSAL && k0 > w0 + 31)) return;
     const unsigned char* const Ks = cur;
     const unsigned char* const Vs = cur + kTileBytes;
-    const bool two = k0 + 32 < kend && (!CAUSAL || k0 + 32 <= w0 + 31);      // wave-uniform, as is the next
-    const bool edge = k0 + 64 > klen || (CAUSAL && k0 + 63 > w0);
+    const bool two = k0 + 32 < kend && (!CAUSAL || k0 + 32 <= w0 + 31);      // wave-uniform
     f32x16 st[2];
 #pragma unroll
     for (int t = 0; t < 2; ++t)
@@ -174,51 +174,49 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DROP ? 3 : 
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) st[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(srows(Ks, 32 * t, ks, lane), qf[ks], st[t], 0, 0, 0);
       }
-    auto seen = [&](int t, int r) __attribute__((always_inline)) {
-      const int key = k0 + 32 * t + tile_row(r, lane);
-      return key < klen && (!CAUSAL || key <= q);
-    };
-    if (edge) {
+    float mloc[2];
 #pragma unroll
-      for (int t = 0; t < 2; ++t)
+    for (int t = 0; t < 2; ++t) {
+      const int kb = k0 + 32 * t;
+      if (kb + 32 > klen || (CAUSAL && kb + 31 > w0)) {      // wave-uniform
 #pragma unroll
-        for (int r = 0; r < 16; ++r) st[t][r] = seen(t, r) ? st[t][r] : -3.0e38f;
+        for (int r = 0; r < 16; ++r) {
+          const int key = kb + tile_row(r, lane);
+          st[t][r] = (key < klen && (!CAUSAL || key <= q)) ? st[t][r] : -3.0e38f;      // its exponential is 0: m2 is -1e30 at least
+        }
+      }
+      mloc[t] = st[t][0];
+#pragma unroll
+      for (int r = 1; r < 16; ++r) mloc[t] = fmaxf(mloc[t], st[t][r]);
     }
-    float mloc = st[0][0];
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+    for (int t = 0; t < 2; ++t) mloc[t] = fmaxf(mloc[t], __shfl_xor(mloc[t], 32));
+    float alpha[2], ps[2];
+    bool moved[2];
 #pragma unroll
-      for (int r = 0; r < 16; ++r) mloc = fmaxf(mloc, st[t][r]);
-    mloc = fmaxf(mloc, __shfl_xor(mloc, 32));
-    const float mn = fmaxf(m2, mloc * SCALE2);
-    if (__any(mn != m2)) {      // otherwise every lane's factor is 1
-      const float alpha = fast_exp2(m2 - mn);
-      lsum *= alpha;
-#pragma unroll
-      for (int db = 0; db < 2; ++db)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
+    for (int t = 0; t < 2; ++t) {
+      const float mn = (t == 0 || two) ? fmaxf(m2, mloc[t] * SCALE2) : m2;
+      alpha[t] = fast_exp2(m2 - mn);
+      moved[t] = __any(mn != m2);      // otherwise every lane's factor is 1
       m2 = mn;
+      ps[t] = 0.f;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        st[t][r] = fast_exp2(fmaf(st[t][r], SCALE2, -mn));
+        ps[t] += st[t][r];
+      }
     }
-    float ps = 0.f;
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) st[t][r] = fast_exp2(fmaf(st[t][r], SCALE2, -m2));
-    if (edge) {
-#pragma unroll
-      for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) st[t][r] = seen(t, r) ? st[t][r] : 0.f;
-    }
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) ps += st[t][r];
-    lsum += ps;
 #pragma unroll
     for (int t = 0; t < 2; ++t)
       if (t == 0 || two) {
+        if (moved[t]) {
+          lsum *= alpha[t];
+#pragma unroll
+          for (int db = 0; db < 2; ++db)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) o[db][r] *= alpha[t];
+        }
+        lsum += ps[t];
         if (DROP) {      // the row sum keeps every key, the value sum only the survivors (scaled)
           f32x16 f;
           drop_tile_keys(drop, site, (((uint64_t)b * a.A + h) * a.Lq + q) * (uint64_t)a.Lk, k0 + 32 * t, lane, f);

@@ -443,6 +443,53 @@ def test_attention_fwd_bwd(hs, mode, B, L, A, lens):
     assert rel(got, want) < (5e-5 if mode == 0 else 1e-2)
 
 
+@pytest.mark.parametrize("causal", [0, 1])
+@pytest.mark.parametrize("L", [40, 64, 88, 128, 200, 448])
+def test_attention_forward_rounds_against_the_maximum_of_32_keys(hs, causal, L):
+    """bf16: a probability is rounded relative to the largest score of the keys up to its own 32, so the largest of every 32 that
+    raises the maximum is exactly one.  Against float64 with these two roundings (probabilities, result) and no other: what is left are
+    ties of a rounding (fp32 scores are good to 1e-6, so 5e-4 of the probabilities, by 2^-8 each, and as many results: 1.3e-4 of
+    the result, bound twice that; a maximum over 64 keys is up to 1.4e-3 off), and since a tie is as far off on either side, the error
+    against the exact result is that of the roundings to (1.3e-4 / 2e-3)^2 / 2 of itself at most, 2e-3, and in the mean over 1e5 results not
+    at all: bound 5e-4 (a maximum over 64 keys: 1e-3 to 1.4e-2 from 64 positions on)."""
+    A, B = 4, 2048 // L
+    H = A * 64
+    gen = torch.Generator(device="cuda").manual_seed(L)
+    q, k, v = (torch.randn(B * L, H, generator=gen, device="cuda").bfloat16() for _ in range(3))
+    lens = torch.tensor([max(1, L - 3 * (i % 12)) for i in range(B)], dtype=torch.int32, device="cuda")
+    ctx = torch.zeros(B * L, H, dtype=torch.bfloat16, device="cuda")
+    lse = torch.zeros(B * A * L, device="cuda")
+    if causal:
+        hs.hs_op_attention_general_fwd(1, q, H, k, v, H, lens, lens, B, L, L, A, 1, ctx, lse)
+    else:
+        hs.hs_op_attention_fwd(1, torch.cat([q, k, v], 1).contiguous(), lens, B, L, A, ctx, lse)
+    torch.cuda.synchronize()
+    heads = lambda x: x.double().view(B, L, A, 64).transpose(1, 2)
+    qh, kh, vh = heads(q), heads(k), heads(v)
+    real = torch.arange(L, device="cuda")[None] < lens[:, None]
+    s = qh @ kh.transpose(-1, -2) / 8.0
+    s = s.masked_fill(~real[:, None, None, :], -1e30)
+    if causal:
+        s = s.masked_fill(~torch.ones(L, L, dtype=torch.bool, device="cuda").tril(), -1e30)
+    exact = torch.softmax(s, -1) @ vh
+    m = torch.full_like(s[..., :1], -1e20)
+    z, o = torch.zeros_like(m), torch.zeros_like(exact)
+    for k0 in range(0, L, 32):
+        t = s[..., k0:k0 + 32]
+        mn = torch.maximum(m, t.amax(-1, keepdim=True))
+        p, scale = torch.exp(t - mn), torch.exp(m - mn)
+        z = z * scale + p.sum(-1, keepdim=True)
+        o = o * scale + p.bfloat16().double() @ vh[..., k0:k0 + 32, :]
+        m = mn
+    want = (o / z).bfloat16().double()
+    rows = real[:, None, :].expand(B, A, L)
+    got, want, exact = heads(ctx)[rows], want[rows], exact[rows]
+    err = lambda a, b: float((a - b).norm() / exact.norm())
+    print(f"L={L} causal={causal}: off the rounded sums {err(got, want):.2e}, error {err(got, exact):.4e}, of the roundings {err(want, exact):.4e}")
+    assert err(got, want) < 2.5e-4
+    assert err(got, exact) < 1.0005 * err(want, exact)
+
+
 # 264 (sequence, head) pairs take one block each, 132 take two: the same numbers either way
 @pytest.mark.parametrize("L", [8, 40, 104, 128])
 def test_attention_backward_in_one_block_and_in_two(hs, L):
