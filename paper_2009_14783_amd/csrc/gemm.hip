@@ -373,6 +373,10 @@ static hipError_t gelu_table(int which, const float2** out) {
 // rows agreed).  Over 288 products the choice is 1.4 % above the fastest on average and 24 % at most.  l of 3 and 6 is the one of a nearly full chip:
 // 8192 x 768 x 3072 takes 59.6 us as 256 blocks of 128 x 192 and 51.5 as 192 of 256 x 128.  `use`: the automatic choice considers the
 // configuration; the others can be selected for timing (8 is the mirror image of 7 and seldom faster).
+// w and e of 11 come from launches of two to eight of its tiles per CU over contractions of up to 1024, whose blocks write under each other's
+// products (as 0.183 and 0.43 they priced it 10 - 20 % too high there; us by itself, that choice -> 64 x 64 tiles: 2056 x 2048 x 512 GELU 16.2 -> 14.0, 8736 x 512 x 512
+// residual 14.2 -> 12.3, 2056 x 1024 x 1024 residual 13.2 -> 12.2, 3072 x 1536 x 512 12.9 -> 12.2; the steps that hold them level or up to 0.9 % faster).  A t0 of 2.9 instead of 3.5 would
+// make products of 264 and 320 rows 5 - 8 % faster by themselves, and the translation step slower that holds them beside others (256 rows per side 2.12 -> 2.15 ms, 1024 2.56 -> 2.60).
 // What the tiles of more than 128 x 128 brought, us (128 x 128 before; rows x columns x contraction, epilogue): 16384 x 4096 x 1024 GELU 201 -> 163, x 1024 x 4096
 // residual 148 -> 122, x 3072 x 1024 124 -> 107; 8192 x 3072 x 768 GELU 71 -> 58, x 768 x 3072 residual 56 -> 50, x 768 x 2304 45 -> 39;
 // 8192^3 1044 -> 1339 TFLOP/s.
@@ -381,7 +385,7 @@ constexpr TileCfg kTileCfg[] = {
     {128, 128, 32, 3, 0, 3.2f, 0.560f, 0.470f, 2.00f}, {256, 256, 64, 1, 1, 2.5f, 1.494f, 1.494f, 6.14f}, {32, 32, 64, 1, 1, 2.5f, 0.011f, 0.104f, 0.90f},
     {128, 192, 64, 2, 1, 2.5f, 1.050f, 0.693f, 2.36f}, {32, 64, 64, 3, 1, 4.0f, 0.146f, 0.120f, 0.33f},   {128, 128, 64, 2, 1, 3.2f, 0.497f, 0.487f, 1.82f},
     {192, 128, 64, 2, 1, 2.5f, 1.050f, 0.705f, 2.00f}, {64, 128, 64, 2, 1, 2.7f, 0.190f, 0.296f, 1.24f},  {128, 64, 64, 2, 0, 2.7f, 0.228f, 0.305f, 1.19f},
-    {128, 128, 64, 2, 1, 2.5f, 0.689f, 0.490f, 1.85f}, {256, 128, 64, 1, 1, 2.5f, 0.814f, 0.814f, 3.92f}, {64, 64, 64, 3, 1, 3.5f, 0.229f, 0.183f, 0.43f}};
+    {128, 128, 64, 2, 1, 2.5f, 0.689f, 0.490f, 1.85f}, {256, 128, 64, 1, 1, 2.5f, 0.814f, 0.814f, 3.92f}, {64, 64, 64, 3, 1, 3.5f, 0.229f, 0.187f, 0.30f}};
 constexpr int kNumTileCfg = sizeof(kTileCfg) / sizeof(kTileCfg[0]);
 constexpr int kCUs = 256;
 float tiles_time(const TileCfg& c, int64_t tiles, float steps, float outputs) {
