@@ -203,10 +203,10 @@ hs_status hs_encoder_fwd(hs_ctx* ctx, const void* w, const int32_t* ids, const i
   // pass (dropout numbers the elements of the whole batch: each half gets the state with its offset).  Not with
   // per-launch timing.
   // (Measured on 64 x 128 tokens, 12 layers: one part 2.76 ms, two 2.43 ms, three 2.49 ms, four 2.46 ms.)
-  // From 2^24 elements per activation on the products fill the chip with 256 x 256 tiles by themselves (16384 x 1024: 256 tiles), and halves
-  // only make for fewer tiles per launch: BERT-large with 16384 rows 156.0 ms per step whole, 159.1 in halves (BERT-base with 17472 rows,
-  // 13.4 million elements: 15.35 whole, 15.15 in halves).
-  const bool split = ctx->prof == nullptr && B >= 2 && T >= 4096 && (int64_t)T * H < ((int64_t)1 << 24);
+  // Large ones too: only where the 256 x 256 tiles of an H-wide output come out as one per CU is a whole batch as good (ms per step in halves, whole;
+  // sequences of 512 positions, BERT-large: 28 32.69, 33.51; 30 35.15, 35.31; 31 (248 tiles) 36.17, 36.11; 32 (256) 37.13, 36.93; 36 42.57, 43.30; BERT-base: 40 15.96,
+  // 16.10; 42 (252) 16.66, 16.66; 43 17.69, 18.17; 56 22.26, 22.96; fp32, BERT-base 43 175.2, 180.2, BERT-large 34 430, 448).
+  const bool split = ctx->prof == nullptr && B >= 2 && T >= 4096;
   const int nparts = split ? 2 : 1;
   if (split) HS_TRY(ensure_side_stream(ctx, 2));
   if (split) {
