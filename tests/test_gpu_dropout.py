@@ -92,6 +92,13 @@ def test_two_layer_bf16_short_sequences_fused_backward():
     run_case(model, "bf16", [128, 100, 64, 17, 128, 96], 128, dict(p=0.1, seed=99, stream=1), 13, 2e-2)
 
 
+@pytest.mark.parametrize("L,B", [(128, 66), (72, 67)])
+def test_two_layer_bf16_more_than_256_heads_in_one_block_each(L, B):
+    """264 and 268 (sequence, head) pairs: the short backward pass does both halves of a pair in one block (up to 256 it takes two)."""
+    model = dict(n_layers=2, hidden=256, n_heads=4, ffn=512, vocab=2000, max_pos=128, ln_eps=1e-12)
+    run_case(model, "bf16", [max(1, L - 3 * (i % 40)) for i in range(B)], L, dict(p=0.1, seed=101, stream=4), 17, 2e-2)
+
+
 def test_two_layer_bf16_long_sequences_two_kernel_backward():
     model = dict(n_layers=2, hidden=256, n_heads=4, ffn=1024, vocab=2000, max_pos=256, ln_eps=1e-12)
     run_case(model, "bf16", [256, 200, 129, 31], 256, dict(p=0.1, seed=5, stream=2), 14, 2e-2)
