@@ -490,6 +490,27 @@ def test_grouped_gradients_on_ragged_wide_tiles(W):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("hidden,ffn", [(320, 1088), (448, 1088)])
+def test_grouped_gradients_on_ragged_middle_tiles(W, hidden, ffn):
+    """1032 rows and three layers handed over together: the grouped launch takes 128 x 128 tiles at widths of 320 and 1088 and 256 x 128 tiles
+    at 448 and 1088, which end inside the widths in both directions, and adds the bias gradients in them; written, then added to."""
+    model = dict(n_layers=3, hidden=hidden, n_heads=hidden // 64, ffn=ffn, vocab=200, max_pos=24, ln_eps=1e-12)
+    ocfg = O.ModelCfg(**model)
+    theta = synth.init_params(O.param_layout(ocfg), 12)
+    rng = synth.rng_for(14)
+    mb = synth.make_micro_batch(rng, [24] + [int(x) for x in rng.integers(1, 25, 42)], 24, model["vocab"], "uniform")
+    worker = W(model, "bf16", theta)
+    loss, g = gpu_micro_grad(worker, mb)
+    ol, og = oracle_micro_grad(ocfg, theta, mb, np.float32)
+    assert abs(loss - ol) / abs(ol) < TOL["bf16"]
+    compare_flat(O.param_layout(ocfg), g, og, TOL["bf16"], "grad")
+    worker.forward_backward(worker.upload(mb), worker.G, 1, 0)
+    torch.cuda.synchronize()
+    compare_flat(O.param_layout(ocfg), worker.G.cpu().numpy() - g, og, TOL["bf16"], "added")
+    worker.close()
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("compute", ["fp32", "bf16"])
 @pytest.mark.parametrize("layers", [1, 2, 9])
 def test_backward_gives_the_same_bits_in_every_workspace_it_accepts(W, layers, compute):
