@@ -1,4 +1,5 @@
-// The bf16 MFMA GEMM kernel with wide block tiles (template); instantiated per operand layout in gemm_wide_*.hip.
+// The register-staged bf16 MFMA GEMM kernel (template over the operand layouts), and what it shares with the direct-to-LDS kernels: the epilogue, the order
+// of the tiles and the lookup of grouped problems.  Instantiated per operand layout in gemm_wide_*.hip.
 #pragma once
 #include <type_traits>
 
@@ -7,18 +8,21 @@
 namespace {
 
 // ------------------------------------------------------------------------------------------
-// bf16 MFMA kernel with wide block tiles
+// bf16 MFMA kernel, operands staged through registers
 // ------------------------------------------------------------------------------------------
-// The same contraction with a block tile of (32 TI WGM) x (32 TJ WGN) x BK and one or two blocks per CU.
-// What changes against the kernel above: each wave owns TI x TJ MFMA tiles (up to 128 x 128), so one operand
-// fragment read from LDS feeds up to four MFMAs and a byte fetched from L2 up to twice as many flops; the
-// main loop is one basic block without masks or selects (ragged edges are handled by clamping the global
-// row of a chunk once, before the loop; only the last k-tiles, which may be partial or absent, go through a
-// guarded copy of the loop body); one barrier per k-tile, placed before the last 16-deep step so that the
-// matrix pipes have queued work while the waves meet; instruction order prescribed per MFMA.
-template <bool KMAJ, int R, int BK, int NT>
+// A block tile of 128 x 128 x 64, two blocks per CU, four waves of 64 x 64: an operand fragment read from LDS feeds two MFMAs.  Four k-tiles in
+// flight: two in register sets, two in LDS.  The main loop is one basic block without masks or selects (ragged edges are handled by clamping the
+// global row of a chunk once, before the loop; a contraction that ends inside a k-tile takes a guarded copy of the loop body);
+// one barrier per k-tile, placed before the last 16-deep step so that the matrix pipes have queued work while the waves meet;
+// instruction order prescribed per MFMA.
+struct WideCfg {
+  static constexpr int TI = 2, TJ = 2, WGM = 2, WGN = 2, BK = 64, NSETS = 2, OCC = 2;      // OCC: blocks per CU the register allocator leaves room for
+  static constexpr int NT = 64 * WGM * WGN, BM = 32 * TI * WGM, BN = 32 * TJ * WGN;
+  static_assert(BM == BN, "one tile type serves both operands");
+};
+template <bool KMAJ>
 struct WideTile {
-  static_assert(BK == 32 || BK == 64, "k-tile of 32 or 64");
+  static constexpr int R = WideCfg::BM, BK = WideCfg::BK, NT = WideCfg::NT;
   static constexpr int CPK = BK / 8;                      // 16-byte chunks of a k-major row
   static constexpr int LD = KMAJ ? BK : (R + MPAD);
   static constexpr int ELEMS = KMAJ ? R * BK : BK * LD;
@@ -26,11 +30,8 @@ struct WideTile {
   static constexpr int NCH = R * BK / 8 / NT;             // chunks per thread
   static_assert(R * BK / 8 % NT == 0, "tile must split evenly over the threads");
   // k-major rows sit in LDS unpadded with their chunks permuted so that 16 consecutive rows read at one
-  // k-offset, and the two 128-byte (four 64-byte) rows that 16 lanes write at once, fall into 16 different
-  // 16-byte bank groups.
-  static __device__ __forceinline__ int swz(int row, int chunk) {
-    return (BK == 64 ? (chunk ^ ((row >> 1) & 7)) : (chunk ^ ((row >> 2) & 3))) * 8;
-  }
+  // k-offset, and the two 128-byte rows that 16 lanes write at once, fall into 16 different 16-byte bank groups.
+  static __device__ __forceinline__ int swz(int row, int chunk) { return (chunk ^ ((row >> 1) & 7)) * 8; }
   // Global side: buffer loads with one 32-bit byte offset per chunk (row clamped into the matrix once) plus a
   // uniform offset that advances by one k-tile per load; reads beyond the operand's last readable chunk return
   // zero instead of faulting.
@@ -106,15 +107,14 @@ struct WideTile {
   }
 };
 
-template <bool AK, bool BKM, int TI, int TJ, int WGM, int WGN, int BK>
+template <bool AK, bool BKM>
 constexpr size_t wide_lds_bytes() {
-  constexpr int NT = 64 * WGM * WGN;
-  const size_t pipe = 2 * sizeof(bf16) * (size_t)(WideTile<AK, 32 * TI * WGM, BK, NT>::ELEMS + WideTile<BKM, 32 * TJ * WGN, BK, NT>::ELEMS);
-  const size_t stage = (size_t)WGM * WGN * 32 * (32 * TJ + 4) * sizeof(float) + kGeluTabN * sizeof(float2);   // + the GELU table
+  const size_t pipe = 2 * sizeof(bf16) * (size_t)(WideTile<AK>::ELEMS + WideTile<BKM>::ELEMS);
+  const size_t stage = (size_t)WideCfg::WGM * WideCfg::WGN * 32 * (32 * WideCfg::TJ + 4) * sizeof(float) + kGeluTabN * sizeof(float2);   // + the GELU table
   return stage > pipe ? stage : pipe;
 }
 
-// Epilogue of a wave's TI x TJ result tiles for the wide kernels, which run one or two blocks per CU: with so few
+// Epilogue of a wave's TI x TJ result tiles for this kernel and the direct-to-LDS ones, which run one to three blocks per CU: with so few
 // waves the memory latency of an epilogue has to be covered inside each wave.  Same staging through LDS as
 // tile_epilogue_lds; the residual / pre-activation values (aux) of the next 32-row slab are requested before the
 // current slab is worked on, and nothing keeps the compiler from overlapping slabs.  Regions that touch the matrix
@@ -207,12 +207,12 @@ __device__ __forceinline__ void tile_epilogue_pipe(const GemmDev& p, const f32x1
 // One block tile of C for the k-range of `split`: main loop and epilogue.
 // NSETS register sets hold the k-tiles in flight from global memory: a tile is requested NSETS iterations
 // before it is written to LDS.  EPIS: bit mask (1 << mode) of the epilogues that are compiled in.
-template <bool AK, bool BKM, int TI, int TJ, int WGM, int WGN, int BK, int NSETS, int EPIS>
+template <bool AK, bool BKM, int EPIS>
 __device__ __forceinline__ void wide_tile(const GemmDev& p, int m0, int n0, int split, unsigned char* lds_raw) {
-  constexpr int NT = 64 * WGM * WGN, BM = 32 * TI * WGM, BN = 32 * TJ * WGN, KS = BK / 16;
-  static_assert(NSETS == 1 || NSETS == 2, "one or two register sets");
-  typedef WideTile<AK, BM, BK, NT> TA;
-  typedef WideTile<BKM, BN, BK, NT> TB;
+  constexpr int TI = WideCfg::TI, TJ = WideCfg::TJ, WGM = WideCfg::WGM, WGN = WideCfg::WGN, BK = WideCfg::BK, NSETS = WideCfg::NSETS;
+  constexpr int NT = WideCfg::NT, KS = BK / 16;
+  typedef WideTile<AK> TA;
+  typedef WideTile<BKM> TB;
   bf16* const sA0 = (bf16*)lds_raw;                       // two A buffers, then two B buffers
   bf16* const sB0 = (bf16*)lds_raw + 2 * TA::ELEMS;
 
@@ -253,10 +253,8 @@ __device__ __forceinline__ void wide_tile(const GemmDev& p, int m0, int n0, int 
   // prologue: tiles 0 .. NSETS requested, tile 0 in LDS buffer 0, its first fragments in registers
   TA::template load<true>(ra[0], ca, kleft(0), tid);
   TB::template load<true>(rb[0], cb, kleft(0), tid);
-  if (NSETS == 2) {
-    TA::template load<true>(ra[NSETS - 1], ca, kleft(1), tid);
-    TB::template load<true>(rb[NSETS - 1], cb, kleft(1), tid);
-  }
+  TA::template load<true>(ra[1], ca, kleft(1), tid);
+  TB::template load<true>(rb[1], cb, kleft(1), tid);
   TA::template store<true>(ra[0], sA0, kleft(0), tid);
   TB::template store<true>(rb[0], sB0, kleft(0), tid);
   TA::template load<true>(ra[0], ca, kleft(NSETS), tid);
@@ -274,10 +272,10 @@ __device__ __forceinline__ void wide_tile(const GemmDev& p, int m0, int n0, int 
   // for the last iterations, whose requests go to tiles that do not exist: those are sent beyond the end of the
   // operand (see `past`), where a buffer load returns zeros without touching memory, and what they bring is written
   // to the LDS buffer nobody reads any more.
-  const unsigned past = 0x80000000u;            // beyond any operand this kernel accepts less one k-tile row range
+  const unsigned past = 0x80000000u;            // beyond an operand of up to 2 GiB (in a larger one: somewhere in it or behind its end)
   auto body = [&](auto fast_tag, auto cur_tag, int t) __attribute__((always_inline)) {
     constexpr bool FAST = decltype(fast_tag)::value;
-    constexpr int cur = decltype(cur_tag)::value, nxt = cur ^ 1, set = (NSETS == 2) ? nxt : 0;
+    constexpr int cur = decltype(cur_tag)::value, nxt = cur ^ 1, set = nxt;
     constexpr int NM = TI * TJ;
     constexpr int NF = TI + TJ;                                         // fragments per step
     constexpr int NWR = TA::NCH + TB::NCH;                              // LDS writes (= global loads) per k-tile
@@ -402,9 +400,8 @@ __device__ __forceinline__ void tile_of_block(int b, int nbx, int nby, int& tm, 
   tn = in_group / gm;
 }
 
-// OCC: blocks per CU the register allocator leaves room for.
-template <bool AK, bool BKM, int TI, int TJ, int WGM, int WGN, int BK, int NSETS, int OCC>
-__global__ __launch_bounds__(64 * WGM * WGN) __attribute__((amdgpu_waves_per_eu(OCC * WGM * WGN / 4, OCC * WGM * WGN / 4)))
+template <bool AK, bool BKM>
+__global__ __launch_bounds__(WideCfg::NT) __attribute__((amdgpu_waves_per_eu(WideCfg::OCC * WideCfg::NT / 256, WideCfg::OCC * WideCfg::NT / 256)))
 void gemm_bf16_wide(GemmDev p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
   // tile order: as in gemm_bf16_mfma (a contiguous range of (split, tile) pairs per XCD, groups of tile rows)
@@ -414,8 +411,8 @@ void gemm_bf16_wide(GemmDev p) {
   if (v < 8 * per_xcd) v = (v & 7) * per_xcd + (v >> 3);
   const int split = v / nb;
   int tm, tn;
-  tile_of_block<(TI * WGM >= 8) ? 4 : 8>(v - split * nb, nbx, nby, tm, tn);
-  wide_tile<AK, BKM, TI, TJ, WGM, WGN, BK, NSETS, reg_staged_epilogues<AK, BKM>()>(p, tm * 32 * TI * WGM, tn * 32 * TJ * WGN, split, lds_raw);
+  tile_of_block<8>(v - split * nb, nbx, nby, tm, tn);
+  wide_tile<AK, BKM, reg_staged_epilogues<AK, BKM>()>(p, tm * WideCfg::BM, tn * WideCfg::BN, split, lds_raw);
 }
 
 // Several products in one launch: block v works on tile v - first_tile[i] of problem i (the problems' tiles are numbered one
@@ -438,33 +435,19 @@ __device__ __forceinline__ GemmDev group_problem(const GemmGroupDev& g, int& tm,
   p.rowsum = tn == 0 ? q.rowsum : nullptr;
   return p;
 }
-template <bool AK, bool BKM, int TI, int TJ, int WGM, int WGN, int BK, int NSETS, int OCC>
-hipError_t launch_wide_one(const GemmDev& p, dim3 grid, hipStream_t s) {
-  constexpr int NT = 64 * WGM * WGN;
-  constexpr size_t lds = wide_lds_bytes<AK, BKM, TI, TJ, WGM, WGN, BK>();
-  static_assert(lds <= 160 * 1024, "tile does not fit the LDS of a CU");
-  auto kern = gemm_bf16_wide<AK, BKM, TI, TJ, WGM, WGN, BK, NSETS, OCC>;
+template <bool AK, bool BKM>
+hipError_t launch_wide(const GemmDev& p, int splits, hipStream_t s) {
+  constexpr size_t lds = wide_lds_bytes<AK, BKM>();
+  static_assert(WideCfg::OCC * lds <= 160 * 1024, "the blocks of a CU do not fit its LDS");
+  auto kern = gemm_bf16_wide<AK, BKM>;
   static bool configured = false;          // per instantiation; the attribute is per process and device-wide
   if (!configured && lds > 48 * 1024) {
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
   configured = true;
-  hipLaunchKernelGGL(kern, grid, dim3(NT), lds, s, p);
+  hipLaunchKernelGGL(kern, dim3((p.N + WideCfg::BN - 1) / WideCfg::BN, (p.M + WideCfg::BM - 1) / WideCfg::BM, splits), dim3(WideCfg::NT), lds, s, p);
   return hipSuccess;
-}
-
-// the configurations of gemm_bf16_wide that are built (numbers: kTileCfg in gemm.hip)
-template <bool AK, bool BKM>
-hipError_t launch_wide_layout(int cfg, const GemmDev& p, int splits, hipStream_t s) {
-#define HS_WIDE(TI, TJ, WGM, WGN, BK, NSETS, OCC)                                                        \
-  return launch_wide_one<AK, BKM, TI, TJ, WGM, WGN, BK, NSETS, OCC>(                                     \
-      p, dim3((p.N + 32 * TJ * WGN - 1) / (32 * TJ * WGN), (p.M + 32 * TI * WGM - 1) / (32 * TI * WGM), splits), s)
-  switch (cfg) {
-    case 5: HS_WIDE(2, 2, 2, 2, 64, 2, 2);
-    default: return hipErrorInvalidValue;
-  }
-#undef HS_WIDE
 }
 
 }  // namespace
