@@ -554,7 +554,10 @@ hs_status launch_gemm_group(hs_ctx* ctx, const GemmArgs* gs, int n, hipStream_t 
       // translation step with 4096 rows per side 4.56 -> 4.47 and 4.74 -> 4.67 (256 x 256); a quarter of them: BERT-base with 8192 rows 7.52 -> 7.69.
       float best = 3.0e38f;
       for (int c : {1, 9, 10, 11}) {
-        const TileCfg& t = kTileCfg[c];
+        TileCfg t = kTileCfg[c];
+        // the grouped 64 x 64 kernel is another one than 11 (it reads fragments ahead) and has its own w and e: with those of 11 passes of up to 64
+        // rows take it instead of 256 x 256 tiles (one row of them) and are slower (32 rows: BERT-base 2.126 -> 2.150 ms per step, BERT-large with 64 5.21 -> 5.32)
+        if (c == 11) { t.w = 0.183f; t.e = 0.43f; }
         const int tiles = count(t.bm, t.bn);
         float steps = 0.0f;
         for (int i = 0; i < gd.n; ++i) steps += (float)(gd.first_tile[i + 1] - gd.first_tile[i]) * ((gd.prob[i].K + 63) / 64);
