@@ -370,7 +370,8 @@ static hipError_t gelu_table(int which, const float2** out) {
 // of a tile.  The constants (us) are fitted to launches on this chip: rows 264 .. 17472, the forward and activation-gradient products of
 // widths 512, 768 and 1024 with their epilogues, weights not in the cache of the launch before (2, 4 and 11, whose launches are shorter than
 // the host takes to enqueue them, to a fit over 32 .. 4104 rows, and their t0 raised together until the translation step at 4096 rows per side and BERT-base at 264
-// rows agreed).  Over 288 products the choice is 1.4 % above the fastest on average and 24 % at most.  l of 3 and 6 is the one of a nearly full chip:
+// rows agreed).  Over 168 products of 264 to 16384 rows the choice is 2.6 % above the fastest tiling on average and 28 % in the worst case (520 rows, contraction
+// of 4096), over 408 of up to 17472 rows in another run, with another card and other buffers, 1.1 % and 12 %.  l of 3 and 6 is the one of a nearly full chip:
 // 8192 x 768 x 3072 takes 59.6 us as 256 blocks of 128 x 192 and 51.5 as 192 of 256 x 128.  `use`: the automatic choice considers the
 // configuration; the others can be selected for timing (8 is the mirror image of 7 and seldom faster).
 // w and e of 11 come from launches of two to eight of its tiles per CU over contractions of up to 1024, whose blocks write under each other's
@@ -450,9 +451,9 @@ static void choose_cfg(const GemmArgs& g, int* cfg, int* splits) {
   int only = -1;
   if (!supported) only = 0;
   else if (gemm_cfg_override >= 0) only = some_size ? gemm_cfg_override : 0;
-  // a few k-tiles per tile and several tiles per CU: three blocks per CU hide the writing better than two (8192 x 3072 x 128: 17.4
-  // against 25.5 us, 30522 x 768 x 64: 14.4 against 18.4; at K = 256 and with a residual the two are level, with an
-  // fp32 result the two win)
+  // a few k-tiles per tile and several tiles per CU: three blocks per CU hide the writing better than what the model would take (8192 x 3072 x 128:
+  // 21.0 against 22.5 us, 16384 x 1536 x 64: 17.2, 18.7, 8736 x 2304 x 192: 20.5, 22.5, 30522 x 768 x 64: 18.4, 18.7; with a residual the two are level, with
+  // an fp32 result the others win)
   if (only < 0 && g.a_kmajor && g.b_kmajor && g.epi == 0 && !g.c_f32 && g.K < 256 && (int64_t)((g.M + 127) / 128) * ((g.N + 127) / 128) > kCUs) only = 0;
   if (supported && !whole_k && only != 0) only = some_size ? 5 : 0;
   const bool gate = g.epi == 5;      // not in the register-staged kernels
@@ -469,13 +470,13 @@ static void choose_cfg(const GemmArgs& g, int* cfg, int* splits) {
     const int64_t most = g.ws ? std::min<int64_t>({32, g.K / (4 * kTileCfg[c].bk), (int64_t)(g.ws_bytes / ((size_t)g.M * g.N * sizeof(float)))}) : 1;
     const int64_t tiles = (int64_t)((g.M + kTileCfg[c].bm - 1) / kTileCfg[c].bm) * ((g.N + kTileCfg[c].bn - 1) / kTileCfg[c].bn);
     for (int sp = 1; sp <= std::max<int64_t>(1, most); sp *= 2) {
-      // 5 and 9 are the same tile (figures with the direct kernel as it was before it read fragments ahead).  The register-staged pipeline (5) has four k-tiles in flight, the direct one (9) two: a block that has
-      // its CU to itself is faster with the first from about 16 whole k-tiles on (A m-major, 3072 x 768 x 8192: 62 against 78 us, at K = 1216
-      // 17.0 against 18.3; 4096 x 1024 x 4096, A k-major: 38 against 46), two blocks that cover each other with the second (the
-      // embedding gradient of the translation step, 37000 x 512: 4.97 against 4.83 ms for the step), and so is any block whose contraction
-      // ends inside a k-tile (3072 x 768 x 520: 16.2 against 12.7).  Of split contractions beyond 8192 the second with twice the splits
-      // is (1216 x 768 x 32768: 10 %).  Forward products are faster with the first either way, the two halves of a batch running
-      // beside each other.
+      // 5 and 9 are the same tile.  The register-staged pipeline (5) has four k-tiles in flight, the direct one (9) two: a block that has
+      // its CU to itself is faster with the first from about 16 whole k-tiles on (us, 5 against 9; A m-major, 3072 x 768 x 8192: 73, 99, at K = 1216 16.9, 18.2;
+      // 4096 x 1024 x 4096, A k-major: 38.7, 44.7, both k-major 38.3, 43.8), two blocks that cover each other with the second
+      // (30522 x 768 x 1232, A m-major: 111, 88; activation gradients of contractions up to 1024 3 % on average over 60 products), and so is any block whose contraction
+      // ends inside a k-tile (3072 x 768 x 520: 15.3, 12.0).  Of split contractions beyond 8192 the second with twice the splits
+      // is (1216 x 768 x 32768: 85, 77).  Forward products take the first: with one tile per CU it is 8 - 20 % faster by itself, with more the second is 3 %
+      // (contractions up to 1024, 96 products) or the first is (longer ones), and twelve training steps of 3 to 20 ms were level to 0.3 % with either.
       const bool lone = !gate && tiles * sp <= kCUs && g.K > 1024 && g.K % 64 == 0 && (sp == 1 || g.K <= 8192);
       if (only < 0 && (c == 5 || c == 9) && c != (forward || lone ? 5 : 9)) continue;
       float steps = (float)((g.K + 63) / 64) / sp;

@@ -24,13 +24,14 @@ struct GroupProb {
   const void *A, *B; float *C, *rowsum;
   int lda, ldb, ldc, M, N, K;
 };
-constexpr int kGroupMax = 48;      // 2.5 KB of kernel arguments
+constexpr int kGroupMax = 48;      // 2.9 KB of kernel arguments
 struct GemmGroupDev {
   int n;                           // problems in use
   float beta;
   int first_tile[kGroupMax + 1];   // first_tile[i] .. first_tile[i + 1] - 1: the tiles of problem i
   GroupProb prob[kGroupMax];
 };
+static_assert(sizeof(GemmGroupDev) <= 4096, "arguments of one launch");
 
 // Piecewise-linear tables of the normal cdf Phi (GELU(x) = x Phi(x)) and of GELU'(x) = Phi(x) + x pdf(x) on
 // [-6, 6]: entry i holds the value at -6 + i h and the increment to the next node, h = 12 / 1024.  Error of the
