@@ -203,10 +203,13 @@ hs_status hs_encoder_fwd(hs_ctx* ctx, const void* w, const int32_t* ids, const i
   // pass (dropout numbers the elements of the whole batch: each half gets the state with its offset).  Not with
   // per-launch timing.
   // (Measured on 64 x 128 tokens, 12 layers: one part 2.76 ms, two 2.43 ms, three 2.49 ms, four 2.46 ms.)
-  // Large ones too: only where the 256 x 256 tiles of an H-wide output come out as one per CU is a whole batch as good (ms per step in halves, whole;
-  // sequences of 512 positions, BERT-large: 28 32.69, 33.51; 30 35.15, 35.31; 31 (248 tiles) 36.17, 36.11; 32 (256) 37.13, 36.93; 36 42.57, 43.30; BERT-base: 40 15.96,
-  // 16.10; 42 (252) 16.66, 16.66; 43 17.69, 18.17; 56 22.26, 22.96; fp32, BERT-base 43 175.2, 180.2, BERT-large 34 430, 448).
-  const bool split = ctx->prof == nullptr && B >= 2 && T >= 4096;
+  // Except where the 256 x 256 tiles of an H-wide bf16 output come out as one for nearly every CU: halves of it have half a round each.  Ms per step in
+  // halves, whole; BERT-large, sequences of 512: 28 (224 tiles) 32.69, 33.51; 30 (240) 35.15, 35.31; 31 (248) 37.33, 37.03; 32 (256) 38.08, 37.72;
+  // 36 (288) 42.57, 43.30; 63 (504) 71.64, 72.26; 128 x 128 (256) 35.71, 35.35; BERT-base: 40 (240) 15.96, 16.10; 41 (246) 16.79, 16.73; 42 (252) 17.05, 16.98;
+  // 43 (258) 17.69, 18.17; 84 (504) 32.73, 33.26; 170 x 128 (255) 15.97, 15.83.  fp32 has no such tiles: BERT-base 43 175.2, 180.2, BERT-large 34 430, 448.
+  const int64_t wide_tiles = (int64_t)((T + 255) / 256) * (H / 256);
+  const bool one_round = dt == HS_BF16 && H >= 768 && H % 256 == 0 && wide_tiles >= 246 && wide_tiles <= 256;
+  const bool split = ctx->prof == nullptr && B >= 2 && T >= 4096 && !one_round;
   const int nparts = split ? 2 : 1;
   if (split) HS_TRY(ensure_side_stream(ctx, 2));
   if (split) {

@@ -114,3 +114,9 @@ def test_large_batch_runs_as_two_halves_with_the_masks_of_the_whole_batch():
     from its offset in the whole batch; the oracle knows nothing of halves."""
     lens = [int(x) for x in synth.draw_lengths(synth.rng_for(40), 64, 5, 64)]
     run_case(synth.MODELS["tiny"], "fp32", lens, 64, dict(p=0.1, seed=77, stream=4), 16, 1e-4)
+
+
+def test_whole_batch_of_one_wide_tile_per_cu():
+    """128 x 128 positions of 1024 columns in bf16: 256 tiles of 256 x 256, the one kind of large batch whose forward pass is not cut in halves."""
+    model = dict(n_layers=1, hidden=1024, n_heads=16, ffn=1024, vocab=512, max_pos=128, ln_eps=1e-12)
+    run_case(model, "bf16", [128 - (i % 9) for i in range(128)], 128, dict(p=0.1, seed=31, stream=6), 18, 2e-2)
