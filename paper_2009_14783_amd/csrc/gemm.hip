@@ -553,6 +553,8 @@ hs_status launch_gemm_group(hs_ctx* ctx, const GemmArgs* gs, int n, hipStream_t 
       // step if all CUs have to be filled -> half of them: BERT-large with 16384 rows 153.3 -> 148.8 (256 x 256 tiles on 192 CUs, and the chain on
       // the others: 480 us against 530, its LayerNorm backward 27 against 54), two updates of 4096 rows 10.7 -> 10.2 (256 x 128), the
       // translation step with 4096 rows per side 4.56 -> 4.47 and 4.74 -> 4.67 (256 x 256); a quarter of them: BERT-base with 8192 rows 7.52 -> 7.69.
+      // Over 30 steps of other sizes (264 to 12288 rows; translation, BERT-base, BERT-large) all CUs are level or up to 3 % slower than half (BERT-large 12 x 512 17.39 -> 17.87,
+      // BERT-base 33 x 128 4.97 -> 5.06, translation 31 x 256 6.51 -> 6.69), a quarter is 1.1 % faster to 2.6 % slower (BERT-base 16 x 128 3.70 -> 3.66, 33 x 128 4.97 -> 5.10).
       float best = 3.0e38f;
       for (int c : {1, 9, 10, 11}) {
         TileCfg t = kTileCfg[c];
