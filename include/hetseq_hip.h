@@ -134,6 +134,20 @@ hs_status hs_set_dropout(hs_ctx* ctx, double p, uint64_t seed, uint32_t stream);
  * state of ctx to mask_out [n] (dev). */
 hs_status hs_dropout_keep_mask(hs_ctx* ctx, uint32_t site, size_t n, uint8_t* mask_out, void* stream);
 
+/* ---- lengths known on the host ----------------------------------------------------------------
+ * Section "Forward Pass": the sequences of a batch are padded to one length.  hs_set_lengths tells the context the lengths of the
+ * batch that the following hs_encoder_fwd / hs_encoder_bwd calls work on (lens_host [B], copied; host state only), so that the
+ * calls can leave the padding out: they compute the real positions only, one matrix row each (bf16 contexts; fp32 ones keep
+ * the padded rows).  The buffers of the calls stay as they are described below, [B, L] with the lengths in `lens` (dev), which must
+ * be the same ones; rows of padded positions of hidden_out are then zeros, and those of d_hidden are not read.  The backward call
+ * of a micro-batch must see the state its forward call saw.  lens_host == NULL (the initial state): padded rows again.  While set,
+ * a forward or backward call over another B or L fails with HS_ERR_STATE.  Calls that are captured into a graph have the sizes of
+ * these lengths in every replay.  HS_ERR_INVALID_ARG for a length outside [1, L]; the state is then as after NULL. */
+hs_status hs_set_lengths(hs_ctx* ctx, const int32_t* lens_host, int32_t B, int32_t L);
+/* The same for hs_s2s_fwd / hs_s2s_bwd: the lengths of both sides, or NULL for both. */
+hs_status hs_s2s_set_lengths(hs_ctx* ctx, const int32_t* src_lens_host, const int32_t* tgt_lens_host, int32_t B, int32_t Ls,
+                             int32_t Lt);
+
 /* ---- host data path ---------------------------------------------------------------------------
  * Section "Dataset and Dataloader": the dataset is split into shards, the lengths of the shards are
  * accumulated and the index of a training instance is mapped to an offset inside its shard; the

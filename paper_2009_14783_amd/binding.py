@@ -69,6 +69,8 @@ _SIGNATURES = {
     "hs_cast_params": (_I32, [_P, _P, _SZ, _I32, _P]),
     "hs_arm_update": (_I32, [_P, _P, _P, _P, _P, _P, _D, _D, _D, _D, _D, _D, _I64]),
     "hs_set_dropout": (_I32, [_P, _D, C.c_uint64, C.c_uint32]),
+    "hs_set_lengths": (_I32, [_P, _P, _I32, _I32]),
+    "hs_s2s_set_lengths": (_I32, [_P, _P, _P, _I32, _I32, _I32]),
     "hs_dropout_keep_mask": (_I32, [_P, C.c_uint32, _SZ, _P, _P]),
     "hs_shard_write": (_I32, [C.c_char_p, _P, _I64, _P]),
     "hs_dataset_open": (_I32, [C.POINTER(C.c_char_p), _I32, _I64, _I32, C.POINTER(_P)]),
@@ -323,6 +325,14 @@ def hs_arm_update(ctx, w, m, v, G, w_lowp_out, denom, lr, beta1, beta2, eps, wei
 
 def hs_set_dropout(ctx, p, seed, stream_no):
     _check(lib().hs_set_dropout(ctx, float(p), int(seed) & 0xFFFFFFFFFFFFFFFF, int(stream_no) & 0xFFFFFFFF), ctx)
+
+
+def hs_set_lengths(ctx, lens_host, B=0, L=0):
+    _check(lib().hs_set_lengths(ctx, _ptr(lens_host), B, L), ctx)
+
+
+def hs_s2s_set_lengths(ctx, src_lens_host, tgt_lens_host, B=0, Ls=0, Lt=0):
+    _check(lib().hs_s2s_set_lengths(ctx, _ptr(src_lens_host), _ptr(tgt_lens_host), B, Ls, Lt), ctx)
 
 
 def hs_dropout_keep_mask(ctx, site, n, mask_out, stream=None):

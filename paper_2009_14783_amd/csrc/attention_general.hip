@@ -38,9 +38,13 @@ struct View {
   int64_t ldq, ldkv;          // row strides in elements
   const int32_t *qlens, *klens;
   int Lq, Lk, A;
+  const int32_t *qfirst, *kfirst;      // packed rows: first row of each sequence, or null (b Lq, b Lk)
 };
 
 __device__ __forceinline__ int clamp_len(int n, int L) { return n < 1 ? 1 : (n > L ? L : n); }
+// first row of sequence b, and the rows that a sequence has: with packed rows the row behind its last one is the next sequence's
+__device__ __forceinline__ int64_t first_row(const int32_t* first, int b, int L) { return first ? first[b] : (int64_t)b * L; }
+__device__ __forceinline__ int row_count(const int32_t* first, int len, int L) { return first ? len : L; }
 
 // ------------------------------------------------------------------------------------------
 // bf16 MFMA
@@ -138,12 +142,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DROP ? 3 : 
   int b, h, row0;
   block_place(b, h, row0);
   const int H = a.A * DH;
-  const int klen = clamp_len(a.klens[b], a.Lk);
+  const int klen = clamp_len(a.klens[b], a.Lk), qrows = a.qfirst ? clamp_len(a.qlens[b], a.Lq) : a.Lq;
+  if (row0 >= qrows) return;      // block-uniform
+  const int64_t qbase = first_row(a.qfirst, b, a.Lq), kbase = first_row(a.kfirst, b, a.Lk);
   const int w0 = row0 + wave * 32, q = w0 + (lane & 31);
   const int kend = CAUSAL ? min(klen, row0 + 128) : klen;      // block-uniform
   Stream ks_, vs_;
-  ks_.init((const bf16*)a.k + (int64_t)b * a.Lk * a.ldkv + h * DH, a.ldkv, lane, wave);
-  vs_.init((const bf16*)a.v + (int64_t)b * a.Lk * a.ldkv + h * DH, a.ldkv, lane, wave);
+  ks_.init((const bf16*)a.k + kbase * a.ldkv + h * DH, a.ldkv, lane, wave);
+  vs_.init((const bf16*)a.v + kbase * a.ldkv + h * DH, a.ldkv, lane, wave);
   auto request = [&](int k0, unsigned char* __restrict__ st) __attribute__((always_inline)) {
     ks_.issue(k0, klen, st, wave);
     vs_.issue(k0, klen, st + kTileBytes, wave);
@@ -152,7 +158,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DROP ? 3 : 
 
   bf16x8 qf[4];
 #pragma unroll
-  for (int ks = 0; ks < 4; ++ks) qf[ks] = frag_rows_global((const bf16*)a.q + (int64_t)b * a.Lq * a.ldq + h * DH, a.ldq, q, a.Lq, ks, lane);
+  for (int ks = 0; ks < 4; ++ks) qf[ks] = frag_rows_global((const bf16*)a.q + qbase * a.ldq + h * DH, a.ldq, q, qrows, ks, lane);
   f32x16 o[2];
   clear(o);
   float m2 = -1.0e30f, lsum = 0.f;
@@ -160,7 +166,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DROP ? 3 : 
   auto step = [&](int k0, const unsigned char* __restrict__ cur, unsigned char* __restrict__ nxt) __attribute__((always_inline)) {
     stage_barrier();
     if (k0 + 64 < kend) request(k0 + 64, nxt);
-    if (w0 >= a.Lq || (CAUSAL && k0 > w0 + 31)) return;
+    if (w0 >= qrows || (CAUSAL && k0 > w0 + 31)) return;
     const unsigned char* const Ks = cur;
     const unsigned char* const Vs = cur + kTileBytes;
     const bool two = k0 + 32 < kend && (!CAUSAL || k0 + 32 <= w0 + 31);      // wave-uniform
@@ -235,9 +241,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DROP ? 3 : 
   // (one copy of the step: a second one for the other stage made launches over short sequences 1 us longer, and took more registers)
   for (int k0 = 0, at = 0; k0 < kend; k0 += 64, at = kStageBytes - at) step(k0, lds + at, lds + kStageBytes - at);
   lsum += __shfl_xor(lsum, 32);
-  if (q < a.Lq && lane < 32) lse[((int64_t)b * a.A + h) * a.Lq + q] = (m2 + __log2f(lsum)) * LN2;
+  if (q < qrows && lane < 32) lse[((int64_t)b * a.A + h) * a.Lq + q] = (m2 + __log2f(lsum)) * LN2;
   __syncthreads();      // every wave is done with the stages
-  store_wave_rows(out + (int64_t)b * a.Lq * H + h * DH, H, w0, a.Lq, o, 1.0f / lsum, lane, (bf16*)lds + wave * 32 * LDT, wide);
+  store_wave_rows(out + qbase * H + h * DH, H, w0, qrows, o, 1.0f / lsum, lane, (bf16*)lds + wave * 32 * LDT, wide);
 }
 
 // dq and dvec[q] = sum_d dO[q,d] O[q,d]
@@ -250,12 +256,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
   int b, h, row0;
   block_place(b, h, row0);
   const int H = a.A * DH;
-  const int klen = clamp_len(a.klens[b], a.Lk), qlen = clamp_len(a.qlens[b], a.Lq);
+  const int klen = clamp_len(a.klens[b], a.Lk), qlen = clamp_len(a.qlens[b], a.Lq), qrows = row_count(a.qfirst, qlen, a.Lq);
+  if (row0 >= qrows) return;      // block-uniform
+  const int64_t qbase = first_row(a.qfirst, b, a.Lq), kbase = first_row(a.kfirst, b, a.Lk);
   const int w0 = row0 + wave * 32, q = w0 + (lane & 31);
   const int kend = row0 >= qlen ? 0 : (CAUSAL ? min(klen, row0 + 128) : klen);
   Stream ks_, vs_;
-  ks_.init((const bf16*)a.k + (int64_t)b * a.Lk * a.ldkv + h * DH, a.ldkv, lane, wave);
-  vs_.init((const bf16*)a.v + (int64_t)b * a.Lk * a.ldkv + h * DH, a.ldkv, lane, wave);
+  ks_.init((const bf16*)a.k + kbase * a.ldkv + h * DH, a.ldkv, lane, wave);
+  vs_.init((const bf16*)a.v + kbase * a.ldkv + h * DH, a.ldkv, lane, wave);
   auto request = [&](int k0, unsigned char* __restrict__ st) __attribute__((always_inline)) {
     ks_.issue(k0, klen, st, wave);
     vs_.issue(k0, klen, st + kTileBytes, wave);
@@ -265,11 +273,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
   // padded queries (q >= qlen) own all-zero fragments and therefore produce zero rows
   bf16x8 qf[4], gf[4];
   float drow = 0.f;
-  const bf16* const go = d_out + (int64_t)b * a.Lq * H + h * DH;
-  const bf16* const oo = out + (int64_t)b * a.Lq * H + h * DH;
+  const bf16* const go = d_out + qbase * H + h * DH;
+  const bf16* const oo = out + qbase * H + h * DH;
 #pragma unroll
   for (int ks = 0; ks < 4; ++ks) {
-    qf[ks] = frag_rows_global((const bf16*)a.q + (int64_t)b * a.Lq * a.ldq + h * DH, a.ldq, q, qlen, ks, lane);
+    qf[ks] = frag_rows_global((const bf16*)a.q + qbase * a.ldq + h * DH, a.ldq, q, qlen, ks, lane);
     gf[ks] = frag_rows_global(go, H, q, qlen, ks, lane);
     const bf16x8 of = frag_rows_global(oo, H, q, qlen, ks, lane);
 #pragma unroll
@@ -326,7 +334,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
   for (int k0 = 0, at = 0; k0 < kend; k0 += 64, at = kStageBytes - at) step(k0, lds + at, lds + kStageBytes - at);
   if (q < a.Lq && lane < 32) dvec[((int64_t)b * a.A + h) * a.Lq + q] = drow;
   __syncthreads();      // every wave is done with the stages
-  store_wave_rows(dq + (int64_t)b * a.Lq * lddq + h * DH, lddq, w0, a.Lq, acc, 0.125f, lane, (bf16*)lds + wave * 32 * LDT, wide);
+  store_wave_rows(dq + qbase * lddq + h * DH, lddq, w0, qrows, acc, 0.125f, lane, (bf16*)lds + wave * 32 * LDT, wide);
 }
 
 // wave owns 32 keys, streams queries / output gradients and the two numbers of each query -> dk, dv
@@ -340,12 +348,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   int b, h, row0;
   block_place(b, h, row0);
   const int H = a.A * DH;
-  const int klen = clamp_len(a.klens[b], a.Lk), qlen = clamp_len(a.qlens[b], a.Lq);
+  const int klen = clamp_len(a.klens[b], a.Lk), qlen = clamp_len(a.qlens[b], a.Lq), krows = row_count(a.kfirst, klen, a.Lk);
+  if (row0 >= krows) return;      // block-uniform
+  const int64_t qbase = first_row(a.qfirst, b, a.Lq), kbase = first_row(a.kfirst, b, a.Lk);
   const int w0 = row0 + wave * 32, kj = w0 + (lane & 31);       // the key this lane owns
   const int qend = row0 >= klen ? 0 : qlen;
   Stream qs_, gs_;
-  qs_.init((const bf16*)a.q + (int64_t)b * a.Lq * a.ldq + h * DH, a.ldq, lane, wave);
-  gs_.init(d_out + (int64_t)b * a.Lq * H + h * DH, H, lane, wave);
+  qs_.init((const bf16*)a.q + qbase * a.ldq + h * DH, a.ldq, lane, wave);
+  gs_.init(d_out + qbase * H + h * DH, H, lane, wave);
   const float* const row_num = (wave == 0 ? lse : dvec) + ((int64_t)b * a.A + h) * a.Lq;
   auto request = [&](int q0, unsigned char* __restrict__ st) __attribute__((always_inline)) {
     qs_.issue(q0, qlen, st, wave);
@@ -362,8 +372,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   bf16x8 kf[4], vf[4];
 #pragma unroll
   for (int ks = 0; ks < 4; ++ks) {
-    kf[ks] = frag_rows_global((const bf16*)a.k + (int64_t)b * a.Lk * a.ldkv + h * DH, a.ldkv, kj, klen, ks, lane);
-    vf[ks] = frag_rows_global((const bf16*)a.v + (int64_t)b * a.Lk * a.ldkv + h * DH, a.ldkv, kj, klen, ks, lane);
+    kf[ks] = frag_rows_global((const bf16*)a.k + kbase * a.ldkv + h * DH, a.ldkv, kj, klen, ks, lane);
+    vf[ks] = frag_rows_global((const bf16*)a.v + kbase * a.ldkv + h * DH, a.ldkv, kj, klen, ks, lane);
   }
   f32x16 dk[2], dv[2];
   clear(dk);
@@ -426,14 +436,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   for (int q0 = qbeg, at = 0; q0 < qend; q0 += 64, at = kStage - at) step(q0, lds + at, lds + kStage - at);
   __syncthreads();      // every wave is done with the stages
   bf16* const area = (bf16*)lds + wave * 32 * LDT;
-  store_wave_rows(dk_out + (int64_t)b * a.Lk * lddkv + h * DH, lddkv, w0, a.Lk, dk, 0.125f, lane, area, wide);
-  store_wave_rows(dv_out + (int64_t)b * a.Lk * lddkv + h * DH, lddkv, w0, a.Lk, dv, 1.0f, lane, area, wide);
+  store_wave_rows(dk_out + kbase * lddkv + h * DH, lddkv, w0, krows, dk, 0.125f, lane, area, wide);
+  store_wave_rows(dv_out + kbase * lddkv + h * DH, lddkv, w0, krows, dv, 1.0f, lane, area, wide);
 }
 
 View make_view(const AttnOperands& x) {
   View v;
   v.q = x.q; v.k = x.k; v.v = x.v; v.ldq = x.ldq; v.ldkv = x.ldkv; v.qlens = x.qlens; v.klens = x.klens;
-  v.Lq = x.Lq; v.Lk = x.Lk; v.A = x.A;
+  v.Lq = x.Lq; v.Lk = x.Lk; v.A = x.A; v.qfirst = x.qfirst; v.kfirst = x.kfirst;
   return v;
 }
 
@@ -468,10 +478,10 @@ void stream_bwd(const AttnOperands& x, int B, const void* out, const float* lse,
 #undef HS_STREAM_BWD
 }
 
-AttnOperands self_operands(const void* qkv, const int32_t* lens, int L, int A) {
+AttnOperands self_operands(const void* qkv, const int32_t* lens, int L, int A, const int32_t* first) {
   const bf16* q = (const bf16*)qkv;
   const int64_t H = (int64_t)A * DH;
-  return AttnOperands{q, q + H, q + 2 * H, 3 * H, 3 * H, lens, lens, L, L, A, 0};
+  return AttnOperands{q, q + H, q + 2 * H, 3 * H, 3 * H, lens, lens, L, L, A, 0, first, first};
 }
 
 AttnF32 f32_problem(const AttnOperands& x) {
@@ -485,6 +495,7 @@ hs_status check_operands(hs_ctx* ctx, int dtype, const AttnOperands& x, const ch
   if (!x.q || !x.k || !x.v || !x.qlens || !x.klens) return hs_fail(ctx, HS_ERR_INVALID_ARG, std::string(who) + ": NULL operand");
   const int64_t H = (int64_t)x.A * 64;
   if (x.ldq < H || x.ldkv < H) return hs_fail(ctx, HS_ERR_SHAPE, std::string(who) + ": row stride smaller than A*64");
+  if (dtype != HS_BF16 && (x.qfirst || x.kfirst)) return hs_fail(ctx, HS_ERR_UNIMPLEMENTED, std::string(who) + ": packed rows in bf16 only");
   if (dtype == HS_BF16) {       // 16-byte fragment loads
     if ((x.ldq & 7) || (x.ldkv & 7) || ((uintptr_t)x.q & 15) || ((uintptr_t)x.k & 15) || ((uintptr_t)x.v & 15))
       return hs_fail(ctx, HS_ERR_SHAPE, std::string(who) + ": bf16 operands must be 16-byte aligned with strides that are multiples of 8");
@@ -533,12 +544,12 @@ hs_status launch_attention_general_bwd(hs_ctx* ctx, int dtype, const AttnOperand
 
 // bf16 self-attention over packed q | k | v rows (see attention.hip)
 void launch_attention_self_fwd(const void* qkv, const int32_t* lens, int B, int L, int A, void* out, float* lse, hipStream_t s, const DropCfg& drop,
-                               uint32_t site) {
-  stream_fwd(self_operands(qkv, lens, L, A), B, out, lse, s, drop, site);
+                               uint32_t site, const int32_t* first) {
+  stream_fwd(self_operands(qkv, lens, L, A, first), B, out, lse, s, drop, site);
 }
 void launch_attention_self_bwd(const void* qkv, const void* out, const float* lse, const void* d_out, const int32_t* lens, int B, int L, int A,
-                               void* dqkv, float* dvec, hipStream_t s, const DropCfg& drop, uint32_t site) {
+                               void* dqkv, float* dvec, hipStream_t s, const DropCfg& drop, uint32_t site, const int32_t* first) {
   const int64_t H = (int64_t)A * DH;
   bf16* const d = (bf16*)dqkv;
-  stream_bwd(self_operands(qkv, lens, L, A), B, out, lse, d_out, d, 3 * H, d + H, d + 2 * H, 3 * H, dvec, s, drop, site);
+  stream_bwd(self_operands(qkv, lens, L, A, first), B, out, lse, d_out, d, 3 * H, d + H, d + 2 * H, 3 * H, dvec, s, drop, site);
 }

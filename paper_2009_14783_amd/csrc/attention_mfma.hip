@@ -36,8 +36,8 @@ constexpr int kFewHeads = 256;
 template <bool DROP>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3)))
 void attn_bwd_fused128_mfma(const bf16* __restrict__ qkv, const bf16* __restrict__ out, const float* __restrict__ lse,
-                            const bf16* __restrict__ d_out, const int32_t* __restrict__ lens, int L, int A, bf16* __restrict__ dqkv,
-                            DropCfg drop, uint32_t site) {
+                            const bf16* __restrict__ d_out, const int32_t* __restrict__ lens, const int32_t* __restrict__ first, int L, int A,
+                            bf16* __restrict__ dqkv, DropCfg drop, uint32_t site) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
   bf16* T0 = (bf16*)lds_raw;               // K, then Q
   bf16* T1 = T0 + 128 * LDT;               // V, then dO
@@ -49,9 +49,11 @@ void attn_bwd_fused128_mfma(const bf16* __restrict__ qkv, const bf16* __restrict
   const int64_t ld = 3 * (int64_t)H;
   int len = lens[b];
   len = len < 1 ? 1 : (len > L ? L : len);
-  const bf16* base = qkv + (int64_t)b * L * ld + h * DH;
-  const bf16* go = d_out + (int64_t)b * L * H + h * DH;
-  const bf16* oo = out + (int64_t)b * L * H + h * DH;
+  const int64_t row0 = first ? first[b] : (int64_t)b * L;
+  const int rows = first ? len : L;              // packed rows: the row behind the last one is the next sequence's
+  const bf16* base = qkv + row0 * ld + h * DH;
+  const bf16* go = d_out + row0 * H + h * DH;
+  const bf16* oo = out + row0 * H + h * DH;
   const int own = wave * 32 + (lane & 31);       // the query, then the key, this lane owns
   const bool wave_active = wave * 32 < len;      // wave-uniform
 
@@ -115,7 +117,7 @@ void attn_bwd_fused128_mfma(const bf16* __restrict__ qkv, const bf16* __restrict
   }
   // ---- keys owned: dk, dv ----
   bf16x8 kf[4], vf[4];
-  bf16* const dst = dqkv + (int64_t)b * L * ld + h * DH;
+  bf16* const dst = dqkv + row0 * ld + h * DH;
   if (queries) {
     // The owned key/value fragments are the last thing read from K and V.  After the barrier a wave's own 32 rows of
     // tile 0 stage the whole-row stores of dq; after the next one the tiles are refilled with Q and dO.
@@ -124,7 +126,7 @@ void attn_bwd_fused128_mfma(const bf16* __restrict__ qkv, const bf16* __restrict
       for (int ks = 0; ks < 4; ++ks) { kf[ks] = frag_rows(T0, wave * 32, ks, lane); vf[ks] = frag_rows(T1, wave * 32, ks, lane); }
     }
     __syncthreads();
-    store_owned_rows_lds(dst, ld, wave * 32, L, acc, 0.125f, lane, T0 + wave * 32 * LDT);
+    store_owned_rows_lds(dst, ld, wave * 32, rows, acc, 0.125f, lane, T0 + wave * 32 * LDT);
     if (!keys) return;
     __syncthreads();
     stage128(T0, base, ld, len, tid);
@@ -183,24 +185,24 @@ void attn_bwd_fused128_mfma(const bf16* __restrict__ qkv, const bf16* __restrict
     }
   }
   __syncthreads();     // every wave is done with Q and dO: own rows of the tiles stage the stores of dk and dv
-  store_owned_rows_lds(dst + H, ld, wave * 32, L, acc, 0.125f, lane, T0 + wave * 32 * LDT);
-  store_owned_rows_lds(dst + 2 * H, ld, wave * 32, L, acc2, 1.0f, lane, T1 + wave * 32 * LDT);
+  store_owned_rows_lds(dst + H, ld, wave * 32, rows, acc, 0.125f, lane, T0 + wave * 32 * LDT);
+  store_owned_rows_lds(dst + 2 * H, ld, wave * 32, rows, acc2, 1.0f, lane, T1 + wave * 32 * LDT);
 }
 
 }  // namespace
 
 void launch_attention_self_fwd(const void* qkv, const int32_t* lens, int B, int L, int A, void* out, float* lse, hipStream_t s, const DropCfg& drop,
-                               uint32_t site);
+                               uint32_t site, const int32_t* first);
 void launch_attention_self_bwd(const void* qkv, const void* out, const float* lse, const void* d_out, const int32_t* lens, int B, int L, int A,
-                               void* dqkv, float* dvec, hipStream_t s, const DropCfg& drop, uint32_t site);
+                               void* dqkv, float* dvec, hipStream_t s, const DropCfg& drop, uint32_t site, const int32_t* first);
 
 void launch_attention_fwd_mfma(const void* qkv, const int32_t* lens, int B, int L, int A, void* out, float* lse, hipStream_t s,
-                               const DropCfg& drop, uint32_t site) {
-  launch_attention_self_fwd(qkv, lens, B, L, A, out, lse, s, drop, site);
+                               const DropCfg& drop, uint32_t site, const int32_t* first) {
+  launch_attention_self_fwd(qkv, lens, B, L, A, out, lse, s, drop, site, first);
 }
 
 void launch_attention_bwd_mfma(const void* qkv, const void* out, const float* lse, const void* d_out, const int32_t* lens, int B, int L,
-                               int A, void* dqkv, float* dvec, hipStream_t s, const DropCfg& drop, uint32_t site) {
+                               int A, void* dqkv, float* dvec, hipStream_t s, const DropCfg& drop, uint32_t site, const int32_t* first) {
   if (L <= 128) {
     constexpr size_t lds = 2 * 128 * LDT * sizeof(bf16) + 2 * 128 * sizeof(float);
     static bool configured = false;
@@ -211,10 +213,10 @@ void launch_attention_bwd_mfma(const void* qkv, const void* out, const float* ls
     }
     const dim3 grid(A, B, (int64_t)A * B <= kFewHeads ? 2 : 1);
     if (drop.thr) hipLaunchKernelGGL(attn_bwd_fused128_mfma<true>, grid, dim3(256), lds, s, (const bf16*)qkv, (const bf16*)out, lse,
-                                     (const bf16*)d_out, lens, L, A, (bf16*)dqkv, drop, site);
+                                     (const bf16*)d_out, lens, first, L, A, (bf16*)dqkv, drop, site);
     else hipLaunchKernelGGL(attn_bwd_fused128_mfma<false>, grid, dim3(256), lds, s, (const bf16*)qkv, (const bf16*)out, lse,
-                            (const bf16*)d_out, lens, L, A, (bf16*)dqkv, drop, site);
+                            (const bf16*)d_out, lens, first, L, A, (bf16*)dqkv, drop, site);
     return;
   }
-  launch_attention_self_bwd(qkv, out, lse, d_out, lens, B, L, A, dqkv, dvec, s, drop, site);
+  launch_attention_self_bwd(qkv, out, lse, d_out, lens, B, L, A, dqkv, dvec, s, drop, site, first);
 }

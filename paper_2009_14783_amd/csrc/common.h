@@ -28,6 +28,11 @@ __device__ __forceinline__ float wave_sum(float v) {
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
   return v;
 }
+__device__ __forceinline__ int wave_sum_int(int v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  return v;
+}
 __device__ __forceinline__ float wave_max(float v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
@@ -159,6 +164,43 @@ struct ModelOff {
 bool hs_cfg_valid(const hs_model_cfg* cfg, std::string* why);
 void hs_model_offsets(const hs_model_cfg& cfg, ModelOff* out);
 
+// Packed rows.  With the lengths of a batch known on the host (hs_set_lengths) the passes work on its real positions only: row first[b] + l of
+// every token-major matrix is position l of sequence b, and padding has no rows.  This is the device side, as kernels take it; `first` and
+// `pad_row` are written by the embedding kernel into the activation arena.
+struct PackedRows {
+  const int32_t* lens;      // [B]
+  int32_t* first;           // [B]
+  int32_t* pad_row;         // [rows]: position b L + l of each row
+  int rows;
+};
+// a range of sequences of it that an embedding kernel fills: lens, first and ids are given from its first sequence, everything else from row 0
+struct PackedPart {
+  const int32_t* lens;
+  int32_t *first, *pad_row;
+  int row0, pos0;           // first packed row and first position of the range
+};
+// length of sequence b, and the rows of the sequences of the range before it (by one wave; a load per 64 sequences)
+__device__ __forceinline__ int packed_len(const int32_t* lens, int b, int L) { return min(max(lens[b], 1), L); }
+__device__ __forceinline__ int packed_before(const int32_t* lens, int b, int L, int lane) {
+  int n = 0;
+  for (int i = lane; i < b; i += 64) n += packed_len(lens, i, L);
+  return wave_sum_int(n);
+}
+// ... and what a context was told: first row of every sequence, and behind the last one the number of rows
+struct HostLens {
+  int B = 0, L = 0;
+  std::vector<int> first;
+  int rows() const { return first[B]; }
+  // the sequence at which the rows are best cut in two
+  int half() const {
+    int b = 1;
+    while (b + 1 < B && 2 * first[b] < rows() && 2 * first[b + 1] - rows() <= rows() - 2 * first[b]) ++b;
+    return b;
+  }
+};
+// false where a length is outside [1, L]
+bool hs_host_lens(HostLens* out, const int32_t* lens, int B, int L);
+
 struct hs_ctx {
   hs_model_cfg cfg;
   ModelOff off;
@@ -176,6 +218,9 @@ struct hs_ctx {
   // translation workload (contexts made by hs_s2s_ctx_create): cfg above holds the shared sizes (n_layers = encoder layers)
   bool is_s2s;
   hs_s2s_cfg s2s;
+  // lengths of the batch that the following calls work on (see hs_set_lengths): one side, or source and target
+  bool lens_set;
+  HostLens lens_a, lens_b;
 };
 
 hs_status hs_fail(hs_ctx* ctx, hs_status st, const std::string& msg);  // records msg, returns st
@@ -204,6 +249,7 @@ struct GemmArgs {
   void* ws; size_t ws_bytes;   // optional scratch for split-K partial sums
   int a_kpad;                  // A k-major: its rows are zero from K up to the next multiple of 64
   const DropCfg* drop; uint32_t drop_site;   // optional (epi == 1): dropout of product + bias before the residual
+  const int32_t* drop_rows;    // the row that numbers the site's elements, for each row of the product (packed rows), or null: its own
 };
 hs_status launch_gemm(hs_ctx* ctx, const GemmArgs& g, hipStream_t s);
 // weight-gradient products (A m-major, B n-major or null for a column of ones, fp32 C = beta C + product, one type and beta; anything
@@ -216,16 +262,20 @@ void gemm_set_variant(int variant);
 // stats: R means, then (stat_ld floats after the first mean; default R) R reciprocal standard deviations
 hs_status launch_layernorm_fwd(hs_ctx* ctx, int dtype, const void* x, const void* gain, const void* bias, void* y,
                                float* stats, int R, int H, float eps, hipStream_t s, int stat_ld = 0);
+// packed rows in, padded rows out (zeros in the padding): x and stats from row 0 of the batch, y, lens and first from the first of B sequences
+hs_status launch_layernorm_fwd_unpack(hs_ctx* ctx, int dtype, const void* x, const void* gain, const void* bias, void* y, float* stats,
+                                      const int32_t* lens, const int32_t* first, int B, int L, int H, float eps, hipStream_t s, int stat_ld);
 size_t layernorm_bwd_scratch(int R, int H);
+// pad_row (packed rows): the position of each row, which numbers the elements of a dropout site; dy_rows > 0: dy has that many padded rows.
 // drop_mode 0: no dropout.  1: dy is the gradient of this LayerNorm's dropped output (site) and is masked as
 // it is read.  2: dx also feeds a dropped branch (site): dxm gets its masked copy and d_colsum sums that copy.
 hs_status launch_layernorm_bwd(hs_ctx* ctx, int dtype, const void* dy, const void* x, const float* stats, const void* gain,
                                void* dx, float* d_gain, float* d_bias, float* d_colsum, float beta, int R, int H,
                                void* partials, hipStream_t s, const DropCfg* drop = nullptr, uint32_t site = 0, int drop_mode = 0,
-                               void* dxm = nullptr);
+                               void* dxm = nullptr, const int32_t* pad_row = nullptr);
 hs_status launch_layernorm_bwd_rows(hs_ctx* ctx, int dtype, const void* dy, const void* x, const float* stats, const void* gain, void* dx,
                                     int R, int H, void* partials, hipStream_t s, const DropCfg* drop = nullptr, uint32_t site = 0,
-                                    int drop_mode = 0, void* dxm = nullptr);
+                                    int drop_mode = 0, void* dxm = nullptr, const int32_t* pad_row = nullptr, int dy_rows = 0);
 hs_status launch_layernorm_bwd_cols(hs_ctx* ctx, const void* partials, float* d_gain, float* d_bias, float* d_colsum, float beta, int R, int H,
                                     hipStream_t s);
 struct LnColsJob { const void* partials; float *d_gain, *d_bias, *d_colsum; };      // what launch_layernorm_bwd_cols is given
@@ -233,18 +283,20 @@ constexpr int kLnColsMax = 48;
 hs_status launch_layernorm_bwd_cols_batch(hs_ctx* ctx, const LnColsJob* jobs, int n, float beta, int R, int H, hipStream_t s);
 hs_status launch_embed_ln_fwd(hs_ctx* ctx, int dtype, const void* word, const void* pos, const void* gain, const void* bias,
                               const int32_t* ids, void* e_pre, void* x0, float* stats, int B, int L, int H, int V, float eps,
-                              hipStream_t s, const DropCfg* drop = nullptr, int stat_ld = 0);
-size_t embed_bwd_scratch(int T, int H);
+                              hipStream_t s, const DropCfg* drop = nullptr, int stat_ld = 0, const PackedPart* pk = nullptr);
+size_t embed_bwd_scratch(int T, int H);      // pk below: de and the sorted positions are packed rows
 // sorted: launch_embed_sort has already run on the same scratch (ordered before this call)
-hs_status launch_embed_sort(hs_ctx* ctx, const int32_t* ids, int T, int V, void* scratch, hipStream_t s);
+hs_status launch_embed_sort(hs_ctx* ctx, const int32_t* ids, int T, int V, void* scratch, hipStream_t s, const PackedRows* pk = nullptr);
 hs_status launch_embed_bwd(hs_ctx* ctx, int dtype, const void* de, const int32_t* ids, int B, int L, int H, int V, int max_pos,
-                           float* g_word, float* g_pos, float beta_pos, void* scratch, hipStream_t s, bool sorted = false);
+                           float* g_word, float* g_pos, float beta_pos, void* scratch, hipStream_t s, bool sorted = false,
+                           const PackedRows* pk = nullptr);
 // drop/site: dropout of the attention probabilities (element ((b*A + h)*L + query)*L + key of the site)
+// first (bf16; packed rows): first row of each of the B sequences, in matrices given from row 0 of the batch; lse and dvec are [B, A, L] all the same
 hs_status launch_attention_fwd(hs_ctx* ctx, int dtype, const void* qkv, const int32_t* lens, int B, int L, int A, void* out,
-                               float* lse, hipStream_t s, const DropCfg* drop = nullptr, uint32_t site = 0);
+                               float* lse, hipStream_t s, const DropCfg* drop = nullptr, uint32_t site = 0, const int32_t* first = nullptr);
 hs_status launch_attention_bwd(hs_ctx* ctx, int dtype, const void* qkv, const void* out, const float* lse, const void* d_out,
                                const int32_t* lens, int B, int L, int A, void* dqkv, float* dvec, hipStream_t s,
-                               const DropCfg* drop = nullptr, uint32_t site = 0);
+                               const DropCfg* drop = nullptr, uint32_t site = 0, const int32_t* first = nullptr);
 size_t colsum_scratch(int R, int C);
 hs_status launch_colsum(hs_ctx* ctx, int dtype, const void* x, int64_t ldx, int R, int C, float* out, float beta, void* partials,
                         hipStream_t s);
@@ -262,6 +314,7 @@ struct AttnOperands {
   int64_t ldq, ldkv;
   const int32_t *qlens, *klens;
   int Lq, Lk, A, causal;
+  const int32_t *qfirst = nullptr, *kfirst = nullptr;      // packed rows (bf16): first row of each sequence, instead of b*Lq and b*Lk
 };
 // fp32 attention: sequences of Lq queries and Lk keys, q/k/v the first rows of sequence 0, lengths per sequence (clamped to 1 .. L)
 struct AttnF32 {
@@ -282,9 +335,9 @@ hs_status launch_attention_general_bwd(hs_ctx* ctx, int dtype, const AttnOperand
 // translation workload (seq2seq_ops.hip)
 hs_status launch_position_table(hs_ctx* ctx, float* pe, int L, int H, hipStream_t s);     // pe [L, H] fp32
 hs_status launch_embed_scale_pos(hs_ctx* ctx, int dtype, const void* emb, const int32_t* ids, const float* pe, void* x, int B, int L, int H, int V,
-                                 float scale, const DropCfg* drop, uint32_t site, hipStream_t s);
+                                 float scale, const DropCfg* drop, uint32_t site, hipStream_t s, const PackedPart* pk = nullptr);
 hs_status launch_mask_scale(hs_ctx* ctx, int dtype, const void* x, void* y, size_t n, float alpha, const DropCfg* drop, uint32_t site,
-                            hipStream_t s);
+                            hipStream_t s, const int32_t* pad_row = nullptr, int H = 0);
 hs_status launch_real_rows(hs_ctx* ctx, const int32_t* lens, int B, int L, int32_t* rows, int capacity, hipStream_t s);
 hs_status launch_smoothed_ce(hs_ctx* ctx, int dtype, const float* logits, int64_t ldl, const int32_t* labels, const int32_t* lens, int M, int L,
                              int V, float eps, void* dlogits, float* row_loss, float* row_nll, float* loss_sum, float* nll_sum,

@@ -121,6 +121,7 @@ hs_status hs_ctx_create(const hs_model_cfg* cfg, hs_ctx** out) {
   c->armed.on = false;
   c->upd = nullptr;
   c->is_s2s = false;
+  c->lens_set = false;
   *out = c;
   return HS_OK;
 }
@@ -339,6 +340,39 @@ extern "C" hs_status hs_checkpoint_read(const char* path, hs_ckpt_header* header
   uint64_t stored = 0;
   if (fread(&stored, 1, sizeof(stored), in.f) != sizeof(stored) || stored != sum.h)
     return hs_fail(nullptr, HS_ERR_STATE, std::string("checkpoint: checksum mismatch in ") + path);
+  return HS_OK;
+}
+
+// ---- lengths of the batch that a context works on -------------------------------------------------
+bool hs_host_lens(HostLens* out, const int32_t* lens, int B, int L) {
+  out->B = B; out->L = L;
+  out->first.assign(B + 1, 0);
+  for (int b = 0; b < B; ++b) {
+    if (lens[b] < 1 || lens[b] > L) return false;
+    out->first[b + 1] = out->first[b] + lens[b];
+  }
+  return true;
+}
+extern "C" hs_status hs_set_lengths(hs_ctx* ctx, const int32_t* lens_host, int32_t B, int32_t L) {
+  if (!ctx) return hs_fail(nullptr, HS_ERR_INVALID_ARG, "hs_set_lengths: ctx is NULL");
+  ctx->lens_set = false;
+  if (!lens_host) return HS_OK;
+  if (ctx->is_s2s) return hs_fail(ctx, HS_ERR_STATE, "hs_set_lengths: the context is one of hs_s2s_ctx_create");
+  if (B < 1 || L < 1 || (int64_t)B * L > (int64_t)1 << 24) return hs_fail(ctx, HS_ERR_SHAPE, "hs_set_lengths: bad size");
+  if (!hs_host_lens(&ctx->lens_a, lens_host, B, L)) return hs_fail(ctx, HS_ERR_INVALID_ARG, "hs_set_lengths: lens[b] outside [1, L]");
+  ctx->lens_set = true;
+  return HS_OK;
+}
+extern "C" hs_status hs_s2s_set_lengths(hs_ctx* ctx, const int32_t* src_lens_host, const int32_t* tgt_lens_host, int32_t B, int32_t Ls, int32_t Lt) {
+  if (!ctx) return hs_fail(nullptr, HS_ERR_INVALID_ARG, "hs_s2s_set_lengths: ctx is NULL");
+  ctx->lens_set = false;
+  if (!src_lens_host && !tgt_lens_host) return HS_OK;
+  if (!ctx->is_s2s) return hs_fail(ctx, HS_ERR_STATE, "hs_s2s_set_lengths: the context was not made by hs_s2s_ctx_create");
+  if (!src_lens_host || !tgt_lens_host) return hs_fail(ctx, HS_ERR_INVALID_ARG, "hs_s2s_set_lengths: the lengths of one side only");
+  if (B < 1 || Ls < 1 || Lt < 1 || (int64_t)B * std::max(Ls, Lt) > (int64_t)1 << 24) return hs_fail(ctx, HS_ERR_SHAPE, "hs_s2s_set_lengths: bad size");
+  if (!hs_host_lens(&ctx->lens_a, src_lens_host, B, Ls) || !hs_host_lens(&ctx->lens_b, tgt_lens_host, B, Lt))
+    return hs_fail(ctx, HS_ERR_INVALID_ARG, "hs_s2s_set_lengths: a length outside [1, L]");
+  ctx->lens_set = true;
   return HS_OK;
 }
 

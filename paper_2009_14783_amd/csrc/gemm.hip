@@ -428,6 +428,7 @@ static GemmDev gemm_dev_args(const GemmArgs& g) {
   p.partial = nullptr; p.k_per_split = g.K; p.gelu_tab = nullptr;
   p.drop = (g.drop && g.drop->thr && g.epi == 1) ? *g.drop : DropCfg{0u, 1.0f, 0u, 0u, 0u};
   p.drop_site = g.drop_site;
+  p.drop_rows = g.drop_rows;
   p.rowsum = nullptr;
   return p;
 }

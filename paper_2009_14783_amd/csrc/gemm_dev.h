@@ -14,6 +14,7 @@ struct GemmDev {
   const float2* gelu_tab;   // wide kernels, GELU epilogues: table for gelu_tab_eval (the cdf for epi 2, GELU' for epi 3)
   DropCfg drop;        // dropout of (product + bias) before the residual is added (epi == 1 only; thr == 0: off)
   uint32_t drop_site;  // element index of the site = row * N + col
+  const int32_t* drop_rows;   // ... with this row instead (packed rows), or null
   float* rowsum;       // grouped weight gradients: rowsum[m] = beta rowsum[m] + sum_k A(m, k) beside the product, or null
 };
 
@@ -45,7 +46,7 @@ namespace {
 // multiple of 4: one generator block per four columns when the row length allows it
 template <int NV>
 __device__ __forceinline__ void drop_row_factors(const GemmDev& p, int row, int col, float (&f)[NV]) {
-  const uint64_t e = (uint64_t)row * (uint64_t)p.N + (uint64_t)col;
+  const uint64_t e = (uint64_t)(p.drop_rows ? p.drop_rows[row] : row) * (uint64_t)p.N + (uint64_t)col;
   if ((p.N & 3) == 0) {
 #pragma unroll
     for (int q = 0; q < NV / 4; ++q) {
@@ -59,7 +60,7 @@ __device__ __forceinline__ void drop_row_factors(const GemmDev& p, int row, int 
   }
 }
 __device__ __forceinline__ float drop_elem(const GemmDev& p, int row, int col) {
-  return drop_factor1(p.drop, p.drop_site, (uint64_t)row * (uint64_t)p.N + (uint64_t)col);
+  return drop_factor1(p.drop, p.drop_site, (uint64_t)(p.drop_rows ? p.drop_rows[row] : row) * (uint64_t)p.N + (uint64_t)col);
 }
 
 template <class T>

@@ -13,11 +13,19 @@ constexpr int MAXCH = 4;   // 4-element chunks per lane (vector access): hidden 
 // 4 consecutive elements as float4 (8-byte access for bfloat16, 16-byte for float)
 template <class T> struct Vec4;
 template <> struct Vec4<float> {
+  typedef float4 Raw;      // as they lie in memory
+  static __device__ __forceinline__ Raw raw(const float* p) { return *(const float4*)p; }
+  static __device__ __forceinline__ float4 value(const Raw& v) { return v; }
+  static __device__ __forceinline__ void reread(Raw&) {}
   static __device__ __forceinline__ float4 ld(const float* p) { return *(const float4*)p; }
   static __device__ __forceinline__ void st(float* p, float4 v) { *(float4*)p = v; }
   static __device__ __forceinline__ float4 round(float4 v) { return v; }
 };
 template <> struct Vec4<bf16> {
+  typedef bf16x4 Raw;
+  static __device__ __forceinline__ Raw raw(const bf16* p) { return *(const bf16x4*)p; }
+  static __device__ __forceinline__ void reread(Raw& v) { asm("" : "+v"(v)); }      // what was converted from it is not kept
+  static __device__ __forceinline__ float4 value(const Raw& v) { return make_float4((float)v[0], (float)v[1], (float)v[2], (float)v[3]); }
   static __device__ __forceinline__ float4 ld(const bf16* p) {
     const bf16x4 v = *(const bf16x4*)p;
     return make_float4((float)v[0], (float)v[1], (float)v[2], (float)v[3]);
@@ -81,18 +89,52 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(const T* __restrict__ x, co
   ln_row<T>(v, nch, H, lane, gain, bias, eps, y + (int64_t)row * H, stats + row, stats + stat_ld + row);
 }
 
+// Row l of sequence b (padded rows) from packed row first[b] + l; zeros where l is padding.
 template <class T>
+__global__ __launch_bounds__(256) void ln_fwd_unpack_kernel(const T* __restrict__ x, const T* __restrict__ gain, const T* __restrict__ bias,
+                                                            T* __restrict__ y, float* __restrict__ stats, const int32_t* __restrict__ lens,
+                                                            const int32_t* __restrict__ first, int R, int L, int H, float eps, int stat_ld) {
+  const int lane = threadIdx.x & 63;
+  const int pos = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (pos >= R) return;
+  const int b = pos / L, l = pos - b * L;
+  const int nch = H / 4;
+  T* const out = y + (int64_t)pos * H;
+  if (l >= packed_len(lens, b, L)) {
+#pragma unroll
+    for (int c = 0; c < MAXCH; ++c) if (c * 64 + lane < nch) Vec4<T>::st(out + 4 * (c * 64 + lane), make_float4(0.f, 0.f, 0.f, 0.f));
+    return;
+  }
+  const int row = first[b] + l;
+  float4 v[MAXCH];
+#pragma unroll
+  for (int c = 0; c < MAXCH; ++c) if (c * 64 + lane < nch) v[c] = Vec4<T>::ld(x + (int64_t)row * H + 4 * (c * 64 + lane));
+  ln_row<T>(v, nch, H, lane, gain, bias, eps, out, stats + row, stats + stat_ld + row);
+}
+
+// PACK: position l of sequence b goes to packed row first[b] + l, padding nowhere; first and pad_row are written here.
+template <class T, bool PACK>
 __global__ __launch_bounds__(256) void embed_ln_fwd_kernel(const T* __restrict__ word, const T* __restrict__ pos,
                                                            const T* __restrict__ gain, const T* __restrict__ bias,
                                                            const int32_t* __restrict__ ids, T* __restrict__ e_pre, T* __restrict__ x0,
                                                            float* __restrict__ stats, int R, int L, int H, int V, float eps, DropCfg drop,
-                                                           int stat_ld) {
+                                                           int stat_ld, PackedPart pk) {
   const int lane = threadIdx.x & 63;
-  const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (row >= R) return;
-  int id = ids[row];
+  const int at = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (at >= R) return;
+  const int b = at / L, l = at - b * L;
+  int row = at;
+  if (PACK) {
+    if (l >= packed_len(pk.lens, b, L)) return;
+    const int f = pk.row0 + packed_before(pk.lens, b, L, lane);
+    row = f + l;
+    if (lane == 0) {
+      pk.pad_row[row] = pk.pos0 + at;
+      if (l == 0) pk.first[b] = f;
+    }
+  }
+  int id = ids[at];
   id = id < 0 ? 0 : (id >= V ? V - 1 : id);  // ids are validated by contract; clamp keeps reads in bounds
-  const int l = row % L;
   const int nch = H / 4;
   float4 v[MAXCH];
 #pragma unroll
@@ -105,116 +147,127 @@ __global__ __launch_bounds__(256) void embed_ln_fwd_kernel(const T* __restrict__
     v[c] = e;
   }
   ln_row<T>(v, nch, H, lane, gain, bias, eps, x0 + (int64_t)row * H, stats + row, stats + stat_ld + row, drop.thr ? &drop : nullptr,
-            site_embedding(), row);
+            site_embedding(), at);
 }
 
 // ------------------------------------------------------------------------------------------
 // LayerNorm backward.  Each wave walks rows with a fixed stride and keeps per-column partial
 // sums of dy*xhat, dy and dx; blocks write partials, a second kernel adds them in block order.
 // ------------------------------------------------------------------------------------------
-// NC: 256-column slots per row that the registers hold (hidden <= 256 NC); EXACT: hidden == 256 NC, no slot is partly used.
-template <class T, int drop_mode, int NC, bool EXACT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NC <= 3 ? 4 : 2, 4))) void ln_bwd_kernel(const T* __restrict__ dy, const T* __restrict__ x, const float* __restrict__ stats,
+// NC: 256-column slots per row that the registers hold (hidden <= 256 NC); EXACT: hidden == 256 NC, no slot is partly used.  NW: waves of a block.
+// A wave holds two rows as they lie in memory (the one it works on and the next one, requested before the reductions of the first) and
+// converts them where they are used: 128 registers with every sum, so that 16 waves share a CU at any width.  Blocks of eight waves with many rows: half as
+// many partial sums to write and to add up as with four.  Rows and column sums, us, against four waves and rows held in fp32 (which spilled 5 to 20
+// registers from 768 columns on): 8192 x 768 16.5 -> 14.0 (38 MB), 16384 x 768 25.9 -> 21.9, 8192 x 512 14.8 -> 11.7, 16384 x 1024 27.6 -> 26.5, 8192 x 1024 18.0 -> 19.0;
+// fp32 8192 x 768 26.4 -> 22.2; the BERT-base step of 64 x 128 7.23 -> 7.12 ms, with dropout 7.86 -> 7.66.
+template <class T, int drop_mode, int NC, bool EXACT, int NW>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(sizeof(T) * NC <= 12 ? 4 : 2, 4))) void ln_bwd_kernel(const T* __restrict__ dy, const T* __restrict__ x, const float* __restrict__ stats,
                                                      const T* __restrict__ gain, T* __restrict__ dx, float* __restrict__ partials,
-                                                     int R, int H, DropCfg drop, uint32_t site, T* __restrict__ dxm) {
+                                                     int R, int H, DropCfg drop, uint32_t site, T* __restrict__ dxm,
+                                                     const int32_t* __restrict__ pad_row, int dy_rows) {
+  // dy_rows > 0: dy has padded rows, row r of x is row pad_row[r] of it (clamped: the address must not depend on what the caller said of lengths)
   // drop_mode 1: dy is the gradient of a dropped OUTPUT of this LayerNorm and is masked as it is read.
   // drop_mode 2: dx feeds a dropped branch (site) besides a residual path: dxm gets the masked copy and the
   //              column sums of dx (the bias gradient of that branch) are taken over the masked values.
-  __shared__ float4 red[4][NC * 64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  typedef typename Vec4<T>::Raw Raw;
+  __shared__ float4 red[NW][NC * 64];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nch = H / 4;
   const float inv_h = 1.0f / (float)H;
-  float4 g[NC], ag[NC], ab[NC], as[NC];
+  float4 ag[NC], ab[NC], as[NC];
+  Raw g[NC];
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
     ag[c] = ab[c] = as[c] = make_float4(0.f, 0.f, 0.f, 0.f);
-    g[c] = (EXACT || c * 64 + lane < nch) ? Vec4<T>::ld(gain + 4 * (c * 64 + lane)) : make_float4(0.f, 0.f, 0.f, 0.f);
+    g[c] = (EXACT || c * 64 + lane < nch) ? Vec4<T>::raw(gain + 4 * (c * 64 + lane)) : Raw{};
   }
-  // Rows of one wave are software-pipelined: the loads of the wave's next row are issued before the
-  // reductions of the current one, so two rows are in flight per wave.
-  const int stride = gridDim.x * 4;
-  int row = blockIdx.x * 4 + wave;
-  float4 nx[NC], ndy[NC];
+  const int stride = gridDim.x * NW;
+  int row = blockIdx.x * NW + wave;
+  Raw nx[NC], ndy[NC];
   float nmu = 0.f, nrstd = 0.f;
-  if (row < R) {
-    nmu = stats[row]; nrstd = stats[R + row];
+  auto request = [&](int r) __attribute__((always_inline)) {
+    nmu = stats[r]; nrstd = stats[R + r];
+    const T* const px = x + (int64_t)r * H;
+    const T* const pd = dy + (int64_t)(dy_rows ? (int)min((unsigned)pad_row[r], (unsigned)dy_rows - 1u) : r) * H;
 #pragma unroll
     for (int c = 0; c < NC; ++c) if (EXACT || c * 64 + lane < nch) {
-      const int64_t o = (int64_t)row * H + 4 * (c * 64 + lane);
-      nx[c] = Vec4<T>::ld(x + o);
-      ndy[c] = Vec4<T>::ld(dy + o);
+      nx[c] = Vec4<T>::raw(px + 4 * (c * 64 + lane));
+      ndy[c] = Vec4<T>::raw(pd + 4 * (c * 64 + lane));
     }
-  }
+  };
+  if (row < R) request(row);
   for (; row < R; row += stride) {
     const float mu = nmu, rstd = nrstd;
-    float4 xh[NC], dyv[NC];
+    const int64_t drop_row0 = (int64_t)((drop_mode && pad_row) ? pad_row[row] : row) * H;
+    Raw rx[NC], rdy[NC];
 #pragma unroll
-    for (int c = 0; c < NC; ++c) { xh[c] = nx[c]; dyv[c] = ndy[c]; }
+    for (int c = 0; c < NC; ++c) { rx[c] = nx[c]; rdy[c] = ndy[c]; }
+    if (row + stride < R) request(row + stride);
+    auto xhat = [&](int c) __attribute__((always_inline)) {
+      const float4 v = Vec4<T>::value(rx[c]);
+      return make_float4((v.x - mu) * rstd, (v.y - mu) * rstd, (v.z - mu) * rstd, (v.w - mu) * rstd);
+    };
+    float4 dyv[drop_mode == 1 ? NC : 1];
     if (drop_mode == 1) {
 #pragma unroll
       for (int c = 0; c < NC; ++c) if (EXACT || c * 64 + lane < nch) {
         float f[4];
-        drop_factors4(drop, site, (uint64_t)((int64_t)row * H + 4 * (c * 64 + lane)) >> 2, f);
-        dyv[c].x *= f[0]; dyv[c].y *= f[1]; dyv[c].z *= f[2]; dyv[c].w *= f[3];
+        drop_factors4(drop, site, (uint64_t)(drop_row0 + 4 * (c * 64 + lane)) >> 2, f);
+        const float4 v = Vec4<T>::value(rdy[c]);
+        dyv[c] = make_float4(v.x * f[0], v.y * f[1], v.z * f[2], v.w * f[3]);
       }
     }
-    const int next = row + stride;
-    if (next < R) {
-      nmu = stats[next]; nrstd = stats[R + next];
-#pragma unroll
-      for (int c = 0; c < NC; ++c) if (EXACT || c * 64 + lane < nch) {
-        const int64_t o = (int64_t)next * H + 4 * (c * 64 + lane);
-        nx[c] = Vec4<T>::ld(x + o);
-        ndy[c] = Vec4<T>::ld(dy + o);
-      }
-    }
+    auto dyat = [&](int c) __attribute__((always_inline)) { return drop_mode == 1 ? dyv[c] : Vec4<T>::value(rdy[c]); };
     float s1 = 0.f, s2 = 0.f;
 #pragma unroll
     for (int c = 0; c < NC; ++c) if (EXACT || c * 64 + lane < nch) {
-      const float4 xv = xh[c];
-      xh[c] = make_float4((xv.x - mu) * rstd, (xv.y - mu) * rstd, (xv.z - mu) * rstd, (xv.w - mu) * rstd);
-      const float4 d = make_float4(dyv[c].x * g[c].x, dyv[c].y * g[c].y, dyv[c].z * g[c].z, dyv[c].w * g[c].w);
+      const float4 xh = xhat(c), y = dyat(c), gv = Vec4<T>::value(g[c]);
+      const float4 d = make_float4(y.x * gv.x, y.y * gv.y, y.z * gv.z, y.w * gv.w);
       s1 += (d.x + d.y) + (d.z + d.w);
-      s2 += (d.x * xh[c].x + d.y * xh[c].y) + (d.z * xh[c].z + d.w * xh[c].w);
+      s2 += (d.x * xh.x + d.y * xh.y) + (d.z * xh.z + d.w * xh.w);
     }
     s1 = wave_sum(s1) * inv_h;
     s2 = wave_sum(s2) * inv_h;
+    if (NC == 4 && sizeof(T) == 2) {      // converted again below: the row in fp32 beside the sums would not fit
+#pragma unroll
+      for (int c = 0; c < NC; ++c) { Vec4<T>::reread(rx[c]); Vec4<T>::reread(g[c]); if (drop_mode != 1) Vec4<T>::reread(rdy[c]); }
+    }
 #pragma unroll
     for (int c = 0; c < NC; ++c) if (EXACT || c * 64 + lane < nch) {
+      const float4 xh = xhat(c), y = dyat(c), gv = Vec4<T>::value(g[c]);
       float4 d;
-      d.x = rstd * (dyv[c].x * g[c].x - s1 - xh[c].x * s2); d.y = rstd * (dyv[c].y * g[c].y - s1 - xh[c].y * s2);
-      d.z = rstd * (dyv[c].z * g[c].z - s1 - xh[c].z * s2); d.w = rstd * (dyv[c].w * g[c].w - s1 - xh[c].w * s2);
+      d.x = rstd * (y.x * gv.x - s1 - xh.x * s2); d.y = rstd * (y.y * gv.y - s1 - xh.y * s2);
+      d.z = rstd * (y.z * gv.z - s1 - xh.z * s2); d.w = rstd * (y.w * gv.w - s1 - xh.w * s2);
       float4 dm = d;
       d = Vec4<T>::round(d);
       Vec4<T>::st(dx + (int64_t)row * H + 4 * (c * 64 + lane), d);
       if (drop_mode == 2) {
         float f[4];
-        drop_factors4(drop, site, (uint64_t)((int64_t)row * H + 4 * (c * 64 + lane)) >> 2, f);
+        drop_factors4(drop, site, (uint64_t)(drop_row0 + 4 * (c * 64 + lane)) >> 2, f);
         dm = Vec4<T>::round(make_float4(dm.x * f[0], dm.y * f[1], dm.z * f[2], dm.w * f[3]));
         Vec4<T>::st(dxm + (int64_t)row * H + 4 * (c * 64 + lane), dm);
       } else {
         dm = d;
       }
-      ag[c].x += dyv[c].x * xh[c].x; ag[c].y += dyv[c].y * xh[c].y; ag[c].z += dyv[c].z * xh[c].z; ag[c].w += dyv[c].w * xh[c].w;
-      ab[c].x += dyv[c].x; ab[c].y += dyv[c].y; ab[c].z += dyv[c].z; ab[c].w += dyv[c].w;
+      ag[c].x += y.x * xh.x; ag[c].y += y.y * xh.y; ag[c].z += y.z * xh.z; ag[c].w += y.w * xh.w;
+      ab[c].x += y.x; ab[c].y += y.y; ab[c].z += y.z; ab[c].w += y.w;
       as[c].x += dm.x; as[c].y += dm.y; as[c].z += dm.z; as[c].w += dm.w;
     }
   }
-  // combine the four waves of the block in wave order, one quantity at a time
+  // combine the waves of the block in wave order, one quantity at a time
   float* out = partials + (int64_t)blockIdx.x * 3 * H;
 #pragma unroll
   for (int q = 0; q < 3; ++q) {
 #pragma unroll
     for (int c = 0; c < NC; ++c) if (EXACT || c * 64 + lane < nch) red[wave][c * 64 + lane] = (q == 0) ? ag[c] : (q == 1 ? ab[c] : as[c]);
     __syncthreads();
-    for (int ch = threadIdx.x; ch < nch; ch += 256) {
-      const float4 a = red[0][ch], b = red[1][ch], c2 = red[2][ch], d = red[3][ch];
-      float4 t;
-      t.x = ((a.x + b.x) + c2.x) + d.x; t.y = ((a.y + b.y) + c2.y) + d.y;
-      t.z = ((a.z + b.z) + c2.z) + d.z; t.w = ((a.w + b.w) + c2.w) + d.w;
+    for (int ch = threadIdx.x; ch < nch; ch += 64 * NW) {
+      float4 t = red[0][ch];
+#pragma unroll
+      for (int w = 1; w < NW; ++w) { const float4 a = red[w][ch]; t.x += a.x; t.y += a.y; t.z += a.z; t.w += a.w; }
       *(float4*)(out + q * H + 4 * ch) = t;
     }
-    __syncthreads();
+    if (q < 2) __syncthreads();
   }
 }
 
@@ -430,13 +483,27 @@ __global__ __launch_bounds__(256) void sum_vector_kernel(const float* __restrict
 // position table: g_pos[l, :] = beta*g_pos[l, :] + sum_b de[b, l, :]; rows l >= L get beta*old.  Four columns per thread, the rows of eight
 // sequences requested together (they are added one after the other): bound by those latencies.  64 x 128 x 768: 61 -> 17 us against
 // one column per thread.
-template <class T>
-__global__ __launch_bounds__(64) void pos_grad_kernel(const T* __restrict__ de, int B, int L, int H, int max_pos, float* __restrict__ g_pos, float beta) {
+// PACK: de has packed rows, row first[b] + l for the sequences of more than l positions.
+template <class T, bool PACK>
+__global__ __launch_bounds__(64) void pos_grad_kernel(const T* __restrict__ de, int B, int L, int H, int max_pos, float* __restrict__ g_pos, float beta,
+                                                      const int32_t* __restrict__ lens, const int32_t* __restrict__ first) {
   const int64_t i = 4 * ((int64_t)blockIdx.x * blockDim.x + threadIdx.x);
   if (i >= (int64_t)max_pos * H) return;
   const int64_t l = i / H, step = (int64_t)L * H;
   float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (l < L) {
+  if (PACK && l < L) {
+    const T* const col = de + (i - l * H);
+    for (int b = 0; b < B; b += 8) {
+      float4 v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (b + u < B && l < packed_len(lens, b + u, L)) v[u] = Vec4<T>::ld(col + (first[b + u] + l) * H);
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u) { s.x += v[u].x; s.y += v[u].y; s.z += v[u].z; s.w += v[u].w; }
+    }
+  } else if (l < L) {
     const T* row = de + i;
     int b = 0;
     for (; b + 8 <= B; b += 8, row += 8 * step) {
@@ -460,7 +527,7 @@ __global__ __launch_bounds__(64) void pos_grad_kernel(const T* __restrict__ de, 
 // Thread t owns the contiguous slice [t*per, (t+1)*per) in every pass, which keeps equal keys in
 // their input order.  Result in (key_out, val_out) after an even number of passes.
 __global__ __launch_bounds__(512) void sort_ids_kernel(const int32_t* __restrict__ ids, int T, int V, int32_t* k0, int32_t* v0,
-                                                        int32_t* k1, int32_t* v1, int npass) {
+                                                        int32_t* k1, int32_t* v1, int npass, const int32_t* __restrict__ pad_row, unsigned positions) {
   constexpr int NT = 512;
   __shared__ int cnt[16 * NT];
   __shared__ int wsum[NT / 64];
@@ -476,7 +543,7 @@ __global__ __launch_bounds__(512) void sort_ids_kernel(const int32_t* __restrict
     for (int d = 0; d < 16; ++d) cnt[d * NT + tid] = 0;
     for (int i = beg; i < end; ++i) {
       int key;
-      if (pass == 0) { key = ids[i]; key = key < 0 ? 0 : (key >= V ? V - 1 : key); } else key = kin[i];
+      if (pass == 0) { key = ids[pad_row ? min((unsigned)pad_row[i], positions - 1u) : (unsigned)i]; key = key < 0 ? 0 : (key >= V ? V - 1 : key); } else key = kin[i];
       cnt[((key >> shift) & 15) * NT + tid]++;
     }
     __syncthreads();
@@ -495,7 +562,7 @@ __global__ __launch_bounds__(512) void sort_ids_kernel(const int32_t* __restrict
     __syncthreads();
     for (int i = beg; i < end; ++i) {
       int key, val;
-      if (pass == 0) { key = ids[i]; key = key < 0 ? 0 : (key >= V ? V - 1 : key); val = i; } else { key = kin[i]; val = vin[i]; }
+      if (pass == 0) { key = ids[pad_row ? min((unsigned)pad_row[i], positions - 1u) : (unsigned)i]; key = key < 0 ? 0 : (key >= V ? V - 1 : key); val = i; } else { key = kin[i]; val = vin[i]; }
       const int pos = cnt[((key >> shift) & 15) * NT + tid]++;
       kout[pos] = key; vout[pos] = val;
     }
@@ -615,35 +682,49 @@ hs_status launch_layernorm_fwd(hs_ctx* ctx, int dtype, const void* x, const void
   return HS_OK;
 }
 
-// Blocks of ln_bwd_kernel: eight rows per block (two per wave, both in flight at once) up to the number of blocks
-// that are resident together, which the kernel's register use sets: four per CU up to 768 columns, three beyond.
-// With few rows one per wave, up to a block per CU (BERT-base, 264 and 176 rows: 4.23 -> 4.13 ms per step, the translation step with 320 rows per
-// side 2.25 -> 2.19); never fewer blocks for more rows, so that the scratch does not shrink as a batch grows.
-static int ln_bwd_blocks(int R, int H) {
-  const int cap = H <= 768 ? 1024 : 768;
-  const int nb = std::max((R + 7) / 8, std::min((R + 3) / 4, 256));
-  return nb < 1 ? 1 : (nb > cap ? cap : nb);
+hs_status launch_layernorm_fwd_unpack(hs_ctx* ctx, int dtype, const void* x, const void* gain, const void* bias, void* y, float* stats,
+                                      const int32_t* lens, const int32_t* first, int B, int L, int H, float eps, hipStream_t s, int stat_ld) {
+  const int R = B * L;
+  if (R <= 0) return HS_OK;
+  KScope scope(prof_of(ctx), KC_LN_FWD, 8.0 * R * H, 2.0 * R * H * esize(dtype), s);
+  dim3 grid((R + 3) / 4);
+  if (dtype == HS_BF16) hipLaunchKernelGGL(ln_fwd_unpack_kernel<bf16>, grid, dim3(256), 0, s, (const bf16*)x, (const bf16*)gain, (const bf16*)bias, (bf16*)y, stats, lens, first, R, L, H, eps, stat_ld);
+  else hipLaunchKernelGGL(ln_fwd_unpack_kernel<float>, grid, dim3(256), 0, s, (const float*)x, (const float*)gain, (const float*)bias, (float*)y, stats, lens, first, R, L, H, eps, stat_ld);
+  LAUNCH_CHECK(ctx, "layernorm_fwd");
+  return HS_OK;
 }
-size_t layernorm_bwd_scratch(int R, int H) { return align_up((size_t)ln_bwd_blocks(R, H) * 3 * H * sizeof(float), 256); }
+
+// Blocks of ln_bwd_kernel.  With few rows (up to a block per CU) blocks of four waves with a row each; beyond, of eight waves with two rows each, both in
+// flight at once, up to the two blocks per CU that are resident together (BERT-base, 264 and 176 rows, one row per wave instead of two: 4.23 -> 4.13 ms per
+// step).  Never fewer blocks for more rows, so that the scratch does not shrink as a batch grows.
+constexpr int kLnBwdFewRows = 1024;
+static int ln_bwd_blocks(int R) {
+  if (R <= kLnBwdFewRows) return std::max((R + 3) / 4, 1);
+  return std::min(std::max((R + 15) / 16, 256), 512);
+}
+size_t layernorm_bwd_scratch(int R, int H) { return align_up((size_t)ln_bwd_blocks(R) * 3 * H * sizeof(float), 256); }
 
 // main kernel: dx and the per-block partial column sums
 hs_status launch_layernorm_bwd_rows(hs_ctx* ctx, int dtype, const void* dy, const void* x, const float* stats, const void* gain, void* dx,
                                     int R, int H, void* partials, hipStream_t s, const DropCfg* drop, uint32_t site, int drop_mode,
-                                    void* dxm) {
+                                    void* dxm, const int32_t* pad_row, int dy_rows) {
   if (R <= 0) return HS_OK;
-  const int nb = ln_bwd_blocks(R, H);
+  const int nb = ln_bwd_blocks(R);
   KScope scope(prof_of(ctx), KC_LN_BWD, 14.0 * R * H, 3.0 * R * H * esize(dtype), s);
   DropCfg d{0u, 1.0f, 0u, 0u, 0u};
   if (drop && drop->thr && drop_mode) d = *drop; else drop_mode = 0;
   if (drop_mode == 2 && !dxm) return hs_fail(ctx, HS_ERR_INVALID_ARG, "layernorm_bwd: masked output buffer missing");
   const int nc = H <= 512 ? 2 : (H + 255) / 256;      // the NC the kernel is built with
   const bool exact = H == 256 * nc;
-#define HS_LN_BWD4(TT, MODE, NC, EX) hipLaunchKernelGGL((ln_bwd_kernel<TT, MODE, NC, EX>), dim3(nb), dim3(256), 0, s, (const TT*)dy, (const TT*)x, stats, \
-                                                       (const TT*)gain, (TT*)dx, (float*)partials, R, H, d, site, (TT*)dxm)
+#define HS_LN_BWD5(TT, MODE, NC, EX, NW) hipLaunchKernelGGL((ln_bwd_kernel<TT, MODE, NC, EX, NW>), dim3(nb), dim3(64 * NW), 0, s, (const TT*)dy, \
+                                                           (const TT*)x, stats, (const TT*)gain, (TT*)dx, (float*)partials, R, H, d, site, (TT*)dxm, \
+                                                           pad_row, pad_row ? dy_rows : 0)
+#define HS_LN_BWD4(TT, MODE, NC, EX) do { if (R <= kLnBwdFewRows) HS_LN_BWD5(TT, MODE, NC, EX, 4); else HS_LN_BWD5(TT, MODE, NC, EX, 8); } while (0)
 #define HS_LN_BWD3(TT, MODE, NC) do { if (exact) HS_LN_BWD4(TT, MODE, NC, true); else HS_LN_BWD4(TT, MODE, NC, false); } while (0)
 #define HS_LN_BWD(TT, MODE) do { if (nc == 2) HS_LN_BWD3(TT, MODE, 2); else if (nc == 3) HS_LN_BWD3(TT, MODE, 3); else HS_LN_BWD3(TT, MODE, 4); } while (0)
   if (dtype == HS_BF16) { if (drop_mode == 0) HS_LN_BWD(bf16, 0); else if (drop_mode == 1) HS_LN_BWD(bf16, 1); else HS_LN_BWD(bf16, 2); }
   else { if (drop_mode == 0) HS_LN_BWD(float, 0); else if (drop_mode == 1) HS_LN_BWD(float, 1); else HS_LN_BWD(float, 2); }
+#undef HS_LN_BWD5
 #undef HS_LN_BWD4
 #undef HS_LN_BWD3
 #undef HS_LN_BWD
@@ -655,7 +736,7 @@ hs_status launch_layernorm_bwd_cols(hs_ctx* ctx, const void* partials, float* d_
                                     hipStream_t s) {
   if (R <= 0 || !(d_gain || d_bias || d_colsum)) return HS_OK;
   KScope scope(prof_of(ctx), KC_LN_BWD, 0.0, 0.0, s);
-  hipLaunchKernelGGL(sum_partials_kernel, dim3((H + 63) / 64, 3), dim3(64 * SP_WAVES), 0, s, (const float*)partials, ln_bwd_blocks(R, H), (int64_t)3 * H,
+  hipLaunchKernelGGL(sum_partials_kernel, dim3((H + 63) / 64, 3), dim3(64 * SP_WAVES), 0, s, (const float*)partials, ln_bwd_blocks(R), (int64_t)3 * H,
                      (int64_t)H, H, d_gain, d_bias, d_colsum, beta);
   LAUNCH_CHECK(ctx, "layernorm_bwd finalize");
   return HS_OK;
@@ -667,30 +748,34 @@ hs_status launch_layernorm_bwd_cols_batch(hs_ctx* ctx, const LnColsJob* jobs, in
     const int m = std::min(n - done, kLnColsMax);
     for (int i = 0; i < m; ++i) t.job[i] = jobs[done + i];
     KScope scope(prof_of(ctx), KC_LN_BWD, 0.0, 0.0, s);
-    hipLaunchKernelGGL(ln_cols_kernel, dim3((H + 63) / 64, 3, m), dim3(64 * SP_WAVES), 0, s, t, ln_bwd_blocks(R, H), H, beta);
+    hipLaunchKernelGGL(ln_cols_kernel, dim3((H + 63) / 64, 3, m), dim3(64 * SP_WAVES), 0, s, t, ln_bwd_blocks(R), H, beta);
     LAUNCH_CHECK(ctx, "layernorm_bwd finalize");
   }
   return HS_OK;
 }
 hs_status launch_layernorm_bwd(hs_ctx* ctx, int dtype, const void* dy, const void* x, const float* stats, const void* gain, void* dx,
                                float* d_gain, float* d_bias, float* d_colsum, float beta, int R, int H, void* partials, hipStream_t s,
-                               const DropCfg* drop, uint32_t site, int drop_mode, void* dxm) {
-  hs_status st = launch_layernorm_bwd_rows(ctx, dtype, dy, x, stats, gain, dx, R, H, partials, s, drop, site, drop_mode, dxm);
+                               const DropCfg* drop, uint32_t site, int drop_mode, void* dxm, const int32_t* pad_row) {
+  hs_status st = launch_layernorm_bwd_rows(ctx, dtype, dy, x, stats, gain, dx, R, H, partials, s, drop, site, drop_mode, dxm, pad_row);
   if (st != HS_OK) return st;
   return launch_layernorm_bwd_cols(ctx, partials, d_gain, d_bias, d_colsum, beta, R, H, s);
 }
 
 hs_status launch_embed_ln_fwd(hs_ctx* ctx, int dtype, const void* word, const void* pos, const void* gain, const void* bias,
                               const int32_t* ids, void* e_pre, void* x0, float* stats, int B, int L, int H, int V, float eps, hipStream_t s,
-                              const DropCfg* drop, int stat_ld) {
+                              const DropCfg* drop, int stat_ld, const PackedPart* pk) {
   const DropCfg dcfg = (drop && drop->thr) ? *drop : DropCfg{0u, 1.0f, 0u, 0u, 0u};
   if (stat_ld <= 0) stat_ld = B * L;
   const int R = B * L;
   if (R <= 0) return HS_OK;
   KScope scope(prof_of(ctx), KC_EMBED, 10.0 * R * H, 4.0 * R * H * esize(dtype), s);
   dim3 grid((R + 3) / 4);
-  if (dtype == HS_BF16) hipLaunchKernelGGL(embed_ln_fwd_kernel<bf16>, grid, dim3(256), 0, s, (const bf16*)word, (const bf16*)pos, (const bf16*)gain, (const bf16*)bias, ids, (bf16*)e_pre, (bf16*)x0, stats, R, L, H, V, eps, dcfg, stat_ld);
-  else hipLaunchKernelGGL(embed_ln_fwd_kernel<float>, grid, dim3(256), 0, s, (const float*)word, (const float*)pos, (const float*)gain, (const float*)bias, ids, (float*)e_pre, (float*)x0, stats, R, L, H, V, eps, dcfg, stat_ld);
+  const PackedPart part = pk ? *pk : PackedPart{};
+#define HS_EMBED(TT, PACK) hipLaunchKernelGGL((embed_ln_fwd_kernel<TT, PACK>), grid, dim3(256), 0, s, (const TT*)word, (const TT*)pos, (const TT*)gain, \
+                                              (const TT*)bias, ids, (TT*)e_pre, (TT*)x0, stats, R, L, H, V, eps, dcfg, stat_ld, part)
+  if (dtype == HS_BF16) { if (pk) HS_EMBED(bf16, true); else HS_EMBED(bf16, false); }
+  else { if (pk) HS_EMBED(float, true); else HS_EMBED(float, false); }
+#undef HS_EMBED
   LAUNCH_CHECK(ctx, "embed_ln_fwd");
   return HS_OK;
 }
@@ -703,7 +788,9 @@ size_t embed_bwd_scratch(int T, int H) {
 
 // stable sort of the token ids (keys) with their positions (values) into the first two arrays of `scratch`; needs only the
 // ids, so it can run ahead of the gradient that launch_embed_bwd scatters
-hs_status launch_embed_sort(hs_ctx* ctx, const int32_t* ids, int T, int V, void* scratch, hipStream_t s) {
+hs_status launch_embed_sort(hs_ctx* ctx, const int32_t* ids, int T, int V, void* scratch, hipStream_t s, const PackedRows* pk) {
+  const int positions = T;
+  if (pk) T = pk->rows;
   if (T <= 0) return HS_OK;
   KScope scope(prof_of(ctx), KC_EMBED, 0.0, 16.0 * T, s);
   int32_t* k0 = (int32_t*)scratch;
@@ -712,22 +799,25 @@ hs_status launch_embed_sort(hs_ctx* ctx, const int32_t* ids, int T, int V, void*
   while ((1 << bits) < V) ++bits;
   int npass = (bits + 3) / 4;
   if (npass & 1) ++npass;  // an even number of passes leaves the result in (k0, v0)
-  hipLaunchKernelGGL(sort_ids_kernel, dim3(1), dim3(512), 0, s, ids, T, V, k0, v0, k1, v1, npass);
+  hipLaunchKernelGGL(sort_ids_kernel, dim3(1), dim3(512), 0, s, ids, T, V, k0, v0, k1, v1, npass, pk ? (const int32_t*)pk->pad_row : nullptr, (unsigned)positions);
   LAUNCH_CHECK(ctx, "sort_ids");
   return HS_OK;
 }
 
 hs_status launch_embed_bwd(hs_ctx* ctx, int dtype, const void* de, const int32_t* ids, int B, int L, int H, int V, int max_pos,
-                           float* g_word, float* g_pos, float beta_pos, void* scratch, hipStream_t s, bool sorted) {
-  const int T = B * L;
+                           float* g_word, float* g_pos, float beta_pos, void* scratch, hipStream_t s, bool sorted, const PackedRows* pk) {
+  const int T = pk ? pk->rows : B * L;
   if (T <= 0) return HS_OK;
-  if (!sorted) { hs_status st = launch_embed_sort(ctx, ids, T, V, scratch, s); if (st != HS_OK) return st; }
+  if (!sorted) { hs_status st = launch_embed_sort(ctx, ids, B * L, V, scratch, s, pk); if (st != HS_OK) return st; }
   KScope scope(prof_of(ctx), KC_EMBED, 2.0 * T * H, (double)T * H * (2.0 * esize(dtype) + 8.0) + 8.0 * max_pos * H, s);
   if (g_pos) {     // a model with a fixed position table has no position gradient
     const int64_t n = (int64_t)max_pos * H;
     dim3 grid((unsigned)((n + 255) / 256));
-    if (dtype == HS_BF16) hipLaunchKernelGGL(pos_grad_kernel<bf16>, grid, dim3(64), 0, s, (const bf16*)de, B, L, H, max_pos, g_pos, beta_pos);
-    else hipLaunchKernelGGL(pos_grad_kernel<float>, grid, dim3(64), 0, s, (const float*)de, B, L, H, max_pos, g_pos, beta_pos);
+    const int32_t *lens = pk ? pk->lens : nullptr, *first = pk ? pk->first : nullptr;
+#define HS_POS_GRAD(TT, PACK) hipLaunchKernelGGL((pos_grad_kernel<TT, PACK>), grid, dim3(64), 0, s, (const TT*)de, B, L, H, max_pos, g_pos, beta_pos, lens, first)
+    if (dtype == HS_BF16) { if (pk) HS_POS_GRAD(bf16, true); else HS_POS_GRAD(bf16, false); }
+    else { if (pk) HS_POS_GRAD(float, true); else HS_POS_GRAD(float, false); }
+#undef HS_POS_GRAD
     LAUNCH_CHECK(ctx, "pos_grad");
   }
   int32_t* k0 = (int32_t*)scratch;

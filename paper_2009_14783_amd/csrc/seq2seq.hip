@@ -87,7 +87,11 @@ bool s2s_cfg_valid(const hs_s2s_cfg* c, std::string* why) {
 // ---- saved activations ------------------------------------------------------------------------
 struct EncActs { void *qkv, *ctx, *y1, *x1, *h, *y2, *x2; float *lse, *st1, *st2; };
 struct DecActs { void *qkv, *ctx, *y1s, *y1, *cq, *ckv, *cctx, *ycs, *yc, *h, *y2s, *y2; float *lse, *clse, *st1, *stc, *st2; };
-struct Acts { float* pe; void *x0, *t0; std::vector<EncActs> enc; std::vector<DecActs> dec; size_t total; };
+struct Acts {
+  float* pe; void *x0, *t0; std::vector<EncActs> enc; std::vector<DecActs> dec;
+  int32_t *src_first, *src_pad, *tgt_first, *tgt_pad;      // packed rows (see PackedRows)
+  size_t total;
+};
 
 Acts carve_acts(const hs_s2s_cfg& c, int B, int Ls, int Lt, void* base) {
   const size_t Ts = (size_t)B * Ls, Tt = (size_t)B * Lt, H = c.hidden, F = c.ffn, es = esize(c.compute), A = c.n_heads;
@@ -113,6 +117,8 @@ Acts carve_acts(const hs_s2s_cfg& c, int B, int Ls, int Lt, void* base) {
     l.y2s = cv.take(Tt * H * es); l.st2 = (float*)cv.take(2 * Tt * sizeof(float));
     l.y2 = (i + 1 < a.dec.size()) ? cv.take(Tt * H * es) : nullptr;      // the last layer writes dec_out
   }
+  a.src_first = (int32_t*)cv.take((size_t)B * sizeof(int32_t)); a.src_pad = (int32_t*)cv.take(Ts * sizeof(int32_t));
+  a.tgt_first = (int32_t*)cv.take((size_t)B * sizeof(int32_t)); a.tgt_pad = (int32_t*)cv.take(Tt * sizeof(int32_t));
   a.total = cv.off;
   return a;
 }
@@ -194,6 +200,17 @@ bool shape_ok(const hs_s2s_cfg& c, int B, int Ls, int Lt, std::string* why) {
   return true;
 }
 
+// Whether the passes over this batch have packed rows, as for the encoder-only model: real positions only, on both sides (ms per
+// step, three quarters of the positions real: 24 pairs of 168 and 176 4.52 -> 4.25; 128 of 32, whose launches last 4 - 13 us either way, 4.34 -> 4.29).
+hs_status packed_pairs(hs_ctx* ctx, const char* who, int B, int Ls, int Lt, bool* packed) {
+  *packed = false;
+  if (!ctx->lens_set || B == 0) return HS_OK;
+  if (ctx->lens_a.B != B || ctx->lens_a.L != Ls || ctx->lens_b.L != Lt)
+    return hs_fail(ctx, HS_ERR_STATE, std::string(who) + ": hs_s2s_set_lengths was given another batch");
+  *packed = ctx->s2s.compute == HS_BF16 && (ctx->lens_a.rows() < B * Ls || ctx->lens_b.rows() < B * Lt);
+  return HS_OK;
+}
+
 const void* W(int dt, const void* w, int64_t off) { return dt == HS_BF16 ? (const void*)((const bf16*)w + off) : (const void*)((const float*)w + off); }
 const void* at(int dt, const void* p, int64_t elems) { return (const char*)p + elems * (int64_t)esize(dt); }
 void* at(int dt, void* p, int64_t elems) { return (char*)p + elems * (int64_t)esize(dt); }
@@ -219,13 +236,14 @@ hs_status linear(hs_ctx* ctx, int dt, int T, int N, int K, const void* x, const 
   g.bias = b; g.epi = relu ? 4 : 0;
   return launch_gemm(ctx, g, s);
 }
-// sum = res + drop(x W^T + b) ; out = LN(sum)
+// sum = res + drop(x W^T + b) ; out = LN(sum) (out null: left to the caller)
 hs_status linear_res_ln(hs_ctx* ctx, int dt, int T, int H, int K, const void* x, const void* Wm, const void* b, const void* res, void* sum,
                         const void* gain, const void* beta, void* out, float* stats, int stat_ld, float eps, const DropCfg* drop,
-                        uint32_t site, hipStream_t s) {
+                        const int32_t* drop_rows, uint32_t site, hipStream_t s) {
   GemmArgs g = gemm_args(dt, 1, 1, T, H, K, x, K, Wm, K, sum, H);
-  g.bias = b; g.epi = 1; g.aux = res; g.ldaux = H; g.drop = drop; g.drop_site = site;
+  g.bias = b; g.epi = 1; g.aux = res; g.ldaux = H; g.drop = drop; g.drop_site = site; g.drop_rows = drop_rows;
   HS_TRY(launch_gemm(ctx, g, s));
+  if (!out) return HS_OK;
   return launch_layernorm_fwd(ctx, dt, sum, gain, beta, out, stats, T, H, eps, s, stat_ld);
 }
 
@@ -286,7 +304,10 @@ hs_status hs_s2s_fwd(hs_ctx* ctx, const void* w, const int32_t* src, const int32
   if (B == 0) return HS_OK;
   if (!w || !src || !src_lens || !tgt_in || !tgt_lens || !acts || !dec_out) return hs_fail(ctx, HS_ERR_INVALID_ARG, "hs_s2s_fwd: NULL buffer");
   const S2SOff o = s2s_offsets(c);
-  const int dt = c.compute, H = c.hidden, F = c.ffn, A = c.n_heads, Ts = B * Ls, Tt = B * Lt;
+  bool packed;
+  HS_TRY(packed_pairs(ctx, "hs_s2s_fwd", B, Ls, Lt, &packed));
+  const HostLens &hs = ctx->lens_a, &ht = ctx->lens_b;
+  const int dt = c.compute, H = c.hidden, F = c.ffn, A = c.n_heads, Ts = packed ? hs.rows() : B * Ls, Tt = packed ? ht.rows() : B * Lt;      // rows
   hipStream_t s = (hipStream_t)stream;
   Acts a = carve_acts(c, B, Ls, Lt, acts);
   const DropCfg* drop = ctx->drop.thr ? &ctx->drop : nullptr;
@@ -304,24 +325,30 @@ hs_status hs_s2s_fwd(hs_ctx* ctx, const void* w, const int32_t* src, const int32
     HS_HIP_CHECK(ctx, hipEventRecord(ctx->events[0], s));
     HS_HIP_CHECK(ctx, hipStreamWaitEvent(ctx->side, ctx->events[0], 0));
   }
-  struct Part { int b0, nb; hipStream_t st; };
-  const Part part[2] = {{0, split ? B / 2 : B, s}, {B / 2, B - B / 2, split ? ctx->side : s}};
+  struct Part { int b0, nb, src0, tgt0, src_n, tgt_n; hipStream_t st; };      // sequences, and first row and rows of either side
+  const int cut = !split ? B : packed ? ht.half() : B / 2;
+  const int src_cut = packed ? hs.first[cut] : cut * Ls, tgt_cut = packed ? ht.first[cut] : cut * Lt;
+  const Part part[2] = {{0, cut, 0, 0, src_cut, tgt_cut, s}, {cut, B - cut, src_cut, tgt_cut, Ts - src_cut, Tt - tgt_cut, split ? ctx->side : s}};
   const int nparts = split ? 2 : 1;
-  DropCfg drop_src[2], drop_tgt[2];      // dropout state of a half for tensors of [Ts, H] and [Tt, H] elements
+  // dropout state of a half for tensors of [B, Ls, H] and [B, Lt, H] elements (the products' elements are numbered by the position if rows are packed)
+  DropCfg drop_src[2], drop_tgt[2];
   for (int k = 0; k < 2; ++k) {
     drop_src[k] = drop_at(ctx->drop, (uint64_t)part[k].b0 * Ls * H);
     drop_tgt[k] = drop_at(ctx->drop, (uint64_t)part[k].b0 * Lt * H);
   }
-  // rows of sequence b0 onwards in a buffer with L positions per sequence and `width` elements per position
-  auto src_rows = [&](const void* p, const Part& pt, int64_t width) { return (const void*)((const char*)p + (int64_t)pt.b0 * Ls * width * es); };
-  auto tgt_rows = [&](const void* p, const Part& pt, int64_t width) { return (const void*)((const char*)p + (int64_t)pt.b0 * Lt * width * es); };
+  // rows of sequence b0 onwards in a buffer of `width` elements per row; row 0 for kernels that find their rows themselves
+  auto src_rows = [&](const void* p, const Part& pt, int64_t width) { return (const void*)((const char*)p + pt.src0 * width * es); };
+  auto tgt_rows = [&](const void* p, const Part& pt, int64_t width) { return (const void*)((const char*)p + pt.tgt0 * width * es); };
+  auto src_base = [&](const void* p, const Part& pt, int64_t width) { return packed ? p : src_rows(p, pt, width); };
+  auto tgt_base = [&](const void* p, const Part& pt, int64_t width) { return packed ? p : tgt_rows(p, pt, width); };
   auto mut = [](const void* p) { return const_cast<void*>(p); };
 
   // ---- encoder ----
   for (int k = 0; k < nparts; ++k) {
     const Part& pt = part[k];
-    HS_TRY(launch_embed_scale_pos(ctx, dt, W(dt, w, o.emb), src + (size_t)pt.b0 * Ls, a.pe, mut(src_rows(a.x0, pt, H)), pt.nb, Ls, H, c.vocab, scale,
-                                  drop ? &drop_src[k] : nullptr, site_src(), pt.st));
+    const PackedPart pk{src_lens + pt.b0, a.src_first + pt.b0, a.src_pad, pt.src0, pt.b0 * Ls};
+    HS_TRY(launch_embed_scale_pos(ctx, dt, W(dt, w, o.emb), src + (size_t)pt.b0 * Ls, a.pe, mut(src_base(a.x0, pt, H)), pt.nb, Ls, H, c.vocab, scale,
+                                  drop ? &drop_src[k] : nullptr, site_src(), pt.st, packed ? &pk : nullptr));
   }
   const void* x = a.x0;
   for (int i = 0; i < c.n_enc; ++i) {
@@ -329,16 +356,19 @@ hs_status hs_s2s_fwd(hs_ctx* ctx, const void* w, const int32_t* src, const int32
     EncActs& la = a.enc[i];
     for (int k = 0; k < nparts; ++k) {
       const Part& pt = part[k];
-      const int T = pt.nb * Ls;
+      const int T = pt.src_n;
       hipStream_t st = pt.st;
+      const DropCfg* dr = !drop ? nullptr : packed ? drop : &drop_src[k];
+      const int32_t* drows = packed ? a.src_pad + pt.src0 : nullptr;
       auto R = [&](const void* p, int64_t width) { return src_rows(p, pt, width); };
       HS_TRY(linear(ctx, dt, T, 3 * H, H, R(x, H), W(dt, w, lo.qkv_w), W(dt, w, lo.qkv_b), mut(R(la.qkv, 3 * H)), st));
-      HS_TRY(launch_attention_fwd(ctx, dt, R(la.qkv, 3 * H), src_lens + pt.b0, pt.nb, Ls, A, mut(R(la.ctx, H)), la.lse + (size_t)pt.b0 * A * Ls, st));
+      HS_TRY(launch_attention_fwd(ctx, dt, src_base(la.qkv, pt, 3 * H), src_lens + pt.b0, pt.nb, Ls, A, mut(src_base(la.ctx, pt, H)),
+                                  la.lse + (size_t)pt.b0 * A * Ls, st, nullptr, 0, packed ? a.src_first + pt.b0 : nullptr));
       HS_TRY(linear_res_ln(ctx, dt, T, H, H, R(la.ctx, H), W(dt, w, lo.o_w), W(dt, w, lo.o_b), R(x, H), mut(R(la.y1, H)), W(dt, w, lo.ln1_g),
-                           W(dt, w, lo.ln1_b), mut(R(la.x1, H)), la.st1 + (size_t)pt.b0 * Ls, Ts, c.ln_eps, drop ? &drop_src[k] : nullptr, site_enc(i, 0), st));
+                           W(dt, w, lo.ln1_b), mut(R(la.x1, H)), la.st1 + pt.src0, Ts, c.ln_eps, dr, drows, site_enc(i, 0), st));
       HS_TRY(linear(ctx, dt, T, F, H, R(la.x1, H), W(dt, w, lo.ffn1_w), W(dt, w, lo.ffn1_b), mut(R(la.h, F)), st, true));
       HS_TRY(linear_res_ln(ctx, dt, T, H, F, R(la.h, F), W(dt, w, lo.ffn2_w), W(dt, w, lo.ffn2_b), R(la.x1, H), mut(R(la.y2, H)), W(dt, w, lo.ln2_g),
-                           W(dt, w, lo.ln2_b), mut(R(la.x2, H)), la.st2 + (size_t)pt.b0 * Ls, Ts, c.ln_eps, drop ? &drop_src[k] : nullptr, site_enc(i, 1), st));
+                           W(dt, w, lo.ln2_b), mut(R(la.x2, H)), la.st2 + pt.src0, Ts, c.ln_eps, dr, drows, site_enc(i, 1), st));
     }
     x = la.x2;
   }
@@ -347,8 +377,9 @@ hs_status hs_s2s_fwd(hs_ctx* ctx, const void* w, const int32_t* src, const int32
   // ---- decoder ----
   for (int k = 0; k < nparts; ++k) {
     const Part& pt = part[k];
-    HS_TRY(launch_embed_scale_pos(ctx, dt, W(dt, w, o.emb), tgt_in + (size_t)pt.b0 * Lt, a.pe, mut(tgt_rows(a.t0, pt, H)), pt.nb, Lt, H, c.vocab,
-                                  scale, drop ? &drop_tgt[k] : nullptr, site_tgt(), pt.st));
+    const PackedPart pk{tgt_lens + pt.b0, a.tgt_first + pt.b0, a.tgt_pad, pt.tgt0, pt.b0 * Lt};
+    HS_TRY(launch_embed_scale_pos(ctx, dt, W(dt, w, o.emb), tgt_in + (size_t)pt.b0 * Lt, a.pe, mut(tgt_base(a.t0, pt, H)), pt.nb, Lt, H, c.vocab,
+                                  scale, drop ? &drop_tgt[k] : nullptr, site_tgt(), pt.st, packed ? &pk : nullptr));
   }
   const void* y = a.t0;
   for (int i = 0; i < c.n_dec; ++i) {
@@ -357,29 +388,35 @@ hs_status hs_s2s_fwd(hs_ctx* ctx, const void* w, const int32_t* src, const int32
     void* y2 = la.y2 ? la.y2 : dec_out;
     for (int k = 0; k < nparts; ++k) {
       const Part& pt = part[k];
-      const int T = pt.nb * Lt, TS = pt.nb * Ls;
+      const int T = pt.tgt_n, TS = pt.src_n;
       hipStream_t st = pt.st;
+      const DropCfg* dr = !drop ? nullptr : packed ? drop : &drop_tgt[k];
+      const int32_t* drows = packed ? a.tgt_pad + pt.tgt0 : nullptr;
+      const int32_t *tf = packed ? a.tgt_first + pt.b0 : nullptr, *sf = packed ? a.src_first + pt.b0 : nullptr;
+      const bool unpack = packed && !la.y2;      // the last layer: the caller's buffer has the padded rows
       auto R = [&](const void* p, int64_t width) { return tgt_rows(p, pt, width); };
       const int32_t* tl = tgt_lens + pt.b0;
       const int32_t* sl = src_lens + pt.b0;
       HS_TRY(linear(ctx, dt, T, 3 * H, H, R(y, H), W(dt, w, lo.qkv_w), W(dt, w, lo.qkv_b), mut(R(la.qkv, 3 * H)), st));
-      const void* qkv = R(la.qkv, 3 * H);
-      AttnOperands self{qkv, at(dt, qkv, H), at(dt, qkv, 2 * H), 3 * (int64_t)H, 3 * (int64_t)H, tl, tl, Lt, Lt, A, 1};
-      HS_TRY(launch_attention_general_fwd(ctx, dt, self, pt.nb, mut(R(la.ctx, H)), la.lse + (size_t)pt.b0 * A * Lt, st));
+      const void* qkv = tgt_base(la.qkv, pt, 3 * H);
+      AttnOperands self{qkv, at(dt, qkv, H), at(dt, qkv, 2 * H), 3 * (int64_t)H, 3 * (int64_t)H, tl, tl, Lt, Lt, A, 1, tf, tf};
+      HS_TRY(launch_attention_general_fwd(ctx, dt, self, pt.nb, mut(tgt_base(la.ctx, pt, H)), la.lse + (size_t)pt.b0 * A * Lt, st));
       HS_TRY(linear_res_ln(ctx, dt, T, H, H, R(la.ctx, H), W(dt, w, lo.o_w), W(dt, w, lo.o_b), R(y, H), mut(R(la.y1s, H)), W(dt, w, lo.ln1_g),
-                           W(dt, w, lo.ln1_b), mut(R(la.y1, H)), la.st1 + (size_t)pt.b0 * Lt, Tt, c.ln_eps, drop ? &drop_tgt[k] : nullptr, site_dec(c, i, 0), st));
+                           W(dt, w, lo.ln1_b), mut(R(la.y1, H)), la.st1 + pt.tgt0, Tt, c.ln_eps, dr, drows, site_dec(c, i, 0), st));
       HS_TRY(linear(ctx, dt, T, H, H, R(la.y1, H), W(dt, w, lo.cq_w), W(dt, w, lo.cq_b), mut(R(la.cq, H)), st));
-      const void* ckv = src_rows(la.ckv, pt, 2 * H);
-      HS_TRY(linear(ctx, dt, TS, 2 * H, H, src_rows(enc_out, pt, H), W(dt, w, lo.ckv_w), W(dt, w, lo.ckv_b), mut(ckv), st));
-      AttnOperands cross{R(la.cq, H), ckv, at(dt, ckv, H), (int64_t)H, 2 * (int64_t)H, tl, sl, Lt, Ls, A, 0};
-      HS_TRY(launch_attention_general_fwd(ctx, dt, cross, pt.nb, mut(R(la.cctx, H)), la.clse + (size_t)pt.b0 * A * Lt, st));
+      HS_TRY(linear(ctx, dt, TS, 2 * H, H, src_rows(enc_out, pt, H), W(dt, w, lo.ckv_w), W(dt, w, lo.ckv_b), mut(src_rows(la.ckv, pt, 2 * H)), st));
+      const void* ckv = src_base(la.ckv, pt, 2 * H);
+      AttnOperands cross{tgt_base(la.cq, pt, H), ckv, at(dt, ckv, H), (int64_t)H, 2 * (int64_t)H, tl, sl, Lt, Ls, A, 0, tf, sf};
+      HS_TRY(launch_attention_general_fwd(ctx, dt, cross, pt.nb, mut(tgt_base(la.cctx, pt, H)), la.clse + (size_t)pt.b0 * A * Lt, st));
       HS_TRY(linear_res_ln(ctx, dt, T, H, H, R(la.cctx, H), W(dt, w, lo.co_w), W(dt, w, lo.co_b), R(la.y1, H), mut(R(la.ycs, H)),
-                           W(dt, w, lo.lnc_g), W(dt, w, lo.lnc_b), mut(R(la.yc, H)), la.stc + (size_t)pt.b0 * Lt, Tt, c.ln_eps, drop ? &drop_tgt[k] : nullptr,
-                           site_dec(c, i, 1), st));
+                           W(dt, w, lo.lnc_g), W(dt, w, lo.lnc_b), mut(R(la.yc, H)), la.stc + pt.tgt0, Tt, c.ln_eps, dr, drows, site_dec(c, i, 1), st));
       HS_TRY(linear(ctx, dt, T, F, H, R(la.yc, H), W(dt, w, lo.ffn1_w), W(dt, w, lo.ffn1_b), mut(R(la.h, F)), st, true));
       HS_TRY(linear_res_ln(ctx, dt, T, H, F, R(la.h, F), W(dt, w, lo.ffn2_w), W(dt, w, lo.ffn2_b), R(la.yc, H), mut(R(la.y2s, H)),
-                           W(dt, w, lo.ln2_g), W(dt, w, lo.ln2_b), mut(R(y2, H)), la.st2 + (size_t)pt.b0 * Lt, Tt, c.ln_eps, drop ? &drop_tgt[k] : nullptr,
+                           W(dt, w, lo.ln2_g), W(dt, w, lo.ln2_b), unpack ? nullptr : mut(R(y2, H)), la.st2 + pt.tgt0, Tt, c.ln_eps, dr, drows,
                            site_dec(c, i, 2), st));
+      if (unpack)
+        HS_TRY(launch_layernorm_fwd_unpack(ctx, dt, la.y2s, W(dt, w, lo.ln2_g), W(dt, w, lo.ln2_b), at(dt, dec_out, (int64_t)pt.b0 * Lt * H), la.st2, tl,
+                                           tf, pt.nb, Lt, H, c.ln_eps, st, Tt));
     }
     y = y2;
   }
@@ -470,9 +507,16 @@ hs_status hs_s2s_bwd(hs_ctx* ctx, const void* w, const void* acts, const int32_t
     return hs_fail(ctx, HS_ERR_INVALID_ARG, "hs_s2s_bwd: NULL buffer");
   if (workspace_bytes < carve_bwd(c, B, Ls, Lt, nullptr).total) return hs_fail(ctx, HS_ERR_WORKSPACE, "hs_s2s_bwd: workspace too small");
   const S2SOff o = s2s_offsets(c);
-  const int dt = c.compute, H = c.hidden, F = c.ffn, A = c.n_heads, Ts = B * Ls, Tt = B * Lt;
+  bool packed;
+  HS_TRY(packed_pairs(ctx, "hs_s2s_bwd", B, Ls, Lt, &packed));
+  const int dt = c.compute, H = c.hidden, F = c.ffn, A = c.n_heads;
+  const int Ts = packed ? ctx->lens_a.rows() : B * Ls, Tt = packed ? ctx->lens_b.rows() : B * Lt;      // rows
   hipStream_t s = (hipStream_t)stream;
   Acts a = carve_acts(c, B, Ls, Lt, const_cast<void*>(acts));
+  const PackedRows packed_src{src_lens, a.src_first, a.src_pad, Ts}, packed_tgt{tgt_lens, a.tgt_first, a.tgt_pad, Tt};
+  const PackedRows *pks = packed ? &packed_src : nullptr, *pkt = packed ? &packed_tgt : nullptr;
+  const int32_t *src_pad = packed ? a.src_pad : nullptr, *tgt_pad = packed ? a.tgt_pad : nullptr;
+  const int32_t *src_first = packed ? a.src_first : nullptr, *tgt_first = packed ? a.tgt_first : nullptr;
   BwdWs ws = carve_bwd(c, B, Ls, Lt, workspace);
   const float beta = accumulate ? 1.f : 0.f;
   const DropCfg* drop = ctx->drop.thr ? &ctx->drop : nullptr;
@@ -525,12 +569,12 @@ hs_status hs_s2s_bwd(hs_ctx* ctx, const void* w, const void* acts, const int32_t
   // LayerNorm backward of a sub-layer: dsum = d(residual sum); the branch takes dsum through the sub-layer's dropout
   // (dmask; dsum itself without dropout).  The column sums of its partials are the gain and bias gradients, and the bias
   // gradient of the sub-layer's last linear map (column sums of the branch gradient).  Returns the branch gradient.
-  auto ln_bwd = [&](int T, std::vector<LnColsJob>& cols, const void* dy, const void* sum, const float* stats, int64_t gain, int64_t lnb,
+  auto ln_bwd = [&](int T, const int32_t* pad_row, std::vector<LnColsJob>& cols, const void* dy, const void* sum, const float* stats, int64_t gain, int64_t lnb,
                     int64_t last_bias, uint32_t site, void* dsum, void* dmask, void* partials, const void** branch) -> hs_status {
     *branch = drop ? dmask : dsum;
     cols.push_back({partials, g + gain, g + lnb, g + last_bias});
     return launch_layernorm_bwd_rows(ctx, dt, dy, sum, stats, W(dt, w, gain), dsum, T, H, partials, s, drop, site, drop ? 2 : 0,
-                                     drop ? dmask : nullptr);
+                                     drop ? dmask : nullptr, pad_row, dy == d_dec_out ? B * Lt : 0);
   };
   // feed-forward backward: from the branch gradient to d(input of the sub-layer) = dsum + dh W1, written to out
   auto ffn_bwd = [&](int T, const BlockOff& lo, const LayerGrads& lg, const void* branch, const void* xin, const void* h, void* out) -> hs_status {
@@ -556,13 +600,14 @@ hs_status hs_s2s_bwd(hs_ctx* ctx, const void* w, const void* acts, const int32_t
     const void* y_in = (i == 0) ? a.t0 : a.dec[i - 1].y2;
     const void* br;
     // feed-forward sub-layer
-    HS_TRY(ln_bwd(Tt, cols_tgt, dcur, la.y2s, la.st2, lo.ln2_g, lo.ln2_b, lo.ffn2_b, site_dec(c, i, 2), lg.s2, lg.m2, lg.p2, &br));
+    HS_TRY(ln_bwd(Tt, tgt_pad, cols_tgt, dcur, la.y2s, la.st2, lo.ln2_g, lo.ln2_b, lo.ffn2_b, site_dec(c, i, 2), lg.s2, lg.m2, lg.p2, &br));
     HS_TRY(ffn_bwd(Tt, lo, lg, br, la.yc, la.h, ws.da));
     // attention over the encoder output
-    HS_TRY(ln_bwd(Tt, cols_tgt, ws.da, la.ycs, la.stc, lo.lnc_g, lo.lnc_b, lo.co_b, site_dec(c, i, 1), lg.sc, lg.mc, lg.pc, &br));
+    HS_TRY(ln_bwd(Tt, tgt_pad, cols_tgt, ws.da, la.ycs, la.stc, lo.lnc_g, lo.lnc_b, lo.co_b, site_dec(c, i, 1), lg.sc, lg.mc, lg.pc, &br));
     wgrad(H, H, Tt, br, H, la.cctx, H, g + lo.co_w);
     HS_TRY(dgrad(Tt, H, H, br, W(dt, w, lo.co_w), ws.dctx, nullptr));
-    AttnOperands cross{la.cq, la.ckv, at(dt, (const void*)la.ckv, H), (int64_t)H, 2 * (int64_t)H, tgt_lens, src_lens, Lt, Ls, A, 0};
+    AttnOperands cross{la.cq, la.ckv, at(dt, (const void*)la.ckv, H), (int64_t)H, 2 * (int64_t)H, tgt_lens, src_lens, Lt, Ls, A, 0,
+                       tgt_first, src_first};
     HS_TRY(launch_attention_general_bwd(ctx, dt, cross, B, la.cctx, la.clse, ws.dctx, lg.dcq, H, lg.dckv, at(dt, lg.dckv, H), 2 * (int64_t)H,
                                         ws.dvec, s));
     bias_grad(lg.dckv, Ts, 2 * H, g + lo.ckv_b);
@@ -573,11 +618,11 @@ hs_status hs_s2s_bwd(hs_ctx* ctx, const void* w, const void* acts, const int32_t
     pe ^= 1; have_denc = true;
     HS_TRY(dgrad(Tt, H, H, lg.dcq, W(dt, w, lo.cq_w), ws.db, lg.sc));
     // causal self-attention
-    HS_TRY(ln_bwd(Tt, cols_tgt, ws.db, la.y1s, la.st1, lo.ln1_g, lo.ln1_b, lo.o_b, site_dec(c, i, 0), lg.s1, lg.m1, lg.p1, &br));
+    HS_TRY(ln_bwd(Tt, tgt_pad, cols_tgt, ws.db, la.y1s, la.st1, lo.ln1_g, lo.ln1_b, lo.o_b, site_dec(c, i, 0), lg.s1, lg.m1, lg.p1, &br));
     wgrad(H, H, Tt, br, H, la.ctx, H, g + lo.o_w);
     HS_TRY(dgrad(Tt, H, H, br, W(dt, w, lo.o_w), ws.dctx, nullptr));
     AttnOperands self{la.qkv, at(dt, (const void*)la.qkv, H), at(dt, (const void*)la.qkv, 2 * H), 3 * (int64_t)H, 3 * (int64_t)H, tgt_lens, tgt_lens,
-                      Lt, Lt, A, 1};
+                      Lt, Lt, A, 1, tgt_first, tgt_first};
     HS_TRY(launch_attention_general_bwd(ctx, dt, self, B, la.ctx, la.lse, ws.dctx, lg.dqkv, 3 * (int64_t)H, at(dt, lg.dqkv, H),
                                         at(dt, lg.dqkv, 2 * H), 3 * (int64_t)H, ws.dvec, s));
     bias_grad(lg.dqkv, Tt, 3 * H, g + lo.qkv_b);
@@ -591,10 +636,10 @@ hs_status hs_s2s_bwd(hs_ctx* ctx, const void* w, const void* acts, const int32_t
   }
   // target embedding: d E[id] += sqrt(H) * (gradient through the embedding dropout).  The scatter (sort of the ids, segment
   // sums) runs on the second stream like the weight gradients; both embedding scatters add into the same slice, in this order.
-  HS_TRY(launch_mask_scale(ctx, dt, dcur, ws.de_tgt, (size_t)Tt * H, scale, drop, site_tgt(), s));
+  HS_TRY(launch_mask_scale(ctx, dt, dcur, ws.de_tgt, (size_t)Tt * H, scale, drop, site_tgt(), s, tgt_pad, H));
   HS_TRY(order(s, sd));
-  HS_TRY(launch_embed_bwd(ctx, dt, ws.de_tgt, tgt_in, B, Lt, H, c.vocab, 0, g + o.emb, nullptr, 0.f, ws.emb, sd));
-  HS_TRY(launch_embed_sort(ctx, src, Ts, c.vocab, ws.emb, sd));      // now, and not behind the last product of the chain
+  HS_TRY(launch_embed_bwd(ctx, dt, ws.de_tgt, tgt_in, B, Lt, H, c.vocab, 0, g + o.emb, nullptr, 0.f, ws.emb, sd, false, pkt));
+  HS_TRY(launch_embed_sort(ctx, src, B * Ls, c.vocab, ws.emb, sd, pks));      // now, and not behind the last product of the chain
 
   // ---- encoder ----
   dcur = ws.denc[pe];
@@ -604,12 +649,12 @@ hs_status hs_s2s_bwd(hs_ctx* ctx, const void* w, const void* acts, const int32_t
     const LayerGrads& lg = ws.enc[i];
     const void* x_in = (i == 0) ? a.x0 : a.enc[i - 1].x2;
     const void* br;
-    HS_TRY(ln_bwd(Ts, cols_src, dcur, la.y2, la.st2, lo.ln2_g, lo.ln2_b, lo.ffn2_b, site_enc(i, 1), lg.s2, lg.m2, lg.p2, &br));
+    HS_TRY(ln_bwd(Ts, src_pad, cols_src, dcur, la.y2, la.st2, lo.ln2_g, lo.ln2_b, lo.ffn2_b, site_enc(i, 1), lg.s2, lg.m2, lg.p2, &br));
     HS_TRY(ffn_bwd(Ts, lo, lg, br, la.x1, la.h, ws.da));
-    HS_TRY(ln_bwd(Ts, cols_src, ws.da, la.y1, la.st1, lo.ln1_g, lo.ln1_b, lo.o_b, site_enc(i, 0), lg.s1, lg.m1, lg.p1, &br));
+    HS_TRY(ln_bwd(Ts, src_pad, cols_src, ws.da, la.y1, la.st1, lo.ln1_g, lo.ln1_b, lo.o_b, site_enc(i, 0), lg.s1, lg.m1, lg.p1, &br));
     wgrad(H, H, Ts, br, H, la.ctx, H, g + lo.o_w);
     HS_TRY(dgrad(Ts, H, H, br, W(dt, w, lo.o_w), ws.dctx, nullptr));
-    HS_TRY(launch_attention_bwd(ctx, dt, la.qkv, la.ctx, la.lse, ws.dctx, src_lens, B, Ls, A, lg.dqkv, ws.dvec, s));
+    HS_TRY(launch_attention_bwd(ctx, dt, la.qkv, la.ctx, la.lse, ws.dctx, src_lens, B, Ls, A, lg.dqkv, ws.dvec, s, nullptr, 0, src_first));
     bias_grad(lg.dqkv, Ts, 3 * H, g + lo.qkv_b);
     wgrad(3 * H, H, Ts, lg.dqkv, 3 * H, x_in, H, g + lo.qkv_w);
     HS_TRY(dgrad(Ts, H, 3 * H, lg.dqkv, W(dt, w, lo.qkv_w), ws.db, lg.s1));
@@ -619,9 +664,9 @@ hs_status hs_s2s_bwd(hs_ctx* ctx, const void* w, const void* acts, const int32_t
       enc_top = i - 1;
     }
   }
-  HS_TRY(launch_mask_scale(ctx, dt, dcur, ws.de_src, (size_t)Ts * H, scale, drop, site_src(), s));
+  HS_TRY(launch_mask_scale(ctx, dt, dcur, ws.de_src, (size_t)Ts * H, scale, drop, site_src(), s, src_pad, H));
   HS_TRY(order(s, sd));
-  HS_TRY(launch_embed_bwd(ctx, dt, ws.de_src, src, B, Ls, H, c.vocab, 0, g + o.emb, nullptr, 0.f, ws.emb, sd, true));
+  HS_TRY(launch_embed_bwd(ctx, dt, ws.de_src, src, B, Ls, H, c.vocab, 0, g + o.emb, nullptr, 0.f, ws.emb, sd, true, pks));
   if (upd.on) HS_TRY(update_slice(ctx, upd, o.emb, o.enc[0].qkv_w, sd, true));      // the shared embedding: its gradient is complete only now
   return order(sd, s);     // everything the second stream did is ordered before whatever the caller enqueues next
 }

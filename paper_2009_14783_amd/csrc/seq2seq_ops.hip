@@ -37,12 +37,23 @@ __global__ __launch_bounds__(256) void position_table_kernel(float* __restrict__
 }
 
 // x[b, l, c] = drop(scale * E[ids[b, l], c] + PE[l, c]); one block per token, four columns per thread
-template <class T>
+// PACK: position l of sequence b goes to packed row first[b] + l, padding nowhere; first and pad_row are written here.
+template <class T, bool PACK>
 __global__ __launch_bounds__(128) void embed_scale_pos_kernel(const T* __restrict__ emb, const int32_t* __restrict__ ids,
                                                               const float* __restrict__ pe, T* __restrict__ x, int L, int H, int V, float scale,
-                                                              DropCfg drop, uint32_t site) {
+                                                              DropCfg drop, uint32_t site, PackedPart pk) {
   const int64_t row = blockIdx.x;
-  const int l = (int)(row % L);
+  const int b = (int)(row / L), l = (int)(row - (int64_t)b * L);
+  int64_t to = row;
+  if (PACK) {
+    if (l >= packed_len(pk.lens, b, L)) return;
+    const int f = pk.row0 + packed_before(pk.lens, b, L, threadIdx.x & 63);
+    to = f + l;
+    if (threadIdx.x == 0) {
+      pk.pad_row[to] = pk.pos0 + (int)row;
+      if (l == 0) pk.first[b] = f;
+    }
+  }
   int id = ids[row];
   id = id < 0 ? 0 : (id >= V ? V - 1 : id);
   for (int c = 4 * threadIdx.x; c < H; c += 512) {
@@ -54,19 +65,24 @@ __global__ __launch_bounds__(128) void embed_scale_pos_kernel(const T* __restric
       drop_factors4(drop, site, ((uint64_t)row * H + c) >> 2, f);
       v.x *= f[0]; v.y *= f[1]; v.z *= f[2]; v.w *= f[3];
     }
-    V4<T>::st(x + row * H + c, v);
+    V4<T>::st(x + to * H + c, v);
   }
 }
 
-// y = alpha * f * x with f the dropout factors of `site` (f = 1 when off); four elements per thread
+// y = alpha * f * x with f the dropout factors of `site` (f = 1 when off); four elements per thread.  pad_row: the position of each (packed) row of
+// H4 groups of four, which numbers the site's elements, or null
 template <class T>
 __global__ __launch_bounds__(256) void mask_scale_kernel(const T* __restrict__ x, T* __restrict__ y, size_t n4, float alpha, DropCfg drop,
-                                                         uint32_t site) {
+                                                         uint32_t site, const int32_t* __restrict__ pad_row, int H4) {
   const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= n4) return;
   float4 v = V4<T>::ld(x + 4 * i);
   float f[4] = {1.f, 1.f, 1.f, 1.f};
-  if (drop.thr) drop_factors4(drop, site, (uint64_t)i, f);
+  if (drop.thr) {
+    uint64_t group = i;
+    if (pad_row) { const int row = (int)(i / H4); group = (uint64_t)pad_row[row] * H4 + (i - (size_t)row * H4); }
+    drop_factors4(drop, site, group, f);
+  }
   v.x *= alpha * f[0]; v.y *= alpha * f[1]; v.z *= alpha * f[2]; v.w *= alpha * f[3];
   V4<T>::st(y + 4 * i, v);
 }
@@ -251,27 +267,31 @@ hs_status launch_position_table(hs_ctx* ctx, float* pe, int L, int H, hipStream_
 }
 
 hs_status launch_embed_scale_pos(hs_ctx* ctx, int dtype, const void* emb, const int32_t* ids, const float* pe, void* x, int B, int L, int H, int V,
-                                 float scale, const DropCfg* drop_in, uint32_t site, hipStream_t s) {
+                                 float scale, const DropCfg* drop_in, uint32_t site, hipStream_t s, const PackedPart* pk) {
   if (B <= 0 || L <= 0) return HS_OK;
   const DropCfg drop = (drop_in && drop_in->thr) ? *drop_in : DropCfg{0u, 1.0f, 0u, 0u, 0u};
   KScope scope(ctx ? ctx->prof : nullptr, KC_EMBED, 2.0 * B * L * H, 2.0 * B * L * H * esize(dtype), s);
   dim3 grid((unsigned)(B * L));
-  if (dtype == HS_BF16) hipLaunchKernelGGL(embed_scale_pos_kernel<bf16>, grid, dim3(128), 0, s, (const bf16*)emb, ids, pe, (bf16*)x, L, H, V, scale, drop, site);
-  else hipLaunchKernelGGL(embed_scale_pos_kernel<float>, grid, dim3(128), 0, s, (const float*)emb, ids, pe, (float*)x, L, H, V, scale, drop, site);
+  const PackedPart part = pk ? *pk : PackedPart{};
+#define HS_EMBED_SCALE(TT, PACK) hipLaunchKernelGGL((embed_scale_pos_kernel<TT, PACK>), grid, dim3(128), 0, s, (const TT*)emb, ids, pe, (TT*)x, L, H, V, \
+                                                    scale, drop, site, part)
+  if (dtype == HS_BF16) { if (pk) HS_EMBED_SCALE(bf16, true); else HS_EMBED_SCALE(bf16, false); }
+  else { if (pk) HS_EMBED_SCALE(float, true); else HS_EMBED_SCALE(float, false); }
+#undef HS_EMBED_SCALE
   S2S_LAUNCH_CHECK(ctx, "embed_scale_pos");
   return HS_OK;
 }
 
 hs_status launch_mask_scale(hs_ctx* ctx, int dtype, const void* x, void* y, size_t n, float alpha, const DropCfg* drop_in, uint32_t site,
-                            hipStream_t s) {
+                            hipStream_t s, const int32_t* pad_row, int H) {
   if (n == 0) return HS_OK;
   if (n & 3) return hs_fail(ctx, HS_ERR_SHAPE, "mask_scale: element count must be a multiple of 4");
   const DropCfg drop = (drop_in && drop_in->thr) ? *drop_in : DropCfg{0u, 1.0f, 0u, 0u, 0u};
   KScope scope(ctx ? ctx->prof : nullptr, KC_ELEMWISE, (double)n, 2.0 * n * esize(dtype), s);
   const size_t n4 = n / 4;
   dim3 grid((unsigned)((n4 + 255) / 256));
-  if (dtype == HS_BF16) hipLaunchKernelGGL(mask_scale_kernel<bf16>, grid, dim3(256), 0, s, (const bf16*)x, (bf16*)y, n4, alpha, drop, site);
-  else hipLaunchKernelGGL(mask_scale_kernel<float>, grid, dim3(256), 0, s, (const float*)x, (float*)y, n4, alpha, drop, site);
+  if (dtype == HS_BF16) hipLaunchKernelGGL(mask_scale_kernel<bf16>, grid, dim3(256), 0, s, (const bf16*)x, (bf16*)y, n4, alpha, drop, site, pad_row, H / 4);
+  else hipLaunchKernelGGL(mask_scale_kernel<float>, grid, dim3(256), 0, s, (const float*)x, (float*)y, n4, alpha, drop, site, pad_row, H / 4);
   S2S_LAUNCH_CHECK(ctx, "mask_scale");
   return HS_OK;
 }

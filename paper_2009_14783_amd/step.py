@@ -89,13 +89,21 @@ class Worker:
             hs.hs_set_dropout(self.ctx, drop["p"] if drop else 0.0, drop["seed"] if drop else 0, drop["stream"] if drop else 0)
             self._drop_on = drop is not None
         w = self.w_compute
-        hs.hs_encoder_fwd(self.ctx, w, d["ids"], d["lens"], d["lens_host"], B, L, self._acts, self._hidden, self._ws,
-                          self._ws_bytes)
-        loss_ptr = self.loss_buf.data_ptr() + 4 * loss_slot
-        hs.hs_mlm_loss(self.ctx, w, self._hidden, d["mlm_pos"], d["mlm_label"], M, B, L, loss_ptr, self._dhidden, g,
-                       accumulate, self._ws, self._ws_bytes)
-        hs.hs_encoder_bwd(self.ctx, w, self._acts, d["ids"], d["lens"], B, L, self._dhidden, g, accumulate, self._ws,
-                          self._ws_bytes)
+        # A captured pass reads the lengths from the device when it is replayed: it keeps the padded rows.
+        packed = B > 0 and d["lens_host"] is not None and self.compute == hs.HS_BF16 and not torch.cuda.is_current_stream_capturing()
+        if packed:
+            hs.hs_set_lengths(self.ctx, d["lens_host"], B, L)
+        try:
+            hs.hs_encoder_fwd(self.ctx, w, d["ids"], d["lens"], d["lens_host"], B, L, self._acts, self._hidden, self._ws,
+                              self._ws_bytes)
+            loss_ptr = self.loss_buf.data_ptr() + 4 * loss_slot
+            hs.hs_mlm_loss(self.ctx, w, self._hidden, d["mlm_pos"], d["mlm_label"], M, B, L, loss_ptr, self._dhidden, g,
+                           accumulate, self._ws, self._ws_bytes)
+            hs.hs_encoder_bwd(self.ctx, w, self._acts, d["ids"], d["lens"], B, L, self._dhidden, g, accumulate, self._ws,
+                              self._ws_bytes)
+        finally:
+            if packed:
+                hs.hs_set_lengths(self.ctx, None)
 
     def accumulate_micro_batches(self, batches: list, fused: bool = True, arm_last=None) -> int:
         """Runs every micro-batch and leaves the SUM of their gradients in G.  Entries that are
@@ -259,8 +267,11 @@ class PairWorker:
         t = lambda k: torch.from_numpy(np.ascontiguousarray(mb[k], dtype=np.int32)).to(dev)
         out = dict(B=int(mb["src"].shape[0]), Ls=int(mb["src"].shape[1]), Lt=int(mb["tgt_in"].shape[1]), src=t("src"), src_lens=t("src_lens"),
                    tgt_in=t("tgt_in"), tgt_out=t("tgt_out"), tgt_lens=t("tgt_lens"),
+                   src_lens_host=np.ascontiguousarray(mb["src_lens"], dtype=np.int32),
                    tgt_lens_host=np.ascontiguousarray(mb["tgt_lens"], dtype=np.int32), n_seq=int(mb["src"].shape[0]),
                    n_tok=int(np.asarray(mb["tgt_lens"]).sum()), drop=mb.get("drop"))
+        # lengths that the padded passes clamp (a source of length 0) are left to them
+        out["packable"] = all(n.size > 0 and n.min() >= 1 and n.max() <= L for n, L in ((out["src_lens_host"], out["Ls"]), (out["tgt_lens_host"], out["Lt"])))
         self._reserve(out["B"], out["Ls"], out["Lt"])
         return out
 
@@ -272,13 +283,20 @@ class PairWorker:
             hs.hs_set_dropout(self.ctx, drop["p"] if drop else 0.0, drop["seed"] if drop else 0, drop["stream"] if drop else 0)
             self._drop_on = drop is not None
         w = self.w_compute
-        hs.hs_s2s_fwd(self.ctx, w, d["src"], d["src_lens"], d["tgt_in"], d["tgt_lens"], B, Ls, Lt, self._acts, self._out)
-        base = self.loss_buf.data_ptr()
-        hs.hs_s2s_loss(self.ctx, w, self._out, d["tgt_out"], d["tgt_lens"], d.get("tgt_lens_host"), B, Lt, self.eps_ls, base + 4 * slot,
-                       base + 4 * (64 + slot),
-                       self._dout, g, accumulate, self._ws, self._ws_bytes)
-        hs.hs_s2s_bwd(self.ctx, w, self._acts, d["src"], d["src_lens"], d["tgt_in"], d["tgt_lens"], B, Ls, Lt, self._dout, g, accumulate,
-                      self._ws, self._ws_bytes)
+        packed = d.get("packable", False) and d.get("tgt_lens_host") is not None and self.compute == hs.HS_BF16 and not torch.cuda.is_current_stream_capturing()
+        if packed:
+            hs.hs_s2s_set_lengths(self.ctx, d["src_lens_host"], d["tgt_lens_host"], B, Ls, Lt)
+        try:
+            hs.hs_s2s_fwd(self.ctx, w, d["src"], d["src_lens"], d["tgt_in"], d["tgt_lens"], B, Ls, Lt, self._acts, self._out)
+            base = self.loss_buf.data_ptr()
+            hs.hs_s2s_loss(self.ctx, w, self._out, d["tgt_out"], d["tgt_lens"], d.get("tgt_lens_host"), B, Lt, self.eps_ls, base + 4 * slot,
+                           base + 4 * (64 + slot),
+                           self._dout, g, accumulate, self._ws, self._ws_bytes)
+            hs.hs_s2s_bwd(self.ctx, w, self._acts, d["src"], d["src_lens"], d["tgt_in"], d["tgt_lens"], B, Ls, Lt, self._dout, g, accumulate,
+                          self._ws, self._ws_bytes)
+        finally:
+            if packed:
+                hs.hs_s2s_set_lengths(self.ctx, None, None)
 
     def train_step(self, batches: list, adam: dict, denom=None, update_in_backward: bool = False):
         """One optimizer step over the uploaded micro-batches (None = a pass without data).  Returns the weight D used

@@ -1,0 +1,102 @@
+"""Packed rows (hs_set_lengths): passes over the real positions only against passes over the padded batch."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2009_14783_amd import binding as hs
+from paper_2009_14783_amd import synth
+from paper_2009_14783_amd.step import PairWorker, Worker
+
+pytestmark = pytest.mark.gpu
+
+# Both passes form the same sums of the same bf16 values; the products run in other tiles and the weight gradients add their rows in another
+# order, so that single activations round the other way (2^-9 each): the bound of every bf16 gradient against the oracle.
+TOL = 2e-2
+
+
+def rel(a, b):
+    a, b = a.double(), b.double()
+    return float((a - b).norm() / b.norm().clamp_min(1e-12))
+
+
+def real_and_padding(hidden, lens, L):
+    h = hidden.view(len(lens), L, -1)
+    real = torch.cat([h[b, :n] for b, n in enumerate(lens)])
+    pad = torch.cat([h[b, n:] for b, n in enumerate(lens)])
+    return real.float(), pad.float()
+
+
+# lengths of 1 and of L, tiles and 128-row blocks that end inside a sequence, one sequence, passes in one part and in two halves (4096 real
+# rows and more) whose cut is not the middle sequence, both attention backward kernels, one width per register plan of the LayerNorm backward
+@pytest.mark.parametrize("hidden,B,L,lens,p", [
+    (256, 6, 128, [1, 128, 33, 97, 64, 2], 0.0), (256, 6, 128, [1, 128, 33, 97, 64, 2], 0.1), (128, 1, 64, [5], 0.1), (256, 5, 256, [256, 1, 129, 128, 40], 0.1),
+    (768, 70, 96, None, 0.1), (512, 40, 200, None, 0.0), (1024, 3, 56, [56, 7, 55], 0.1)])
+def test_encoder_pass_over_real_rows(hidden, B, L, lens, p):
+    model = dict(n_layers=2, hidden=hidden, n_heads=hidden // 64, ffn=2 * hidden, vocab=1000, max_pos=256, ln_eps=1e-12)
+    lens = lens or [max(1, L - (b * b) // 40) for b in range(B)]
+    theta = synth.init_params(hs.hs_param_layout(hs.make_cfg(**model)), 71)
+    mb = synth.make_micro_batch(synth.rng_for(72), lens, L, model["vocab"], "zipf")
+    wk = Worker(model, "bf16", theta)
+    d = wk.upload(dict(mb, drop=dict(p=p, seed=9, stream=3) if p else None))
+    out = []
+    for use in (dict(d, lens_host=None), d):      # without lengths on the host: padded rows
+        wk.G.fill_(float("nan"))
+        wk._hidden.fill_(float("nan"))
+        wk.forward_backward(use, wk.G, 0, 0)
+        torch.cuda.synchronize()
+        out.append((float(wk.loss_buf[0]), wk.G.clone(), *real_and_padding(wk._hidden[:B * L * hidden], lens, L)))
+    (l0, g0, h0, _), (l1, g1, h1, pad) = out
+    assert abs(l0 - l1) / abs(l0) < 1e-3 and rel(h1, h0) < TOL, (l0, l1, rel(h1, h0))
+    assert bool((pad == 0).all())
+    for name, off, r, c in hs.hs_param_layout(hs.make_cfg(**model)):
+        assert rel(g1[off:off + r * c], g0[off:off + r * c]) < TOL, name
+    wk.forward_backward(d, wk.G, 0, 0)            # the same bits again
+    torch.cuda.synchronize()
+    assert torch.equal(wk.G, g1)
+    wk.close()
+
+
+@pytest.mark.parametrize("B,Ls,Lt,p", [(5, 24, 32, 0.0), (3, 136, 72, 0.1), (130, 32, 40, 0.1)])
+def test_pair_pass_over_real_rows(B, Ls, Lt, p):
+    model = dict(n_enc=2, n_dec=2, hidden=128, n_heads=2, ffn=256, vocab=500, max_pos=160)
+    sl, tl = [max(1, Ls - 3 * (b % 9)) for b in range(B)], [max(1, Lt - 5 * (b % 7)) for b in range(B)]
+    sl[0], tl[-1] = 1, 1
+    layout = hs.hs_s2s_param_layout(hs.make_s2s_cfg(**model))
+    wk = PairWorker(model, "bf16", synth.init_params(layout, 73))
+    mb = synth.make_pair_batch(synth.rng_for(74), sl, tl, Ls, Lt, model["vocab"], "uniform")
+    d = wk.upload(dict(mb, drop=dict(p=p, seed=8, stream=5) if p else None))
+    out = []
+    for use in (dict(d, packable=False), d):
+        wk.G.fill_(float("nan"))
+        wk._out.fill_(float("nan"))
+        wk.forward_backward(use, wk.G, 0, 0)
+        torch.cuda.synchronize()
+        out.append((float(wk.loss_buf[0]), wk.G.clone(), *real_and_padding(wk._out[:B * Lt * 128], tl, Lt)))
+    (l0, g0, h0, _), (l1, g1, h1, pad) = out
+    assert abs(l0 - l1) / abs(l0) < 1e-3 and rel(h1, h0) < TOL
+    assert bool((pad == 0).all())
+    # per stack and not per tensor: a ReLU gate within rounding of zero that falls the other way moves a small tensor by more than the bound
+    for stack in ("emb", "enc0", "enc1", "dec0", "dec1"):
+        at = [slice(off, off + r * c) for name, off, r, c in layout if name.startswith(stack)]
+        assert rel(torch.cat([g1[s] for s in at]), torch.cat([g0[s] for s in at])) < TOL, stack
+    wk.close()
+
+
+def test_gradient_rows_of_the_padding_are_not_read():
+    model = dict(n_layers=1, hidden=128, n_heads=2, ffn=256, vocab=200, max_pos=64, ln_eps=1e-12)
+    wk = Worker(model, "bf16", synth.init_params(hs.hs_param_layout(hs.make_cfg(**model)), 75))
+    lens, L = [64, 9, 30], 64
+    d = wk.upload(synth.make_micro_batch(synth.rng_for(76), lens, L, 200, "uniform"))
+    wk.forward_backward(d, wk.G, 0, 0)
+    torch.cuda.synchronize()
+    want = wk.G.clone()
+    hs.hs_set_lengths(wk.ctx, d["lens_host"], 3, L)
+    hs.hs_encoder_fwd(wk.ctx, wk.w_compute, d["ids"], d["lens"], None, 3, L, wk._acts, wk._hidden, wk._ws, wk._ws_bytes)
+    hs.hs_mlm_loss(wk.ctx, wk.w_compute, wk._hidden, d["mlm_pos"], d["mlm_label"], d["M"], 3, L, wk.loss_buf, wk._dhidden, wk.G, 0, wk._ws, wk._ws_bytes)
+    dh = wk._dhidden[:3 * L * 128].view(3, L, 128)
+    for b, n in enumerate(lens):
+        dh[b, n:] = float("nan")
+    hs.hs_encoder_bwd(wk.ctx, wk.w_compute, wk._acts, d["ids"], d["lens"], 3, L, wk._dhidden, wk.G, 0, wk._ws, wk._ws_bytes)
+    torch.cuda.synchronize()
+    assert torch.equal(wk.G, want)
+    wk.close()

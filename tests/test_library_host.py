@@ -129,3 +129,40 @@ def test_batcher_degenerate_and_errors():
         hs.hs_make_batches([10, 0], 64, 100, 0)
     with pytest.raises(hs.HsError):
         hs.hs_make_batches([10], 0, 100, 0)
+
+
+def test_lengths_of_another_batch_are_refused():
+    """hs_set_lengths: bad lengths leave the state unset, and a call over another shape than the one that was set launches nothing."""
+    ctx = hs.hs_ctx_create(hs.make_cfg(**synth.MODELS["tiny"], compute=hs.HS_BF16))
+    some = np.zeros(64, np.int32)                          # stands for device memory: no call below gets as far as a launch
+    fwd = lambda B, L: hs.hs_encoder_fwd(ctx, some, some, some, None, B, L, some, some, some, 0, stream=0)
+    lens = np.array([3, 8, 1], np.int32)
+    for bad in (np.array([3, 9, 1], np.int32), np.array([3, 0, 1], np.int32)):
+        with pytest.raises(hs.HsError) as e:
+            hs.hs_set_lengths(ctx, bad, 3, 8)
+        assert e.value.status == 1
+    for B, L in ((0, 8), (3, 0)):
+        with pytest.raises(hs.HsError) as e:
+            hs.hs_set_lengths(ctx, lens, B, L)
+        assert e.value.status == 2
+    hs.hs_set_lengths(ctx, lens, 3, 8)
+    for B, L in ((2, 8), (3, 16)):
+        with pytest.raises(hs.HsError) as e:
+            fwd(B, L)
+        assert e.value.status == 4 and "hs_set_lengths" in str(e.value)
+    fwd(0, 8)                                              # an empty batch has no rows of either kind
+    with pytest.raises(hs.HsError) as e:
+        hs.hs_s2s_set_lengths(ctx, lens, lens, 3, 8, 8)    # not a context of the translation model
+    assert e.value.status == 4
+    hs.hs_set_lengths(ctx, None)
+    hs.hs_ctx_destroy(ctx)
+    ctx = hs.hs_s2s_ctx_create(hs.make_s2s_cfg(**synth.S2S_MODELS["s2s_tiny"], compute=hs.HS_BF16))
+    with pytest.raises(hs.HsError) as e:
+        hs.hs_s2s_set_lengths(ctx, lens, None, 3, 8, 8)
+    assert e.value.status == 1
+    hs.hs_s2s_set_lengths(ctx, lens, lens, 3, 8, 16)
+    with pytest.raises(hs.HsError) as e:
+        hs.hs_s2s_fwd(ctx, some, some, some, some, some, 3, 8, 8, some, some, stream=0)
+    assert e.value.status == 4
+    hs.hs_s2s_set_lengths(ctx, None, None)
+    hs.hs_ctx_destroy(ctx)
