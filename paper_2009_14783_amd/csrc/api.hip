@@ -168,7 +168,7 @@ GemmArgs gemm_args(int dtype, int ak, int bk, int M, int N, int K, const void* A
   g.dtype = dtype; g.a_kmajor = ak; g.b_kmajor = bk; g.M = M; g.N = N; g.K = K;
   g.A = A; g.lda = lda; g.B = B; g.ldb = ldb; g.C = C; g.ldc = ldc;
   g.c_f32 = 0; g.beta = 0.f; g.bias = nullptr; g.epi = 0; g.aux = nullptr; g.ldaux = 0; g.C2 = nullptr;
-  g.ws = nullptr; g.ws_bytes = 0; g.a_kpad = 0;
+  g.ws = nullptr; g.ws_bytes = 0; g.a_kpad = 0; g.beside = 0;
   g.drop = nullptr; g.drop_site = 0;
   return g;
 }
@@ -268,7 +268,7 @@ hs_status hs_encoder_fwd(hs_ctx* ctx, const void* w, const int32_t* ids, const i
       const DropCfg* dr = !drop ? nullptr : packed ? drop : &drop_rows[k];
       // q | k | v = x Wqkv^T + b
       GemmArgs g = gemm_args(dt, 1, 1, Tp, 3 * H, H, rows(x, pt, H), H, W(ctx, w, lo.qkv_w), H, rows_w(la.qkv, pt, 3 * H), 3 * H);
-      g.bias = W(ctx, w, lo.qkv_b);
+      g.bias = W(ctx, w, lo.qkv_b); g.beside = split;
       HS_TRY(launch_gemm(ctx, g, st));
       const void* const qkv = packed ? la.qkv : rows(la.qkv, pt, 3 * H);
       HS_TRY(launch_attention_fwd(ctx, dt, qkv, lens + pt.b0, pt.nb, L, c.n_heads, packed ? la.ctx : rows_w(la.ctx, pt, H),
@@ -276,18 +276,18 @@ hs_status hs_encoder_fwd(hs_ctx* ctx, const void* w, const int32_t* ids, const i
                                   packed ? a.first + pt.b0 : nullptr));
       // y1 = x + ctx Wo^T + bo ; x1 = LN(y1)
       g = gemm_args(dt, 1, 1, Tp, H, H, rows(la.ctx, pt, H), H, W(ctx, w, lo.o_w), H, rows_w(la.y1, pt, H), H);
-      g.bias = W(ctx, w, lo.o_b); g.epi = 1; g.aux = rows(x, pt, H); g.ldaux = H;
+      g.bias = W(ctx, w, lo.o_b); g.beside = split; g.epi = 1; g.aux = rows(x, pt, H); g.ldaux = H;
       g.drop = dr; g.drop_site = site_attention_out(i); g.drop_rows = packed ? a.pad_row + pt.row0 : nullptr;
       HS_TRY(launch_gemm(ctx, g, st));
       HS_TRY(launch_layernorm_fwd(ctx, dt, rows(la.y1, pt, H), W(ctx, w, lo.ln1_g), W(ctx, w, lo.ln1_b), rows_w(la.x1, pt, H),
                                   la.st1 + pt.row0, Tp, H, c.ln_eps, st, T));
       // hpre = x1 W1^T + b1 ; h = GELU(hpre)
       g = gemm_args(dt, 1, 1, Tp, F, H, rows(la.x1, pt, H), H, W(ctx, w, lo.ffn1_w), H, rows_w(la.hpre, pt, F), F);
-      g.bias = W(ctx, w, lo.ffn1_b); g.epi = 2; g.C2 = rows_w(la.h, pt, F);
+      g.bias = W(ctx, w, lo.ffn1_b); g.beside = split; g.epi = 2; g.C2 = rows_w(la.h, pt, F);
       HS_TRY(launch_gemm(ctx, g, st));
       // y2 = x1 + h W2^T + b2 ; x2 = LN(y2)
       g = gemm_args(dt, 1, 1, Tp, H, F, rows(la.h, pt, F), F, W(ctx, w, lo.ffn2_w), F, rows_w(la.y2, pt, H), H);
-      g.bias = W(ctx, w, lo.ffn2_b); g.epi = 1; g.aux = rows(la.x1, pt, H); g.ldaux = H;
+      g.bias = W(ctx, w, lo.ffn2_b); g.beside = split; g.epi = 1; g.aux = rows(la.x1, pt, H); g.ldaux = H;
       g.drop = dr; g.drop_site = site_ffn_out(i); g.drop_rows = packed ? a.pad_row + pt.row0 : nullptr;
       HS_TRY(launch_gemm(ctx, g, st));
       if (packed && !la.x2)      // the caller's buffer has the padded rows

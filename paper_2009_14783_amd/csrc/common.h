@@ -247,6 +247,7 @@ struct GemmArgs {
   const void* bias;
   int epi; const void* aux; int64_t ldaux; void* C2;
   void* ws; size_t ws_bytes;   // optional scratch for split-K partial sums
+  int beside;                  // a launch like this one runs beside it, on the other half of a batch
   int a_kpad;                  // A k-major: its rows are zero from K up to the next multiple of 64
   const DropCfg* drop; uint32_t drop_site;   // optional (epi == 1): dropout of product + bias before the residual
   const int32_t* drop_rows;    // the row that numbers the site's elements, for each row of the product (packed rows), or null: its own

@@ -386,7 +386,8 @@ constexpr TileCfg kTileCfg[] = {
     {128, 128, 32, 3, 0, 3.2f, 0.560f, 0.470f, 2.00f}, {256, 256, 64, 1, 1, 2.5f, 1.494f, 1.494f, 6.14f}, {32, 32, 64, 1, 1, 2.5f, 0.011f, 0.104f, 0.90f},
     {128, 192, 64, 2, 1, 2.5f, 1.050f, 0.693f, 2.36f}, {32, 64, 64, 3, 1, 4.0f, 0.146f, 0.120f, 0.33f},   {128, 128, 64, 2, 1, 3.2f, 0.497f, 0.487f, 1.82f},
     {192, 128, 64, 2, 1, 2.5f, 1.050f, 0.705f, 2.00f}, {64, 128, 64, 2, 1, 2.7f, 0.190f, 0.296f, 1.24f},  {128, 64, 64, 2, 0, 2.7f, 0.228f, 0.305f, 1.19f},
-    {128, 128, 64, 2, 1, 2.5f, 0.689f, 0.490f, 1.85f}, {256, 128, 64, 1, 1, 2.5f, 0.814f, 0.814f, 3.92f}, {64, 64, 64, 3, 1, 3.5f, 0.229f, 0.187f, 0.30f}};
+    {128, 128, 64, 2, 1, 2.5f, 0.689f, 0.490f, 1.85f}, {256, 128, 64, 1, 1, 2.5f, 0.814f, 0.814f, 3.92f}, {64, 64, 64, 3, 1, 3.5f, 0.229f, 0.187f, 0.30f},
+    {128, 128, 64, 1, 1, 1.4f, 0.482f, 0.390f, 2.42f}, {64, 64, 64, 2, 1, 3.6f, 0.196f, 0.197f, 0.46f}};
 constexpr int kNumTileCfg = sizeof(kTileCfg) / sizeof(kTileCfg[0]);
 constexpr int kCUs = 256;
 float tiles_time(const TileCfg& c, int64_t tiles, float steps, float outputs) {
@@ -465,6 +466,12 @@ static void choose_cfg(const GemmArgs& g, int* cfg, int* splits) {
   *cfg = 0; *splits = 1;
   for (int c = 0; c < kNumTileCfg; ++c) {
     if (only >= 0 ? c != only : !kTileCfg[c].use) continue;
+    // 12 and 13 are for long contractions of a product that has the chip: with 12 k-tiles their shorter k-tile does not pay for the ring that has to be filled (as the model
+    // prices them they would be taken there too; BERT-base 64 x 128 7.25 -> 7.33 ms per step), and a block that needs a CU's whole LDS keeps the other
+    // half of a forward batch off it (K = 3072 in the halves of 64 x 128: 7.14 -> 7.19).  Their constants were fitted to the choice that comes out: over
+    // 8 products, three widths and 24 row counts from 264 to 17472 2 % faster, 4 % from 776 to 5200 rows.  Two updates of BERT-base with 32 sequences of 64 to
+    // 128 positions 9.03 -> 8.71 ms.
+    if (only < 0 && c >= 12 && (g.K < 1536 || g.beside)) continue;
     // With a scratch buffer the contraction can be split over blocks: partial sums go out as fp32 and are added by a second
     // launch (3 us and their way through memory and back at 3.5 TB/s; for contractions beyond 8192, 5 us at the 10 TB/s that the sums get
     // on their way through the caches: 768 x 768 x 32768, both operands k-major, 81 -> 70 us; 3072 x 768 x 16384 152 -> 111).

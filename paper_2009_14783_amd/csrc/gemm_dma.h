@@ -434,6 +434,13 @@ typedef DmaCfg<1, 1, 2, 2, 1, 64, 3, 3, true> Dma64x64Group;
 typedef DmaCfg<1, 2, 2, 2, 1, 64, 3, 2, true> Dma64x128;
 typedef DmaCfg<2, 1, 2, 2, 1, 64, 3, 2, true> Dma128x64;
 typedef DmaCfg<2, 2, 2, 2, 1, 64, 2, 2, true> Dma128x128;
+// For products of about one tile per CU and a long contraction: twice the waves of Dma128x128, which cover each other's reads and waits where no second block
+// does, and a ring of four; 64 x 64 with fragments read ahead and a ring of four, two blocks per CU.  us against the fastest of the others: 3136 x 768 x 3072
+// 29.3 -> 24.6, 3136 x 768 x 2304 (B n-major) 23.4 -> 19.8, 2056 x 1024 x 4096 35.4 -> 30.1; 64 x 64: 1032 x 768 x 3072 16.0 -> 13.3, 520 x 1024 x 4096 19.1 -> 15.9.
+// (Measured and not kept: rings of six to nine stages with four waves, level; four waves of 128 x 128, 128 x 64 or 96 x 128, 5 - 30 % slower than eight
+// waves of half the size: one wave per SIMD has nothing to run under its waits.)
+typedef DmaCfg<2, 1, 2, 4, 1, 64, 4, 1, true> Dma128x128Lone;
+typedef DmaCfg<1, 1, 2, 2, 1, 64, 4, 2, true> Dma64x64Lone;
 typedef DmaCfg<2, 3, 2, 2, 1, 64, 2, 2, true> Dma128x192;
 typedef DmaCfg<3, 2, 2, 2, 1, 64, 2, 2, true> Dma192x128;
 typedef DmaCfg<2, 2, 4, 2, 1, 64, 3, 1, true> Dma256x128;

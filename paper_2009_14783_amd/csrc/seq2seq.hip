@@ -231,17 +231,18 @@ uint32_t site_enc(int layer, int which) { return 2 + 2 * (uint32_t)layer + which
 uint32_t site_dec(const hs_s2s_cfg& c, int layer, int which) { return 2 + 2 * (uint32_t)c.n_enc + 3 * (uint32_t)layer + which; }
 
 // y = x W^T + b, or its ReLU
-hs_status linear(hs_ctx* ctx, int dt, int T, int N, int K, const void* x, const void* Wm, const void* b, void* y, hipStream_t s, bool relu = false) {
+hs_status linear(hs_ctx* ctx, int dt, int T, int N, int K, const void* x, const void* Wm, const void* b, void* y, hipStream_t s, bool beside,
+                 bool relu = false) {
   GemmArgs g = gemm_args(dt, 1, 1, T, N, K, x, K, Wm, K, y, N);
-  g.bias = b; g.epi = relu ? 4 : 0;
+  g.bias = b; g.epi = relu ? 4 : 0; g.beside = beside;
   return launch_gemm(ctx, g, s);
 }
 // sum = res + drop(x W^T + b) ; out = LN(sum) (out null: left to the caller)
 hs_status linear_res_ln(hs_ctx* ctx, int dt, int T, int H, int K, const void* x, const void* Wm, const void* b, const void* res, void* sum,
                         const void* gain, const void* beta, void* out, float* stats, int stat_ld, float eps, const DropCfg* drop,
-                        const int32_t* drop_rows, uint32_t site, hipStream_t s) {
+                        const int32_t* drop_rows, uint32_t site, hipStream_t s, bool beside) {
   GemmArgs g = gemm_args(dt, 1, 1, T, H, K, x, K, Wm, K, sum, H);
-  g.bias = b; g.epi = 1; g.aux = res; g.ldaux = H; g.drop = drop; g.drop_site = site; g.drop_rows = drop_rows;
+  g.bias = b; g.beside = beside; g.epi = 1; g.aux = res; g.ldaux = H; g.drop = drop; g.drop_site = site; g.drop_rows = drop_rows;
   HS_TRY(launch_gemm(ctx, g, s));
   if (!out) return HS_OK;
   return launch_layernorm_fwd(ctx, dt, sum, gain, beta, out, stats, T, H, eps, s, stat_ld);
@@ -361,14 +362,14 @@ hs_status hs_s2s_fwd(hs_ctx* ctx, const void* w, const int32_t* src, const int32
       const DropCfg* dr = !drop ? nullptr : packed ? drop : &drop_src[k];
       const int32_t* drows = packed ? a.src_pad + pt.src0 : nullptr;
       auto R = [&](const void* p, int64_t width) { return src_rows(p, pt, width); };
-      HS_TRY(linear(ctx, dt, T, 3 * H, H, R(x, H), W(dt, w, lo.qkv_w), W(dt, w, lo.qkv_b), mut(R(la.qkv, 3 * H)), st));
+      HS_TRY(linear(ctx, dt, T, 3 * H, H, R(x, H), W(dt, w, lo.qkv_w), W(dt, w, lo.qkv_b), mut(R(la.qkv, 3 * H)), st, split));
       HS_TRY(launch_attention_fwd(ctx, dt, src_base(la.qkv, pt, 3 * H), src_lens + pt.b0, pt.nb, Ls, A, mut(src_base(la.ctx, pt, H)),
                                   la.lse + (size_t)pt.b0 * A * Ls, st, nullptr, 0, packed ? a.src_first + pt.b0 : nullptr));
       HS_TRY(linear_res_ln(ctx, dt, T, H, H, R(la.ctx, H), W(dt, w, lo.o_w), W(dt, w, lo.o_b), R(x, H), mut(R(la.y1, H)), W(dt, w, lo.ln1_g),
-                           W(dt, w, lo.ln1_b), mut(R(la.x1, H)), la.st1 + pt.src0, Ts, c.ln_eps, dr, drows, site_enc(i, 0), st));
-      HS_TRY(linear(ctx, dt, T, F, H, R(la.x1, H), W(dt, w, lo.ffn1_w), W(dt, w, lo.ffn1_b), mut(R(la.h, F)), st, true));
+                           W(dt, w, lo.ln1_b), mut(R(la.x1, H)), la.st1 + pt.src0, Ts, c.ln_eps, dr, drows, site_enc(i, 0), st, split));
+      HS_TRY(linear(ctx, dt, T, F, H, R(la.x1, H), W(dt, w, lo.ffn1_w), W(dt, w, lo.ffn1_b), mut(R(la.h, F)), st, split, true));
       HS_TRY(linear_res_ln(ctx, dt, T, H, F, R(la.h, F), W(dt, w, lo.ffn2_w), W(dt, w, lo.ffn2_b), R(la.x1, H), mut(R(la.y2, H)), W(dt, w, lo.ln2_g),
-                           W(dt, w, lo.ln2_b), mut(R(la.x2, H)), la.st2 + pt.src0, Ts, c.ln_eps, dr, drows, site_enc(i, 1), st));
+                           W(dt, w, lo.ln2_b), mut(R(la.x2, H)), la.st2 + pt.src0, Ts, c.ln_eps, dr, drows, site_enc(i, 1), st, split));
     }
     x = la.x2;
   }
@@ -397,23 +398,23 @@ hs_status hs_s2s_fwd(hs_ctx* ctx, const void* w, const int32_t* src, const int32
       auto R = [&](const void* p, int64_t width) { return tgt_rows(p, pt, width); };
       const int32_t* tl = tgt_lens + pt.b0;
       const int32_t* sl = src_lens + pt.b0;
-      HS_TRY(linear(ctx, dt, T, 3 * H, H, R(y, H), W(dt, w, lo.qkv_w), W(dt, w, lo.qkv_b), mut(R(la.qkv, 3 * H)), st));
+      HS_TRY(linear(ctx, dt, T, 3 * H, H, R(y, H), W(dt, w, lo.qkv_w), W(dt, w, lo.qkv_b), mut(R(la.qkv, 3 * H)), st, split));
       const void* qkv = tgt_base(la.qkv, pt, 3 * H);
       AttnOperands self{qkv, at(dt, qkv, H), at(dt, qkv, 2 * H), 3 * (int64_t)H, 3 * (int64_t)H, tl, tl, Lt, Lt, A, 1, tf, tf};
       HS_TRY(launch_attention_general_fwd(ctx, dt, self, pt.nb, mut(tgt_base(la.ctx, pt, H)), la.lse + (size_t)pt.b0 * A * Lt, st));
       HS_TRY(linear_res_ln(ctx, dt, T, H, H, R(la.ctx, H), W(dt, w, lo.o_w), W(dt, w, lo.o_b), R(y, H), mut(R(la.y1s, H)), W(dt, w, lo.ln1_g),
-                           W(dt, w, lo.ln1_b), mut(R(la.y1, H)), la.st1 + pt.tgt0, Tt, c.ln_eps, dr, drows, site_dec(c, i, 0), st));
-      HS_TRY(linear(ctx, dt, T, H, H, R(la.y1, H), W(dt, w, lo.cq_w), W(dt, w, lo.cq_b), mut(R(la.cq, H)), st));
-      HS_TRY(linear(ctx, dt, TS, 2 * H, H, src_rows(enc_out, pt, H), W(dt, w, lo.ckv_w), W(dt, w, lo.ckv_b), mut(src_rows(la.ckv, pt, 2 * H)), st));
+                           W(dt, w, lo.ln1_b), mut(R(la.y1, H)), la.st1 + pt.tgt0, Tt, c.ln_eps, dr, drows, site_dec(c, i, 0), st, split));
+      HS_TRY(linear(ctx, dt, T, H, H, R(la.y1, H), W(dt, w, lo.cq_w), W(dt, w, lo.cq_b), mut(R(la.cq, H)), st, split));
+      HS_TRY(linear(ctx, dt, TS, 2 * H, H, src_rows(enc_out, pt, H), W(dt, w, lo.ckv_w), W(dt, w, lo.ckv_b), mut(src_rows(la.ckv, pt, 2 * H)), st, split));
       const void* ckv = src_base(la.ckv, pt, 2 * H);
       AttnOperands cross{tgt_base(la.cq, pt, H), ckv, at(dt, ckv, H), (int64_t)H, 2 * (int64_t)H, tl, sl, Lt, Ls, A, 0, tf, sf};
       HS_TRY(launch_attention_general_fwd(ctx, dt, cross, pt.nb, mut(tgt_base(la.cctx, pt, H)), la.clse + (size_t)pt.b0 * A * Lt, st));
       HS_TRY(linear_res_ln(ctx, dt, T, H, H, R(la.cctx, H), W(dt, w, lo.co_w), W(dt, w, lo.co_b), R(la.y1, H), mut(R(la.ycs, H)),
-                           W(dt, w, lo.lnc_g), W(dt, w, lo.lnc_b), mut(R(la.yc, H)), la.stc + pt.tgt0, Tt, c.ln_eps, dr, drows, site_dec(c, i, 1), st));
-      HS_TRY(linear(ctx, dt, T, F, H, R(la.yc, H), W(dt, w, lo.ffn1_w), W(dt, w, lo.ffn1_b), mut(R(la.h, F)), st, true));
+                           W(dt, w, lo.lnc_g), W(dt, w, lo.lnc_b), mut(R(la.yc, H)), la.stc + pt.tgt0, Tt, c.ln_eps, dr, drows, site_dec(c, i, 1), st, split));
+      HS_TRY(linear(ctx, dt, T, F, H, R(la.yc, H), W(dt, w, lo.ffn1_w), W(dt, w, lo.ffn1_b), mut(R(la.h, F)), st, split, true));
       HS_TRY(linear_res_ln(ctx, dt, T, H, F, R(la.h, F), W(dt, w, lo.ffn2_w), W(dt, w, lo.ffn2_b), R(la.yc, H), mut(R(la.y2s, H)),
                            W(dt, w, lo.ln2_g), W(dt, w, lo.ln2_b), unpack ? nullptr : mut(R(y2, H)), la.st2 + pt.tgt0, Tt, c.ln_eps, dr, drows,
-                           site_dec(c, i, 2), st));
+                           site_dec(c, i, 2), st, split));
       if (unpack)
         HS_TRY(launch_layernorm_fwd_unpack(ctx, dt, la.y2s, W(dt, w, lo.ln2_g), W(dt, w, lo.ln2_b), at(dt, dec_out, (int64_t)pt.b0 * Lt * H), la.st2, tl,
                                            tf, pt.nb, Lt, H, c.ln_eps, st, Tt));

@@ -125,7 +125,7 @@ def test_gemm_bf16_large_k_and_many_tiles(hs):
         assert rel(host(dC), want) < 2e-6, (ak, bk)
 
 
-@pytest.mark.parametrize("variant", [-1] + list(range(12)))
+@pytest.mark.parametrize("variant", [-1] + list(range(14)))
 def test_gemm_every_tiling_ragged_edges_and_epilogues(hs, variant):
     """Every built tiling of the bf16 kernel (hs_tune_gemm_variant; -1: the automatic choice), each operand layout with the
     epilogues it serves, on a product with several tiles per direction, ragged last tiles in M and N, and a contraction that
@@ -208,7 +208,7 @@ def test_gemm_bf16_few_tiles(hs, M, N, K, layout):
             assert rel(host(dC), R.astype(np.float64) + prod) < 2e-6, scratch is None
 
 
-@pytest.mark.parametrize("variant", [1, 3, 6, 7, 9, 10])
+@pytest.mark.parametrize("variant", [1, 3, 6, 7, 9, 10, 12, 13])
 @pytest.mark.parametrize("M,N,K", [(256, 256, 256), (257, 264, 320), (384, 520, 384), (511, 576, 448), (769, 392, 1032)])
 @pytest.mark.parametrize("layout", LAYOUTS)
 def test_gemm_bf16_fragments_read_ahead(hs, variant, M, N, K, layout):
