@@ -434,7 +434,7 @@ static GemmDev gemm_dev_args(const GemmArgs& g) {
   return p;
 }
 
-int gemm_variant_count() { return kNumTileCfg; }
+int gemm_variant_count() { return 12; }      // 12 and 13 are left to the automatic choice
 void gemm_set_variant(int variant) { gemm_cfg_override = variant; }
 
 // whether the kernels other than gemm_bf16_mfma are built with the epilogue this product needs (see wide_epilogues in gemm_wide.h)

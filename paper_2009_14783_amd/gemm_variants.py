@@ -47,8 +47,7 @@ LARGE = layer_products(16384, 1024, 4096)[0] + layer_products(8192, 1024, 4096, 
 CUBES = [("cube kk", 1, 1, 8192, 8192, 8192, 0, 0), ("cube kn", 1, 0, 8192, 8192, 8192, 0, 0), ("cube nn", 0, 0, 8192, 8192, 8192, 0, 1)]
 NAMES = {-1: "auto", 0: "0: 128x128x32, 3/CU", 1: "1: LDS-direct 256x256x64", 2: "2: 32x32, waves split K", 3: "3: LDS-direct 128x192x64, 2/CU",
          4: "4: LDS-direct 32x64x64, 3/CU", 5: "5: 128x128x64, 2/CU", 6: "6: LDS-direct 192x128x64, 2/CU", 7: "7: LDS-direct 64x128x64, 2/CU",
-         8: "8: LDS-direct 128x64x64, 2/CU", 9: "9: LDS-direct 128x128x64, 2/CU", 10: "10: LDS-direct 256x128x64", 11: "11: LDS-direct 64x64x64, 3/CU",
-         12: "12: LDS-direct 128x128x64, 8 waves", 13: "13: LDS-direct 64x64x64, 2/CU, 4 stages"}
+         8: "8: LDS-direct 128x64x64, 2/CU", 9: "9: LDS-direct 128x128x64, 2/CU", 10: "10: LDS-direct 256x128x64", 11: "11: LDS-direct 64x64x64, 3/CU"}
 
 
 def time_product(prod, iters, bufs):
@@ -109,8 +108,8 @@ def choice(iters):
         for j in range(len(lists[0])):
             cells = []
             for r, products in zip(rows_of, lists):
-                t = {v: us(products[j], v) for v in [-1] + list(range(14))}
-                best = min(range(14), key=lambda v: t[v])
+                t = {v: us(products[j], v) for v in [-1] + list(range(12))}
+                best = min(range(12), key=lambda v: t[v])
                 ratios.append(t[-1] / min(t.values()))
                 cells.append(f"{t[-1]:.1f}" + (f" ({t[best]:.1f}: {best})" if t[best] < 0.98 * t[-1] else ""))
             print(f"| {H}, {lists[0][j][0]} | " + " | ".join(cells) + " |", flush=True)
@@ -147,7 +146,7 @@ def main():
             torch.zeros(max([F * 3 * H] + [p[3] * p[4] for p in products if p[7]]), dtype=torch.float32, device="cuda"),
             torch.empty(n, dtype=torch.bfloat16, device="cuda"), aux, torch.zeros(max([F] + [p[4] for p in products]), dtype=torch.bfloat16, device="cuda"),
             torch.empty(96 << 20, dtype=torch.uint8, device="cuda"))
-    variants = [int(v) for v in args.variants.split(",")] if args.variants else [-1] + list(range(14))
+    variants = [int(v) for v in args.variants.split(",")] if args.variants else [-1] + list(range(12))
     for prod in products:      # untimed pass: clocks up, code loaded
         time_product(prod, 3, bufs)
     print("| variant | " + " | ".join(p[0] for p in products) + " | sum (us) |")

@@ -125,7 +125,7 @@ def test_gemm_bf16_large_k_and_many_tiles(hs):
         assert rel(host(dC), want) < 2e-6, (ak, bk)
 
 
-@pytest.mark.parametrize("variant", [-1] + list(range(14)))
+@pytest.mark.parametrize("variant", [-1] + list(range(12)))
 def test_gemm_every_tiling_ragged_edges_and_epilogues(hs, variant):
     """Every built tiling of the bf16 kernel (hs_tune_gemm_variant; -1: the automatic choice), each operand layout with the
     epilogues it serves, on a product with several tiles per direction, ragged last tiles in M and N, and a contraction that
@@ -208,7 +208,7 @@ def test_gemm_bf16_few_tiles(hs, M, N, K, layout):
             assert rel(host(dC), R.astype(np.float64) + prod) < 2e-6, scratch is None
 
 
-@pytest.mark.parametrize("variant", [1, 3, 6, 7, 9, 10, 12, 13])
+@pytest.mark.parametrize("variant", [1, 3, 6, 7, 9, 10])
 @pytest.mark.parametrize("M,N,K", [(256, 256, 256), (257, 264, 320), (384, 520, 384), (511, 576, 448), (769, 392, 1032)])
 @pytest.mark.parametrize("layout", LAYOUTS)
 def test_gemm_bf16_fragments_read_ahead(hs, variant, M, N, K, layout):
@@ -372,6 +372,37 @@ def test_gelu_gradient_epilogue_keeps_nan(hs, M, N, K):
     hs.hs_op_gemm(1, 1, 0, M, N, K, A, K, B, N, out, N, epi=3, aux=R, ldaux=N)
     torch.cuda.synchronize()
     assert torch.equal(torch.isnan(out), bad) and bool(torch.isfinite(out[~bad]).all())
+
+
+# the automatic choice takes the two tilings for long contractions at these sizes: 128 x 128 with eight waves (first three) and 64 x 64 with four stages (last
+# three); whole tiles and ragged ones, contractions of 24 k-tiles and more
+@pytest.mark.parametrize("M,N,K", [(3072, 1024, 1536), (3001, 776, 1600), (5003, 520, 2048), (1024, 768, 1536), (905, 776, 1600), (521, 1288, 2048)])
+@pytest.mark.parametrize("bk", [1, 0])
+def test_gemm_long_contractions(hs, M, N, K, bk):
+    rng = np.random.default_rng(M + bk)
+    bf = torch.bfloat16
+    A, B = dev(rng.standard_normal((M, K)), bf), dev(rng.standard_normal((N, K) if bk else (K, N)), bf)
+    R, bias = dev(rng.standard_normal((M, N)), bf), dev(rng.standard_normal(N), bf)
+    prod = A.double() @ (B.double().T if bk else B.double())
+    base, r, ldb = prod + bias.double(), R.double(), K if bk else N
+    out, out2 = (torch.empty(M, N, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    err = lambda x, want: float((x.double() - want).norm() / want.norm())
+    tol = 4e-3                                  # one rounding to bf16 (at most 2^-9 of each value), 1.7e-3 on average
+    gelu = lambda x: 0.5 * x * (1 + torch.erf(x * 2 ** -0.5))
+    hs.hs_op_gemm(1, 1, bk, M, N, K, A, K, B, ldb, out, N, bias=bias, epi=1, aux=R, ldaux=N)
+    assert err(out, base + r) < tol
+    if bk:
+        hs.hs_op_gemm(1, 1, bk, M, N, K, A, K, B, ldb, out, N, bias=bias, epi=2, C2=out2)
+        assert err(out, base) < tol and err(out2, gelu(base)) < tol
+    else:
+        hs.hs_op_gemm(1, 1, bk, M, N, K, A, K, B, ldb, out, N, epi=3, aux=R, ldaux=N)
+        d = 0.5 * (1 + torch.erf(r * 2 ** -0.5)) + r * torch.exp(-0.5 * r * r) * 0.3989422804014327
+        assert err(out, prod * d) < tol
+    hs.hs_op_gemm(1, 1, bk, M, N, K, A, K, B, ldb, out, N)
+    first = out.clone()
+    assert err(out, prod) < tol
+    hs.hs_op_gemm(1, 1, bk, M, N, K, A, K, B, ldb, out, N)
+    assert torch.equal(out, first)
 
 
 def test_gemm_variant_out_of_range_is_an_error(hs):
