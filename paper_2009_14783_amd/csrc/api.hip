@@ -91,6 +91,7 @@ struct BwdSet { void *dy2, *dy1, *dy2m, *dy1m, *dh, *dqkv, *ln_part2, *ln_part1;
 struct BwdWs {
   std::vector<BwdSet> set;
   void *dxa, *dxb, *dctx, *ln_part, *emb, *gemm_ws;
+  uint8_t* touched;      // rows of the word embedding (see update_rows)
   float* dvec;
   size_t total, gemm_ws_bytes;
 };
@@ -111,6 +112,7 @@ BwdWs carve_bwd(const hs_model_cfg& c, size_t rows, int B, int L, int sets, void
   w.emb = cv.take(embed_bwd_scratch((int)T, (int)H));
   w.gemm_ws_bytes = gemm_scratch_bytes(c);
   w.gemm_ws = cv.take(w.gemm_ws_bytes);
+  w.touched = (uint8_t*)cv.take(c.vocab);
   w.total = cv.off;
   return w;
 }
@@ -392,20 +394,6 @@ hs_status hs_arm_update(hs_ctx* ctx, float* w, float* m, float* v, float* G, voi
 
 }  // extern "C"
 
-// normalise + Adam on the parameters [begin, end) of an armed update; one_pass: both in one kernel, for slices that no large products
-// run beside (beside them the one kernel, with four streams read and five written, measured slower than the two)
-hs_status update_slice(hs_ctx* ctx, const hs_ctx::Armed& u, int64_t begin, int64_t end, hipStream_t s, bool one_pass) {
-  const size_t n = (size_t)(end - begin);
-  if (n == 0) return HS_OK;
-  hs_status st = HS_OK;
-  if (!one_pass) st = hs_grad_accum_normalize(u.G + begin, nullptr, n, 0, u.denom, s);
-  if (st != HS_OK) return hs_fail(ctx, st, hs_last_error(nullptr));
-  void* wl = u.wl ? (void*)((bf16*)u.wl + begin) : nullptr;
-  st = hs_normalize_adam_step(u.w + begin, u.m + begin, u.v + begin, u.G + begin, wl, n, one_pass ? u.denom : 0.0, u.lr, u.beta1, u.beta2, u.eps, u.wd, u.t, s);
-  if (st != HS_OK) return hs_fail(ctx, st, hs_last_error(nullptr));
-  return HS_OK;
-}
-
 extern "C" {
 
 static hs_status encoder_bwd_impl(hs_ctx* ctx, const hs_ctx::Armed& upd, const void* w, const void* acts, const int32_t* ids,
@@ -427,7 +415,7 @@ static hs_status encoder_bwd_impl(hs_ctx* ctx, const hs_ctx::Armed& upd, const v
   std::string why;
   if (!shape_ok(ctx, B, L, &why)) return hs_fail(ctx, HS_ERR_SHAPE, "hs_encoder_bwd: " + why);
   if (B == 0) {      // nothing to back-propagate: an armed update still takes place, on the caller's stream
-    if (upd.on) return update_slice(ctx, upd, 0, ctx->off.total, (hipStream_t)stream, true);
+    if (upd.on) return update_slice(ctx, upd, 0, ctx->off.total, (hipStream_t)stream, UPD_ALONE);
     return HS_OK;
   }
   if (!w || !acts || !ids || !lens || !d_hidden || !g || !workspace) return hs_fail(ctx, HS_ERR_INVALID_ARG, "hs_encoder_bwd: NULL buffer");
@@ -456,6 +444,8 @@ static hs_status encoder_bwd_impl(hs_ctx* ctx, const hs_ctx::Armed& upd, const v
   if (overlap) HS_TRY(ensure_side_stream(ctx, (size_t)4 * NL + 8));
   if (own_upd && !ctx->upd) HS_HIP_CHECK(ctx, hipStreamCreateWithFlags(&ctx->upd, hipStreamNonBlocking));
   hipStream_t sd = overlap ? ctx->side : s, su = own_upd ? ctx->upd : sd;
+  const UpdateForm beside = !overlap ? UPD_ALONE : own_upd ? UPD_BESIDE_LARGE : UPD_BESIDE_SHORT;
+  const bool split_rows = upd.on && overlap && update_splits_rows(c.vocab, H, T);
   size_t next_event = 0;
   // work enqueued on `to` from here on comes after what is on `from` now
   auto order = [&](hipStream_t from, hipStream_t to) -> hs_status {
@@ -488,7 +478,14 @@ static hs_status encoder_bwd_impl(hs_ctx* ctx, const hs_ctx::Armed& upd, const v
   }
   if (upd.on) {
     HS_TRY(order(sd, su));
-    HS_TRY(update_slice(ctx, upd, o.head_t_w, o.total, su, !own_upd));
+    HS_TRY(update_slice(ctx, upd, o.head_t_w, o.total, su, beside));
+    // The word embedding was last read by hs_mlm_loss, and the rows of ids that are not in this batch have their gradient: their update (most of the table's
+    // 34 bytes per parameter) goes beside the backward pass, and only the batch's rows are left for its end.
+    if (split_rows) {
+      HS_TRY(launch_fill_zero(ctx, ws.touched, c.vocab, su));
+      HS_TRY(launch_mark_rows(ctx, ids, B * L, c.vocab, ws.touched, su));
+      HS_TRY(update_rows(ctx, upd, o.emb_word, c.vocab, H, ws.touched, 0, su));
+    }
   }
   const void* dcur = d_hidden;
   int chunk_top = NL - 1;                    // the highest layer whose gradients are not yet enqueued
@@ -557,7 +554,8 @@ static hs_status encoder_bwd_impl(hs_ctx* ctx, const hs_ctx::Armed& upd, const v
         HS_HIP_CHECK(ctx, hipStreamWaitEvent(su, done[i], 0));
         HS_TRY(order(s, su));
       }
-      HS_TRY(update_slice(ctx, upd, lo.qkv_w, chunk_top + 1 < NL ? o.layer[chunk_top + 1].qkv_w : o.head_t_w, su, !own_upd));
+      // (behind the last layers only the embedding's gradients are left on the chain)
+      HS_TRY(update_slice(ctx, upd, lo.qkv_w, chunk_top + 1 < NL ? o.layer[chunk_top + 1].qkv_w : o.head_t_w, su, i == 0 && !own_upd ? UPD_ALONE : beside));
     }
     if (chunk_done) chunk_top = i - 1;
   }
@@ -566,10 +564,16 @@ static hs_status encoder_bwd_impl(hs_ctx* ctx, const hs_ctx::Armed& upd, const v
                               g + o.emb_ln_b, nullptr, beta, T, H, ws.ln_part, s, drop, site_embedding(), drop ? 1 : 0, nullptr, pad_row));
   if (overlap) HS_HIP_CHECK(ctx, hipStreamWaitEvent(s, sorted, 0));
   HS_TRY(launch_embed_bwd(ctx, dt, ws.dxa, ids, B, L, H, c.vocab, c.max_pos, g + o.emb_word, g + o.emb_pos, beta, ws.emb, s, overlap, pk));
-  if (upd.on) HS_TRY(update_slice(ctx, upd, 0, o.layer[0].qkv_w, s, true));      // the embedding tables and their LayerNorm last, on the chain
+  if (split_rows) {      // the embedding tables and their LayerNorm last, on the chain; the flags were set on su
+    HS_TRY(order(su, s));
+    HS_TRY(update_rows(ctx, upd, o.emb_word, c.vocab, H, ws.touched, 1, s));
+    HS_TRY(update_slice(ctx, upd, o.emb_pos, o.layer[0].qkv_w, s, UPD_ALONE));
+  } else if (upd.on) {
+    HS_TRY(update_slice(ctx, upd, 0, o.layer[0].qkv_w, s, UPD_ALONE));
+  }
   // everything the other streams did is ordered before whatever the caller enqueues next
   HS_TRY(order(sd, s));
-  if (own_upd) HS_TRY(order(su, s));
+  if (own_upd && !split_rows) HS_TRY(order(su, s));
   return HS_OK;
 }
 

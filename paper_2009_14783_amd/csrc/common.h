@@ -224,8 +224,15 @@ struct hs_ctx {
 };
 
 hs_status hs_fail(hs_ctx* ctx, hs_status st, const std::string& msg);  // records msg, returns st
-// normalise + Adam on the parameters [begin, end) of an armed update (api.hip)
-hs_status update_slice(hs_ctx* ctx, const hs_ctx::Armed& u, int64_t begin, int64_t end, hipStream_t s, bool one_pass);
+// normalise + Adam on the parameters [begin, end) of an armed update (optim.hip), in a form for what runs beside it: nothing, the short kernels of a pass over
+// few rows, or large products
+enum UpdateForm { UPD_ALONE, UPD_BESIDE_SHORT, UPD_BESIDE_LARGE };
+hs_status update_slice(hs_ctx* ctx, const hs_ctx::Armed& u, int64_t begin, int64_t end, hipStream_t s, UpdateForm form);
+// An embedding table's gradient is final early but for the rows of the batch's ids: touched[id] says which, and update_rows updates the others (want 0)
+// or these (want 1) of the V rows of H from parameter `begin` on (optim.hip).
+bool update_splits_rows(int V, int H, int rows);
+hs_status launch_mark_rows(hs_ctx* ctx, const int32_t* ids, int n, int V, uint8_t* touched, hipStream_t s);
+hs_status update_rows(hs_ctx* ctx, const hs_ctx::Armed& u, int64_t begin, int V, int H, const uint8_t* touched, int want, hipStream_t s);
 #define HS_HIP_CHECK(ctx, expr)                                                              \
   do {                                                                                       \
     hipError_t e_ = (expr);                                                                  \

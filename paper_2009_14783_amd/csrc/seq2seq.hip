@@ -152,6 +152,7 @@ struct BwdWs {
   void *da, *db, *dctx, *denc[2], *de_tgt, *de_src, *emb;
   std::vector<LayerGrads> enc, dec;
   float* dvec;
+  uint8_t* touched;      // rows of the shared embedding (see update_rows)
   size_t total;
 };
 BwdWs carve_bwd(const hs_s2s_cfg& c, int B, int Ls, int Lt, void* base) {
@@ -177,6 +178,7 @@ BwdWs carve_bwd(const hs_s2s_cfg& c, int B, int Ls, int Lt, void* base) {
   }
   w.dvec = (float*)cv.take((size_t)B * c.n_heads * std::max(Ls, Lt) * sizeof(float));
   w.emb = cv.take(embed_bwd_scratch((int)Tm, (int)H));
+  w.touched = (uint8_t*)cv.take(c.vocab);
   w.total = cv.off;
   return w;
 }
@@ -501,7 +503,7 @@ hs_status hs_s2s_bwd(hs_ctx* ctx, const void* w, const void* acts, const int32_t
   std::string why;
   if (!shape_ok(c, B, Ls, Lt, &why)) return hs_fail(ctx, HS_ERR_SHAPE, "hs_s2s_bwd: " + why);
   if (B == 0) {      // nothing to back-propagate: an armed update still takes place, on the caller's stream
-    if (upd.on) return update_slice(ctx, upd, 0, s2s_offsets(c).total, (hipStream_t)stream, true);
+    if (upd.on) return update_slice(ctx, upd, 0, s2s_offsets(c).total, (hipStream_t)stream, UPD_ALONE);
     return HS_OK;
   }
   if (!w || !acts || !src || !src_lens || !tgt_in || !tgt_lens || !d_dec_out || !g || !workspace)
@@ -531,7 +533,7 @@ hs_status hs_s2s_bwd(hs_ctx* ctx, const void* w, const void* acts, const int32_t
   // With per-launch timing enabled everything stays on the caller's stream.
   const bool overlap = ctx->prof == nullptr;
   constexpr int per_hand_over = 3;
-  const size_t n_events = (size_t)c.n_dec + c.n_enc + 6;
+  const size_t n_events = (size_t)c.n_dec + c.n_enc + 7;
   if (overlap) HS_TRY(ensure_side_stream(ctx, n_events));
   hipStream_t sd = overlap ? ctx->side : s;
   size_t next_event = 0;
@@ -560,7 +562,8 @@ hs_status hs_s2s_bwd(hs_ctx* ctx, const void* w, const void* acts, const int32_t
     HS_TRY(launch_layernorm_bwd_cols_batch(ctx, cols_src.data(), (int)cols_src.size(), beta, Ts, H, sd));
     HS_TRY(launch_gemm_group(ctx, dw.data(), (int)dw.size(), sd));
     dw.clear(); cols_tgt.clear(); cols_src.clear();
-    return upd.on ? update_slice(ctx, upd, begin, end, sd, true) : HS_OK;
+    const bool last = begin == o.enc[0].qkv_w;      // behind them only the source embedding's gradient is left
+    return upd.on ? update_slice(ctx, upd, begin, end, sd, overlap && !last ? UPD_BESIDE_SHORT : UPD_ALONE) : HS_OK;
   };
   auto dgrad = [&](int T, int N, int K, const void* dy, const void* Wm, void* dx, const void* res) {   // dx [T,N] = dy [T,K] W [K,N] (+ res)
     GemmArgs ga = gemm_args(dt, 1, 0, T, N, K, dy, K, Wm, N, dx, N);
@@ -588,6 +591,15 @@ hs_status hs_s2s_bwd(hs_ctx* ctx, const void* w, const void* acts, const int32_t
     return dgrad(T, H, F, lg.dh, W(dt, w, lo.ffn1_w), out, lg.s2);
   };
 
+  // The shared embedding was last read by hs_s2s_loss: the rows that this batch does not hold are updated now, as in the encoder-only model.
+  const bool split_rows = upd.on && overlap && update_splits_rows(c.vocab, H, std::max(Ts, Tt));
+  if (split_rows) {
+    HS_TRY(order(s, sd));
+    HS_TRY(launch_fill_zero(ctx, ws.touched, c.vocab, sd));
+    HS_TRY(launch_mark_rows(ctx, src, B * Ls, c.vocab, ws.touched, sd));
+    HS_TRY(launch_mark_rows(ctx, tgt_in, B * Lt, c.vocab, ws.touched, sd));
+    HS_TRY(update_rows(ctx, upd, o.emb, c.vocab, H, ws.touched, 0, sd));
+  }
   // ---- decoder ----
   const void* enc_out = a.enc[c.n_enc - 1].x2;
   const void* dcur = d_dec_out;
@@ -668,7 +680,9 @@ hs_status hs_s2s_bwd(hs_ctx* ctx, const void* w, const void* acts, const int32_t
   HS_TRY(launch_mask_scale(ctx, dt, dcur, ws.de_src, (size_t)Ts * H, scale, drop, site_src(), s, src_pad, H));
   HS_TRY(order(s, sd));
   HS_TRY(launch_embed_bwd(ctx, dt, ws.de_src, src, B, Ls, H, c.vocab, 0, g + o.emb, nullptr, 0.f, ws.emb, sd, true, pks));
-  if (upd.on) HS_TRY(update_slice(ctx, upd, o.emb, o.enc[0].qkv_w, sd, true));      // the shared embedding: its gradient is complete only now
+  // the shared embedding: its gradient is complete only now
+  if (split_rows) HS_TRY(update_rows(ctx, upd, o.emb, c.vocab, H, ws.touched, 1, sd));
+  else if (upd.on) HS_TRY(update_slice(ctx, upd, o.emb, o.enc[0].qkv_w, sd, UPD_ALONE));
   return order(sd, s);     // everything the second stream did is ordered before whatever the caller enqueues next
 }
 

@@ -100,3 +100,43 @@ def test_gradient_rows_of_the_padding_are_not_read():
     torch.cuda.synchronize()
     assert torch.equal(wk.G, want)
     wk.close()
+
+
+def same_state(a, b, names):
+    for k in names:
+        assert torch.equal(getattr(a, k), getattr(b, k)), k
+
+
+# 33000 x 128 parameters and more: the embedding's rows that the last micro-batch does not hold are updated in front of its backward pass, up to 4096 rows
+@pytest.mark.parametrize("compute,B,L", [("bf16", 5, 24), ("bf16", 34, 128), ("fp32", 3, 32)])
+def test_embedding_rows_updated_in_two_parts_give_the_bits_of_one(compute, B, L):
+    model = dict(n_layers=2, hidden=128, n_heads=2, ffn=256, vocab=33001, max_pos=128, ln_eps=1e-12)
+    theta = synth.init_params(hs.hs_param_layout(hs.make_cfg(**model)), 77)
+    a, b = Worker(model, compute, theta), Worker(model, compute, theta)
+    adam = dict(lr=1e-3, beta1=0.9, beta2=0.999, eps=1e-8, weight_decay=0.01)
+    for t in range(2):
+        mbs = [synth.make_micro_batch(synth.rng_for(78 + 2 * t + i), [max(1, L - 3 * (k % 7)) for k in range(B)], L, model["vocab"], "zipf") for i in range(2)]
+        mbs[1]["ids"][0, :2] = [0, model["vocab"] - 1]
+        a.train_step([a.upload(mb) for mb in mbs], adam)
+        b.train_step([b.upload(mb) for mb in mbs], adam, update_in_backward=False)
+        torch.cuda.synchronize()
+        same_state(a, b, ("w", "m", "v", "G") + (("w_lowp",) if compute == "bf16" else ()))
+    a.close(); b.close()
+
+
+@pytest.mark.parametrize("compute,B,Ls,Lt", [("bf16", 4, 24, 32), ("bf16", 130, 32, 40), ("fp32", 3, 16, 24)])
+def test_pair_step_of_a_large_model_gives_the_bits_of_the_separate_update(compute, B, Ls, Lt):
+    model = dict(n_enc=2, n_dec=2, hidden=128, n_heads=2, ffn=256, vocab=33001, max_pos=64)
+    theta = synth.init_params(hs.hs_s2s_param_layout(hs.make_s2s_cfg(**model)), 79)
+    a, b = PairWorker(model, compute, theta), PairWorker(model, compute, theta)
+    adam = dict(lr=1e-3, beta1=0.9, beta2=0.98, eps=1e-9)
+    for t in range(2):
+        lens = lambda L, k: [max(1, L - k * (i % 5)) for i in range(B)]
+        mbs = [synth.make_pair_batch(synth.rng_for(80 + 2 * t + i), lens(Ls, 3), lens(Lt, 4), Ls, Lt, model["vocab"], "zipf") for i in range(2)]
+        D = a.train_step([a.upload(mb) for mb in mbs], adam)
+        for i, mb in enumerate(mbs):
+            b.forward_backward(b.upload(mb), b.G, i, i)
+        hs.hs_normalize_adam_step(b.w, b.m, b.v, b.G, b.w_lowp, b.P, D, adam["lr"], adam["beta1"], adam["beta2"], adam["eps"], 0.0, t + 1)
+        torch.cuda.synchronize()
+        same_state(a, b, ("w", "m", "v", "G") + (("w_lowp",) if compute == "bf16" else ()))
+    a.close(); b.close()
