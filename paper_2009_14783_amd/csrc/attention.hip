@@ -2,7 +2,7 @@
 // qkv is [B*L, 3H]: per token the query, key and value vectors of all heads; head h occupies
 // columns h*64 .. h*64+63 of each third.  Key l' of sequence b takes part iff l' < lens[b].
 //
-// This file: the dispatch by type.  bf16: attention_mfma.hip; fp32: attention_f32.hip.
+// This file: the dispatch by type.  bf16: attention_general.hip (and attention_mfma.hip); fp32: attention_f32.hip.
 #include "common.h"
 
 namespace {
@@ -15,9 +15,9 @@ AttnF32 f32_problem(const void* qkv, const int32_t* lens, int L, int A, const Dr
 }
 }  // namespace
 
-void launch_attention_fwd_mfma(const void* qkv, const int32_t* lens, int B, int L, int A, void* out, float* lse, hipStream_t s,
+void launch_attention_self_fwd(const void* qkv, const int32_t* lens, int B, int L, int A, void* out, float* lse, hipStream_t s,
                                const DropCfg& drop, uint32_t site, const int32_t* first);
-void launch_attention_bwd_mfma(const void* qkv, const void* out, const float* lse, const void* d_out, const int32_t* lens, int B, int L,
+void launch_attention_self_bwd(const void* qkv, const void* out, const float* lse, const void* d_out, const int32_t* lens, int B, int L,
                                int A, void* dqkv, float* dvec, hipStream_t s, const DropCfg& drop, uint32_t site, const int32_t* first);
 
 hs_status launch_attention_fwd(hs_ctx* ctx, int dtype, const void* qkv, const int32_t* lens, int B, int L, int A, void* out, float* lse,
@@ -29,7 +29,7 @@ hs_status launch_attention_fwd(hs_ctx* ctx, int dtype, const void* qkv, const in
   const double fl = 4.0 * B * A * (double)L * L * D;
   const double by = (double)B * L * A * D * 4.0 * esize(dtype);
   KScope scope(ctx ? ctx->prof : nullptr, KC_ATTN_FWD, fl, by, s);
-  if (dtype == HS_BF16) launch_attention_fwd_mfma(qkv, lens, B, L, A, out, lse, s, drop, site, first);
+  if (dtype == HS_BF16) launch_attention_self_fwd(qkv, lens, B, L, A, out, lse, s, drop, site, first);
   else launch_attention_f32_fwd(f32_problem(qkv, lens, L, A, drop, site), B, (float*)out, lse, s);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hs_fail(ctx, HS_ERR_HIP, std::string("attention_fwd: ") + hipGetErrorString(e));
@@ -47,7 +47,7 @@ hs_status launch_attention_bwd(hs_ctx* ctx, int dtype, const void* qkv, const vo
   const double by = (double)B * L * A * D * 8.0 * esize(dtype);
   KScope scope(ctx ? ctx->prof : nullptr, KC_ATTN_BWD, fl, by, s);
   if (dtype == HS_BF16) {
-    launch_attention_bwd_mfma(qkv, out, lse, d_out, lens, B, L, A, dqkv, dvec, s, drop, site, first);
+    launch_attention_self_bwd(qkv, out, lse, d_out, lens, B, L, A, dqkv, dvec, s, drop, site, first);
   } else {
     float* d = (float*)dqkv;
     launch_attention_f32_bwd(f32_problem(qkv, lens, L, A, drop, site), B, (const float*)out, lse, (const float*)d_out, d, 3 * (int64_t)A * D,

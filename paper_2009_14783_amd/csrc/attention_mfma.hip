@@ -1,6 +1,6 @@
-// bf16 MFMA self-attention (head dimension 64), fp32 softmax statistics: the backward pass of sequences of at most 128 positions.
-// Everything else goes to the streaming kernels of attention_general.hip, where the tile scheme of both (owned rows in registers,
-// transposed score tiles) is described.
+// bf16 MFMA attention backward (head dimension 64), fp32 softmax statistics, for at most 128 queries and 128 keys per sequence: self-attention, causal
+// or not, and attention over another sequence.  Everything else goes to the streaming kernels of attention_general.hip, where the tile scheme of both (owned rows in
+// registers, transposed score tiles) is described.
 #include "attention_tiles.h"
 
 namespace {
@@ -8,74 +8,87 @@ namespace {
 using namespace attn_tiles;
 
 // ------------------------------------------------------------------------------------------
-// backward for sequences of at most 128 positions: one block per (sequence, head), no second launch.  Every
-// wave first owns 32 queries (dq) with K and V streamed from two LDS tiles, then 32 keys (dk, dv) with Q and dO
-// streamed from the SAME two tiles: owned rows never need LDS (their fragments come straight from global memory,
-// or out of the tiles just before they are overwritten), so a block takes 37 KiB of LDS and three of them share a CU -
-// one round for the 768 blocks of 64 sequences x 12 heads, and the second staging phase of one block runs under
-// the arithmetic of the others.
+// One launch, a block of W waves per (sequence, head) pair for up to 32 W queries and keys.  Every wave first owns 32 queries (dq) with K and V
+// streamed from two LDS tiles, then 32 keys (dk, dv) with Q and dO streamed from the SAME two tiles: owned rows never need LDS (their fragments come
+// straight from global memory, or out of the tiles just before they are overwritten), so a block of four waves takes 37 KiB of LDS and three of them
+// share a CU - one round for the 768 blocks of 64 sequences x 12 heads, and the second staging phase of one block runs under the arithmetic of the
+// others.  What bounds it is that chain: load, store, product, softmax, product, store, twice.  Blocks are as small as their pairs: with four waves
+// for every pair, three of them idle up to 32 positions and hold the places of others (100 sequences of 56 x 12 heads: 25.7 -> 20.9 us).
 // Scores start from -8 lse and their gradients from -dO . O, and only cut tiles are masked, as in attention_general.hip (the BERT-base step of 64 x
-// 128 with dropout 8.17 -> 8.08 ms, without level).
+// 128 with dropout 8.17 -> 8.08 ms, without level).  For the translation model's 128 x 8 pairs of 32 positions, against four
+// waves per pair (self-attention, 17 us) and two streaming launches (causal and over the encoder output, 17 us now 11): step 4.34 -> 4.14 ms, the
+// same bits.
 // ------------------------------------------------------------------------------------------
-__device__ __forceinline__ void stage128(bf16* tile, const bf16* __restrict__ src, int64_t ld, int row_limit, int tid) {
+struct ShortOperands {
+  const bf16 *q, *k, *v, *out, *d_out;      // first row of sequence 0
+  bf16 *dq, *dk, *dv;
+  int64_t ldq, ldkv, lddq, lddkv;
+  const float* lse;
+  const int32_t *qlens, *klens, *qfirst, *kfirst;      // first: packed rows, or null
+  int Lq, Lk, A;
+};
+
+// rows 0 .. 32 W - 1 of one matrix, by the 64 W threads of a pair
+template <int W>
+__device__ __forceinline__ void stage_rows(bf16* tile, const bf16* __restrict__ src, int64_t ld, int row_limit, int tid) {
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const int c = tid + i * 256;
+    const int c = tid + i * 64 * W;
     const int r = c >> 3, col = (c & 7) * 8;
     uint4 v = make_uint4(0, 0, 0, 0);
     if (r < row_limit) v = *(const uint4*)(src + (int64_t)r * ld + col);
     *(uint4*)(tile + r * LDT + col) = v;
   }
 }
+// between the waves of a pair; one wave's LDS operations execute in order anyway
+template <int W>
+__device__ __forceinline__ void pair_barrier() {
+  if (W > 1) __syncthreads();
+  else asm volatile("" ::: "memory");
+}
 
-// Up to this many (sequence, head) pairs, the two halves go to a block each: the chip has room for both, and a block's chain is half as long
-// (BERT-base, 5 sequences of 88 positions in two passes: 4.23 -> 4.08 ms per step).  Beyond, the second set of loads costs what the shorter chain
-// gives (768 pairs: 7.50 -> 7.54 ms per step; 384: level).
-constexpr int kFewHeads = 256;
+// Up to this many waves in all, about one per SIMD, the two halves of a pair go to a block each: the chip has room for both, and a block's chain is
+// half as long (256 pairs of up to 32 positions: 8.5 -> 7.5 us; 480 pairs of up to 64: 13.1 -> 12.7 us; BERT-base, 5 sequences of 88 positions in two
+// passes: 4.23 -> 4.08 ms per step).  Beyond, the second set of loads costs more than the shorter chain gives (1024 pairs of 32: 11.1 -> 11.9 us; 384
+// pairs of 128, 1536 waves: level).
+constexpr int kFewWaves = 960;
 
-template <bool DROP>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3)))
-void attn_bwd_fused128_mfma(const bf16* __restrict__ qkv, const bf16* __restrict__ out, const float* __restrict__ lse,
-                            const bf16* __restrict__ d_out, const int32_t* __restrict__ lens, const int32_t* __restrict__ first, int L, int A,
-                            bf16* __restrict__ dqkv, DropCfg drop, uint32_t site) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
-  bf16* T0 = (bf16*)lds_raw;               // K, then Q
-  bf16* T1 = T0 + 128 * LDT;               // V, then dO
-  float* st0_s = (float*)(T1 + 128 * LDT);      // what a query's scores and their gradients start from: -8 lse, -dO . O
-  float* dp0_s = st0_s + 128;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+template <int W, bool CAUSAL, bool DROP>
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(3, 3))) void attn_bwd_short_mfma(ShortOperands x, DropCfg drop, uint32_t site) {
+  __shared__ __attribute__((aligned(16))) bf16 T0[32 * W * LDT];      // K, then Q
+  __shared__ __attribute__((aligned(16))) bf16 T1[32 * W * LDT];      // V, then dO
+  __shared__ float st0_s[32 * W], dp0_s[32 * W];      // what a query's scores and their gradients start from: -8 lse, -dO . O
+  const int tid = threadIdx.x, lane = tid & 63, w0 = __builtin_amdgcn_readfirstlane(tid >> 6) * 32;
   const int b = blockIdx.y, h = blockIdx.x;
-  const int H = A * DH;
-  const int64_t ld = 3 * (int64_t)H;
-  int len = lens[b];
-  len = len < 1 ? 1 : (len > L ? L : len);
-  const int64_t row0 = first ? first[b] : (int64_t)b * L;
-  const int rows = first ? len : L;              // packed rows: the row behind the last one is the next sequence's
-  const bf16* base = qkv + row0 * ld + h * DH;
-  const bf16* go = d_out + row0 * H + h * DH;
-  const bf16* oo = out + row0 * H + h * DH;
-  const int own = wave * 32 + (lane & 31);       // the query, then the key, this lane owns
-  const bool wave_active = wave * 32 < len;      // wave-uniform
+  const int H = x.A * DH;
+  const int qlen = min(max(x.qlens[b], 1), x.Lq), klen = min(max(x.klens[b], 1), x.Lk);
+  const int qrows = x.qfirst ? qlen : x.Lq, krows = x.kfirst ? klen : x.Lk;      // packed: the row behind the last is the next sequence's
+  const int64_t qbase = x.qfirst ? x.qfirst[b] : (int64_t)b * x.Lq, kbase = x.kfirst ? x.kfirst[b] : (int64_t)b * x.Lk;
+  const bf16* const q = x.q + qbase * x.ldq + h * DH;
+  const bf16* const k = x.k + kbase * x.ldkv + h * DH;
+  const bf16* const v = x.v + kbase * x.ldkv + h * DH;
+  const bf16* const go = x.d_out + qbase * H + h * DH;
+  const bf16* const oo = x.out + qbase * H + h * DH;
+  const int own = w0 + (lane & 31);       // the query, then the key, this lane owns
 
   const bool queries = blockIdx.z == 0, keys = queries == (gridDim.z == 1);      // the halves this block does
-  stage128(T0, queries ? base + H : base, ld, len, tid);
-  stage128(T1, queries ? base + 2 * H : go, queries ? ld : H, len, tid);
+  stage_rows<W>(T0, queries ? k : q, queries ? x.ldkv : x.ldq, queries ? klen : qlen, tid);
+  stage_rows<W>(T1, queries ? v : go, queries ? x.ldkv : H, queries ? klen : qlen, tid);
   // the owned queries' fragments of Q and dO, and the row dot product sum_d dO*O (lanes l and l + 32 hold the two halves of a row)
   bf16x8 qf[4], gf[4];
   float drow = 0.f;
 #pragma unroll
   for (int ks = 0; ks < 4; ++ks) {
-    qf[ks] = frag_rows_global(base, ld, own, len, ks, lane);
-    gf[ks] = frag_rows_global(go, H, own, len, ks, lane);
-    const bf16x8 of = frag_rows_global(oo, H, own, len, ks, lane);
+    qf[ks] = frag_rows_global(q, x.ldq, own, qlen, ks, lane);
+    gf[ks] = frag_rows_global(go, H, own, qlen, ks, lane);
+    const bf16x8 of = frag_rows_global(oo, H, own, qlen, ks, lane);
 #pragma unroll
     for (int e = 0; e < 8; ++e) drow = fmaf((float)gf[ks][e], (float)of[e], drow);
   }
   drow += __shfl_xor(drow, 32);
-  const float st0 = (own < len) ? lse[((int64_t)b * A + h) * L + own] * -8.0f : 0.f;      // 8: the scores are not scaled yet
-  const bool own_cut = wave * 32 + 32 > len;      // some of the wave's rows are padding (wave-uniform)
+  const float st0 = (own < qlen) ? x.lse[((int64_t)b * x.A + h) * x.Lq + own] * -8.0f : 0.f;      // 8: the scores are not scaled yet
   if (lane < 32) { dp0_s[own] = -drow; st0_s[own] = st0; }
-  __syncthreads();
+  pair_barrier<W>();
 
   f32x16 acc[2], acc2[2];
 #pragma unroll
@@ -83,8 +96,9 @@ void attn_bwd_fused128_mfma(const bf16* __restrict__ qkv, const bf16* __restrict
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[db][r] = 0.f;
   // ---- queries owned: dq ----
-  if (queries && wave_active) {
-    for (int kb = 0; kb < len; kb += 32) {
+  if (queries && w0 < qlen) {
+    const int kend = CAUSAL ? min(klen, w0 + 32) : klen;
+    for (int kb = 0; kb < kend; kb += 32) {
       f32x16 st, dp;
 #pragma unroll
       for (int r = 0; r < 16; ++r) { st[r] = st0; dp[r] = DROP ? 0.f : -drow; }
@@ -95,15 +109,18 @@ void attn_bwd_fused128_mfma(const bf16* __restrict__ qkv, const bf16* __restrict
       }
       if (DROP) {
         f32x16 f;
-        drop_tile_keys(drop, site, (((uint64_t)b * A + h) * L + own) * (uint64_t)L, kb, lane, f);
+        drop_tile_keys(drop, site, (((uint64_t)b * x.A + h) * x.Lq + own) * (uint64_t)x.Lk, kb, lane, f);
 #pragma unroll
         for (int r = 0; r < 16; ++r) dp[r] = fmaf(dp[r], f[r], -drow);
       }
 #pragma unroll
       for (int r = 0; r < 16; ++r) st[r] = fast_exp2(st[r] * SCALE2);
-      if (own_cut || kb + 32 > len) {
+      if (w0 + 32 > qlen || kb + 32 > klen || (CAUSAL && kb + 31 > w0)) {      // wave-uniform
 #pragma unroll
-        for (int r = 0; r < 16; ++r) st[r] = (kb + tile_row(r, lane) < len && own < len) ? st[r] : 0.f;
+        for (int r = 0; r < 16; ++r) {
+          const int key = kb + tile_row(r, lane);
+          st[r] = (key < klen && own < qlen && (!CAUSAL || key <= own)) ? st[r] : 0.f;
+        }
       }
 #pragma unroll
       for (int r = 0; r < 16; ++r) st[r] *= dp[r];
@@ -117,34 +134,33 @@ void attn_bwd_fused128_mfma(const bf16* __restrict__ qkv, const bf16* __restrict
   }
   // ---- keys owned: dk, dv ----
   bf16x8 kf[4], vf[4];
-  bf16* const dst = dqkv + row0 * ld + h * DH;
   if (queries) {
     // The owned key/value fragments are the last thing read from K and V.  After the barrier a wave's own 32 rows of
     // tile 0 stage the whole-row stores of dq; after the next one the tiles are refilled with Q and dO.
     if (keys) {
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks) { kf[ks] = frag_rows(T0, wave * 32, ks, lane); vf[ks] = frag_rows(T1, wave * 32, ks, lane); }
+      for (int ks = 0; ks < 4; ++ks) { kf[ks] = frag_rows(T0, w0, ks, lane); vf[ks] = frag_rows(T1, w0, ks, lane); }
     }
-    __syncthreads();
-    store_owned_rows_lds(dst, ld, wave * 32, rows, acc, 0.125f, lane, T0 + wave * 32 * LDT);
+    pair_barrier<W>();
+    store_owned_rows_lds(x.dq + qbase * x.lddq + h * DH, x.lddq, w0, qrows, acc, 0.125f, lane, T0 + w0 * LDT);
     if (!keys) return;
-    __syncthreads();
-    stage128(T0, base, ld, len, tid);
-    stage128(T1, go, H, len, tid);
-    __syncthreads();
+    pair_barrier<W>();
+    stage_rows<W>(T0, q, x.ldq, qlen, tid);
+    stage_rows<W>(T1, go, H, qlen, tid);
+    pair_barrier<W>();
   } else {
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
-      kf[ks] = frag_rows_global(base + H, ld, own, len, ks, lane);
-      vf[ks] = frag_rows_global(base + 2 * H, ld, own, len, ks, lane);
+      kf[ks] = frag_rows_global(k, x.ldkv, own, klen, ks, lane);
+      vf[ks] = frag_rows_global(v, x.ldkv, own, klen, ks, lane);
     }
   }
 #pragma unroll
   for (int db = 0; db < 2; ++db)
 #pragma unroll
     for (int r = 0; r < 16; ++r) { acc[db][r] = 0.f; acc2[db][r] = 0.f; }
-  if (wave_active) {
-    for (int qb = 0; qb < len; qb += 32) {
+  if (w0 < klen) {
+    for (int qb = CAUSAL ? w0 : 0; qb < qlen; qb += 32) {
       f32x16 st, dp;
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
@@ -158,13 +174,16 @@ void attn_bwd_fused128_mfma(const bf16* __restrict__ qkv, const bf16* __restrict
       }
 #pragma unroll
       for (int r = 0; r < 16; ++r) st[r] = fast_exp2(st[r] * SCALE2);
-      if (own_cut || qb + 32 > len) {
+      if (w0 + 32 > klen || qb + 32 > qlen || (CAUSAL && qb < w0 + 31)) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) st[r] = (qb + tile_row(r, lane) < len && own < len) ? st[r] : 0.f;
+        for (int r = 0; r < 16; ++r) {
+          const int qi = qb + tile_row(r, lane);
+          st[r] = (qi < qlen && own < klen && (!CAUSAL || own <= qi)) ? st[r] : 0.f;
+        }
       }
       if (DROP) {
         f32x16 f;
-        drop_tile_queries(drop, site, ((uint64_t)b * A + h) * L, L, qb, own, lane, f);
+        drop_tile_queries(drop, site, ((uint64_t)b * x.A + h) * x.Lq, x.Lk, qb, own, lane, f);
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           dp[r] = st[r] * fmaf(f[r], dp[r], dp0_s[qb + tile_row(r, lane)]);
@@ -184,39 +203,32 @@ void attn_bwd_fused128_mfma(const bf16* __restrict__ qkv, const bf16* __restrict
       }
     }
   }
-  __syncthreads();     // every wave is done with Q and dO: own rows of the tiles stage the stores of dk and dv
-  store_owned_rows_lds(dst + H, ld, wave * 32, rows, acc, 0.125f, lane, T0 + wave * 32 * LDT);
-  store_owned_rows_lds(dst + 2 * H, ld, wave * 32, rows, acc2, 1.0f, lane, T1 + wave * 32 * LDT);
+  pair_barrier<W>();     // every wave is done with Q and dO: own rows of the tiles stage the stores of dk and dv
+  store_owned_rows_lds(x.dk + kbase * x.lddkv + h * DH, x.lddkv, w0, krows, acc, 0.125f, lane, T0 + w0 * LDT);
+  store_owned_rows_lds(x.dv + kbase * x.lddkv + h * DH, x.lddkv, w0, krows, acc2, 1.0f, lane, T1 + w0 * LDT);
+}
+
+template <int W>
+void launch_short(const ShortOperands& x, int B, bool causal, hipStream_t s, const DropCfg& drop, uint32_t site) {
+  const dim3 grid(x.A, B, (int64_t)x.A * B * W <= kFewWaves ? 2 : 1);
+  if (causal) hipLaunchKernelGGL((attn_bwd_short_mfma<W, true, false>), grid, dim3(64 * W), 0, s, x, drop, site);
+  else if (drop.thr) hipLaunchKernelGGL((attn_bwd_short_mfma<W, false, true>), grid, dim3(64 * W), 0, s, x, drop, site);
+  else hipLaunchKernelGGL((attn_bwd_short_mfma<W, false, false>), grid, dim3(64 * W), 0, s, x, drop, site);
 }
 
 }  // namespace
 
-void launch_attention_self_fwd(const void* qkv, const int32_t* lens, int B, int L, int A, void* out, float* lse, hipStream_t s, const DropCfg& drop,
-                               uint32_t site, const int32_t* first);
-void launch_attention_self_bwd(const void* qkv, const void* out, const float* lse, const void* d_out, const int32_t* lens, int B, int L, int A,
-                               void* dqkv, float* dvec, hipStream_t s, const DropCfg& drop, uint32_t site, const int32_t* first);
-
-void launch_attention_fwd_mfma(const void* qkv, const int32_t* lens, int B, int L, int A, void* out, float* lse, hipStream_t s,
-                               const DropCfg& drop, uint32_t site, const int32_t* first) {
-  launch_attention_self_fwd(qkv, lens, B, L, A, out, lse, s, drop, site, first);
+// Whether a problem has a short form (16-byte rows of the gradients; causal: without dropout), and the launch
+bool attention_bwd_is_short(const AttnOperands& x, const void* dq, int64_t lddq, const void* dk, const void* dv, int64_t lddkv) {
+  auto wide = [](const void* p, int64_t ld) { return !((uintptr_t)p & 15) && !(ld & 7); };
+  return x.Lq <= 128 && x.Lk <= 128 && wide(dq, lddq) && wide(dk, lddkv) && wide(dv, lddkv);
 }
-
-void launch_attention_bwd_mfma(const void* qkv, const void* out, const float* lse, const void* d_out, const int32_t* lens, int B, int L,
-                               int A, void* dqkv, float* dvec, hipStream_t s, const DropCfg& drop, uint32_t site, const int32_t* first) {
-  if (L <= 128) {
-    constexpr size_t lds = 2 * 128 * LDT * sizeof(bf16) + 2 * 128 * sizeof(float);
-    static bool configured = false;
-    if (!configured) {
-      (void)hipFuncSetAttribute((const void*)attn_bwd_fused128_mfma<false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      (void)hipFuncSetAttribute((const void*)attn_bwd_fused128_mfma<true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      configured = true;
-    }
-    const dim3 grid(A, B, (int64_t)A * B <= kFewHeads ? 2 : 1);
-    if (drop.thr) hipLaunchKernelGGL(attn_bwd_fused128_mfma<true>, grid, dim3(256), lds, s, (const bf16*)qkv, (const bf16*)out, lse,
-                                     (const bf16*)d_out, lens, first, L, A, (bf16*)dqkv, drop, site);
-    else hipLaunchKernelGGL(attn_bwd_fused128_mfma<false>, grid, dim3(256), lds, s, (const bf16*)qkv, (const bf16*)out, lse,
-                            (const bf16*)d_out, lens, first, L, A, (bf16*)dqkv, drop, site);
-    return;
-  }
-  launch_attention_self_bwd(qkv, out, lse, d_out, lens, B, L, A, dqkv, dvec, s, drop, site, first);
+void launch_attention_bwd_short(const AttnOperands& x, int B, const void* out, const float* lse, const void* d_out, void* dq, int64_t lddq, void* dk, void* dv,
+                                int64_t lddkv, hipStream_t s, const DropCfg& drop, uint32_t site) {
+  const ShortOperands o{(const bf16*)x.q, (const bf16*)x.k, (const bf16*)x.v, (const bf16*)out, (const bf16*)d_out, (bf16*)dq, (bf16*)dk, (bf16*)dv,
+                        x.ldq, x.ldkv, lddq, lddkv, lse, x.qlens, x.klens, x.qfirst, x.kfirst, x.Lq, x.Lk, x.A};
+  const int L = x.Lq > x.Lk ? x.Lq : x.Lk;
+  if (L <= 32) launch_short<1>(o, B, x.causal, s, drop, site);
+  else if (L <= 64) launch_short<2>(o, B, x.causal, s, drop, site);
+  else launch_short<4>(o, B, x.causal, s, drop, site);
 }

@@ -630,6 +630,31 @@ def test_streaming_attention_at_block_edges(hs, causal, L, lens):
         assert rel(host(got), flat(want)) < 1e-2
 
 
+# one, two and four waves per (sequence, head) pair at their edges, few and many pairs (up to 960 waves the halves of a pair go to two blocks)
+@pytest.mark.parametrize("causal,Lq,Lk", [(0, 8, 32), (0, 32, 24), (0, 40, 32), (0, 24, 64), (0, 64, 72), (0, 128, 8), (1, 32, 32), (1, 64, 64), (1, 40, 40), (1, 128, 128)])
+@pytest.mark.parametrize("B,A", [(5, 3), (2, 1), (70, 8), (301, 1)])
+def test_short_attention_backward_gives_the_bits_of_the_streaming_kernels(hs, causal, Lq, Lk, B, A):
+    """Gradients of 16-byte rows come from the kernel for up to 128 positions, gradients that are only 8-byte aligned from the streaming ones."""
+    g = torch.Generator(device="cuda").manual_seed(Lq + Lk + B)
+    H = 64 * A
+    mk = lambda rows, width: torch.randn(rows, width, generator=g, device="cuda").to(torch.bfloat16)
+    q, kv, dctx = mk(B * Lq, H), mk(B * Lk, 2 * H), mk(B * Lq, H)
+    ql = torch.randint(1, Lq + 1, (B,), generator=g, device="cuda", dtype=torch.int32)
+    kl = ql if causal else torch.randint(1, Lk + 1, (B,), generator=g, device="cuda", dtype=torch.int32)
+    ctx, lse, dvec = torch.zeros(B * Lq, H, dtype=torch.bfloat16, device="cuda"), torch.zeros(B * A * Lq, device="cuda"), torch.zeros(B * A * Lq, device="cuda")
+    k, v = kv.data_ptr(), kv.data_ptr() + 2 * H
+    hs.hs_op_attention_general_fwd(1, q, H, k, v, 2 * H, ql, kl, B, Lq, Lk, A, causal, ctx, lse)
+    out = []
+    for off, ld in ((0, H), (4, H + 4)):
+        gr = [torch.full((n * ld + 4,), 7.0, dtype=torch.bfloat16, device="cuda")[off:off + n * ld].view(n, ld) for n in (B * Lq, B * Lk, B * Lk)]
+        hs.hs_op_attention_general_bwd(1, q, H, k, v, 2 * H, ql, kl, B, Lq, Lk, A, causal, ctx, lse, dctx, gr[0].data_ptr(), ld, gr[1].data_ptr(),
+                                       gr[2].data_ptr(), ld, dvec)
+        out.append(gr)
+    torch.cuda.synchronize()
+    for a, b in zip(*out):
+        assert torch.equal(a, b[:, :H]) and bool((b[:, H:] == 7.0).all()) and bool(torch.isfinite(a).all())
+
+
 @pytest.mark.parametrize("causal", [0, 1])
 @pytest.mark.parametrize("L,length", [(40, 37), (72, 72), (104, 65)])
 @pytest.mark.parametrize("what,row", [("k", 20), ("v", 33), ("v_inf", 36), ("q", 7), ("dO", 31)])
