@@ -404,6 +404,26 @@ def test_edge_cases_empty_batch_and_longest_buffers(hs):
     wk.close()
 
 
+# rows of one chunk and less, at and behind an edge of a chunk (2048 columns), the longest that registers hold and the first that they do not
+@pytest.mark.parametrize("compute", ["fp32", "bf16"])
+@pytest.mark.parametrize("vocab", [40, 2048, 2049, 4097, 36994, 40959, 40961])
+def test_loss_rows_of_any_length(hs, compute, vocab):
+    model, ocfg, theta, wk = _setup("s2s_tiny", compute, 51, dict(n_enc=1, n_dec=1, vocab=vocab))
+    mb = synth.make_pair_batch(synth.rng_for(52), [16, 9, 24], [20, 32, 7], 24, 32, vocab, "uniform")
+    ol, on, og, _, _ = S.micro_batch_grad(ocfg, theta.astype(np.float64), mb, 0.1)
+    for host_lens in (True, False):       # the real rows only; padding rows too, which get zeros
+        d = wk.upload(mb)
+        if not host_lens:
+            d = dict(d, tgt_lens_host=None)
+        wk.G.fill_(float("nan"))
+        wk.forward_backward(d, wk.G, 0, 0)
+        torch.cuda.synchronize()
+        loss, nll = float(wk.loss_buf[0]), float(wk.loss_buf[64])
+        assert abs(loss - ol) / abs(ol) < TOL[compute] and abs(nll - on) / abs(on) < TOL[compute]
+        compare_flat(S.param_layout(ocfg), wk.G.cpu().numpy(), og, TOL[compute], "grad", rounded_weights_grad(ocfg, theta, mb) if compute == "bf16" else None)
+    wk.close()
+
+
 @pytest.mark.parametrize("compute", ["fp32", "bf16"])
 def test_projection_over_real_rows_only_equals_projection_over_all_rows(hs, compute):
     """With the target lengths on the host the padding rows are left out of the vocabulary projection; without them every
