@@ -72,8 +72,13 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(3, 3))) 
   const int own = w0 + (lane & 31);       // the query, then the key, this lane owns
 
   const bool queries = blockIdx.z == 0, keys = queries == (gridDim.z == 1);      // the halves this block does
-  stage_rows<W>(T0, queries ? k : q, queries ? x.ldkv : x.ldq, queries ? klen : qlen, tid);
-  stage_rows<W>(T1, queries ? v : go, queries ? x.ldkv : H, queries ? klen : qlen, tid);
+  if (queries) {
+    stage_rows<W>(T0, k, x.ldkv, klen, tid);
+    stage_rows<W>(T1, v, x.ldkv, klen, tid);
+  } else {
+    stage_rows<W>(T0, q, x.ldq, qlen, tid);
+    stage_rows<W>(T1, go, H, qlen, tid);
+  }
   // the owned queries' fragments of Q and dO, and the row dot product sum_d dO*O (lanes l and l + 32 hold the two halves of a row)
   bf16x8 qf[4], gf[4];
   float drow = 0.f;
