@@ -470,8 +470,9 @@ static void choose_cfg(const GemmArgs& g, int* cfg, int* splits) {
     // prices them they would be taken there too; BERT-base 64 x 128 7.25 -> 7.33 ms per step), and a block that needs a CU's whole LDS keeps the other
     // half of a forward batch off it (K = 3072 in the halves of 64 x 128: 7.14 -> 7.19).  Their constants were fitted to the choice that comes out: over
     // 8 products, three widths and 24 row counts from 264 to 17472 2 % faster, 4 % from 776 to 5200 rows.  Two updates of BERT-base with 32 sequences of 64 to
-    // 128 positions 9.03 -> 8.71 ms.
-    if (only < 0 && c >= 12 && (g.K < 1536 || g.beside)) continue;
+    // 128 positions 9.03 -> 8.71 ms.  Not with an m-major A: both operands then go through the transposing reads, which those constants do not know, and the
+    // products that are not grouped have many tiles per CU (37000 x 512 x 3135 with 12: 166 us, without 140; x 4096 206, 184).
+    if (only < 0 && c >= 12 && (g.K < 1536 || g.beside || !g.a_kmajor)) continue;
     // With a scratch buffer the contraction can be split over blocks: partial sums go out as fp32 and are added by a second
     // launch (3 us and their way through memory and back at 3.5 TB/s; for contractions beyond 8192, 5 us at the 10 TB/s that the sums get
     // on their way through the caches: 768 x 768 x 32768, both operands k-major, 81 -> 70 us; 3072 x 768 x 16384 152 -> 111).

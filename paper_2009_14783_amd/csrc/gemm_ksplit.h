@@ -170,10 +170,13 @@ hipError_t launch_layout(int cfg, const GemmDev& p, int splits, hipStream_t s) {
     case 10: return launch_dma_one<Dma256x128, AK, BKM>(p, splits, s);
     case 11: return launch_dma_one<Dma64x64, AK, BKM>(p, splits, s);
     case 5: return launch_wide<AK, BKM>(p, splits, s);
-    case 12: return launch_dma_one<Dma128x128Lone, AK, BKM>(p, splits, s);
-    case 13: return launch_dma_one<Dma64x64Lone, AK, BKM>(p, splits, s);
-    default: return hipErrorInvalidValue;
+    default: break;
   }
+  if constexpr (AK) {      // never chosen with an m-major A
+    if (cfg == 12) return launch_dma_one<Dma128x128Lone, AK, BKM>(p, splits, s);
+    if (cfg == 13) return launch_dma_one<Dma64x64Lone, AK, BKM>(p, splits, s);
+  }
+  return hipErrorInvalidValue;
 }
 
 }  // namespace
