@@ -13,11 +13,12 @@ using namespace attn_tiles;
 // straight from global memory, or out of the tiles just before they are overwritten), so a block of four waves takes 37 KiB of LDS and three of them
 // share a CU - one round for the 768 blocks of 64 sequences x 12 heads, and the second staging phase of one block runs under the arithmetic of the
 // others.  What bounds it is that chain: load, store, product, softmax, product, store, twice.  Blocks are as small as their pairs: with four waves
-// for every pair, three of them idle up to 32 positions and hold the places of others (100 sequences of 56 x 12 heads: 25.7 -> 20.9 us).
+// for every pair, three of them idle up to 32 positions and hold the places of others (100 sequences of 56 x 12 heads: 25.7 -> 20.7 us).
+// Three waves per SIMD cost the variant with dropout 24 spilled registers; two without a spill are slower (64 x 128 step 7.66 -> 7.69 ms).
 // Scores start from -8 lse and their gradients from -dO . O, and only cut tiles are masked, as in attention_general.hip (the BERT-base step of 64 x
-// 128 with dropout 8.17 -> 8.08 ms, without level).  For the translation model's 128 x 8 pairs of 32 positions, against four
-// waves per pair (self-attention, 17 us) and two streaming launches (causal and over the encoder output, 17 us now 11): step 4.34 -> 4.14 ms, the
-// same bits.
+// 128 with dropout 8.17 -> 8.08 ms, without level).  For the translation model's 128 x 8 pairs of 32 positions,
+// where four waves per pair (self-attention) and two streaming launches (causal, and over the encoder output) took 17 us each, one launch takes 10.7:
+// its step 4.22 -> 4.04 ms, the same bits.
 // ------------------------------------------------------------------------------------------
 struct ShortOperands {
   const bf16 *q, *k, *v, *out, *d_out;      // first row of sequence 0
