@@ -139,7 +139,9 @@ hs_status hs_dropout_keep_mask(hs_ctx* ctx, uint32_t site, size_t n, uint8_t* ma
  * batch that the following hs_encoder_fwd / hs_encoder_bwd calls work on (lens_host [B], copied; host state only), so that the
  * calls can leave the padding out: they compute the real positions only, one matrix row each (bf16 contexts; fp32 ones keep
  * the padded rows).  The buffers of the calls stay as they are described below, [B, L] with the lengths in `lens` (dev), which must
- * be the same ones; rows of padded positions of hidden_out are then zeros, and those of d_hidden are not read.  The backward call
+ * be the same ones: the host's size every matrix.  Should `lens` hold others when the kernels run, whose sum is not the same, the
+ * results are wrong and hold NaN, an armed update applies them, and no call reads or writes outside its buffers.  Rows of padded
+ * positions of hidden_out are then zeros, and those of d_hidden are not read.  The backward call
  * of a micro-batch must see the state its forward call saw.  lens_host == NULL (the initial state): padded rows again.  While set,
  * a forward or backward call over another B or L fails with HS_ERR_STATE.  Calls that are captured into a graph have the sizes of
  * these lengths in every replay.  HS_ERR_INVALID_ARG for a length outside [1, L]; the state is then as after NULL. */

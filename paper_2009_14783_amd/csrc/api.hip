@@ -18,7 +18,7 @@ struct LayerActs { void *qkv, *ctx, *y1, *x1, *hpre, *h, *y2, *x2; float *lse, *
 struct Acts {
   void *e_pre, *x0; float* emb_stats;
   std::vector<LayerActs> layer;
-  int32_t *first, *pad_row;      // packed rows (see PackedRows)
+  int32_t *first, *len, *pad_row;      // packed rows (see PackedRows)
   size_t total;
 };
 
@@ -38,7 +38,7 @@ Acts carve_acts(const hs_model_cfg& c, int B, int L, void* base) {
     l.y2 = cv.take(T * H * es); l.st2 = (float*)cv.take(2 * T * sizeof(float));
     l.x2 = (i + 1 < c.n_layers) ? cv.take(T * H * es) : nullptr;   // the last layer writes hidden_out
   }
-  a.first = (int32_t*)cv.take((size_t)B * sizeof(int32_t));
+  a.first = (int32_t*)cv.take((size_t)B * sizeof(int32_t)); a.len = (int32_t*)cv.take((size_t)B * sizeof(int32_t));
   a.pad_row = (int32_t*)cv.take(T * sizeof(int32_t));
   a.total = cv.off;
   return a;
@@ -251,7 +251,7 @@ hs_status hs_encoder_fwd(hs_ctx* ctx, const void* w, const int32_t* ids, const i
   }
   for (int k = 0; k < nparts; ++k) {
     const Part& pt = part[k];
-    const PackedPart pk{lens + pt.b0, a.first + pt.b0, a.pad_row, pt.row0, pt.b0 * L};
+    const PackedPart pk{lens + pt.b0, a.first + pt.b0, a.len + pt.b0, a.pad_row, pt.nb, pt.row0, pt.rows, pt.b0 * L};
     const Part whole{0, B, 0, T, s};
     const Part& at = packed ? whole : pt;
     HS_TRY(launch_embed_ln_fwd(ctx, dt, W(ctx, w, o.emb_word), W(ctx, w, o.emb_pos), W(ctx, w, o.emb_ln_g), W(ctx, w, o.emb_ln_b),
@@ -273,7 +273,7 @@ hs_status hs_encoder_fwd(hs_ctx* ctx, const void* w, const int32_t* ids, const i
       g.bias = W(ctx, w, lo.qkv_b); g.beside = split;
       HS_TRY(launch_gemm(ctx, g, st));
       const void* const qkv = packed ? la.qkv : rows(la.qkv, pt, 3 * H);
-      HS_TRY(launch_attention_fwd(ctx, dt, qkv, lens + pt.b0, pt.nb, L, c.n_heads, packed ? la.ctx : rows_w(la.ctx, pt, H),
+      HS_TRY(launch_attention_fwd(ctx, dt, qkv, (packed ? a.len : lens) + pt.b0, pt.nb, L, c.n_heads, packed ? la.ctx : rows_w(la.ctx, pt, H),
                                   la.lse + (size_t)pt.b0 * c.n_heads * L, st, drop ? &drop_prob[k] : nullptr, site_attention_prob(i),
                                   packed ? a.first + pt.b0 : nullptr));
       // y1 = x + ctx Wo^T + bo ; x1 = LN(y1)
@@ -294,7 +294,7 @@ hs_status hs_encoder_fwd(hs_ctx* ctx, const void* w, const int32_t* ids, const i
       HS_TRY(launch_gemm(ctx, g, st));
       if (packed && !la.x2)      // the caller's buffer has the padded rows
         HS_TRY(launch_layernorm_fwd_unpack(ctx, dt, la.y2, W(ctx, w, lo.ln2_g), W(ctx, w, lo.ln2_b), (char*)hidden_out + (size_t)pt.b0 * L * H * es,
-                                           la.st2, lens + pt.b0, a.first + pt.b0, pt.nb, L, H, c.ln_eps, st, T));
+                                           la.st2, a.len + pt.b0, a.first + pt.b0, pt.nb, L, H, c.ln_eps, st, T));
       else
         HS_TRY(launch_layernorm_fwd(ctx, dt, rows(la.y2, pt, H), W(ctx, w, lo.ln2_g), W(ctx, w, lo.ln2_b), rows_w(x2, pt, H),
                                     la.st2 + pt.row0, Tp, H, c.ln_eps, st, T));
@@ -429,7 +429,7 @@ static hs_status encoder_bwd_impl(hs_ctx* ctx, const hs_ctx::Armed& upd, const v
   Acts a = carve_acts(c, B, L, const_cast<void*>(acts));
   const BwdPlan plan = bwd_plan(c, T, B, L, workspace_bytes);
   BwdWs ws = carve_bwd(c, T, B, L, plan.sets, workspace);
-  const PackedRows packed_batch{lens, a.first, a.pad_row, T}, *pk = packed ? &packed_batch : nullptr;
+  const PackedRows packed_batch{a.len, a.first, a.pad_row, T}, *pk = packed ? &packed_batch : nullptr;
   const int32_t* const pad_row = packed ? a.pad_row : nullptr;
   const float beta = accumulate ? 1.f : 0.f;
   const DropCfg* drop = ctx->drop.thr ? &ctx->drop : nullptr;
@@ -518,7 +518,7 @@ static hs_status encoder_bwd_impl(hs_ctx* ctx, const hs_ctx::Armed& upd, const v
     // dctx = dy1 Wo
     ga = gemm_args(dt, 1, 0, T, H, H, dy1b, H, W(ctx, w, lo.o_w), H, ws.dctx, H);
     HS_TRY(run_gemm(ga));
-    HS_TRY(launch_attention_bwd(ctx, dt, la.qkv, la.ctx, la.lse, ws.dctx, lens, B, L, c.n_heads, q.dqkv, ws.dvec, s, drop,
+    HS_TRY(launch_attention_bwd(ctx, dt, la.qkv, la.ctx, la.lse, ws.dctx, packed ? a.len : lens, B, L, c.n_heads, q.dqkv, ws.dvec, s, drop,
                                 site_attention_prob(i), packed ? a.first : nullptr));
     // dW2 [H,F] = dy2^T h, dW1 [F,H] = dhpre^T x1, dWqkv [3H,H] = dqkv^T x_in, dWo [H,H] = dy1^T ctx, and the two bias gradients that
     // are not by-products of a LayerNorm backward

@@ -165,19 +165,20 @@ bool hs_cfg_valid(const hs_model_cfg* cfg, std::string* why);
 void hs_model_offsets(const hs_model_cfg& cfg, ModelOff* out);
 
 // Packed rows.  With the lengths of a batch known on the host (hs_set_lengths) the passes work on its real positions only: row first[b] + l of
-// every token-major matrix is position l of sequence b, and padding has no rows.  This is the device side, as kernels take it; `first` and
-// `pad_row` are written by the embedding kernel into the activation arena.
+// every token-major matrix is position l of sequence b, and padding has no rows.  This is the device side, as kernels take it; `first`,
+// `len` and `pad_row` are written by the embedding kernel into the activation arena.
 struct PackedRows {
-  const int32_t* lens;      // [B]
-  int32_t* first;           // [B]
-  int32_t* pad_row;         // [rows]: position b L + l of each row
+  const int32_t* len;       // [B]: rows of each sequence
+  const int32_t* first;     // [B]
+  const int32_t* pad_row;   // [rows]: position b L + l of each row
   int rows;
 };
-// a range of sequences of it that an embedding kernel fills: lens, first and ids are given from its first sequence, everything else from row 0
+// a range of sequences of it that an embedding kernel fills: lens (the caller's), first, len and ids are given from its first sequence, everything else
+// from row 0
 struct PackedPart {
   const int32_t* lens;
-  int32_t *first, *pad_row;
-  int row0, pos0;           // first packed row and first position of the range
+  int32_t *first, *len, *pad_row;
+  int nb, row0, rows, pos0;      // sequences, first packed row, rows and first position of the range
 };
 // length of sequence b, and the rows of the sequences of the range before it (by one wave; a load per 64 sequences)
 __device__ __forceinline__ int packed_len(const int32_t* lens, int b, int L) { return min(max(lens[b], 1), L); }
@@ -185,6 +186,22 @@ __device__ __forceinline__ int packed_before(const int32_t* lens, int b, int L, 
   int n = 0;
   for (int i = lane; i < b; i += 64) n += packed_len(lens, i, L);
   return wave_sum_int(n);
+}
+// The packed row of position l < n of sequence b (n its length; by one wave), or -1 where it has none; first, len and pad_row are written.  The matrices have
+// the rows of the lengths that the host was told.  Should lens say another number, no kernel may leave them: positions beyond the last row are dropped
+// here, and as the other kernels go by `first` and `len` they stay inside too.  *bad: the numbers differ; true of one row at least, which the caller
+// makes NaN, so that such a batch has no plausible result.
+__device__ __forceinline__ int packed_row(const PackedPart& pk, int b, int l, int n, int L, int lane, bool* bad) {
+  const int f = packed_before(pk.lens, b, L, lane);
+  if (l == 0 && lane == 0) {
+    pk.first[b] = pk.row0 + min(f, pk.rows - 1);
+    pk.len[b] = max(min(n, pk.rows - f), 1);
+  }
+  const int r = f + l;
+  if (r >= pk.rows) return -1;
+  if (lane == 0) pk.pad_row[pk.row0 + r] = pk.pos0 + b * L + l;
+  *bad = (b == pk.nb - 1 && l == n - 1) != (r == pk.rows - 1);
+  return pk.row0 + r;
 }
 // ... and what a context was told: first row of every sequence, and behind the last one the number of rows
 struct HostLens {
@@ -270,9 +287,9 @@ void gemm_set_variant(int variant);
 // stats: R means, then (stat_ld floats after the first mean; default R) R reciprocal standard deviations
 hs_status launch_layernorm_fwd(hs_ctx* ctx, int dtype, const void* x, const void* gain, const void* bias, void* y,
                                float* stats, int R, int H, float eps, hipStream_t s, int stat_ld = 0);
-// packed rows in, padded rows out (zeros in the padding): x and stats from row 0 of the batch, y, lens and first from the first of B sequences
+// packed rows in, padded rows out (zeros in the padding): x and stats from row 0 of the batch, y, len and first from the first of B sequences
 hs_status launch_layernorm_fwd_unpack(hs_ctx* ctx, int dtype, const void* x, const void* gain, const void* bias, void* y, float* stats,
-                                      const int32_t* lens, const int32_t* first, int B, int L, int H, float eps, hipStream_t s, int stat_ld);
+                                      const int32_t* len, const int32_t* first, int B, int L, int H, float eps, hipStream_t s, int stat_ld);
 size_t layernorm_bwd_scratch(int R, int H);
 // pad_row (packed rows): the position of each row, which numbers the elements of a dropout site; dy_rows > 0: dy has that many padded rows.
 // drop_mode 0: no dropout.  1: dy is the gradient of this LayerNorm's dropped output (site) and is masked as

@@ -92,7 +92,7 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(const T* __restrict__ x, co
 // Row l of sequence b (padded rows) from packed row first[b] + l; zeros where l is padding.
 template <class T>
 __global__ __launch_bounds__(256) void ln_fwd_unpack_kernel(const T* __restrict__ x, const T* __restrict__ gain, const T* __restrict__ bias,
-                                                            T* __restrict__ y, float* __restrict__ stats, const int32_t* __restrict__ lens,
+                                                            T* __restrict__ y, float* __restrict__ stats, const int32_t* __restrict__ len,
                                                             const int32_t* __restrict__ first, int R, int L, int H, float eps, int stat_ld) {
   const int lane = threadIdx.x & 63;
   const int pos = blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -100,7 +100,7 @@ __global__ __launch_bounds__(256) void ln_fwd_unpack_kernel(const T* __restrict_
   const int b = pos / L, l = pos - b * L;
   const int nch = H / 4;
   T* const out = y + (int64_t)pos * H;
-  if (l >= packed_len(lens, b, L)) {
+  if (l >= len[b]) {
 #pragma unroll
     for (int c = 0; c < MAXCH; ++c) if (c * 64 + lane < nch) Vec4<T>::st(out + 4 * (c * 64 + lane), make_float4(0.f, 0.f, 0.f, 0.f));
     return;
@@ -112,7 +112,7 @@ __global__ __launch_bounds__(256) void ln_fwd_unpack_kernel(const T* __restrict_
   ln_row<T>(v, nch, H, lane, gain, bias, eps, out, stats + row, stats + stat_ld + row);
 }
 
-// PACK: position l of sequence b goes to packed row first[b] + l, padding nowhere; first and pad_row are written here.
+// PACK: position l of sequence b goes to its packed row, padding nowhere.
 template <class T, bool PACK>
 __global__ __launch_bounds__(256) void embed_ln_fwd_kernel(const T* __restrict__ word, const T* __restrict__ pos,
                                                            const T* __restrict__ gain, const T* __restrict__ bias,
@@ -124,14 +124,12 @@ __global__ __launch_bounds__(256) void embed_ln_fwd_kernel(const T* __restrict__
   if (at >= R) return;
   const int b = at / L, l = at - b * L;
   int row = at;
+  bool bad = false;
   if (PACK) {
-    if (l >= packed_len(pk.lens, b, L)) return;
-    const int f = pk.row0 + packed_before(pk.lens, b, L, lane);
-    row = f + l;
-    if (lane == 0) {
-      pk.pad_row[row] = pk.pos0 + at;
-      if (l == 0) pk.first[b] = f;
-    }
+    const int n = packed_len(pk.lens, b, L);
+    if (l >= n) return;
+    row = packed_row(pk, b, l, n, L, lane, &bad);
+    if (row < 0) return;
   }
   int id = ids[at];
   id = id < 0 ? 0 : (id >= V ? V - 1 : id);  // ids are validated by contract; clamp keeps reads in bounds
@@ -142,7 +140,8 @@ __global__ __launch_bounds__(256) void embed_ln_fwd_kernel(const T* __restrict__
     const int col = 4 * (c * 64 + lane);
     const float4 a = Vec4<T>::ld(word + (int64_t)id * H + col), b = Vec4<T>::ld(pos + (int64_t)l * H + col);
     // the sum is rounded to the activation type because that is what the backward pass re-reads
-    const float4 e = Vec4<T>::round(make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w));
+    float4 e = Vec4<T>::round(make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w));
+    if (PACK && bad) e.x = __builtin_nanf("");
     Vec4<T>::st(e_pre + (int64_t)row * H + col, e);
     v[c] = e;
   }
@@ -503,7 +502,7 @@ __global__ __launch_bounds__(256) void sum_vector_kernel(const float* __restrict
 // PACK: de has packed rows, row first[b] + l for the sequences of more than l positions.
 template <class T, bool PACK>
 __global__ __launch_bounds__(64) void pos_grad_kernel(const T* __restrict__ de, int B, int L, int H, int max_pos, float* __restrict__ g_pos, float beta,
-                                                      const int32_t* __restrict__ lens, const int32_t* __restrict__ first) {
+                                                      const int32_t* __restrict__ len, const int32_t* __restrict__ first) {
   const int64_t i = 4 * ((int64_t)blockIdx.x * blockDim.x + threadIdx.x);
   if (i >= (int64_t)max_pos * H) return;
   const int64_t l = i / H, step = (int64_t)L * H;
@@ -515,7 +514,7 @@ __global__ __launch_bounds__(64) void pos_grad_kernel(const T* __restrict__ de, 
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
         v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (b + u < B && l < packed_len(lens, b + u, L)) v[u] = Vec4<T>::ld(col + (first[b + u] + l) * H);
+        if (b + u < B && l < len[b + u]) v[u] = Vec4<T>::ld(col + (first[b + u] + l) * H);
       }
 #pragma unroll
       for (int u = 0; u < 8; ++u) { s.x += v[u].x; s.y += v[u].y; s.z += v[u].z; s.w += v[u].w; }
@@ -700,13 +699,13 @@ hs_status launch_layernorm_fwd(hs_ctx* ctx, int dtype, const void* x, const void
 }
 
 hs_status launch_layernorm_fwd_unpack(hs_ctx* ctx, int dtype, const void* x, const void* gain, const void* bias, void* y, float* stats,
-                                      const int32_t* lens, const int32_t* first, int B, int L, int H, float eps, hipStream_t s, int stat_ld) {
+                                      const int32_t* len, const int32_t* first, int B, int L, int H, float eps, hipStream_t s, int stat_ld) {
   const int R = B * L;
   if (R <= 0) return HS_OK;
   KScope scope(prof_of(ctx), KC_LN_FWD, 8.0 * R * H, 2.0 * R * H * esize(dtype), s);
   dim3 grid((R + 3) / 4);
-  if (dtype == HS_BF16) hipLaunchKernelGGL(ln_fwd_unpack_kernel<bf16>, grid, dim3(256), 0, s, (const bf16*)x, (const bf16*)gain, (const bf16*)bias, (bf16*)y, stats, lens, first, R, L, H, eps, stat_ld);
-  else hipLaunchKernelGGL(ln_fwd_unpack_kernel<float>, grid, dim3(256), 0, s, (const float*)x, (const float*)gain, (const float*)bias, (float*)y, stats, lens, first, R, L, H, eps, stat_ld);
+  if (dtype == HS_BF16) hipLaunchKernelGGL(ln_fwd_unpack_kernel<bf16>, grid, dim3(256), 0, s, (const bf16*)x, (const bf16*)gain, (const bf16*)bias, (bf16*)y, stats, len, first, R, L, H, eps, stat_ld);
+  else hipLaunchKernelGGL(ln_fwd_unpack_kernel<float>, grid, dim3(256), 0, s, (const float*)x, (const float*)gain, (const float*)bias, (float*)y, stats, len, first, R, L, H, eps, stat_ld);
   LAUNCH_CHECK(ctx, "layernorm_fwd");
   return HS_OK;
 }
@@ -816,7 +815,7 @@ hs_status launch_embed_sort(hs_ctx* ctx, const int32_t* ids, int T, int V, void*
   while ((1 << bits) < V) ++bits;
   int npass = (bits + 3) / 4;
   if (npass & 1) ++npass;  // an even number of passes leaves the result in (k0, v0)
-  hipLaunchKernelGGL(sort_ids_kernel, dim3(1), dim3(512), 0, s, ids, T, V, k0, v0, k1, v1, npass, pk ? (const int32_t*)pk->pad_row : nullptr, (unsigned)positions);
+  hipLaunchKernelGGL(sort_ids_kernel, dim3(1), dim3(512), 0, s, ids, T, V, k0, v0, k1, v1, npass, pk ? pk->pad_row : nullptr, (unsigned)positions);
   LAUNCH_CHECK(ctx, "sort_ids");
   return HS_OK;
 }
@@ -830,8 +829,8 @@ hs_status launch_embed_bwd(hs_ctx* ctx, int dtype, const void* de, const int32_t
   if (g_pos) {     // a model with a fixed position table has no position gradient
     const int64_t n = (int64_t)max_pos * H;
     dim3 grid((unsigned)((n + 255) / 256));
-    const int32_t *lens = pk ? pk->lens : nullptr, *first = pk ? pk->first : nullptr;
-#define HS_POS_GRAD(TT, PACK) hipLaunchKernelGGL((pos_grad_kernel<TT, PACK>), grid, dim3(64), 0, s, (const TT*)de, B, L, H, max_pos, g_pos, beta_pos, lens, first)
+    const int32_t *len = pk ? pk->len : nullptr, *first = pk ? pk->first : nullptr;
+#define HS_POS_GRAD(TT, PACK) hipLaunchKernelGGL((pos_grad_kernel<TT, PACK>), grid, dim3(64), 0, s, (const TT*)de, B, L, H, max_pos, g_pos, beta_pos, len, first)
     if (dtype == HS_BF16) { if (pk) HS_POS_GRAD(bf16, true); else HS_POS_GRAD(bf16, false); }
     else { if (pk) HS_POS_GRAD(float, true); else HS_POS_GRAD(float, false); }
 #undef HS_POS_GRAD

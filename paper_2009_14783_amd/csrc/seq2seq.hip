@@ -89,7 +89,7 @@ struct EncActs { void *qkv, *ctx, *y1, *x1, *h, *y2, *x2; float *lse, *st1, *st2
 struct DecActs { void *qkv, *ctx, *y1s, *y1, *cq, *ckv, *cctx, *ycs, *yc, *h, *y2s, *y2; float *lse, *clse, *st1, *stc, *st2; };
 struct Acts {
   float* pe; void *x0, *t0; std::vector<EncActs> enc; std::vector<DecActs> dec;
-  int32_t *src_first, *src_pad, *tgt_first, *tgt_pad;      // packed rows (see PackedRows)
+  int32_t *src_first, *src_len, *src_pad, *tgt_first, *tgt_len, *tgt_pad;      // packed rows (see PackedRows)
   size_t total;
 };
 
@@ -117,8 +117,8 @@ Acts carve_acts(const hs_s2s_cfg& c, int B, int Ls, int Lt, void* base) {
     l.y2s = cv.take(Tt * H * es); l.st2 = (float*)cv.take(2 * Tt * sizeof(float));
     l.y2 = (i + 1 < a.dec.size()) ? cv.take(Tt * H * es) : nullptr;      // the last layer writes dec_out
   }
-  a.src_first = (int32_t*)cv.take((size_t)B * sizeof(int32_t)); a.src_pad = (int32_t*)cv.take(Ts * sizeof(int32_t));
-  a.tgt_first = (int32_t*)cv.take((size_t)B * sizeof(int32_t)); a.tgt_pad = (int32_t*)cv.take(Tt * sizeof(int32_t));
+  a.src_first = (int32_t*)cv.take((size_t)B * sizeof(int32_t)); a.src_len = (int32_t*)cv.take((size_t)B * sizeof(int32_t)); a.src_pad = (int32_t*)cv.take(Ts * sizeof(int32_t));
+  a.tgt_first = (int32_t*)cv.take((size_t)B * sizeof(int32_t)); a.tgt_len = (int32_t*)cv.take((size_t)B * sizeof(int32_t)); a.tgt_pad = (int32_t*)cv.take(Tt * sizeof(int32_t));
   a.total = cv.off;
   return a;
 }
@@ -349,7 +349,7 @@ hs_status hs_s2s_fwd(hs_ctx* ctx, const void* w, const int32_t* src, const int32
   // ---- encoder ----
   for (int k = 0; k < nparts; ++k) {
     const Part& pt = part[k];
-    const PackedPart pk{src_lens + pt.b0, a.src_first + pt.b0, a.src_pad, pt.src0, pt.b0 * Ls};
+    const PackedPart pk{src_lens + pt.b0, a.src_first + pt.b0, a.src_len + pt.b0, a.src_pad, pt.nb, pt.src0, pt.src_n, pt.b0 * Ls};
     HS_TRY(launch_embed_scale_pos(ctx, dt, W(dt, w, o.emb), src + (size_t)pt.b0 * Ls, a.pe, mut(src_base(a.x0, pt, H)), pt.nb, Ls, H, c.vocab, scale,
                                   drop ? &drop_src[k] : nullptr, site_src(), pt.st, packed ? &pk : nullptr));
   }
@@ -365,7 +365,7 @@ hs_status hs_s2s_fwd(hs_ctx* ctx, const void* w, const int32_t* src, const int32
       const int32_t* drows = packed ? a.src_pad + pt.src0 : nullptr;
       auto R = [&](const void* p, int64_t width) { return src_rows(p, pt, width); };
       HS_TRY(linear(ctx, dt, T, 3 * H, H, R(x, H), W(dt, w, lo.qkv_w), W(dt, w, lo.qkv_b), mut(R(la.qkv, 3 * H)), st, split));
-      HS_TRY(launch_attention_fwd(ctx, dt, src_base(la.qkv, pt, 3 * H), src_lens + pt.b0, pt.nb, Ls, A, mut(src_base(la.ctx, pt, H)),
+      HS_TRY(launch_attention_fwd(ctx, dt, src_base(la.qkv, pt, 3 * H), (packed ? a.src_len : src_lens) + pt.b0, pt.nb, Ls, A, mut(src_base(la.ctx, pt, H)),
                                   la.lse + (size_t)pt.b0 * A * Ls, st, nullptr, 0, packed ? a.src_first + pt.b0 : nullptr));
       HS_TRY(linear_res_ln(ctx, dt, T, H, H, R(la.ctx, H), W(dt, w, lo.o_w), W(dt, w, lo.o_b), R(x, H), mut(R(la.y1, H)), W(dt, w, lo.ln1_g),
                            W(dt, w, lo.ln1_b), mut(R(la.x1, H)), la.st1 + pt.src0, Ts, c.ln_eps, dr, drows, site_enc(i, 0), st, split));
@@ -380,7 +380,7 @@ hs_status hs_s2s_fwd(hs_ctx* ctx, const void* w, const int32_t* src, const int32
   // ---- decoder ----
   for (int k = 0; k < nparts; ++k) {
     const Part& pt = part[k];
-    const PackedPart pk{tgt_lens + pt.b0, a.tgt_first + pt.b0, a.tgt_pad, pt.tgt0, pt.b0 * Lt};
+    const PackedPart pk{tgt_lens + pt.b0, a.tgt_first + pt.b0, a.tgt_len + pt.b0, a.tgt_pad, pt.nb, pt.tgt0, pt.tgt_n, pt.b0 * Lt};
     HS_TRY(launch_embed_scale_pos(ctx, dt, W(dt, w, o.emb), tgt_in + (size_t)pt.b0 * Lt, a.pe, mut(tgt_base(a.t0, pt, H)), pt.nb, Lt, H, c.vocab,
                                   scale, drop ? &drop_tgt[k] : nullptr, site_tgt(), pt.st, packed ? &pk : nullptr));
   }
@@ -398,8 +398,8 @@ hs_status hs_s2s_fwd(hs_ctx* ctx, const void* w, const int32_t* src, const int32
       const int32_t *tf = packed ? a.tgt_first + pt.b0 : nullptr, *sf = packed ? a.src_first + pt.b0 : nullptr;
       const bool unpack = packed && !la.y2;      // the last layer: the caller's buffer has the padded rows
       auto R = [&](const void* p, int64_t width) { return tgt_rows(p, pt, width); };
-      const int32_t* tl = tgt_lens + pt.b0;
-      const int32_t* sl = src_lens + pt.b0;
+      const int32_t* tl = (packed ? a.tgt_len : tgt_lens) + pt.b0;
+      const int32_t* sl = (packed ? a.src_len : src_lens) + pt.b0;
       HS_TRY(linear(ctx, dt, T, 3 * H, H, R(y, H), W(dt, w, lo.qkv_w), W(dt, w, lo.qkv_b), mut(R(la.qkv, 3 * H)), st, split));
       const void* qkv = tgt_base(la.qkv, pt, 3 * H);
       AttnOperands self{qkv, at(dt, qkv, H), at(dt, qkv, 2 * H), 3 * (int64_t)H, 3 * (int64_t)H, tl, tl, Lt, Lt, A, 1, tf, tf};
@@ -516,10 +516,11 @@ hs_status hs_s2s_bwd(hs_ctx* ctx, const void* w, const void* acts, const int32_t
   const int Ts = packed ? ctx->lens_a.rows() : B * Ls, Tt = packed ? ctx->lens_b.rows() : B * Lt;      // rows
   hipStream_t s = (hipStream_t)stream;
   Acts a = carve_acts(c, B, Ls, Lt, const_cast<void*>(acts));
-  const PackedRows packed_src{src_lens, a.src_first, a.src_pad, Ts}, packed_tgt{tgt_lens, a.tgt_first, a.tgt_pad, Tt};
+  const PackedRows packed_src{a.src_len, a.src_first, a.src_pad, Ts}, packed_tgt{a.tgt_len, a.tgt_first, a.tgt_pad, Tt};
   const PackedRows *pks = packed ? &packed_src : nullptr, *pkt = packed ? &packed_tgt : nullptr;
   const int32_t *src_pad = packed ? a.src_pad : nullptr, *tgt_pad = packed ? a.tgt_pad : nullptr;
   const int32_t *src_first = packed ? a.src_first : nullptr, *tgt_first = packed ? a.tgt_first : nullptr;
+  const int32_t *src_rows = packed ? a.src_len : src_lens, *tgt_rows = packed ? a.tgt_len : tgt_lens;      // of each sequence
   BwdWs ws = carve_bwd(c, B, Ls, Lt, workspace);
   const float beta = accumulate ? 1.f : 0.f;
   const DropCfg* drop = ctx->drop.thr ? &ctx->drop : nullptr;
@@ -619,7 +620,7 @@ hs_status hs_s2s_bwd(hs_ctx* ctx, const void* w, const void* acts, const int32_t
     HS_TRY(ln_bwd(Tt, tgt_pad, cols_tgt, ws.da, la.ycs, la.stc, lo.lnc_g, lo.lnc_b, lo.co_b, site_dec(c, i, 1), lg.sc, lg.mc, lg.pc, &br));
     wgrad(H, H, Tt, br, H, la.cctx, H, g + lo.co_w);
     HS_TRY(dgrad(Tt, H, H, br, W(dt, w, lo.co_w), ws.dctx, nullptr));
-    AttnOperands cross{la.cq, la.ckv, at(dt, (const void*)la.ckv, H), (int64_t)H, 2 * (int64_t)H, tgt_lens, src_lens, Lt, Ls, A, 0,
+    AttnOperands cross{la.cq, la.ckv, at(dt, (const void*)la.ckv, H), (int64_t)H, 2 * (int64_t)H, tgt_rows, src_rows, Lt, Ls, A, 0,
                        tgt_first, src_first};
     HS_TRY(launch_attention_general_bwd(ctx, dt, cross, B, la.cctx, la.clse, ws.dctx, lg.dcq, H, lg.dckv, at(dt, lg.dckv, H), 2 * (int64_t)H,
                                         ws.dvec, s));
@@ -634,7 +635,7 @@ hs_status hs_s2s_bwd(hs_ctx* ctx, const void* w, const void* acts, const int32_t
     HS_TRY(ln_bwd(Tt, tgt_pad, cols_tgt, ws.db, la.y1s, la.st1, lo.ln1_g, lo.ln1_b, lo.o_b, site_dec(c, i, 0), lg.s1, lg.m1, lg.p1, &br));
     wgrad(H, H, Tt, br, H, la.ctx, H, g + lo.o_w);
     HS_TRY(dgrad(Tt, H, H, br, W(dt, w, lo.o_w), ws.dctx, nullptr));
-    AttnOperands self{la.qkv, at(dt, (const void*)la.qkv, H), at(dt, (const void*)la.qkv, 2 * H), 3 * (int64_t)H, 3 * (int64_t)H, tgt_lens, tgt_lens,
+    AttnOperands self{la.qkv, at(dt, (const void*)la.qkv, H), at(dt, (const void*)la.qkv, 2 * H), 3 * (int64_t)H, 3 * (int64_t)H, tgt_rows, tgt_rows,
                       Lt, Lt, A, 1, tgt_first, tgt_first};
     HS_TRY(launch_attention_general_bwd(ctx, dt, self, B, la.ctx, la.lse, ws.dctx, lg.dqkv, 3 * (int64_t)H, at(dt, lg.dqkv, H),
                                         at(dt, lg.dqkv, 2 * H), 3 * (int64_t)H, ws.dvec, s));
@@ -667,7 +668,7 @@ hs_status hs_s2s_bwd(hs_ctx* ctx, const void* w, const void* acts, const int32_t
     HS_TRY(ln_bwd(Ts, src_pad, cols_src, ws.da, la.y1, la.st1, lo.ln1_g, lo.ln1_b, lo.o_b, site_enc(i, 0), lg.s1, lg.m1, lg.p1, &br));
     wgrad(H, H, Ts, br, H, la.ctx, H, g + lo.o_w);
     HS_TRY(dgrad(Ts, H, H, br, W(dt, w, lo.o_w), ws.dctx, nullptr));
-    HS_TRY(launch_attention_bwd(ctx, dt, la.qkv, la.ctx, la.lse, ws.dctx, src_lens, B, Ls, A, lg.dqkv, ws.dvec, s, nullptr, 0, src_first));
+    HS_TRY(launch_attention_bwd(ctx, dt, la.qkv, la.ctx, la.lse, ws.dctx, src_rows, B, Ls, A, lg.dqkv, ws.dvec, s, nullptr, 0, src_first));
     bias_grad(lg.dqkv, Ts, 3 * H, g + lo.qkv_b);
     wgrad(3 * H, H, Ts, lg.dqkv, 3 * H, x_in, H, g + lo.qkv_w);
     HS_TRY(dgrad(Ts, H, 3 * H, lg.dqkv, W(dt, w, lo.qkv_w), ws.db, lg.s1));

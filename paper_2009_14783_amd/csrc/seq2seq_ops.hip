@@ -37,7 +37,7 @@ __global__ __launch_bounds__(256) void position_table_kernel(float* __restrict__
 }
 
 // x[b, l, c] = drop(scale * E[ids[b, l], c] + PE[l, c]); one block per token, four columns per thread
-// PACK: position l of sequence b goes to packed row first[b] + l, padding nowhere; first and pad_row are written here.
+// PACK: position l of sequence b goes to its packed row, padding nowhere.
 template <class T, bool PACK>
 __global__ __launch_bounds__(128) void embed_scale_pos_kernel(const T* __restrict__ emb, const int32_t* __restrict__ ids,
                                                               const float* __restrict__ pe, T* __restrict__ x, int L, int H, int V, float scale,
@@ -45,14 +45,12 @@ __global__ __launch_bounds__(128) void embed_scale_pos_kernel(const T* __restric
   const int64_t row = blockIdx.x;
   const int b = (int)(row / L), l = (int)(row - (int64_t)b * L);
   int64_t to = row;
+  bool bad = false;
   if (PACK) {
-    if (l >= packed_len(pk.lens, b, L)) return;
-    const int f = pk.row0 + packed_before(pk.lens, b, L, threadIdx.x & 63);
-    to = f + l;
-    if (threadIdx.x == 0) {
-      pk.pad_row[to] = pk.pos0 + (int)row;
-      if (l == 0) pk.first[b] = f;
-    }
+    const int n = packed_len(pk.lens, b, L);
+    if (l >= n) return;
+    to = packed_row(pk, b, l, n, L, threadIdx.x & 63, &bad);      // (each wave of the block, with the same result)
+    if (to < 0) return;
   }
   int id = ids[row];
   id = id < 0 ? 0 : (id >= V ? V - 1 : id);
@@ -65,6 +63,7 @@ __global__ __launch_bounds__(128) void embed_scale_pos_kernel(const T* __restric
       drop_factors4(drop, site, ((uint64_t)row * H + c) >> 2, f);
       v.x *= f[0]; v.y *= f[1]; v.z *= f[2]; v.w *= f[3];
     }
+    if (PACK && bad) v.x = __builtin_nanf("");
     V4<T>::st(x + to * H + c, v);
   }
 }
@@ -251,6 +250,8 @@ __global__ __launch_bounds__(1024) void real_rows_kernel(const int32_t* __restri
     if (threadIdx.x == 1023) base_s += scan[1023];
     __syncthreads();
   }
+  // lengths that sum to less than the host was told: every row that is gathered is still a position
+  for (int k = base_s + threadIdx.x; k < capacity; k += 1024) rows[k] = 0;
   // a caller whose count exceeds the real one still gets valid positions (position 0) in the tail
   for (int k = base_s + threadIdx.x; k < capacity; k += 1024) rows[k] = 0;
 }

@@ -140,3 +140,69 @@ def test_pair_step_of_a_large_model_gives_the_bits_of_the_separate_update(comput
         torch.cuda.synchronize()
         same_state(a, b, ("w", "m", "v", "G") + (("w_lowp",) if compute == "bf16" else ()))
     a.close(); b.close()
+
+
+def with_guards(wk, *names):
+    """Replaces the worker's byte arenas by ones with 1 MiB of a pattern behind them; returns a check that it is all there."""
+    ends = []
+    for name in names:
+        old = getattr(wk, name)
+        n = old.numel() * old.element_size()
+        new = torch.full((n + (1 << 20),), 0xA5, dtype=torch.uint8, device="cuda")
+        setattr(wk, name, new if old.dtype == torch.uint8 else new.view(old.dtype))
+        ends.append(new[n:])
+    return lambda: all(bool((e == 0xA5).all()) for e in ends)
+
+
+# `lens` on the device that no longer are the lengths the host was told, with a larger and a smaller sum, in one part and in two halves: NaN and not
+# plausible numbers, every buffer kept, and the right lengths give the right bits again
+@pytest.mark.parametrize("B,L", [(6, 64), (48, 128)])
+@pytest.mark.parametrize("p", [0.0, 0.1])
+def test_lengths_on_the_device_that_are_not_the_host_s(B, L, p):
+    model = dict(n_layers=2, hidden=128, n_heads=2, ffn=256, vocab=500, max_pos=128, ln_eps=1e-12)
+    wk = Worker(model, "bf16", synth.init_params(hs.hs_param_layout(hs.make_cfg(**model)), 81))
+    lens = [max(1, L - (b % 5) * 6) for b in range(B)]
+    assert (sum(lens) >= 4096) == (B == 48)
+    d = wk.upload(dict(synth.make_micro_batch(synth.rng_for(82), lens, L, 500, "uniform"), drop=dict(p=p, seed=9, stream=3) if p else None))
+    kept = with_guards(wk, "_acts", "_ws", "_hidden", "_dhidden")
+    wk.forward_backward(d, wk.G, 0, 0)
+    torch.cuda.synchronize()
+    want, right = wk.G.clone(), d["lens"].clone()
+    assert bool(torch.isfinite(want).all())
+    for wrong in (torch.full_like(right, L), torch.ones_like(right), right.clamp(max=L // 2), torch.where(torch.arange(B, device="cuda") < B // 2, L, right)):
+        d["lens"].copy_(wrong)
+        wk.G.zero_()
+        wk.forward_backward(d, wk.G, 0, 0)
+        torch.cuda.synchronize()
+        assert kept() and bool(torch.isnan(wk.G).any())
+    d["lens"].copy_(right)
+    wk.forward_backward(d, wk.G, 0, 0)
+    torch.cuda.synchronize()
+    assert kept() and torch.equal(wk.G, want)
+    wk.close()
+
+
+@pytest.mark.parametrize("B,Ls,Lt", [(5, 32, 24), (130, 40, 48)])
+def test_pair_lengths_on_the_device_that_are_not_the_host_s(B, Ls, Lt):
+    model = dict(n_enc=2, n_dec=2, hidden=128, n_heads=2, ffn=256, vocab=500, max_pos=160)
+    wk = PairWorker(model, "bf16", synth.init_params(hs.hs_s2s_param_layout(hs.make_s2s_cfg(**model)), 83))
+    sl, tl = [max(1, Ls - 3 * (b % 6)) for b in range(B)], [max(1, Lt - 2 * (b % 7)) for b in range(B)]
+    d = wk.upload(synth.make_pair_batch(synth.rng_for(84), sl, tl, Ls, Lt, 500, "uniform"))
+    kept = with_guards(wk, "_acts", "_ws", "_out", "_dout")
+    wk.forward_backward(d, wk.G, 0, 0)
+    torch.cuda.synchronize()
+    want = wk.G.clone()
+    assert bool(torch.isfinite(want).all())
+    for side, L in (("src_lens", Ls), ("tgt_lens", Lt)):
+        right = d[side].clone()
+        for wrong in (torch.full_like(right, L), torch.ones_like(right), right.clamp(max=L // 2)):
+            d[side].copy_(wrong)
+            wk.G.zero_()
+            wk.forward_backward(d, wk.G, 0, 0)
+            torch.cuda.synchronize()
+            assert kept() and bool(torch.isnan(wk.G).any())
+        d[side].copy_(right)
+    wk.forward_backward(d, wk.G, 0, 0)
+    torch.cuda.synchronize()
+    assert kept() and torch.equal(wk.G, want)
+    wk.close()
