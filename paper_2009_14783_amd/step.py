@@ -68,7 +68,8 @@ class Worker:
             self._dhidden = torch.empty(n, dtype=self.act_dtype, device=self.device)
 
     def upload(self, mb: dict) -> dict:
-        """Host micro-batch (numpy) -> device tensors; done before the timed region."""
+        """Host micro-batch (numpy) -> device tensors; done before the timed region.  `lens_host` belongs to `lens`: in bf16 it sizes the passes
+        over this batch, so who refills `lens` on the device refills it too, or sets it to None (padded rows)."""
         dev = self.device
         out = dict(B=int(mb["ids"].shape[0]), L=int(mb["ids"].shape[1]), M=int(mb["mlm_pos"].size),
                    lens_host=np.ascontiguousarray(mb["lens"], dtype=np.int32),
@@ -77,6 +78,10 @@ class Worker:
                    mlm_pos=torch.from_numpy(np.ascontiguousarray(mb["mlm_pos"], dtype=np.int32)).to(dev),
                    mlm_label=torch.from_numpy(np.ascontiguousarray(mb["mlm_label"], dtype=np.int32)).to(dev),
                    n_seq=int(mb["ids"].shape[0]), drop=mb.get("drop"))
+        # lengths that hs_encoder_fwd refuses, and targets at positions of the padding, which packed rows do not have, are left to the padded passes
+        lens, pos, L = out["lens_host"], np.asarray(mb["mlm_pos"]).reshape(-1), out["L"]
+        out["packable"] = bool(lens.size > 0 and lens.min() >= 1 and lens.max() <= L and
+                               (pos.size == 0 or (pos.min() >= 0 and pos.max() < lens.size * L and (pos % L < lens[pos // L]).all())))
         self._reserve(out["B"], out["L"], out["M"])
         return out
 
@@ -90,7 +95,7 @@ class Worker:
             self._drop_on = drop is not None
         w = self.w_compute
         # A captured pass reads the lengths from the device when it is replayed: it keeps the padded rows.
-        packed = B > 0 and d["lens_host"] is not None and self.compute == hs.HS_BF16 and not torch.cuda.is_current_stream_capturing()
+        packed = d.get("packable", False) and d["lens_host"] is not None and self.compute == hs.HS_BF16 and not torch.cuda.is_current_stream_capturing()
         if packed:
             hs.hs_set_lengths(self.ctx, d["lens_host"], B, L)
         try:
@@ -270,7 +275,8 @@ class PairWorker:
                    src_lens_host=np.ascontiguousarray(mb["src_lens"], dtype=np.int32),
                    tgt_lens_host=np.ascontiguousarray(mb["tgt_lens"], dtype=np.int32), n_seq=int(mb["src"].shape[0]),
                    n_tok=int(np.asarray(mb["tgt_lens"]).sum()), drop=mb.get("drop"))
-        # lengths that the padded passes clamp (a source of length 0) are left to them
+        # lengths that the padded passes clamp (a source of length 0) are left to them.  The lengths on the host belong to those on the device: in bf16
+        # they size the passes, so who refills the device's refills them too, or sets them to None (padded rows)
         out["packable"] = all(n.size > 0 and n.min() >= 1 and n.max() <= L for n, L in ((out["src_lens_host"], out["Ls"]), (out["tgt_lens_host"], out["Lt"])))
         self._reserve(out["B"], out["Ls"], out["Lt"])
         return out
@@ -284,7 +290,8 @@ class PairWorker:
             hs.hs_set_dropout(self.ctx, drop["p"] if drop else 0.0, drop["seed"] if drop else 0, drop["stream"] if drop else 0)
             self._drop_on = drop is not None
         w = self.w_compute
-        packed = d.get("packable", False) and d.get("tgt_lens_host") is not None and self.compute == hs.HS_BF16 and not torch.cuda.is_current_stream_capturing()
+        packed = (d.get("packable", False) and d.get("src_lens_host") is not None and d.get("tgt_lens_host") is not None and
+                  self.compute == hs.HS_BF16 and not torch.cuda.is_current_stream_capturing())
         if packed:
             hs.hs_s2s_set_lengths(self.ctx, d["src_lens_host"], d["tgt_lens_host"], B, Ls, Lt)
         try:

@@ -206,3 +206,34 @@ def test_pair_lengths_on_the_device_that_are_not_the_host_s(B, Ls, Lt):
     torch.cuda.synchronize()
     assert kept() and torch.equal(wk.G, want)
     wk.close()
+
+
+@pytest.mark.parametrize("compute", ["bf16", "fp32"])
+def test_targets_in_the_padding_keep_the_padded_rows(compute):
+    """A target at a padded position has a hidden state and a gradient in the padded passes; packed rows have none."""
+    model = dict(n_layers=2, hidden=128, n_heads=2, ffn=256, vocab=200, max_pos=64, ln_eps=1e-12)
+    wk = Worker(model, compute, synth.init_params(hs.hs_param_layout(hs.make_cfg(**model)), 85))
+    mb = synth.make_micro_batch(synth.rng_for(86), [64, 9, 30], 64, 200, "uniform")
+    mb["mlm_pos"] = np.array([3, 64 + 8, 64 + 9, 64 + 40, 128 + 29], np.int32)      # the third and the fourth are padding
+    mb["mlm_label"] = np.arange(5, dtype=np.int32)
+    d = wk.upload(mb)
+    out = []
+    for use in (dict(d, lens_host=None), d):
+        wk.G.fill_(float("nan"))
+        wk.forward_backward(use, wk.G, 0, 0)
+        torch.cuda.synchronize()
+        out.append((wk.loss_buf[:1].clone(), wk.G.clone()))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1]) and bool(torch.isfinite(out[0][1]).all())
+    wk.close()
+
+
+def test_packable_batches():
+    model = dict(n_layers=1, hidden=128, n_heads=2, ffn=256, vocab=200, max_pos=64, ln_eps=1e-12)
+    wk = Worker(model, "bf16", synth.init_params(hs.hs_param_layout(hs.make_cfg(**model)), 87))
+    def packable(lens, pos):
+        mb = dict(ids=np.ones((len(lens), 16), np.int32), lens=np.array(lens, np.int32), mlm_pos=np.array(pos, np.int32), mlm_label=np.zeros(len(pos), np.int32))
+        return wk.upload(mb)["packable"]
+    assert packable([16, 5], [0, 15, 16, 20]) and packable([1, 1], []) and packable([1, 1], [0, 16])
+    assert not packable([16, 5], [0, 21]) and not packable([16, 5], [32]) and not packable([16, 5], [-1]) and not packable([0, 5], [16]) and not packable([17, 5], [0])
+    assert not packable([], [])
+    wk.close()
