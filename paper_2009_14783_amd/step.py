@@ -308,11 +308,12 @@ class PairWorker:
             if packed:
                 hs.hs_s2s_set_lengths(self.ctx, None, None)
 
-    def train_step(self, batches: list, adam: dict, denom=None, update_in_backward: bool = False):
+    def train_step(self, batches: list, adam: dict, denom=None, update_in_backward=None):
         """One optimizer step over the uploaded micro-batches (None = a pass without data).  Returns the weight D used
-        (the number of real target tokens by default).  update_in_backward: normalisation and Adam are armed for the last
+        (the number of real target tokens by default).  update_in_backward True: normalisation and Adam are armed for the last
         micro-batch's backward pass, which applies them layer by layer as soon as a layer's gradient is final (same
-        arithmetic, same bits as the separate call).  Without it that is so from 4 M parameters on: below, the launches per layer
+        arithmetic, same bits as the separate call).  False: the separate call behind the pass, so that a backward pass that fails leaves the
+        weights as they were.  None (default): armed from 4 M parameters on: below, the launches per layer
         cost more than the one update behind the pass (toy model 0.602 -> 0.610 ms per step); above, the update of 0.43 ms runs beside
         the pass (ms per step of the base model: 320 rows per side 2.15 -> 1.96, 4096 4.18 -> 4.08, 8064 6.71 -> 6.65)."""
         assert len(batches) <= 64
@@ -320,7 +321,7 @@ class PairWorker:
         real = [i for i, d in enumerate(batches) if d is not None]
         D = float(denom if denom is not None else max(sum(batches[i]["n_tok"] for i in real), 1))
         self.t += 1
-        first, in_backward = True, update_in_backward or self.P >= 4 << 20
+        first, in_backward = True, self.P >= 4 << 20 if update_in_backward is None else update_in_backward
         arm = lambda: hs.hs_arm_update(self.ctx, self.w, self.m, self.v, self.G, self.w_lowp, D, adam["lr"], adam["beta1"], adam["beta2"],
                                        adam["eps"], adam.get("weight_decay", 0.0), self.t)
         for i, d in enumerate(batches):

@@ -237,3 +237,23 @@ def test_packable_batches():
     assert not packable([16, 5], [0, 21]) and not packable([16, 5], [32]) and not packable([16, 5], [-1]) and not packable([0, 5], [16]) and not packable([17, 5], [0])
     assert not packable([], [])
     wk.close()
+
+
+@pytest.mark.parametrize("vocab,by_size", [(33001, True), (500, False)])
+def test_pair_step_has_the_form_that_it_was_asked_for(monkeypatch, vocab, by_size):
+    """update_in_backward: True and False force the form at any size, None goes by it; the same bits in every form."""
+    model = dict(n_enc=1, n_dec=1, hidden=128, n_heads=2, ffn=256, vocab=vocab, max_pos=64)
+    theta = synth.init_params(hs.hs_s2s_param_layout(hs.make_s2s_cfg(**model)), 88)
+    mb = synth.make_pair_batch(synth.rng_for(89), [16, 9], [24, 5], 16, 24, vocab, "zipf")
+    arm, armed, out = hs.hs_arm_update, [], []
+    monkeypatch.setattr(hs, "hs_arm_update", lambda *a: (armed.append(1), arm(*a)))
+    for form, want in ((True, True), (False, False), (None, by_size)):
+        wk = PairWorker(model, "bf16", theta)
+        armed.clear()
+        wk.train_step([wk.upload(mb)], dict(lr=1e-3, beta1=0.9, beta2=0.98, eps=1e-9), update_in_backward=form)
+        torch.cuda.synchronize()
+        assert bool(armed) == want
+        out.append((wk.w.clone(), wk.m.clone(), wk.v.clone(), wk.G.clone(), wk.w_lowp.clone()))
+        wk.close()
+    for other in out[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(out[0], other))
