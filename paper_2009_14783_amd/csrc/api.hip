@@ -462,7 +462,7 @@ static hs_status encoder_bwd_impl(hs_ctx* ctx, const hs_ctx::Armed& upd, const v
     // the products first: in front of them the column sums (4 us) wait until the chain leaves them room (28 us with 8192 rows, 92 with 16384 of
     // 1024 columns), and the products with them; BERT-base with 8192 rows 7.29 -> 7.16 ms per step, BERT-large with 16384 145.2 -> 144.0
     HS_TRY(launch_gemm_group(ctx, dw.data(), (int)dw.size(), sd));
-    HS_TRY(launch_layernorm_bwd_cols_batch(ctx, cols.data(), (int)cols.size(), beta, T, H, sd));
+    HS_TRY(launch_layernorm_bwd_cols_batch(ctx, dt, cols.data(), (int)cols.size(), beta, T, H, sd));
     cols.clear(); dw.clear();
     return HS_OK;
   };
@@ -621,7 +621,7 @@ hs_status hs_op_layernorm_bwd(int32_t dtype, const void* dy, const void* x, cons
 // instead of a caller buffer.  Each GPU holds its own copy at its own address, resolved once per device.
 namespace {
 constexpr int kNoAllocMaxRows = 1 << 24, kNoAllocMaxH = 1024;
-constexpr size_t kNoAllocFloats = (size_t)768 * 3 * kNoAllocMaxH;      // the row kernel writes at most 512 blocks x 3 x H
+constexpr size_t kNoAllocFloats = (size_t)768 * 3 * kNoAllocMaxH;      // the row kernel writes at most 768 blocks x 3 x H
 static __device__ __align__(256) float scratch[kNoAllocFloats];        // 9 MiB per GPU, held until the process ends
 constexpr int kMaxDevices = 64;
 float* scratch_ptr[kMaxDevices] = {};                                    // device address of `scratch`, per device

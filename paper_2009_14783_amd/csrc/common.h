@@ -301,11 +301,11 @@ hs_status launch_layernorm_bwd(hs_ctx* ctx, int dtype, const void* dy, const voi
 hs_status launch_layernorm_bwd_rows(hs_ctx* ctx, int dtype, const void* dy, const void* x, const float* stats, const void* gain, void* dx,
                                     int R, int H, void* partials, hipStream_t s, const DropCfg* drop = nullptr, uint32_t site = 0,
                                     int drop_mode = 0, void* dxm = nullptr, const int32_t* pad_row = nullptr, int dy_rows = 0);
-hs_status launch_layernorm_bwd_cols(hs_ctx* ctx, const void* partials, float* d_gain, float* d_bias, float* d_colsum, float beta, int R, int H,
+hs_status launch_layernorm_bwd_cols(hs_ctx* ctx, int dtype, const void* partials, float* d_gain, float* d_bias, float* d_colsum, float beta, int R, int H,
                                     hipStream_t s);
 struct LnColsJob { const void* partials; float *d_gain, *d_bias, *d_colsum; };      // what launch_layernorm_bwd_cols is given
 constexpr int kLnColsMax = 48;
-hs_status launch_layernorm_bwd_cols_batch(hs_ctx* ctx, const LnColsJob* jobs, int n, float beta, int R, int H, hipStream_t s);
+hs_status launch_layernorm_bwd_cols_batch(hs_ctx* ctx, int dtype, const LnColsJob* jobs, int n, float beta, int R, int H, hipStream_t s);
 hs_status launch_embed_ln_fwd(hs_ctx* ctx, int dtype, const void* word, const void* pos, const void* gain, const void* bias,
                               const int32_t* ids, void* e_pre, void* x0, float* stats, int B, int L, int H, int V, float eps,
                               hipStream_t s, const DropCfg* drop = nullptr, int stat_ld = 0, const PackedPart* pk = nullptr);

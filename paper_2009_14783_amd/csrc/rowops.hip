@@ -155,10 +155,12 @@ __global__ __launch_bounds__(256) void embed_ln_fwd_kernel(const T* __restrict__
 // ------------------------------------------------------------------------------------------
 // NC: 256-column slots per row that the registers hold (hidden <= 256 NC); EXACT: hidden == 256 NC, no slot is partly used.  NW: waves of a block.
 // A wave holds two rows as they lie in memory (the one it works on and the next one, requested before the reductions of the first) and
-// converts them where they are used: 128 registers with every sum, so that 16 waves share a CU at any width.  Blocks of eight waves with many rows: half as
-// many partial sums to write and to add up as with four.  Rows and column sums, us, against four waves and rows held in fp32 (which spilled 5 to 20
-// registers from 768 columns on): 8192 x 768 16.5 -> 14.0 (38 MB), 16384 x 768 25.9 -> 21.9, 8192 x 512 14.8 -> 11.7, 16384 x 1024 27.6 -> 26.5, 8192 x 1024 18.0 -> 19.0;
-// fp32 8192 x 768 26.4 -> 22.2; the BERT-base step of 64 x 128 7.23 -> 7.12 ms, with dropout 7.86 -> 7.66.
+// converts them where they are used: at most 128 registers with every sum, so that 16 waves share a CU, in bf16 at any width and in fp32 up to 768
+// columns; beyond, fp32 takes 151 to 168 (12 waves per CU; 192 where the output is dropped).  Spilled to fit: at 1024 columns in bf16 4 with a dropped branch and 29 with a
+// dropped output (one launch of a pass), at 768 in fp32 6 and 24, else none.  Blocks of eight waves with many rows: half as many partial sums to
+// write and to add up as with four; ln_bwd_waves says where not.  Rows and column sums, us, against four waves and rows held in fp32 (which spilled 5 to 20
+// registers from 768 columns on): 8192 x 768 16.9 -> 13.4 (38 MB), 16384 x 768 25.8 -> 21.0, 8192 x 512 14.5 -> 11.1, 16384 x 1024 27.4 -> 26.2, 8192 x 1024 17.7 -> 17.7;
+// fp32 8192 x 768 26.2 -> 21.2; the BERT-base step of 64 x 128 7.23 -> 7.12 ms, with dropout 7.86 -> 7.66.
 template <class T, int drop_mode, int NC, bool EXACT, int NW>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(sizeof(T) * NC <= 12 ? 4 : 2, 4))) void ln_bwd_kernel(const T* __restrict__ dy, const T* __restrict__ x, const float* __restrict__ stats,
                                                      const T* __restrict__ gain, T* __restrict__ dx, float* __restrict__ partials,
@@ -712,20 +714,32 @@ hs_status launch_layernorm_fwd_unpack(hs_ctx* ctx, int dtype, const void* x, con
 
 // Blocks of ln_bwd_kernel.  With few rows (up to a block per CU) blocks of four waves with a row each; beyond, of eight waves with two rows each, both in
 // flight at once, up to the two blocks per CU that are resident together (BERT-base, 264 and 176 rows, one row per wave instead of two: 4.23 -> 4.13 ms per
-// step).  Never fewer blocks for more rows, so that the scratch does not shrink as a batch grows.
+// step).  In fp32 a wave takes 151 registers and more beyond 768 columns, which leaves twelve to a CU, and a block of eight has four of their places idle: blocks
+// of four, but for whole 1024 columns from 8192 rows on, where rows are level and the sums of fewer blocks are faster.  Rows alone, eight -> four waves, us:
+// 5000 x 1024 18.1 -> 16.6, 7000 x 1024 21.2 -> 20.4, 8192 x 1024 23.5, 23.6 (with the column sums 27.2, 28.3), 6000 x 832 17.4 -> 15.5, 8192 x 832 20.9 -> 19.5,
+// 4096 x 832 9.9, 9.9.  In bf16 six thousand rows of 1024 columns are faster in blocks of four as well (11.5 -> 10.4), but not the step they are in, which adds up
+// their sums: BERT-large with 12 x 512 positions 17.31 -> 17.38 ms.
 constexpr int kLnBwdFewRows = 1024;
-static int ln_bwd_blocks(int R) {
+static int ln_bwd_waves(int dtype, int R, int H) {
+  return R <= kLnBwdFewRows || (dtype != HS_BF16 && H > 768 && R > 4096 && (R < 8192 || H < 1024)) ? 4 : 8;
+}
+static int ln_bwd_blocks(int dtype, int R, int H) {
   if (R <= kLnBwdFewRows) return std::max((R + 3) / 4, 1);
+  if (ln_bwd_waves(dtype, R, H) == 4) return std::min((R + 7) / 8, 768);
   return std::min(std::max((R + 15) / 16, 256), 512);
 }
-size_t layernorm_bwd_scratch(int R, int H) { return align_up((size_t)ln_bwd_blocks(R) * 3 * H * sizeof(float), 256); }
+// room for the most blocks of either type and any number of rows up to R, so that the scratch does not shrink as a batch grows
+size_t layernorm_bwd_scratch(int R, int H) {
+  const int blocks = H > 768 && R > 4096 ? std::min((R + 7) / 8, 768) : ln_bwd_blocks(HS_BF16, R, H);
+  return align_up((size_t)blocks * 3 * H * sizeof(float), 256);
+}
 
 // main kernel: dx and the per-block partial column sums
 hs_status launch_layernorm_bwd_rows(hs_ctx* ctx, int dtype, const void* dy, const void* x, const float* stats, const void* gain, void* dx,
                                     int R, int H, void* partials, hipStream_t s, const DropCfg* drop, uint32_t site, int drop_mode,
                                     void* dxm, const int32_t* pad_row, int dy_rows) {
   if (R <= 0) return HS_OK;
-  const int nb = ln_bwd_blocks(R);
+  const int nb = ln_bwd_blocks(dtype, R, H), waves = ln_bwd_waves(dtype, R, H);
   KScope scope(prof_of(ctx), KC_LN_BWD, 14.0 * R * H, 3.0 * R * H * esize(dtype), s);
   DropCfg d{0u, 1.0f, 0u, 0u, 0u};
   if (drop && drop->thr && drop_mode) d = *drop; else drop_mode = 0;
@@ -735,7 +749,7 @@ hs_status launch_layernorm_bwd_rows(hs_ctx* ctx, int dtype, const void* dy, cons
 #define HS_LN_BWD5(TT, MODE, NC, EX, NW) hipLaunchKernelGGL((ln_bwd_kernel<TT, MODE, NC, EX, NW>), dim3(nb), dim3(64 * NW), 0, s, (const TT*)dy, \
                                                            (const TT*)x, stats, (const TT*)gain, (TT*)dx, (float*)partials, R, H, d, site, (TT*)dxm, \
                                                            pad_row, pad_row ? dy_rows : 0)
-#define HS_LN_BWD4(TT, MODE, NC, EX) do { if (R <= kLnBwdFewRows) HS_LN_BWD5(TT, MODE, NC, EX, 4); else HS_LN_BWD5(TT, MODE, NC, EX, 8); } while (0)
+#define HS_LN_BWD4(TT, MODE, NC, EX) do { if (waves == 4) HS_LN_BWD5(TT, MODE, NC, EX, 4); else HS_LN_BWD5(TT, MODE, NC, EX, 8); } while (0)
 #define HS_LN_BWD3(TT, MODE, NC) do { if (exact) HS_LN_BWD4(TT, MODE, NC, true); else HS_LN_BWD4(TT, MODE, NC, false); } while (0)
 #define HS_LN_BWD(TT, MODE) do { if (nc == 2) HS_LN_BWD3(TT, MODE, 2); else if (nc == 3) HS_LN_BWD3(TT, MODE, 3); else HS_LN_BWD3(TT, MODE, 4); } while (0)
   if (dtype == HS_BF16) { if (drop_mode == 0) HS_LN_BWD(bf16, 0); else if (drop_mode == 1) HS_LN_BWD(bf16, 1); else HS_LN_BWD(bf16, 2); }
@@ -748,23 +762,23 @@ hs_status launch_layernorm_bwd_rows(hs_ctx* ctx, int dtype, const void* dy, cons
   return HS_OK;
 }
 // fixed-order sum of the partials into the three gradient vectors (may run on another stream)
-hs_status launch_layernorm_bwd_cols(hs_ctx* ctx, const void* partials, float* d_gain, float* d_bias, float* d_colsum, float beta, int R, int H,
+hs_status launch_layernorm_bwd_cols(hs_ctx* ctx, int dtype, const void* partials, float* d_gain, float* d_bias, float* d_colsum, float beta, int R, int H,
                                     hipStream_t s) {
   if (R <= 0 || !(d_gain || d_bias || d_colsum)) return HS_OK;
   KScope scope(prof_of(ctx), KC_LN_BWD, 0.0, 0.0, s);
-  hipLaunchKernelGGL(sum_partials_kernel, dim3((H + 63) / 64, 3), dim3(64 * SP_WAVES), 0, s, (const float*)partials, ln_bwd_blocks(R), (int64_t)3 * H,
+  hipLaunchKernelGGL(sum_partials_kernel, dim3((H + 63) / 64, 3), dim3(64 * SP_WAVES), 0, s, (const float*)partials, ln_bwd_blocks(dtype, R, H), (int64_t)3 * H,
                      (int64_t)H, H, d_gain, d_bias, d_colsum, beta);
   LAUNCH_CHECK(ctx, "layernorm_bwd finalize");
   return HS_OK;
 }
 // the same for several layers of the same shape
-hs_status launch_layernorm_bwd_cols_batch(hs_ctx* ctx, const LnColsJob* jobs, int n, float beta, int R, int H, hipStream_t s) {
+hs_status launch_layernorm_bwd_cols_batch(hs_ctx* ctx, int dtype, const LnColsJob* jobs, int n, float beta, int R, int H, hipStream_t s) {
   for (int done = 0; R > 0 && done < n; done += kLnColsMax) {
     LnColsTable t;
     const int m = std::min(n - done, kLnColsMax);
     for (int i = 0; i < m; ++i) t.job[i] = jobs[done + i];
     KScope scope(prof_of(ctx), KC_LN_BWD, 0.0, 0.0, s);
-    hipLaunchKernelGGL(ln_cols_kernel, dim3((H + 63) / 64, 3, m), dim3(64 * SP_WAVES), 0, s, t, ln_bwd_blocks(R), H, beta);
+    hipLaunchKernelGGL(ln_cols_kernel, dim3((H + 63) / 64, 3, m), dim3(64 * SP_WAVES), 0, s, t, ln_bwd_blocks(dtype, R, H), H, beta);
     LAUNCH_CHECK(ctx, "layernorm_bwd finalize");
   }
   return HS_OK;
@@ -774,7 +788,7 @@ hs_status launch_layernorm_bwd(hs_ctx* ctx, int dtype, const void* dy, const voi
                                const DropCfg* drop, uint32_t site, int drop_mode, void* dxm, const int32_t* pad_row) {
   hs_status st = launch_layernorm_bwd_rows(ctx, dtype, dy, x, stats, gain, dx, R, H, partials, s, drop, site, drop_mode, dxm, pad_row);
   if (st != HS_OK) return st;
-  return launch_layernorm_bwd_cols(ctx, partials, d_gain, d_bias, d_colsum, beta, R, H, s);
+  return launch_layernorm_bwd_cols(ctx, dtype, partials, d_gain, d_bias, d_colsum, beta, R, H, s);
 }
 
 hs_status launch_embed_ln_fwd(hs_ctx* ctx, int dtype, const void* word, const void* pos, const void* gain, const void* bias,

@@ -559,8 +559,8 @@ hs_status hs_s2s_bwd(hs_ctx* ctx, const void* w, const void* acts, const int32_t
   auto enqueue_grads = [&](int64_t begin, int64_t end) -> hs_status {
     HS_TRY(order(s, sd));
     // (the products first, as in the encoder-only model, are level to 0.5 % slower here: 128 x 32 x 32 4.280 -> 4.300 ms per step, 24 x 168 x 176 4.447 -> 4.458)
-    HS_TRY(launch_layernorm_bwd_cols_batch(ctx, cols_tgt.data(), (int)cols_tgt.size(), beta, Tt, H, sd));
-    HS_TRY(launch_layernorm_bwd_cols_batch(ctx, cols_src.data(), (int)cols_src.size(), beta, Ts, H, sd));
+    HS_TRY(launch_layernorm_bwd_cols_batch(ctx, dt, cols_tgt.data(), (int)cols_tgt.size(), beta, Tt, H, sd));
+    HS_TRY(launch_layernorm_bwd_cols_batch(ctx, dt, cols_src.data(), (int)cols_src.size(), beta, Ts, H, sd));
     HS_TRY(launch_gemm_group(ctx, dw.data(), (int)dw.size(), sd));
     dw.clear(); cols_tgt.clear(); cols_src.clear();
     const bool last = begin == o.enc[0].qkv_w;      // behind them only the source embedding's gradient is left

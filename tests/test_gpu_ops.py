@@ -450,6 +450,13 @@ def test_layernorm_fwd_bwd(hs, mode, R, H):
     assert rel(host(gb), wdb) < 1e-5
 
 
+# both sides of each line in the rule of the backward kernel's blocks: four waves, eight, and beyond 768 columns four again
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("R,H", [(1024, 896), (1025, 896), (4096, 1024), (4097, 1024), (4097, 832), (4097, 768), (8191, 1024), (8192, 1024), (8200, 832)])
+def test_layernorm_bwd_blocks(hs, mode, R, H):
+    test_layernorm_fwd_bwd(hs, mode, R, H)
+
+
 def attention_reference(qkv, lens, B, L, A):
     H = A * 64
     q, k, v = (qkv[:, j * H:(j + 1) * H].reshape(B, L, A, 64).transpose(0, 2, 1, 3) for j in range(3))

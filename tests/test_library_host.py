@@ -166,3 +166,11 @@ def test_lengths_of_another_batch_are_refused():
     assert e.value.status == 4
     hs.hs_s2s_set_lengths(ctx, None, None)
     hs.hs_ctx_destroy(ctx)
+
+
+@pytest.mark.parametrize("H", [128, 768, 832, 1024])
+def test_layernorm_scratch_never_falls(H):
+    """A scratch buffer for the most rows of a program serves every smaller number of them."""
+    rows = sorted(set(range(1, 20000, 37)) | {1023, 1024, 1025, 4095, 4096, 4097, 6144, 8191, 8192, 8193, 1 << 17})
+    sizes = [hs.hs_op_layernorm_bwd_scratch(R, H) for R in rows]
+    assert all(a <= b for a, b in zip(sizes, sizes[1:]))
