@@ -94,7 +94,8 @@ def test_two_layer_bf16_short_sequences_fused_backward():
 
 @pytest.mark.parametrize("L,B", [(128, 66), (72, 67)])
 def test_two_layer_bf16_more_than_256_heads_in_one_block_each(L, B):
-    """264 and 268 (sequence, head) pairs: the short backward pass does both halves of a pair in one block (up to 256 it takes two)."""
+    """264 and 268 (sequence, head) pairs of four waves: the short backward pass does both halves of a pair in one block (up to 960 waves, 240 of
+    these pairs, it takes two)."""
     model = dict(n_layers=2, hidden=256, n_heads=4, ffn=512, vocab=2000, max_pos=128, ln_eps=1e-12)
     run_case(model, "bf16", [max(1, L - 3 * (i % 40)) for i in range(B)], L, dict(p=0.1, seed=101, stream=4), 17, 2e-2)
 
@@ -114,6 +115,15 @@ def test_large_batch_runs_as_two_halves_with_the_masks_of_the_whole_batch():
     from its offset in the whole batch; the oracle knows nothing of halves."""
     lens = [int(x) for x in synth.draw_lengths(synth.rng_for(40), 64, 5, 64)]
     run_case(synth.MODELS["tiny"], "fp32", lens, 64, dict(p=0.1, seed=77, stream=4), 16, 1e-4)
+
+
+def test_two_halves_over_real_rows_with_the_masks_of_the_padded_batch():
+    """The same in bf16, where the halves have a row per real position (4334 of 4608), cut at the 32nd of 64 sequences or later: the oracle numbers
+    the elements of the padded batch."""
+    lens = [72 - (b * b) // 310 for b in range(64)]
+    assert 4096 <= sum(lens) < 64 * 72
+    model = dict(n_layers=2, hidden=128, n_heads=2, ffn=256, vocab=1000, max_pos=128, ln_eps=1e-12)
+    run_case(model, "bf16", lens, 72, dict(p=0.1, seed=78, stream=4), 19, 2e-2)
 
 
 def test_whole_batch_of_one_wide_tile_per_cu():

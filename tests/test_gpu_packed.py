@@ -257,3 +257,99 @@ def test_pair_step_has_the_form_that_it_was_asked_for(monkeypatch, vocab, by_siz
         wk.close()
     for other in out[1:]:
         assert all(torch.equal(a, b) for a, b in zip(out[0], other))
+
+
+# a pass over 4096 real rows and more runs as two halves, whose cut (19 of 40) is not the middle sequence: masks numbered from the second half's first
+# sequence in the attention, by position in the products and the embedding
+@pytest.mark.parametrize("hidden,B,L,step", [(512, 40, 200, 40), (256, 70, 96, 150)])
+def test_encoder_halves_over_real_rows_with_dropout(hidden, B, L, step):
+    lens = [max(1, L - (b * b) // step) for b in range(B)]
+    assert 4096 <= sum(lens) < B * L
+    first = np.concatenate([[0], np.cumsum(lens)])
+    assert int(np.argmin(abs(2 * first - first[-1]))) != B // 2
+    test_encoder_pass_over_real_rows(hidden, B, L, lens, 0.1)
+
+
+def replays_equal_eager(step, state, refill, eager, n=4):
+    """Captures step(); every replay, with state restored and refill(k) in front, must leave what eager(k) leaves."""
+    saved = [t.clone() for t in state]
+    step()                                             # streams, events and tables that the first call makes
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        step()
+    for k in range(n):
+        for t, s in zip(state, saved):
+            t.copy_(s)
+        refill(k)
+        graph.replay()
+        torch.cuda.synchronize()
+        got = [t.clone() for t in state]
+        for a, b in zip(got, eager(k)):
+            assert bool(torch.isfinite(a).all()) and torch.equal(a, b), k
+
+
+STATE = ("w", "m", "v", "G", "w_lowp")
+
+
+@pytest.mark.parametrize("B,L", [(6, 64), (48, 128)])
+def test_captured_step_reads_the_lengths_of_its_replay(B, L):
+    """A captured step keeps the padded rows: its replays take ids and lengths that are on the device by then.  One part and two halves."""
+    model = dict(n_layers=2, hidden=128, n_heads=2, ffn=256, vocab=33001, max_pos=128, ln_eps=1e-12)
+    theta = synth.init_params(hs.hs_param_layout(hs.make_cfg(**model)), 90)
+    adam = dict(lr=1e-3, beta1=0.9, beta2=0.999, eps=1e-8)
+    batch = lambda k: dict(synth.make_micro_batch(synth.rng_for(91 + k), [max(1, L - (3 + k) * (b % 7)) for b in range(B)], L, 33001, "zipf"),
+                           mlm_pos=np.arange(B, dtype=np.int32) * L, mlm_label=np.arange(B, dtype=np.int32), drop=dict(p=0.1, seed=9, stream=3))
+    a, b = Worker(model, "bf16", theta), Worker(model, "bf16", theta)
+    d = a.upload(batch(0))
+    assert d["packable"]
+    def refill(k):
+        new = a.upload(batch(k))
+        for name in ("ids", "lens"):
+            d[name].copy_(new[name])
+    def step():
+        a.t = 0
+        a.train_step([d], adam)
+    def eager(k):
+        b.t = 0
+        for t, s in zip((b.w, b.m, b.v, b.w_lowp), first):
+            t.copy_(s)
+        b.train_step([dict(b.upload(batch(k)), lens_host=None)], adam)
+        torch.cuda.synchronize()
+        return [getattr(b, n) for n in STATE]
+    first = [b.w.clone(), b.m.clone(), b.v.clone(), b.w_lowp.clone()]
+    replays_equal_eager(step, [getattr(a, n) for n in STATE], refill, eager)
+    a.close(); b.close()
+
+
+# without the target lengths on the host every position goes through the projection, and replays may have others; with them the number of rows is captured
+@pytest.mark.parametrize("B,Ls,Lt", [(5, 24, 32), (130, 32, 40)])
+@pytest.mark.parametrize("host_lens", [False, True])
+def test_captured_pair_step_reads_the_lengths_of_its_replay(B, Ls, Lt, host_lens):
+    model = dict(n_enc=2, n_dec=2, hidden=128, n_heads=2, ffn=256, vocab=33001, max_pos=64)
+    theta = synth.init_params(hs.hs_s2s_param_layout(hs.make_s2s_cfg(**model)), 92)
+    adam = dict(lr=1e-3, beta1=0.9, beta2=0.98, eps=1e-9)
+    def batch(k):
+        sl, tl = [max(1, Ls - (2 + k) * (b % 5)) for b in range(B)], [max(1, Lt - (3 + (0 if host_lens else k)) * (b % 6)) for b in range(B)]
+        return dict(synth.make_pair_batch(synth.rng_for(93 + k), sl, tl, Ls, Lt, 33001, "zipf"), drop=dict(p=0.1, seed=8, stream=5))
+    keep = (lambda d: d) if host_lens else (lambda d: dict(d, tgt_lens_host=None))
+    a, b = PairWorker(model, "bf16", theta), PairWorker(model, "bf16", theta)
+    d = keep(a.upload(batch(0)))
+    assert d["packable"]
+    def refill(k):
+        new = a.upload(batch(k))
+        for name in ("src", "src_lens", "tgt_in", "tgt_out", "tgt_lens"):
+            d[name].copy_(new[name])
+    def step():
+        a.t = 0
+        a.train_step([d], adam, denom=1000)
+    def eager(k):
+        b.t = 0
+        for t, s in zip((b.w, b.m, b.v, b.w_lowp), first):
+            t.copy_(s)
+        b.train_step([dict(keep(b.upload(batch(k))), packable=False)], adam, denom=1000)
+        torch.cuda.synchronize()
+        return [getattr(b, n) for n in STATE]
+    first = [b.w.clone(), b.m.clone(), b.v.clone(), b.w_lowp.clone()]
+    replays_equal_eager(step, [getattr(a, n) for n in STATE], refill, eager)
+    a.close(); b.close()
