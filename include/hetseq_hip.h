@@ -107,7 +107,9 @@ size_t hs_workspace_bytes(const hs_model_cfg* cfg, int32_t B, int32_t L, int32_t
  * hs_encoder_bwd call on ctx whose gradient buffer g is G: that call then normalises and updates
  * every parameter group (head, each layer, embeddings) as soon as the group's gradient is final, on
  * streams of the context beside the rest of the backward pass (what is final last on the caller's), and
- * joins that work before it returns work to the caller's stream.  Arm it for the LAST micro-batch of an update only (denom is
+ * joins that work before it returns work to the caller's stream.  Of the word embedding the rows that no id of the batch names are
+ * final when the call starts and may be updated in front of the pass, the batch's rows come last: nothing else may read or write w, m, v,
+ * G or the copy from the time the call is enqueued until its work is done.  Arm it for the LAST micro-batch of an update only (denom is
  * the global sample count of the whole update); hs_mlm_loss of that micro-batch must already have been
  * enqueued on the same stream with the same G.  All pointers dev, sizes = hs_param_count; the
  * armed state is cleared by the backward call that consumes it (also when that call fails).
@@ -376,7 +378,7 @@ hs_status hs_s2s_loss(hs_ctx* ctx, const void* w, const void* dec_out, const int
 /* Backward through decoder and encoder down to the embedding.  Gradients of enc*. and dec*. go to g (overwritten when
  * accumulate == 0, added when 1); emb is ALWAYS added to (call hs_s2s_loss first).  An update armed with hs_arm_update is
  * consumed by this call as by hs_encoder_bwd: each layer's slice of the flat buffers is normalised and updated as soon as
- * its gradient is final, the shared embedding last. */
+ * its gradient is final; of the shared embedding the rows of the ids in src and tgt_in last, the others at any time from the start of the call on. */
 hs_status hs_s2s_bwd(hs_ctx* ctx, const void* w, const void* acts, const int32_t* src, const int32_t* src_lens, const int32_t* tgt_in,
                      const int32_t* tgt_lens, int32_t B, int32_t Ls, int32_t Lt, const void* d_dec_out, float* g, int32_t accumulate,
                      void* workspace, size_t workspace_bytes, void* stream);
