@@ -439,6 +439,13 @@ hs_status hs_op_gemm(int32_t dtype, int32_t a_kmajor, int32_t b_kmajor, int32_t 
  * other thread launches work.  HS_ERR_INVALID_ARG for numbers outside [-1, 11]. */
 hs_status hs_tune_gemm_variant(int32_t variant);
 
+/* Which tiling hs_op_gemm takes for a bf16 product with these arguments and so many bytes of scratch, and into how many parts it splits
+ * the contraction: 0 .. 11 as above, 12 and 13 the two for long contractions that only the automatic choice takes (128 x 128 by eight waves, 64 x 64
+ * with a ring of four stages).  a_padded: A k-major with rows that are zero from K up to the next multiple of 64, which the loss calls have.
+ * Host only, no GPU needed. */
+hs_status hs_gemm_choice(int32_t a_kmajor, int32_t b_kmajor, int32_t M, int32_t N, int32_t K, int32_t c_f32, int32_t epi,
+                         int32_t a_padded, size_t scratch_bytes, int32_t* variant, int32_t* splits);
+
 /* y = LN(x) over rows of length H; writes mean and reciprocal std per row (stats [2, R] float). */
 hs_status hs_op_layernorm_fwd(int32_t dtype, const void* x, const void* gain, const void* bias, void* y,
                               float* stats, int32_t R, int32_t H, float eps, void* stream);

@@ -91,6 +91,7 @@ _SIGNATURES = {
     "hs_fill_zero": (_I32, [_P, _SZ, _P]),
     "hs_weighted_loss": (_I32, [_P, _I32, _D, _P, _P]),
     "hs_tune_gemm_variant": (_I32, [_I32]),
+    "hs_gemm_choice": (_I32, [_I32, _I32, _I32, _I32, _I32, _I32, _I32, _I32, _SZ, C.POINTER(_I32), C.POINTER(_I32)]),
     "hs_op_gemm": (_I32, [_I32, _I32, _I32, _I32, _I32, _I32, _P, _I64, _P, _I64, _P, _I64, _I32, _F, _P, _I32, _P, _I64, _P, _P, _SZ, _P]),
     "hs_op_layernorm_fwd": (_I32, [_I32, _P, _P, _P, _P, _P, _I32, _I32, _F, _P]),
     "hs_op_layernorm_bwd_scratch": (_SZ, [_I32, _I32]),
@@ -374,6 +375,13 @@ def hs_op_gemm(dtype, a_kmajor, b_kmajor, M, N, K, A, lda, B, ldb, Cm, ldc, c_f3
                ldaux=0, C2=None, scratch=None, scratch_bytes=0, stream=None):
     _check(lib().hs_op_gemm(dtype, a_kmajor, b_kmajor, M, N, K, _ptr(A), lda, _ptr(B), ldb, _ptr(Cm), ldc, c_f32, beta,
                             _ptr(bias), epi, _ptr(aux), ldaux, _ptr(C2), _ptr(scratch), scratch_bytes, _stream(stream)))
+
+
+def hs_gemm_choice(a_kmajor, b_kmajor, M, N, K, c_f32=0, epi=0, a_padded=0, scratch_bytes=0):
+    """(tiling, number of splits) of a bf16 product."""
+    variant, splits = _I32(), _I32()
+    _check(lib().hs_gemm_choice(a_kmajor, b_kmajor, M, N, K, c_f32, epi, a_padded, scratch_bytes, C.byref(variant), C.byref(splits)))
+    return variant.value, splits.value
 
 
 def hs_tune_gemm_variant(variant: int):

@@ -585,6 +585,19 @@ hs_status hs_tune_gemm_variant(int32_t variant) {
   return HS_OK;
 }
 
+hs_status hs_gemm_choice(int32_t a_kmajor, int32_t b_kmajor, int32_t M, int32_t N, int32_t K, int32_t c_f32, int32_t epi, int32_t a_padded,
+                         size_t scratch_bytes, int32_t* variant, int32_t* splits) {
+  if (M < 1 || N < 1 || K < 1 || epi < 0 || epi > 3 || (!a_kmajor && b_kmajor) || !variant || !splits)
+    return hs_fail(nullptr, HS_ERR_INVALID_ARG, "hs_gemm_choice: bad argument");
+  GemmArgs g = gemm_args(HS_BF16, a_kmajor ? 1 : 0, b_kmajor ? 1 : 0, M, N, K, nullptr, 0, nullptr, 0, nullptr, 0);
+  g.c_f32 = c_f32 ? 1 : 0; g.epi = epi; g.a_kpad = a_padded ? 1 : 0;
+  g.ws = scratch_bytes ? (void*)splits : nullptr; g.ws_bytes = scratch_bytes;      // only asked whether there is one
+  int v, n;
+  gemm_choice(g, &v, &n);
+  *variant = v; *splits = n;
+  return HS_OK;
+}
+
 hs_status hs_op_gemm(int32_t dtype, int32_t a_kmajor, int32_t b_kmajor, int32_t M, int32_t N, int32_t K, const void* A, int64_t lda,
                      const void* B, int64_t ldb, void* C, int64_t ldc, int32_t c_f32, float beta, const void* bias, int32_t epi,
                      const void* aux, int64_t ldaux, void* C2, void* scratch, size_t scratch_bytes, void* stream) {

@@ -283,6 +283,7 @@ hs_status launch_gemm_group(hs_ctx* ctx, const GemmArgs* gs, int n, hipStream_t 
 // timing runs: every bf16 product with M, N, K >= 256 that configuration `variant` can serve uses it (-1: automatic choice); process-wide
 int gemm_variant_count();
 void gemm_set_variant(int variant);
+void gemm_choice(const GemmArgs& g, int* variant, int* splits);      // of a bf16 product; pointers are not followed
 
 // stats: R means, then (stat_ld floats after the first mean; default R) R reciprocal standard deviations
 hs_status launch_layernorm_fwd(hs_ctx* ctx, int dtype, const void* x, const void* gain, const void* bias, void* y,

@@ -434,7 +434,7 @@ static GemmDev gemm_dev_args(const GemmArgs& g) {
   return p;
 }
 
-int gemm_variant_count() { return 12; }      // 12 and 13 are left to the automatic choice
+int gemm_variant_count() { return 12; }      // 12 and 13 are left to the automatic choice (gemm_choice says where it takes them)
 void gemm_set_variant(int variant) { gemm_cfg_override = variant; }
 
 // whether the kernels other than gemm_bf16_mfma are built with the epilogue this product needs (see wide_epilogues in gemm_wide.h)
@@ -503,6 +503,8 @@ static void choose_cfg(const GemmArgs& g, int* cfg, int* splits) {
     }
   }
 }
+
+void gemm_choice(const GemmArgs& g, int* variant, int* splits) { choose_cfg(g, variant, splits); }
 
 // Weight-gradient products (A m-major, B n-major or null for a column of ones, fp32 C = beta C + product, one type and beta for all) in as
 // few launches of the grouped kernel as their number allows: no split-K, no partial sums in memory, one ramp-up and one tail.

@@ -127,8 +127,8 @@ def test_gemm_bf16_large_k_and_many_tiles(hs):
 
 @pytest.mark.parametrize("variant", [-1] + list(range(12)))
 def test_gemm_every_tiling_ragged_edges_and_epilogues(hs, variant):
-    """Every built tiling of the bf16 kernel (hs_tune_gemm_variant; -1: the automatic choice), each operand layout with the
-    epilogues it serves, on a product with several tiles per direction, ragged last tiles in M and N, and a contraction that
+    """Every tiling of the bf16 kernel that can be selected (hs_tune_gemm_variant; -1: the automatic choice, which alone takes the two tilings
+    of test_gemm_long_contractions), each operand layout with the epilogues it serves, on a product with several tiles per direction, ragged last tiles in M and N, and a contraction that
     is (1024) or is not (1000) a whole number of k-tiles."""
     rng = np.random.default_rng(100 + variant)
     M, N = 520, 392
@@ -403,6 +403,55 @@ def test_gemm_long_contractions(hs, M, N, K, bk):
     assert err(out, prod) < tol
     hs.hs_op_gemm(1, 1, bk, M, N, K, A, K, B, ldb, out, N)
     assert torch.equal(out, first)
+
+
+# the same tilings where the contraction is split: 128 x 128 in four and eight parts, whole and ragged tiles, either type of result
+@pytest.mark.parametrize("M,N,K,splits", [(1216, 512, 16384, 4), (400, 768, 30528, 8), (1209, 520, 16384, 4)])
+@pytest.mark.parametrize("bk", [1, 0])
+def test_gemm_long_contractions_in_parts(hs, M, N, K, splits, bk):
+    scratch = torch.full((96 << 20,), 0xFF, dtype=torch.uint8, device="cuda")      # NaN where a partial sum is not written
+    g = torch.Generator(device="cuda").manual_seed(M + bk)
+    mk = lambda *shape: torch.randn(*shape, generator=g, device="cuda").to(torch.bfloat16)
+    A, B, R = mk(M, K), mk(N, K) if bk else mk(K, N), mk(M, N)
+    prod = A.double() @ (B.double().T if bk else B.double())
+    err = lambda x, want: float((x.double() - want).norm() / want.norm())
+    for f32, epi in ((0, 0), (0, 1), (1, 0)) if bk else ((0, 0), (0, 1)):
+        assert hs.hs_gemm_choice(1, bk, M, N, K, f32, epi, 0, scratch.numel()) == (12, splits)
+        out = torch.empty(M, N, dtype=torch.float32 if f32 else torch.bfloat16, device="cuda")
+        hs.hs_op_gemm(1, 1, bk, M, N, K, A, K, B, K if bk else N, out, N, c_f32=f32, epi=epi, aux=R if epi else None, ldaux=N, scratch=scratch,
+                      scratch_bytes=scratch.numel())
+        # fp32: a chain of 4096 sums, each rounded by 2^-24 of the sum so far at most: 64 x 2^-24 = 4e-6 if they fall at random
+        assert err(out, prod + (R.double() if epi else 0)) < (1e-5 if f32 else 4e-3)
+
+
+# d logits E over a vocabulary that ends inside a k-tile: 128 x 128 in four parts with a contraction of 16362; half of the labels lie behind the last whole k-tile,
+# so that those columns carry half of the gradient
+@pytest.mark.parametrize("hidden,M", [(512, 1216), (768, 1209)])
+def test_masked_lm_gradient_over_a_ragged_vocabulary(hs, hidden, M):
+    V, B, L = 16362, 10, 128
+    model = dict(n_layers=1, hidden=hidden, n_heads=hidden // 64, ffn=512, vocab=V, max_pos=L, ln_eps=1e-12)
+    cfg = hs.make_cfg(**model, compute=hs.HS_BF16)
+    ctx, H = hs.hs_ctx_create(cfg), hidden
+    ws = torch.empty(hs.hs_workspace_bytes(cfg, B, L, M), dtype=torch.uint8, device="cuda")
+    assert hs.hs_gemm_choice(1, 0, M, H, V, 0, 0, 1, max(32 << 20, 8 * H * max(512, 3 * H) * 4)) == (12, 4)
+    g = torch.Generator(device="cuda").manual_seed(M)
+    w = (0.05 * torch.randn(hs.hs_param_count(cfg), generator=g, device="cuda")).to(torch.bfloat16)
+    hidden_in = torch.randn(B * L, H, generator=g, device="cuda").to(torch.bfloat16)
+    pos = torch.randperm(B * L, generator=g, device="cuda")[:M].sort().values.int()
+    label = torch.randint(0, V, (M,), generator=g, device="cuda", dtype=torch.int32)
+    label[::2] = torch.randint(V // 64 * 64, V, ((M + 1) // 2,), generator=g, device="cuda", dtype=torch.int32)
+    G, dh, loss = torch.zeros(w.numel(), device="cuda"), torch.empty_like(hidden_in), torch.zeros(1, device="cuda")
+    hs.hs_mlm_loss(ctx, w, hidden_in, pos, label, M, B, L, loss, dh, G, 0, ws, ws.numel())
+    torch.cuda.synchronize()
+    p = {name: w[off:off + r * c].double().view(r, c) if r > 1 and c > 1 else w[off:off + r * c].double() for name, off, r, c in hs.hs_param_layout(cfg)}
+    x = hidden_in.double().requires_grad_()
+    t = torch.nn.functional.gelu(x[pos.long()] @ p["head.t.w"].T + p["head.t.b"])
+    t = torch.nn.functional.layer_norm(t, (H,), p["head.ln.g"], p["head.ln.b"], 1e-12)
+    want = torch.nn.functional.cross_entropy(t @ p["emb.word"].T + p["head.dec.b"], label.long(), reduction="sum")
+    want.backward()
+    assert abs(float(loss) - want.item()) < 1e-3 * want.item()
+    assert float((dh.double() - x.grad).norm() / x.grad.norm()) < 2e-2
+    hs.hs_ctx_destroy(ctx)
 
 
 def test_gemm_variant_out_of_range_is_an_error(hs):

@@ -174,3 +174,20 @@ def test_layernorm_scratch_never_falls(H):
     rows = sorted(set(range(1, 20000, 37)) | {1023, 1024, 1025, 4095, 4096, 4097, 6144, 8191, 8192, 8193, 1 << 17})
     sizes = [hs.hs_op_layernorm_bwd_scratch(R, H) for R in rows]
     assert all(a <= b for a, b in zip(sizes, sizes[1:]))
+
+
+# the sizes of test_gemm_long_contractions, and where the two tilings must not be taken
+def test_choice_of_the_tilings_for_long_contractions():
+    for want, sizes in ((12, [(3072, 1024, 1536), (3001, 776, 1600), (5003, 520, 2048)]), (13, [(1024, 768, 1536), (905, 776, 1600), (521, 1288, 2048)])):
+        for M, N, K in sizes:
+            for b_kmajor, epi in ((1, 0), (1, 1), (1, 2), (0, 0), (0, 1), (0, 3)):
+                assert hs.hs_gemm_choice(1, b_kmajor, M, N, K, epi=epi) == (want, 1)
+    rng = np.random.default_rng(5)
+    for M, N, K in rng.integers(1, 20000, (300, 3)).tolist():
+        K = (K + 63) // 64 * 64
+        assert hs.hs_gemm_choice(0, 0, M, N, K, c_f32=1, scratch_bytes=96 << 20)[0] < 12      # A m-major
+        assert hs.hs_gemm_choice(1, K // 64 % 2, M, N, 64 + K % 1472)[0] < 12                 # contractions below 1536
+        assert hs.hs_gemm_choice(1, 1, M, N, K)[1] == 1                                       # without scratch there is one part
+    for bad in ((0, 1, 64, 64, 64), (1, 1, 0, 64, 64), (1, 1, 64, 64, 0)):
+        with pytest.raises(hs.HsError):
+            hs.hs_gemm_choice(*bad)
