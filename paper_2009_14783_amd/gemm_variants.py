@@ -11,7 +11,8 @@ contraction length, is served by the library's fallback kernel; the automatic ch
 forward pass and of the activation-gradient chain (the grouped weight-gradient launch keeps its own tiling).
 --large takes the products of a BERT-large layer instead (16384 tokens = 32 x 512, and `half`: the 8192 of a forward half-batch).
 --choice times the forward and activation-gradient products of widths 512, 768 and 1024 over 264 to 16384 rows with every tiling, operands
-rotating over eight copies, and prints what the automatic choice takes beside the fastest tiling.
+rotating over eight copies, and prints what the automatic choice takes beside the fastest tiling.  Tilings 12 and 13 cannot be selected: where the automatic choice
+takes one of them, its number and the fastest of the others stand beside its time.
 --cube times 8192 x 8192 x 8192 products in the three operand layouts instead (no epilogue; fp32 output for the m-major layout).
 --products keeps the named products only (for counter runs under a profiler).
 Prints Markdown.  Needs the GPU and the built library; no oracle, no CPU path.
@@ -102,7 +103,7 @@ def choice(iters):
 
     print("| width, product | " + " | ".join(f"{r} rows" for r in rows_of) + " |")
     print("|---|" + "---|" * len(rows_of))
-    ratios = []
+    ratios, lone = [], []      # lone: fastest other tiling over 12 or 13 where these are chosen
     for H in (512, 768, 1024):
         lists = [sum(layer_products(r, H, 4 * H), []) for r in rows_of]
         for j in range(len(lists[0])):
@@ -111,11 +112,18 @@ def choice(iters):
                 t = {v: us(products[j], v) for v in [-1] + list(range(12))}
                 best = min(range(12), key=lambda v: t[v])
                 ratios.append(t[-1] / min(t.values()))
-                cells.append(f"{t[-1]:.1f}" + (f" ({t[best]:.1f}: {best})" if t[best] < 0.98 * t[-1] else ""))
+                _, ak, bk, M, N, K, epi, _ = products[j]
+                hs.hs_tune_gemm_variant(-1)
+                took, _ = hs.hs_gemm_choice(ak, bk, M, N, K, epi=epi)
+                if took >= 12:
+                    lone.append(t[best] / t[-1])
+                cells.append(f"{t[-1]:.1f}" + (f" [{took}]" if took >= 12 else "") +
+                             (f" ({t[best]:.1f}: {best})" if t[best] < 0.98 * t[-1] or took >= 12 else ""))
             print(f"| {H}, {lists[0][j][0]} | " + " | ".join(cells) + " |", flush=True)
     hs.hs_tune_gemm_variant(-1)
-    print(f"\nus; in brackets the fastest tiling and its time where it is more than 2 % faster.  Automatic choice over fastest: mean "
-          f"{sum(ratios) / len(ratios):.3f}, largest {max(ratios):.2f} over {len(ratios)} products.")
+    print(f"\nus; in brackets the fastest tiling and its time where it is more than 2 % faster, and beside 12 and 13.  Automatic choice over fastest: mean "
+          f"{sum(ratios) / len(ratios):.3f}, largest {max(ratios):.2f} over {len(ratios)} products; fastest other tiling over 12 and 13 where these are taken: mean "
+          f"{sum(lone) / max(1, len(lone)):.3f} over {len(lone)}.")
 
 
 def main():
