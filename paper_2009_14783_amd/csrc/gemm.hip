@@ -370,8 +370,8 @@ static hipError_t gelu_table(int which, const float2** out) {
 // of a tile.  The constants (us) are fitted to launches on this chip: rows 264 .. 17472, the forward and activation-gradient products of
 // widths 512, 768 and 1024 with their epilogues, weights not in the cache of the launch before (2, 4 and 11, whose launches are shorter than
 // the host takes to enqueue them, to a fit over 32 .. 4104 rows, and their t0 raised together until the translation step at 4096 rows per side and BERT-base at 264
-// rows agreed).  Over 168 products of 264 to 16384 rows the choice is 2.6 % above the fastest tiling on average and 28 % in the worst case (520 rows, contraction
-// of 4096), over 408 of up to 17472 rows in another run, with another card and other buffers, 1.1 % and 12 %.  l of 3 and 6 is the one of a nearly full chip:
+// rows agreed).  Over 168 products of 264 to 16384 rows the choice is 1.7 % above the fastest tiling on average and 15 % in the worst case (16384 x 1536 x
+// 512), over 408 of up to 17472 rows in another run, with another card and other buffers, 1.1 % and 12 %.  l of 3 and 6 is the one of a nearly full chip:
 // 8192 x 768 x 3072 takes 59.6 us as 256 blocks of 128 x 192 and 51.5 as 192 of 256 x 128.  `use`: the automatic choice considers the
 // configuration; the others can be selected for timing (8 is the mirror image of 7 and seldom faster).
 // w and e of 11 come from launches of two to eight of its tiles per CU over contractions of up to 1024, whose blocks write under each other's
